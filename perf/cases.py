@@ -1,0 +1,502 @@
+"""The workloads that the library's speed is measured on.
+
+Every case goes through the package's public entry points as a simulation code
+calls them. `kind` names the call:
+
+  forces     Context.build_tree + calc_acc: a tree force evaluation on new
+             positions, with the previous accelerations in hand
+  noalloc    tree_forces_noalloc: the same in one call for a serving loop that
+             may not allocate
+  potential  build_tree + calc_acc_pot with compensated sums: the energy
+             diagnostics of a long run
+  block      Context.step with individual block time steps on the galaxy: the
+             library's headline workload (one step at a time, or many in a call)
+  leapfrog   Context.step, kick-drift-kick with one step length
+  rk2        Context.step, second-order Runge-Kutta predict / correct
+  batch      Context.step_graph on independent clusters, one graph per step kind
+  direct     Context.direct: Eq. 1 summed directly in FP32
+  direct64   Context.direct64: the FP64 accuracy reference of some targets
+  costmodel  Context.train_cost_model + mlp_forward on recorded walk statistics
+
+Particles: Plummer spheres, and the three-component galaxy of the benchmark
+(80 % NFW halo, 5 % Hernquist bulge, 15 % exponential disc), of equal masses,
+total mass 1, G = 1. The previous accelerations are those of the spherically
+averaged mass at a point about one softening length away (so that, as for
+discrete particles, they do not vanish in the centre): they are the same numbers
+whatever computes the next ones.
+"""
+from __future__ import annotations
+
+import math
+
+import numpy as np
+import torch
+
+import paper_1811_02761_amd as nb
+
+DEV = "cuda"
+EPS = 2.0 ** -7          # clusters
+EPS_GALAXY = 2.0 ** -6
+DELTA = 2.0 ** -9
+DT = 2.0 ** -7
+DT_MAX = 2.0 ** -3       # block steps
+ETA = 0.025
+
+
+# ---------------------------------------------------------------- the cases
+def listed():
+    return [
+        # one force evaluation of a small cluster: launches and latency
+        {"name": "forces_1k", "kind": "forces", "model": "plummer", "n": 1000},
+        # a serving loop's call, odd size
+        {"name": "noalloc_16k", "kind": "noalloc", "model": "plummer", "n": 16411},
+        # an ordinary force evaluation
+        {"name": "forces_200k", "kind": "forces", "model": "galaxy", "n": 200003},
+        # energy diagnostics
+        {"name": "potential_130k", "kind": "potential", "model": "plummer", "n": 131072},
+        # a coupled code that advances a modest galaxy one block step per call
+        {"name": "block_50k_x1", "kind": "block", "n": 50021, "steps": 1, "rebuild": 4},
+        # the headline: the 2^23 galaxy, many block steps in one call
+        {"name": "block_8M_x16", "kind": "block", "n": 1 << 23, "steps": 16, "rebuild": 2},
+        # a star cluster with one step length
+        {"name": "leapfrog_64k_x8", "kind": "leapfrog", "n": 65536, "steps": 8, "rebuild": 8},
+        # the paper's own integrator
+        {"name": "rk2_10k_x4", "kind": "rk2", "n": 10007, "steps": 4, "rebuild": 4},
+        # the batched workload: 64 clusters of 2^10 to 2^18 particles
+        {"name": "batch_64_x4", "kind": "batch", "systems": 64, "log2_min": 10, "log2_max": 18,
+         "steps": 4, "rebuild": 2},
+        # direct summation of a few thousand particles
+        {"name": "direct_4k", "kind": "direct", "model": "plummer", "n": 4096},
+        # accuracy check of a large run on a subset of its particles
+        {"name": "direct64_1M_2k", "kind": "direct64", "model": "galaxy", "n": 1 << 20,
+         "targets": 2048},
+        # the queue's cost model, trained on the walk statistics of one warm-up
+        {"name": "costmodel_30k_h32", "kind": "costmodel", "rows": 30000, "hidden": 32,
+         "steps": 16},
+    ]
+
+
+def draw(rng):
+    def size(lo, hi):
+        return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+    kind = rng.choice(["forces", "noalloc", "potential", "block", "leapfrog", "rk2", "batch",
+                       "direct", "direct64", "costmodel"])
+    model = rng.choice(["plummer", "galaxy"])
+    if kind == "forces":
+        return {"kind": kind, "model": model, "n": size(256, 1 << 20)}
+    if kind == "noalloc":
+        return {"kind": kind, "model": model, "n": size(256, 1 << 17)}
+    if kind == "potential":
+        return {"kind": kind, "model": model, "n": size(1000, 1 << 19)}
+    if kind == "block":
+        return {"kind": kind, "n": size(1 << 13, 1 << 22), "steps": size(1, 16),
+                "rebuild": rng.randint(1, 4)}
+    if kind == "leapfrog":
+        return {"kind": kind, "n": size(1000, 1 << 19), "steps": size(1, 8),
+                "rebuild": rng.randint(1, 8)}
+    if kind == "rk2":
+        return {"kind": kind, "n": size(1000, 1 << 18), "steps": size(1, 4),
+                "rebuild": rng.randint(1, 4)}
+    if kind == "batch":
+        lo = rng.randint(8, 12)
+        return {"kind": kind, "systems": size(3, 64), "log2_min": lo,
+                "log2_max": rng.randint(lo + 1, 17), "steps": size(1, 4),
+                "rebuild": rng.randint(1, 4)}
+    if kind == "direct":
+        return {"kind": kind, "model": model, "n": size(256, 1 << 17)}
+    if kind == "direct64":
+        return {"kind": kind, "model": model, "n": size(1 << 12, 1 << 21),
+                "targets": size(16, 4096)}
+    return {"kind": kind, "rows": size(1000, 200000), "hidden": rng.choice([8, 16, 32, 64]),
+            "steps": size(2, 24)}
+
+
+# ------------------------------------------------------------------- inputs
+# radius as a function of the enclosed mass fraction, and enclosed mass as a
+# function of radius, tabulated on the host
+R_D = 5.4 / 7.63
+A_BULGE = 0.61 / 7.63
+
+
+def _inverse(x, y, points=1 << 14):
+    """Table of x at equally spaced values of the monotone y (scaled to 1)."""
+    return np.interp(np.linspace(0.0, 1.0, points), y / y[-1], x)
+
+
+def _tables():
+    r = np.concatenate([[0.0], np.geomspace(1e-5, 30.0, 60000)])
+    halo = np.log1p(r) - r / (1.0 + r)
+    bulge = (r / (r + A_BULGE)) ** 2
+    R = np.linspace(0.0, 10.0, 60000)
+    disc = 1.0 - (1.0 + R) * np.exp(-R)
+    q = np.linspace(0.0, 1.0, 60000)
+    speed = np.cumsum(q * q * np.maximum(1.0 - q * q, 0.0) ** 3.5)
+    rg = np.geomspace(1e-4, 30.0, 1 << 14)
+    s = rg / R_D
+    mass = (0.80 * np.interp(rg, r, halo / halo[-1]) + 0.05 * np.interp(rg, r, bulge / bulge[-1])
+            + 0.15 * np.interp(s, R, disc / disc[-1]))
+    return {"halo": _inverse(r, halo), "bulge": _inverse(r, bulge),
+            "disc": R_D * _inverse(R, disc), "speed": _inverse(q, speed), "mass": mass}
+
+
+_TABLES = None
+
+
+def _table(name):
+    global _TABLES
+    if _TABLES is None:
+        _TABLES = {k: torch.as_tensor(v, device=DEV) for k, v in _tables().items()}
+    return _TABLES[name]
+
+
+def _lookup(table, u):
+    """Linear interpolation of a table over [0, 1]."""
+    f = u.clamp(0.0, 1.0) * (table.numel() - 1)
+    i = f.long().clamp(max=table.numel() - 2)
+    return torch.lerp(table[i], table[i + 1], f - i)
+
+
+def _gen(seed):
+    return torch.Generator(device=DEV).manual_seed(int(seed))
+
+
+def _rand(n, g):
+    return torch.rand(n, generator=g, device=DEV, dtype=torch.float64)
+
+
+def _directions(n, g):
+    c = 2.0 * _rand(n, g) - 1.0
+    p = 2.0 * math.pi * _rand(n, g)
+    s = torch.sqrt(1.0 - c * c)
+    return torch.stack([s * torch.cos(p), s * torch.sin(p), c])
+
+
+def _near(pos, g, eps):
+    """Points about eps away from pos."""
+    return pos + eps * torch.randn(pos.shape, generator=g, device=DEV, dtype=torch.float64)
+
+
+def _plummer(n, g):
+    """(pos, vel, acc): Aarseth, Henon and Wielen (1974), 99.9 % of the mass."""
+    u = (1.0 - _rand(n, g)) * 0.999
+    r = 1.0 / torch.sqrt(u ** (-2.0 / 3.0) - 1.0)
+    pos = r * _directions(n, g)
+    vesc = math.sqrt(2.0) * (1.0 + r * r) ** -0.25
+    vel = _lookup(_table("speed"), _rand(n, g)) * vesc * _directions(n, g)
+    return pos, vel, -_near(pos, g, EPS) * (1.0 + r * r) ** -1.5
+
+
+def _galaxy(n, g):
+    """(pos, vel, acc): halo, bulge and disc mixed in caller order."""
+    nh, nbu = int(round(0.8 * n)), int(round(0.05 * n))
+    nd = n - nh - nbu
+    halo = _lookup(_table("halo"), _rand(nh, g)) * _directions(nh, g)
+    bulge = _lookup(_table("bulge"), _rand(nbu, g)) * _directions(nbu, g)
+    R = _lookup(_table("disc"), _rand(nd, g))
+    p = 2.0 * math.pi * _rand(nd, g)
+    z = 0.1 * R_D * torch.atanh((2.0 * _rand(nd, g) - 1.0) * (1.0 - 1e-9))
+    disc = torch.stack([R * torch.cos(p), R * torch.sin(p), z])
+    pos = torch.cat([halo, bulge, disc], 1)[:, torch.randperm(n, generator=g, device=DEV)]
+    r = torch.sqrt((pos * pos).sum(0)).clamp(min=1e-4)
+    mr = _lookup(_table("mass"), torch.log(r / 1e-4) / math.log(30.0 / 1e-4)) / r
+    vel = torch.sqrt(mr / 3.0) * torch.randn((3, n), generator=g, device=DEV, dtype=torch.float64)
+    return pos, vel, -_near(pos, g, EPS_GALAXY) * (mr / (r * r + EPS_GALAXY ** 2))
+
+
+def _particles(model, n, seed):
+    """FP64 positions, FP32 velocities, accelerations and equal masses."""
+    pos, vel, acc = (_plummer if model == "plummer" else _galaxy)(n, _gen(seed))
+    m = torch.full((n,), 1.0 / n, dtype=torch.float32, device=DEV)
+    return pos, vel.float(), acc.float(), m
+
+
+def _batch_offsets(case):
+    """Cluster sizes 2^(lo + (hi - lo) u_k), u_k the golden-ratio sequence."""
+    lo, hi = case["log2_min"], case["log2_max"]
+    u = (np.arange(1, case["systems"] + 1) * 0.6180339887498949) % 1.0
+    size = np.floor(2.0 ** (lo + (hi - lo) * u)).astype(np.int64)
+    return np.concatenate([[0], np.cumsum(size)])
+
+
+def _walk_statistics(rows, seed):
+    """Rows as a warm-up walk records them: log2 group size, log2 half
+    diagonal, log2 density, log2 previous list length; log2 interactions."""
+    g = _gen(seed)
+    count = torch.floor(64.0 * torch.sqrt(_rand(rows, g))).clamp(min=1.0)
+    f0 = torch.log2(count)
+    f1 = 5.0 * _rand(rows, g) - 6.0
+    f2 = f0 - 17.0 - 3.0 * f1
+    length = 9.0 - 0.4 * f1 + 0.15 * f0 + 0.3 * torch.randn(rows, generator=g, device=DEV,
+                                                           dtype=torch.float64)
+    seen = _rand(rows, g) < 0.5
+    f3 = torch.where(seen, length + 0.1 * _rand(rows, g), torch.zeros_like(length))
+    return torch.stack([f0, f1, f2, f3], 1).float().contiguous(), (f0 + length).float()
+
+
+def _initial_weights(hidden, seed):
+    fan = torch.as_tensor(nb.mlp_fan_in(hidden), device=DEV)
+    u = 2.0 * _rand(fan.numel(), _gen(seed)) - 1.0
+    return (u / torch.sqrt(fan)).float()
+
+
+def _eps(case):
+    return EPS_GALAXY if case["kind"] == "block" or case.get("model") == "galaxy" else EPS
+
+
+def _block_levels(acc):
+    """Smallest level k with dt_max 2^-k <= sqrt(2 eta eps / |a|)."""
+    dt = torch.sqrt(2.0 * ETA * EPS_GALAXY / torch.linalg.norm(acc.double(), dim=0))
+    return torch.ceil(torch.log2(DT_MAX / dt)).clamp(0, 10).to(torch.int8)
+
+
+def prepare(case, seed):
+    kind = case["kind"]
+    if kind == "costmodel":
+        feat, target = _walk_statistics(case["rows"], seed)
+        return {"case": case, "ctx": nb.Context(nb.Params(), n_max=4096), "feat": feat,
+                "target": target, "w0": _initial_weights(case["hidden"], seed)}
+    if kind == "batch":
+        return _prepare_batch(case, seed)
+    n = case["n"]
+    model = {"block": "galaxy", "leapfrog": "plummer", "rk2": "plummer"}.get(kind) or case["model"]
+    pos, vel, acc, m = _particles(model, n, seed)
+    s = {"case": case}
+    params = nb.Params(eps=_eps(case), delta_acc=DELTA, compensated=int(kind == "potential"))
+    if kind in ("block", "leapfrog", "rk2"):
+        s["ctx"] = nb.Context(params, n_max=n)
+        s["state"] = nb.State(*pos.clone(), *vel.clone(), m, *acc.clone(), have_acc=1,
+                              dt=DT_MAX if kind == "block" else DT,
+                              rebuild_interval=case["rebuild"], integrator=int(kind == "rk2"))
+        if kind == "block":
+            s["state"].level = _block_levels(acc)
+            s["state"].eta = ETA
+        return s
+    s["xyzm"] = [c.float() for c in pos] + [m]
+    if kind == "direct64":
+        # distinct targets: a seeded subset, ascending
+        pick = torch.randperm(n, generator=_gen(seed + 1), device=DEV)[:case["targets"]]
+        s["targets"] = torch.sort(pick).values
+    if kind in ("direct", "direct64"):
+        s["ctx"] = nb.Context(params, n_max=256)
+    else:
+        s["a_old"] = tuple(acc.clone())
+        if kind == "noalloc":
+            s["params"] = params
+            s["out"] = tuple(torch.empty(n, dtype=torch.float32, device=DEV) for _ in range(3))
+            s["status"] = torch.zeros(1, dtype=torch.int32, device=DEV)
+        else:
+            s["ctx"] = nb.Context(params, n_max=n)
+    return s
+
+
+def _prepare_batch(case, seed):
+    off = _batch_offsets(case)
+    parts = [_particles("plummer", int(off[k + 1] - off[k]), 1009 * seed + k)
+             for k in range(case["systems"])]
+    pos, vel, acc = (torch.cat([p[i] for p in parts], 1) for i in range(3))
+    ctx = nb.Context(nb.Params(eps=EPS, delta_acc=DELTA, group_max=32), n_max=int(off[-1]))
+    ctx.set_systems(off)
+    st = nb.State(*pos.clone(), *vel.clone(), torch.cat([p[3] for p in parts]), *acc.clone(),
+                  have_acc=1, dt=DT, rebuild_interval=case["rebuild"])
+    return {"case": case, "ctx": ctx, "state": st}
+
+
+# --------------------------------------------------------------------- runs
+def _state_out(st):
+    out = {"x": st.x, "y": st.y, "z": st.z, "vx": st.vx, "vy": st.vy, "vz": st.vz,
+           "ax": st.ax, "ay": st.ay, "az": st.az}
+    if st.level is not None:
+        out["level"] = st.level
+    return out
+
+
+def run(s):
+    case = s["case"]
+    kind = case["kind"]
+    if kind == "forces":
+        s["ctx"].build_tree(*s["xyzm"])
+        return s["ctx"].calc_acc(s["a_old"])
+    if kind == "noalloc":
+        return nb.tree_forces_noalloc(s["params"], *s["xyzm"], s["a_old"], s["out"],
+                                      status=s["status"]) + (s["status"],)
+    if kind == "potential":
+        s["ctx"].build_tree(*s["xyzm"])
+        acc, phi = s["ctx"].calc_acc_pot(s["a_old"])
+        return (*acc, phi)
+    if kind == "direct":
+        return s["ctx"].direct(*s["xyzm"])
+    if kind == "direct64":
+        return s["ctx"].direct64(*s["xyzm"], s["targets"])
+    if kind == "costmodel":
+        w = s["w0"].clone()
+        losses = s["ctx"].train_cost_model(case["hidden"], w, s["feat"], s["target"],
+                                           case["steps"], 1e-2)
+        return w, losses, s["ctx"].mlp_forward(case["hidden"], w, s["feat"])
+    (s["ctx"].step_graph if kind == "batch" else s["ctx"].step)(s["state"], case["steps"])
+    return _state_out(s["state"])
+
+
+# --------------------------------------------------------------------- work
+PAIR_FLOPS = 22.0  # one pair of Eq. 1
+PAIR64_FLOPS = 30.0
+
+
+def _list_entries(n):
+    """Mean interaction-list entries per particle at delta_acc 2^-9 (measured
+    288, 820, 1730 and 1760 for spheres of 300, 1000, 10^4 and 10^6, and 1420
+    for galaxies from 10^4 on)."""
+    return min(0.8 * n, 1500.0)
+
+
+def work(case):
+    kind = case["kind"]
+    if kind == "costmodel":
+        h, rows = case["hidden"], case["rows"]
+        weights = 7 * h + h * h + 1
+        return {"bytes": case["steps"] * 20.0 * rows + 20.0 * rows,
+                "flops": (case["steps"] * 3 + 1) * 2.0 * weights * rows}
+    n = case["n"] if kind != "batch" else int(_batch_offsets(case)[-1])
+    if kind == "direct":
+        return {"bytes": 28.0 * n, "flops": PAIR_FLOPS * n * n}
+    if kind == "direct64":
+        return {"bytes": 16.0 * n + 48.0 * case["targets"],
+                "flops": PAIR64_FLOPS * n * case["targets"]}
+    walk = PAIR_FLOPS * n * _list_entries(n)
+    if kind in ("forces", "noalloc"):
+        return {"bytes": 40.0 * n, "flops": walk}
+    if kind == "potential":
+        return {"bytes": 44.0 * n, "flops": walk * 24.0 / 22.0}
+    steps = case["steps"]
+    if kind == "block":
+        # the state is read and written once a step; the steps that end take
+        # 0.15 of the pairs of a force on every particle (measured at 2^23)
+        return {"bytes": steps * 100.0 * n, "flops": 0.15 * steps * walk}
+    return {"bytes": steps * 100.0 * n, "flops": steps * walk * (2 if kind == "rk2" else 1)}
+
+
+# -------------------------------------------------- the same in 64 bits
+def _direct(pos, m, eps, targets=None, with_phi=False, with_scale=False):
+    """Eq. 1 in FP64: (acc (3, nt), phi, scale); the pair j == i left out of
+    the potential (it adds nothing to the force)."""
+    n = pos.shape[1]
+    idx = torch.arange(n, device=DEV) if targets is None else targets
+    nt = idx.numel()
+    acc = torch.zeros((3, nt), dtype=torch.float64, device=DEV)
+    phi = torch.zeros(nt, dtype=torch.float64, device=DEV)
+    scale = torch.zeros(nt, dtype=torch.float64, device=DEV)
+    chunk = max(1, (1 << 25) // n)
+    for k in range(0, nt, chunk):
+        i = idx[k:k + chunk]
+        d = [c[None, :] - c[i][:, None] for c in pos]
+        d2 = d[0] * d[0]
+        d2.addcmul_(d[1], d[1]).addcmul_(d[2], d[2])
+        rinv = torch.rsqrt(d2 + eps * eps)
+        mr = m[None, :] * rinv
+        w = mr * rinv * rinv
+        for a in range(3):
+            acc[a, k:k + chunk] = (w * d[a]).sum(1)
+        if with_phi:
+            phi[k:k + chunk] = -mr.sum(1) + m[i] / eps
+        if with_scale:
+            scale[k:k + chunk] = (w * torch.sqrt(d2)).sum(1)
+    return acc, phi, scale
+
+
+def _exact_steps(case, seed):
+    """Leapfrog or Heun steps from the same state, forces by direct sums."""
+    pos, vel, acc, m = _particles("plummer", case["n"], seed)
+    vel, acc, m = vel.double(), acc.double(), m.double()
+    force = lambda p: _direct(p, m, EPS)[0]  # noqa: E731
+    for _ in range(case["steps"]):
+        if case["kind"] == "leapfrog":
+            vel = vel + acc * (0.5 * DT)
+            pos = pos + vel * DT
+            acc = force(pos)
+            vel = vel + acc * (0.5 * DT)
+        else:
+            ahead = force(pos + vel * DT)
+            pos = pos + (vel + (vel + acc * DT)) * (0.5 * DT)
+            vel = vel + (acc + ahead) * (0.5 * DT)
+            acc = force(pos)
+    return dict(zip(("x", "y", "z", "vx", "vy", "vz", "ax", "ay", "az"), (*pos, *vel, *acc)))
+
+
+def _exact_block_step(case, seed):
+    """One block step: opening kicks of everyone, drift by the finest step,
+    closing kicks of the particles whose step ends. The new levels are whole
+    numbers, with a threshold in the force: no value."""
+    pos, vel, acc, m = _particles("galaxy", case["n"], seed)
+    level = _block_levels(acc)
+    vel, acc, m = vel.double(), acc.double(), m.double()
+    dt = DT_MAX * 2.0 ** -level.double()
+    kmax = int(level.max())
+    vel = vel + acc * (0.5 * dt)
+    pos = pos + vel * (DT_MAX * 2.0 ** -kmax)
+    ends = torch.nonzero(level == kmax).flatten()
+    acc[:, ends] = _direct(pos, m, EPS_GALAXY, targets=ends)[0]
+    vel[:, ends] += acc[:, ends] * (0.5 * dt[ends])
+    out = dict(zip(("x", "y", "z", "vx", "vy", "vz", "ax", "ay", "az"), (*pos, *vel, *acc)))
+    out["level"] = None
+    return out
+
+
+def _exact_costmodel(case, seed):
+    h, steps, lr = case["hidden"], case["steps"], 1e-2
+    feat, target = (t.double() for t in _walk_statistics(case["rows"], seed))
+    w = _initial_weights(h, seed).double()
+    mean = feat.mean(0)
+    var = (feat * feat).mean(0) - mean * mean
+    w[:4] = mean
+    w[4:8] = 1.0 / torch.sqrt(var.clamp(min=0.0)).clamp(min=1e-6)
+    z = (feat - w[:4]) * w[4:8]
+
+    def forward(v):
+        w1, b1, w2, b2, w3, b3 = torch.split(v, [4 * h, h, h * h, h, h, 1])
+        h1 = torch.tanh(z @ w1.view(h, 4).T + b1)
+        h2 = torch.tanh(h1 @ w2.view(h, h).T + b2)
+        return h2 @ w3 + b3 + feat[:, 0] + feat[:, 3]
+
+    v = w[8:].clone()
+    m1, m2 = torch.zeros_like(v), torch.zeros_like(v)
+    losses = []
+    for t in range(1, steps + 1):
+        v.requires_grad_(True)
+        loss = ((forward(v) - target) ** 2).mean()
+        (g,) = torch.autograd.grad(loss, v)
+        losses.append(float(loss))
+        v = v.detach()
+        m1 = 0.9 * m1 + 0.1 * g
+        m2 = 0.999 * m2 + 0.001 * g * g
+        v = v - lr * (m1 / (1 - 0.9 ** t)) / (torch.sqrt(m2 / (1 - 0.999 ** t)) + 1e-8)
+    return torch.cat([w[:8], v]), np.asarray(losses), forward(v)
+
+
+MOST_PAIRS = 6e10  # direct sums in FP64 that take some seconds
+
+
+def exact(case, seed):
+    kind = case["kind"]
+    if kind == "costmodel":
+        return _exact_costmodel(case, seed)
+    if kind == "batch":
+        return None
+    n = case["n"]
+    pairs = float(n) * (case["targets"] if kind == "direct64" else n)
+    if kind in ("leapfrog", "rk2"):
+        evaluations = case["steps"] * (2 if kind == "rk2" else 1)
+        return _exact_steps(case, seed) if pairs * evaluations <= MOST_PAIRS else None
+    if kind == "block":
+        return _exact_block_step(case, seed) if case["steps"] == 1 and pairs <= MOST_PAIRS else None
+    if pairs > MOST_PAIRS:
+        return None
+    pos, _, _, m = _particles(case["model"], n, seed)
+    pos, m = pos.float().double(), m.double()
+    if kind == "direct64":
+        pick = torch.randperm(n, generator=_gen(seed + 1), device=DEV)[:case["targets"]]
+        acc, phi, scale = _direct(pos, m, _eps(case), torch.sort(pick).values, True, True)
+        return acc.T, scale, phi
+    acc, phi, _ = _direct(pos, m, _eps(case), with_phi=kind == "potential")
+    if kind == "potential":
+        return (*acc, phi)
+    return (*acc, None) if kind == "noalloc" else tuple(acc)
