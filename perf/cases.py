@@ -86,7 +86,7 @@ def draw(rng):
     if kind == "forces":
         return {"kind": kind, "model": model, "n": size(256, 1 << 20)}
     if kind == "noalloc":
-        return {"kind": kind, "model": model, "n": size(256, 1 << 17)}
+        return {"kind": kind, "model": model, "n": size(256, 40000)}
     if kind == "potential":
         return {"kind": kind, "model": model, "n": size(1000, 1 << 19)}
     if kind == "block":
