@@ -74,8 +74,8 @@ enum {
  *                of two >= 64; 0 = the cell capacity rounded up to a power
  *                of two, at most 16384, which no tree can fill: the stack
  *                holds at most 512 cells per level). A group whose stack
- *                outgrows a smaller cap is walked again by a few wavefronts
- *                with a 16384-cell stack, so the results never depend on it.
+ *                outgrows a smaller cap is walked again with a stack of that
+ *                size, so the results never depend on it.
  *  list_tile   : interaction-list entries held in LDS per wavefront before a
  *                flush (multiple of 64, 64..2048; 0 = 192).
  *  waves_per_cu: resident wavefronts per compute unit of the persistent walk
@@ -385,8 +385,9 @@ int32_t nbody_rebuild_allowed(int64_t next_tick, int64_t step_ticks);
  * call returns NBODY_ENOMEM when the layout for (p, n) does not fit). It
  * calls no allocator: no context, no events, no host copies; everything is
  * enqueued on hip_stream and the call returns at once. p as for
- * nbody_create; frontier_cap above 256 (or 0) is taken as 256, walk_split,
- * order and calcnode_sync are fixed (none of them changes a result: the
+ * nbody_create; frontier_cap is taken as what the scratch has room for (at
+ * most the value given, unless 0), order and calcnode_sync are fixed (none of
+ * them changes a result: the
  * accelerations equal those of the context path bit for bit). x, y, z, m:
  * device FP32, caller order, length n; ax_old..az_old: a_old of Eq. 2, or all
  * NULL for the bootstrap criterion; ax..az: device outputs, caller order.

@@ -206,7 +206,8 @@ nbody_status status_from_bits(int32_t b) {
 
 namespace nb {
 
-Layout make_layout(const nbody_params &p, int64_t n, int num_cu, bool stepping) {
+Layout make_layout(const nbody_params &p, int64_t n, int num_cu, bool stepping,
+                   int64_t split_slots) {
   Layout L{};  // offsets not taken below stay 0 (caught by carve_complete)
   L.n_max = n;
   L.cell_cap = n + cdiv(21 * n, p.leaf_max + 1) + 2;
@@ -215,9 +216,6 @@ Layout make_layout(const nbody_params &p, int64_t n, int num_cu, bool stepping) 
   L.walk_waves = (int64_t)num_cu * eff_waves(p);
   L.num_cu = num_cu;
   L.frontier_cap = eff_frontier(p, L.cell_cap);
-  // the walk's stack holds at most 512 cells per tree level (22 levels)
-  L.frontier2_cap = 16384;
-  L.retry_waves = 2 * kWalkWavesPerWG;
   size_t o = 0;
   auto take = [&](size_t bytes) {
     const size_t r = o;
@@ -254,21 +252,33 @@ Layout make_layout(const nbody_params &p, int64_t n, int num_cu, bool stepping) 
   L.off_ghash = take(8 * N);
   L.off_order = take(4 * N);
   L.off_prevcnt = take(4 * N);
-  L.off_frontier = take(4 * (size_t)L.walk_waves * (size_t)L.frontier_cap);
+  // heavy groups (walked in parts): slots for about one part per 16 particles;
+  // stacks in the main pass's buffer, with room for at least 64 workgroups of
+  // the last pass (a stack and two fronts each). A stack holds at most 512
+  // cells per tree level (22 levels), and no more than the tree has.
+  L.heavy_slots = std::min<int64_t>(std::max<int64_t>(n / (stepping ? 16 : 64), 64), 65536);
+  L.heavy_cap = 64;
+  while (L.heavy_cap < L.cell_cap && L.heavy_cap < 16384) L.heavy_cap <<= 1;
+  const int64_t end_words = L.heavy_cap + 2 * (int64_t)kFrontCap;
+  const int64_t fwords = std::max<int64_t>(L.walk_waves * L.frontier_cap, 64 * end_words);
+  L.heavy_waves = (int)std::min<int64_t>(L.walk_waves, fwords / L.heavy_cap) / kWalkWavesPerWG *
+                  kWalkWavesPerWG;
+  L.heavy_end_blocks = (int)std::min<int64_t>(512, fwords / end_words);
+  L.off_frontier = take(4 * (size_t)fwords);
   L.off_atmp = take(12 * N);
   L.off_retry = take(4 * N);
-  L.off_frontier2 = take(4 * (size_t)L.retry_waves * (size_t)L.frontier2_cap);
-  L.off_feat = take(16 * N);
-  L.off_target = take(4 * N);
-  L.off_pred = take(4 * N);
   L.off_plast = take(4 * N);
-  L.off_okeys = take(16 * N);
-  L.off_qtmp = take(4 * N);
-  L.off_mlpw = take(4 * (size_t)kMlpMaxParams);
-  L.off_mlpm = take(4 * (size_t)kMlpMaxParams);
-  L.off_mlpv = take(4 * (size_t)kMlpMaxParams);
-  L.off_mlpg = take(4 * (size_t)(kMlpMaxParams + 1));
-  L.off_mlppart = take(4 * (size_t)kMlpWaves * (size_t)(kMlpMaxParams + 1));
+  const size_t Q = stepping ? N : 0, W = stepping ? (size_t)kMlpMaxParams : 0;
+  L.off_feat = take(16 * Q);
+  L.off_target = take(4 * Q);
+  L.off_pred = take(4 * Q);
+  L.off_okeys = take(16 * Q);
+  L.off_qtmp = take(4 * Q);
+  L.off_mlpw = take(4 * W);
+  L.off_mlpm = take(4 * W);
+  L.off_mlpv = take(4 * W);
+  L.off_mlpg = take(4 * (W + 1));
+  L.off_mlppart = take(4 * (stepping ? (size_t)kMlpWaves * (W + 1) : 0));
   L.off_gref = take(4 * N);
   L.off_sysoff = take(4 * (size_t)(kMaxSystems + 1));
   L.off_sysbox = take(32 * (size_t)kMaxSystems);
@@ -277,7 +287,8 @@ Layout make_layout(const nbody_params &p, int64_t n, int num_cu, bool stepping) 
   L.off_asort = take(16 * N);
   // split walk: one slot per queued group while the queue is shorter than
   // 4 x the walk's wavefronts (no walk splits a longer queue)
-  L.split_slots = std::max<int64_t>(1, std::min<int64_t>(4 * L.walk_waves, n));
+  L.split_slots = std::max<int64_t>(
+      1, std::min<int64_t>(std::min<int64_t>(4 * L.walk_waves, n), split_slots));
   L.off_split = take((size_t)kSplitSlotBytes * (size_t)L.split_slots);
   L.off_gid = take(4 * N);
   L.off_gflag = take(4 * N);
@@ -289,6 +300,11 @@ Layout make_layout(const nbody_params &p, int64_t n, int num_cu, bool stepping) 
   L.off_longcnt = take(4 * (size_t)L.build_blocks);
   L.off_longslot = take(4 * (size_t)L.build_blocks * kLevels);
   L.off_wpart = take(8 * 4 * (size_t)kStatBlocks);
+  L.off_heavy = take(4 * N);
+  L.off_hparts = take(16 * (size_t)L.heavy_slots);
+  L.off_hrec = take(8 * (size_t)L.heavy_slots);
+  L.off_hfront = take(4 * (size_t)kHeavyFrontPerSlot * (size_t)L.heavy_slots);
+  L.off_hsum = take(4 * (size_t)heavy_part_words(p.compensated) * (size_t)L.heavy_slots);
   // key-ordered block-step state, two sets (none without stepping: the
   // pointers then share one empty offset and are never used); each set's
   // region, from its positions on, spans at least 64 bytes per particle: it
@@ -355,7 +371,6 @@ Ptrs carve(void *base, const Layout &L) {
   P.frontier = reinterpret_cast<uint32_t *>(b + L.off_frontier);
   P.atmp = reinterpret_cast<float *>(b + L.off_atmp);
   P.retry = reinterpret_cast<uint32_t *>(b + L.off_retry);
-  P.frontier2 = reinterpret_cast<uint32_t *>(b + L.off_frontier2);
   P.feat = reinterpret_cast<float4 *>(b + L.off_feat);
   P.target = reinterpret_cast<float *>(b + L.off_target);
   P.pred = reinterpret_cast<float *>(b + L.off_pred);
@@ -382,6 +397,11 @@ Ptrs carve(void *base, const Layout &L) {
   P.longcnt = reinterpret_cast<uint32_t *>(b + L.off_longcnt);
   P.longslot = reinterpret_cast<uint32_t *>(b + L.off_longslot);
   P.wpart = reinterpret_cast<unsigned long long *>(b + L.off_wpart);
+  P.heavy = reinterpret_cast<uint32_t *>(b + L.off_heavy);
+  P.hparts = reinterpret_cast<uint4 *>(b + L.off_hparts);
+  P.hrec = reinterpret_cast<uint2 *>(b + L.off_hrec);
+  P.hfront = reinterpret_cast<uint32_t *>(b + L.off_hfront);
+  P.hsum = reinterpret_cast<float *>(b + L.off_hsum);
   for (int c = 0; c < 2; ++c) {
     P.kpos[c] = reinterpret_cast<double *>(b + L.off_kpos[c]);
     P.kvel[c] = reinterpret_cast<float *>(b + L.off_kvel[c]);
@@ -503,12 +523,14 @@ WalkCfg walk_cfg(const nbody_ctx *ctx, bool bootstrap, bool queued) {
   c.waves_per_cu = eff_waves(ctx->p);
   c.num_cu = ctx->num_cu;
   c.use_order = queued ? 1 : 0;
-  c.frontier2_cap = ctx->L.frontier2_cap;
-  c.retry_waves = ctx->L.retry_waves;
   c.batch = ctx->sys_r > 0;
   c.asort_out = false;
   c.split = ctx->p.walk_split;
   c.split_slots = ctx->L.split_slots;
+  c.heavy_slots = ctx->L.heavy_slots;
+  c.heavy_cap = ctx->L.heavy_cap;
+  c.heavy_waves = ctx->L.heavy_waves;
+  c.heavy_end_blocks = ctx->L.heavy_end_blocks;
   return c;
 }
 
@@ -740,7 +762,6 @@ nbody_status do_calc(nbody_ctx *ctx, const float *axo, const float *ayo, const f
   const int sp = span_begin(ctx, 1);
   launch_walk(wc, out_perm, ctx->n, ax, ay, az, P, ctx->st);
   span_end(ctx, sp);
-  launch_walk_retry(wc, out_perm, ctx->n, ax, ay, az, P, ctx->st);
   // the tree's first walk with the acceleration criterion is its reference
   const bool record = !boot && ctx->mac_walks == 0;
   if (!boot) ctx->mac_walks++;
@@ -1636,15 +1657,29 @@ nbody_status nbody_tree_forces_noalloc(const nbody_params *p, void *hip_stream, 
   if (cu <= 0) return NBODY_EHIP;
   void *ws = nullptr;
   if ((s = static_scratch(dev, &ws)) != NBODY_OK) return s;
-  // a small depth-first stack (groups that outgrow it go to the retry pass)
-  // and no split walk keep the layout small; neither changes any result
+  // The call fits if the layout with the smallest stacks (and split-walk sums
+  // for a group per particle) does. A group that outgrows its stack is walked
+  // again, so the stacks then take what the groups that a tree has in earnest
+  // (8 particles and more) leave of the split-walk sums: at 16411 particles,
+  // 256-cell stacks sent a third of the groups to the retry pass (3.2 ms of
+  // the call's 3.8). Neither changes any result.
   nbody_params q = *p;
-  if (q.frontier_cap == 0 || q.frontier_cap > 256) q.frontier_cap = 256;
-  q.walk_split = 1;
+  const int64_t cap = q.frontier_cap == 0 ? 16384 : q.frontier_cap;
   q.order = 0;
   q.calcnode_sync = kCalcNodeLevels;
-  const Layout L = make_layout(q, n, cu, false);
-  if (L.total > kStaticScratchBytes) return NBODY_ENOMEM;
+  q.frontier_cap = (int32_t)std::min<int64_t>(cap, 256);
+  if (make_layout(q, n, cu, false).total > kStaticScratchBytes) return NBODY_ENOMEM;
+  const int64_t slots = std::max<int64_t>(n / 8, 64);
+  Layout L = make_layout(q, n, cu, false, slots);
+  while (q.frontier_cap < cap && q.frontier_cap < L.heavy_cap) {
+    q.frontier_cap *= 2;
+    const Layout M = make_layout(q, n, cu, false, slots);
+    if (M.total > kStaticScratchBytes) {
+      q.frontier_cap /= 2;
+      break;
+    }
+    L = M;
+  }
   nbody_ctx c;  // on the stack: no events, no pinned memory
   c.p = q;
   c.order = 0;

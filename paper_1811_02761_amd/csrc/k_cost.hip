@@ -281,7 +281,12 @@ __global__ __launch_bounds__(256) void k_adam(int64_t np, float *__restrict__ w,
 
 // Queue sort keys: one 8-bit digit, larger predicted cost first (quarter-octave
 // buckets); equal digits keep group order in the stable digit sort, which
-// covers the queue's entries only (the count is read on the device).
+// covers the queue's entries only (the count is read on the device). Predicted
+// costs below 2^kBulkLog2 interactions (modes 1 and 2) share one bucket: no
+// such group decides when the walk ends, and in group order neighbours share
+// cells in the caches (2^23 galaxy, block steps, rebuild every 2nd step: 2.44
+// ms per walk with the bulk ordered, 2.36 with it in group order, plain 2.51).
+constexpr float kBulkLog2 = 18.0f;
 __global__ __launch_bounds__(256) void k_cost_keys(
     const DevScalars *__restrict__ sc, const uint32_t *__restrict__ queue, int mode,
     const float4 *__restrict__ feat, const float *__restrict__ pred,
@@ -296,7 +301,8 @@ __global__ __launch_bounds__(256) void k_cost_keys(
     // mode 1: log2(count) + log2(1 + previous list length); mode 2: the
     // model; mode 3: the log2 interactions the last ordered walk recorded
     const float c = mode == 2 ? pred[g] : mode == 3 ? target[g] : f.x + f.w;
-    const float q = fminf(fmaxf(c * 4.0f, 0.0f), 254.0f);  // NaN -> 0
+    const float lo = mode == 3 ? 0.0f : 4.0f * kBulkLog2;
+    const float q = fminf(fmaxf(c * 4.0f, lo), 254.0f);  // NaN -> lo
     keys[i] = 254u - (uint32_t)q;
     vals[i] = g;
   }

@@ -4,19 +4,29 @@
 // the smallest member |a_old| (correctly rounded sqrt of the FP32 sum of
 // squares, or the key-ordered mirror's w) and delta_acc times it; gbox[2g] =
 // (lo, delta_acc |a_old|min), gbox[2g + 1] = (hi, |a_old|min). Without a_old
-// (bootstrap) both acceleration words are 0.
+// (bootstrap) both acceleration words are 0. Also clears the walk's counters.
 #include "nbody_internal.h"
 
 namespace nb {
 
 __global__ __launch_bounds__(256) void k_group_bounds(
-    const DevScalars *__restrict__ sc, const uint32_t *__restrict__ queue,
+    DevScalars *__restrict__ sc, const uint32_t *__restrict__ queue,
     const uint32_t *__restrict__ gbegin,
     const uint32_t *__restrict__ gcount, const float4 *__restrict__ xyzm,
     const uint32_t *__restrict__ perm, const float *__restrict__ axo,
     const float *__restrict__ ayo, const float *__restrict__ azo,
     const float4 *__restrict__ asort, float delta_acc,
     float4 *__restrict__ gbox) {
+  // the coming walk's queues start empty
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    sc->queue_head = 0;
+    sc->retry_head = 0;
+    sc->nretry = 0;
+    sc->nheavy = 0;
+    sc->nhpart = 0;
+    sc->nhfront = 0;
+    sc->heavy_head = 0;
+  }
   // the queued groups (block steps) or every group
   const uint32_t nq = queue ? sc->nqueue : sc->ngroup;
   const uint32_t wstride = gridDim.x * (blockDim.x >> 6);

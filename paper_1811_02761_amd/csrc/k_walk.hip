@@ -34,6 +34,19 @@
 // order and writes the results. This turns a queue of q heavy groups into
 // K q tasks of a quarter or half the arithmetic each.
 //
+// Heavy groups: a few groups meet far longer lists than the rest (members
+// scattered over a sparse outskirt: their box spans the dense centre, and
+// nearly every particle is an entry). One group's walk is a serial chain, so
+// such a group decided the walk's time (sphere of 2*10^5 particles: mean list
+// 1840, longest 199938; 3.2 ms, of which all other groups needed 0.4). A group
+// whose list exceeds heavy_limit() of its walk root's particles is therefore
+// left by the main pass and walked in parts: k_walk_mid cuts the part of the
+// tree that the group meets into an ordered front of cells (breadth first,
+// the group's own MAC) and the front into parts of about equal particle
+// counts; k_heavy_walk walks each part like a group of its own (its stack
+// starts with the part's cells), and k_heavy_end adds the parts' sums in
+// order. Front, parts and sums depend on the tree and the group alone.
+//
 // Lane layout: groups of at most 8, 16 or 32 members use S = 8, 4 or 2
 // "streams": lane = stream * (64 / S) + member, stream s adds the entries
 // whose list index is s mod S, and the S partial sums are combined at the
@@ -44,6 +57,8 @@
 // any member's distance) and |a_old| the smallest previous acceleration in
 // the group; accept iff d^2 > b^2 and delta_acc*|a_old|*d^4 >= G m b^2, all in
 // FP32. Without a_old (bootstrap) accept iff d^2 > 4 b^2.
+#include <algorithm>
+
 #include "nbody_internal.h"
 
 namespace nb {
@@ -60,8 +75,15 @@ struct WalkArgs {
   const uint32_t *qcount;  // queue length (device)
   const uint32_t *groot;   // per group root cell (nullptr: the root, cell 0)
   float4 *asort;           // key-ordered copy of the outputs with |a| (nullptr: none)
-  uint32_t *retry;         // overflowing groups go here (nullptr: report instead)
+  const uint32_t *cpcount;
+  uint32_t *retry;         // the groups left to the retry pass
   uint32_t *nretry;
+  uint32_t *heavy;         // the groups over heavy_limit()
+  uint4 *hparts;           // parts of heavy groups: (group, front begin, cells, -)
+  uint2 *hrec;             // per heavy group: first part, parts (0: no room)
+  uint32_t *hfront;        // the fronts' cells
+  float *hsum;             // per part: partial sums per lane
+  uint32_t hslots, hfront_cap, hwords;  // capacities of hparts / hfront; words per part
   uint32_t *head;          // the work queue's claim counter
   uint32_t *frontier;
   uint32_t *gent;
@@ -75,6 +97,7 @@ struct WalkArgs {
   uint32_t tile;
   uint32_t fmask;
   int bootstrap;
+  int may_retry;           // overflowing groups are walked again (else reported)
   int split_mode;          // -1 never (retry pass), 0 by queue length, else 1, 2, 4
   uint32_t split_slots;
 };
@@ -85,6 +108,46 @@ __device__ __forceinline__ uint32_t split_factor(uint32_t ng, uint32_t waves, ui
   if (comp || mode < 0 || ng > slots || ng > 4u * waves) return 1u;
   if (mode > 0) return (uint32_t)mode;
   return ng < 2u * waves ? 4u : ng < 4u * waves ? 2u : 1u;
+}
+
+// Longest list that one wavefront walks, for a walk root holding n particles.
+// At 2*10^5 particles a limit of 4096 leaves 1.3 % of the particles over it
+// and bounds the main pass's longest chain. In larger trees lists grow and
+// thousands of groups keep the chip busy while a long one is walked: the limit
+// grows with them (in the 2^23 galaxy, 32768 instead of 2^17 made the block
+// steps' walks 4 % shorter in group order and 1 % longer in the learned order).
+__host__ __device__ __forceinline__ uint32_t heavy_limit(uint32_t n) {
+  const uint32_t q = n / 64u;
+  return q < 4096u ? 4096u : q;
+}
+constexpr uint32_t kPartWork = 1024;   // particles under a part's cells, about
+constexpr uint32_t kMaxParts = 128;
+// a front cell holding more particles is opened further
+__device__ __forceinline__ uint32_t front_cell_max(uint32_t n) {
+  const uint32_t q = n / 256u;
+  return q < 64u ? 64u : q > 2048u ? 2048u : q;
+}
+
+// Group-wise MAC (see above): the cell with node words A = (com, b^2) and
+// q = B.y against the group's box, dA = delta_acc |a_old|.
+__device__ __forceinline__ bool mac_accept(float4 A, float q, float4 glo, float4 ghi, float dA,
+                                           int bootstrap) {
+  const float tx = fmaxf(fmaxf(glo.x - A.x, A.x - ghi.x), 0.0f);
+  const float ty = fmaxf(fmaxf(glo.y - A.y, A.y - ghi.y), 0.0f);
+  const float tz = fmaxf(fmaxf(glo.z - A.z, A.z - ghi.z), 0.0f);
+  const float d2 = __builtin_fmaf(tz, tz, __builtin_fmaf(ty, ty, tx * tx));
+  bool accept = false;
+  if (d2 > A.w) {
+    if (bootstrap) {
+      const float four_b2 = 4.0f * A.w;
+      accept = d2 > four_b2;
+    } else {
+      const float d4 = d2 * d2;
+      const float lhs = dA * d4;
+      accept = lhs >= q;
+    }
+  }
+  return accept;
 }
 
 __device__ __forceinline__ uint64_t mix64(uint64_t v) {
@@ -241,8 +304,8 @@ __device__ __forceinline__ void flush_run(const float4 *__restrict__ list, uint3
 // Flush the tile's cnt entries: whole blocks of 64 entries (the last one
 // possibly short), each into u0 followed by a rotation of the sums (the
 // compensated sum: all into its one sum). nblk counts the blocks added.
-template <bool kComp, bool kPot>
-__device__ __forceinline__ void flush_tile(float4 *__restrict__ list, uint32_t cnt, uint32_t K,
+template <bool kComp, bool kPot, uint32_t K>
+__device__ __forceinline__ void flush_tile(float4 *__restrict__ list, uint32_t cnt,
                                            uint32_t lane, uint32_t stream, uint32_t S,
                                            float4 pi, float eps2, RunSums<kComp, kPot> &R,
                                            uint32_t &nblk) {
@@ -297,261 +360,512 @@ __device__ __forceinline__ void store_group_result(const WalkArgs &a, uint32_t g
   }
 }
 
-template <bool kComp, bool kHash, bool kPot>
-__device__ __forceinline__ void walk_body(const WalkArgs &a, float4 *lds_list) {
-  const uint32_t wv = threadIdx.x >> 6;
-  const uint32_t lane = lane_id();
-  // LDS: per wave a list tile, then per wave the chunk's owner table
-  const uint32_t TS = a.tile + kListPad;  // tile + padding slots
-  float4 *list = lds_list + wv * TS;
-  float4 *s_ent = lds_list + kWalkWavesPerWG * TS + wv * 64;
-  uint32_t *s_incl =
-      reinterpret_cast<uint32_t *>(lds_list + kWalkWavesPerWG * (TS + 64)) + wv * 128;
-  uint32_t *s_src = s_incl + 64;
+// One wavefront's LDS: the chunk's owner table, then a list tile with its
+// padding (one base register: the parts are at fixed offsets).
+struct WaveLds {
+  float4 *base;
+  __device__ __forceinline__ float4 *ent() const { return base; }
+  __device__ __forceinline__ uint32_t *incl() const {
+    return reinterpret_cast<uint32_t *>(base + 64);
+  }
+  __device__ __forceinline__ uint32_t *src() const { return incl() + 64; }
+  __device__ __forceinline__ float4 *list() const { return base + 96; }
+};
+__device__ __forceinline__ WaveLds wave_lds(float4 *lds, uint32_t wv, uint32_t tile) {
+  return WaveLds{lds + wv * (tile + kListPad + 96u)};
+}
+
+// The group a wavefront walks for, per lane.
+struct WalkGroup {
+  float4 glo, ghi, pi;
+  uint32_t gb, gc, S, Wd, stream;
+};
+__device__ __forceinline__ WalkGroup load_group(const WalkArgs &a, uint32_t g, uint32_t lane) {
+  WalkGroup w;
+  w.gb = a.gbegin[g];
+  w.gc = a.gcount[g];
+  w.glo = a.gbox[2 * g];
+  w.ghi = a.gbox[2 * g + 1];
+  w.S = stream_count(w.gc);
+  w.Wd = 64u / w.S;
+  const uint32_t member = lane & (w.Wd - 1);
+  w.stream = lane / w.Wd;
+  w.pi = a.xyzm[w.gb + (member < w.gc ? member : 0u)];
+  return w;
+}
+
+// Entry counts of groups without results yet.
+constexpr uint32_t kEntNone = 0xffffffffu;   // failed
+constexpr uint32_t kEntHeavy = 0xfffffffeu;  // left to the parts' walk
+constexpr uint32_t kEntRetry = 0xfffffffdu;  // left to the retry pass
+// How a walk ended (wave-uniform).
+constexpr uint32_t kEndOverflow = 1, kEndCorrupt = 2, kEndHeavy = 4;
+
+// Traverse the subtrees of the `top` cells on the stack and add their list
+// (with K > 1 the blocks of this part) into R; entries counts the list.
+// Stops when the list exceeds `limit` entries.
+template <bool kComp, bool kHash, bool kPot, uint32_t K>
+__device__ __forceinline__ uint32_t walk_list(const WalkArgs &a, const WaveLds &l,
+                                              const WalkGroup &w, uint32_t *stk, uint32_t F,
+                                              uint32_t top, uint32_t part, uint32_t limit,
+                                              uint32_t ncell, uint32_t lane,
+                                              RunSums<kComp, kPot> &R, uint32_t &entries,
+                                              uint64_t &hsum) {
+  float4 *list = l.list();
+  float4 *s_ent = l.ent();
+  uint32_t *s_incl = l.incl(), *s_src = l.src();
+  const float dA = w.glo.w;
+  const uint32_t npart = a.n;
+  uint32_t visited = 0, cnt = 0;
+  uint32_t nblk = 0;  // list blocks this wavefront has added
+  uint32_t end = 0;
+  while (top > 0) {
+    const uint32_t nc = min(64u, top);
+    visited += nc;
+    if (visited > ncell) {  // a tree visits each cell at most once
+      end = kEndCorrupt;
+      break;
+    }
+    top -= nc;
+    const uint32_t cc = lane < nc ? stk[top + lane] : 0u;
+    const bool bad_c = lane < nc && cc >= ncell;
+    const bool has = lane < nc && !bad_c;
+    const uint32_t c = has ? cc : 0u;
+    float4 A = make_float4(0.f, 0.f, 0.f, 0.f), B = A;
+    if (has) {
+      A = a.nodeA[c];
+      B = a.nodeB[c];
+    }
+    const uint32_t w0 = __float_as_uint(B.z), w1 = __float_as_uint(B.w);
+    {
+      const bool lf = (w1 & kLeafBit) != 0u;
+      const uint32_t k = w1 & ~kLeafBit;
+      const bool bad_n = has && (lf ? (w0 > npart || k > npart - w0)
+                                    : (k > 8u || w0 > ncell || k > ncell - w0));
+      if (__ballot(bad_c || bad_n)) {
+        end = kEndCorrupt;
+        break;
+      }
+    }
+    const bool accept = has && mac_accept(A, B.y, w.glo, w.ghi, dA, a.bootstrap);
+    const bool leaf = (w1 & kLeafBit) != 0u;
+    const uint32_t ne = !has ? 0u : accept ? 1u : leaf ? (w1 & ~kLeafBit) : 0u;
+    const uint32_t nch = (has && !accept && !leaf) ? w1 : 0u;
+    // children -> stack (over the popped chunk, in lane order) and entries
+    // -> list: one scan of both counts (children <= 8 per lane, so at most
+    // 512 per chunk: 10 bits; entries in the 22 bits above), or two scans
+    // when a leaf is so large (coincident particles) that they might not fit
+    uint32_t chi, chtot, ei, etot;
+    if (__ballot(ne >= 65536u) == 0ull) {  // (wave-uniform)
+      const uint32_t both = wave_incl_scan_dpp((ne << 10) | nch);
+      const uint32_t btot = wave_last(both);
+      chi = both & 1023u;
+      chtot = btot & 1023u;
+      ei = both >> 10;
+      etot = btot >> 10;
+    } else {
+      chi = wave_incl_scan_dpp(nch);
+      chtot = wave_last(chi);
+      ei = wave_incl_scan_dpp(ne);
+      etot = wave_last(ei);
+    }
+    if (top + chtot > F) {
+      end = kEndOverflow;
+      break;
+    }
+    // every lane has read its candidate before any lane overwrites it
+    __builtin_amdgcn_wave_barrier();
+    for (uint32_t k = 0; k < nch; ++k) stk[top + chi - nch + k] = w0 + k;
+    top += chtot;
+    // entries -> LDS list (flushing full tiles). Lane k owns entries
+    // [incl_k - ne_k, incl_k); the copy is cooperative: lane r of the wave
+    // fetches entry done + r, finding its owner by binary search. With
+    // K > 1 only this part's blocks are copied.
+    if (kHash) {
+      if (accept) hsum += mix64((uint64_t)c);
+      else if (ne)
+        for (uint32_t k = 0; k < ne; ++k) hsum += mix64((1ull << 40) + w0 + k);
+    }
+    s_incl[lane] = ei;
+    s_src[lane] = accept ? 0xffffffffu : w0;
+    if (accept) s_ent[lane] = make_float4(A.x, A.y, A.z, B.x);
+    __builtin_amdgcn_wave_barrier();
+    uint32_t done = 0;
+    while (done < etot) {
+      const uint32_t J = entries + done;  // list index of the next entry
+      uint32_t seg;
+      if (K == 1u) {
+        seg = min(a.tile - cnt, etot - done);
+      } else {
+        // the rest of block J / 64 within this chunk; the tile (a multiple
+        // of 64 entries) holds whole blocks, so it always has room
+        seg = min(kBlk - (J & (kBlk - 1u)), etot - done);
+        if (((J / kBlk) & (K - 1u)) != part) {
+          done += seg;
+          continue;
+        }
+      }
+      for (uint32_t r = lane; r < seg; r += 64u) {
+        const uint32_t j = done + r;
+        uint32_t k = 0;
+#pragma unroll
+        for (uint32_t s = 32; s >= 1; s >>= 1)
+          if (s_incl[k + s - 1] <= j) k += s;
+        const uint32_t src = s_src[k];
+        const uint32_t first = k ? s_incl[k - 1] : 0u;
+        list[cnt + r] = (src == 0xffffffffu) ? s_ent[k] : a.xyzm[src + (j - first)];
+      }
+      cnt += seg;
+      done += seg;
+      if (cnt == a.tile) {
+        __builtin_amdgcn_wave_barrier();
+        flush_tile<kComp, kPot, K>(list, cnt, lane, w.stream, w.S, w.pi, a.eps2, R, nblk);
+        __builtin_amdgcn_wave_barrier();
+        cnt = 0;
+      }
+    }
+    __builtin_amdgcn_wave_barrier();  // owner table is rewritten next chunk
+    entries += etot;
+    if (entries > limit) {
+      end = kEndHeavy;
+      break;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+  if (end) cnt = 0;
+  __builtin_amdgcn_wave_barrier();
+  flush_tile<kComp, kPot, K>(list, cnt, lane, w.stream, w.S, w.pi, a.eps2, R, nblk);
+  __builtin_amdgcn_wave_barrier();
+  // complete the rotation period (4 / K blocks): then u_k is sum part + K k
+  if constexpr (!kComp)
+    for (; nblk & (RunSums<kComp, kPot>::kNum / K - 1u); ++nblk) R.advance(K);
+  return end;
+}
+
+// 64-bit sum over the wavefront, in every lane.
+__device__ __forceinline__ uint64_t wave_sum64(uint64_t v) {
+  uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
+  for (int d = 32; d >= 1; d >>= 1) {  // by 32-bit halves with carries
+    const uint32_t olo = __shfl_xor(lo, d, 64), ohi = __shfl_xor(hi, d, 64);
+    const uint32_t nlo = lo + olo;
+    hi = hi + ohi + (nlo < lo ? 1u : 0u);
+    lo = nlo;
+  }
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// Results of a whole group from each lane's sums.
+template <bool kPot>
+__device__ __forceinline__ void finish_group(const WalkArgs &a, const WalkGroup &w,
+                                             uint32_t lane, float sx, float sy, float sz,
+                                             float sw) {
+  stream_reduce(w.Wd, sx, sy, sz);
+  store_group_result(a, w.gb, w.gc, lane, sx, sy, sz);
+  if constexpr (kPot) {
+    // the member's own entry (r = eps exactly) is in its list: add its
+    // term back, phi_i = G (sum_j -m_j / r_j + m_i / eps)
+    stream_reduce1(w.Wd, sw);
+    if (lane < w.gc) {
+      const float self = w.pi.w * __builtin_amdgcn_rsqf(a.eps2);
+      a.phi[a.perm ? a.perm[w.gb + lane] : w.gb + lane] = a.G * (sw + self);
+    }
+  }
+}
+
+// Claims the next task beyond the nw first ones. The empty asm pins the
+// wave-uniform result here, before the loop's back edge.
+__device__ __forceinline__ uint32_t next_task(const WalkArgs &a, uint32_t nw, uint32_t lane) {
+  const uint32_t claim = atomicAdd(a.head, lane == 0 ? 1u : 0u);
+  uint32_t t = __builtin_amdgcn_readfirstlane(claim);
+  asm volatile("" : "+s"(t));
+  return nw + t;
+}
+
+// The persistent loop with K wavefronts per group (a power of two): task t is
+// part t mod K of queue position t / K. K is a constant here: as a run-time
+// value it cost the loop 3 vector registers (75 against 72), one resident
+// wavefront per SIMD, and spilled scalars.
+template <bool kComp, bool kHash, bool kPot, uint32_t K>
+__device__ __forceinline__ void walk_loop(const WalkArgs &a, const WaveLds &l, uint32_t ng,
+                                          uint32_t wv, uint32_t lane) {
   uint32_t *stk =
       a.frontier + (size_t)(blockIdx.x * kWalkWavesPerWG + wv) * (size_t)(a.fmask + 1);
-  const uint32_t F = a.fmask + 1;
-  const uint32_t ng = *a.qcount;
   const uint32_t ncell = a.sc->ncell;
-  const uint32_t npart = a.n;
-  // K wavefronts per group (a power of two); task t is part t mod K of
-  // queue position t / K
-  // (the compensated sum and the potential variant are never split)
-  const uint32_t K = split_factor(ng, gridDim.x * kWalkWavesPerWG, a.split_slots, a.split_mode,
-                                  kComp || kPot);
-  const uint32_t kshift = K == 4u ? 2u : K == 2u ? 1u : 0u;
+  constexpr uint32_t kshift = K == 4u ? 2u : K == 2u ? 1u : 0u;
+  // A wavefront's first task is its own number; it claims further ones only
+  // while there are more tasks than wavefronts. (When every wavefront made a
+  // first claim, 8192 atomics on one word, about 13 ns each, took 105 us of a
+  // walk of 132 tasks that needed 40.)
   // No lane-predicated region may sit in this loop: the compiler threads such
   // regions across the back-edge, and a wave that re-enters with lane 0 masked
   // off reads a stale queue index. Every lane joins the queue atomic (lane 0
   // adds 1, the rest 0) and the per-group results below are stored by every
   // lane (same value, same address).
-  for (;;) {
-    const uint32_t claim = atomicAdd(a.head, lane == 0 ? 1u : 0u);
-    const uint32_t task = __builtin_amdgcn_readfirstlane(claim);
+  const uint32_t nw = gridDim.x * kWalkWavesPerWG;
+  const uint32_t ntask = ng << kshift;
+  uint32_t task = __builtin_amdgcn_readfirstlane(blockIdx.x * kWalkWavesPerWG + wv);
+  for (bool first = true; first || ntask > nw; first = false) {
+    if (!first) task = next_task(a, nw, lane);
+    if (task >= ntask) break;
     const uint32_t qi = task >> kshift;
     const uint32_t part = task & (K - 1u);
-    if (qi >= ng) break;
     const uint32_t g = a.order ? a.order[qi] : qi;
-    const uint32_t gb = a.gbegin[g], gc = a.gcount[g];
-    const float4 glo = a.gbox[2 * g], ghi = a.gbox[2 * g + 1];
-    const float dA = glo.w;
-    const uint32_t S = stream_count(gc);
-    const uint32_t Wd = 64u / S;
-    const uint32_t member = lane & (Wd - 1);
-    const uint32_t stream = lane / Wd;
-    const bool mem_ok = member < gc;
-    const float4 pi = a.xyzm[gb + (mem_ok ? member : 0u)];
+    const WalkGroup w = load_group(a, g, lane);
+    const uint32_t root = a.groot ? a.groot[g] : 0u;
+    const uint32_t limit = heavy_limit(a.groot ? a.cpcount[root] : a.n);
+    stk[0] = root;  // (same value in every lane)
     RunSums<kComp, kPot> R;
     uint64_t hsum = 0;
-    stk[0] = a.groot ? a.groot[g] : 0u;  // the walk's root (same value in every lane)
-    uint32_t top = 1, visited = 0, cnt = 0;
-    uint32_t entries = 0;  // list entries so far (list index of the next one)
-    uint32_t nblk = 0;     // list blocks this wavefront has added
-    bool overflow = false, corrupt = false;
-    while (top > 0) {
-      const uint32_t nc = min(64u, top);
-      visited += nc;
-      if (visited > ncell) {  // a tree visits each cell at most once
-        corrupt = true;
-        break;
-      }
-      top -= nc;
-      const uint32_t cc = lane < nc ? stk[top + lane] : 0u;
-      const bool bad_c = lane < nc && cc >= ncell;
-      const bool has = lane < nc && !bad_c;
-      const uint32_t c = has ? cc : 0u;
-      float4 A = make_float4(0.f, 0.f, 0.f, 0.f), B = A;
-      if (has) {
-        A = a.nodeA[c];
-        B = a.nodeB[c];
-      }
-      const uint32_t w0 = __float_as_uint(B.z), w1 = __float_as_uint(B.w);
-      {
-        const bool lf = (w1 & kLeafBit) != 0u;
-        const uint32_t k = w1 & ~kLeafBit;
-        const bool bad_n = has && (lf ? (w0 > npart || k > npart - w0)
-                                      : (k > 8u || w0 > ncell || k > ncell - w0));
-        if (__ballot(bad_c || bad_n)) {
-          corrupt = true;
-          break;
-        }
-      }
-      bool accept = false;
-      if (has) {
-        const float tx = fmaxf(fmaxf(glo.x - A.x, A.x - ghi.x), 0.0f);
-        const float ty = fmaxf(fmaxf(glo.y - A.y, A.y - ghi.y), 0.0f);
-        const float tz = fmaxf(fmaxf(glo.z - A.z, A.z - ghi.z), 0.0f);
-        const float d2 = __builtin_fmaf(tz, tz, __builtin_fmaf(ty, ty, tx * tx));
-        if (d2 > A.w) {
-          if (a.bootstrap) {
-            const float four_b2 = 4.0f * A.w;
-            accept = d2 > four_b2;
-          } else {
-            const float d4 = d2 * d2;
-            const float lhs = dA * d4;
-            accept = lhs >= B.y;
-          }
-        }
-      }
-      const bool leaf = (w1 & kLeafBit) != 0u;
-      const uint32_t ne = !has ? 0u : accept ? 1u : leaf ? (w1 & ~kLeafBit) : 0u;
-      const uint32_t nch = (has && !accept && !leaf) ? w1 : 0u;
-      // children -> stack (over the popped chunk, in lane order) and entries
-      // -> list: one scan of both counts (children <= 8 per lane, so at most
-      // 512 per chunk: 10 bits; entries in the 22 bits above), or two scans
-      // when a leaf is so large (coincident particles) that they might not fit
-      uint32_t chi, chtot, ei, etot;
-      if (__ballot(ne >= 65536u) == 0ull) {  // (wave-uniform)
-        const uint32_t both = wave_incl_scan_dpp((ne << 10) | nch);
-        const uint32_t btot = wave_last(both);
-        chi = both & 1023u;
-        chtot = btot & 1023u;
-        ei = both >> 10;
-        etot = btot >> 10;
-      } else {
-        chi = wave_incl_scan_dpp(nch);
-        chtot = wave_last(chi);
-        ei = wave_incl_scan_dpp(ne);
-        etot = wave_last(ei);
-      }
-      if (top + chtot > F) {
-        overflow = true;
-        break;
-      }
-      // every lane has read its candidate before any lane overwrites it
-      __builtin_amdgcn_wave_barrier();
-      for (uint32_t k = 0; k < nch; ++k) stk[top + chi - nch + k] = w0 + k;
-      top += chtot;
-      // entries -> LDS list (flushing full tiles). Lane k owns entries
-      // [incl_k - ne_k, incl_k); the copy is cooperative: lane r of the wave
-      // fetches entry done + r, finding its owner by binary search. With
-      // K > 1 only this part's blocks are copied.
-      if (kHash) {
-        if (accept) hsum += mix64((uint64_t)c);
-        else if (ne)
-          for (uint32_t k = 0; k < ne; ++k) hsum += mix64((1ull << 40) + w0 + k);
-      }
-      s_incl[lane] = ei;
-      s_src[lane] = accept ? 0xffffffffu : w0;
-      if (accept) s_ent[lane] = make_float4(A.x, A.y, A.z, B.x);
-      __builtin_amdgcn_wave_barrier();
-      uint32_t done = 0;
-      while (done < etot) {
-        const uint32_t J = entries + done;  // list index of the next entry
-        uint32_t seg;
-        if (K == 1u) {
-          seg = min(a.tile - cnt, etot - done);
-        } else {
-          // the rest of block J / 64 within this chunk; the tile (a multiple
-          // of 64 entries) holds whole blocks, so it always has room
-          seg = min(kBlk - (J & (kBlk - 1u)), etot - done);
-          if (((J / kBlk) & (K - 1u)) != part) {
-            done += seg;
-            continue;
-          }
-        }
-        for (uint32_t r = lane; r < seg; r += 64u) {
-          const uint32_t j = done + r;
-          uint32_t k = 0;
-#pragma unroll
-          for (uint32_t s = 32; s >= 1; s >>= 1)
-            if (s_incl[k + s - 1] <= j) k += s;
-          const uint32_t src = s_src[k];
-          const uint32_t first = k ? s_incl[k - 1] : 0u;
-          list[cnt + r] = (src == 0xffffffffu) ? s_ent[k] : a.xyzm[src + (j - first)];
-        }
-        cnt += seg;
-        done += seg;
-        if (cnt == a.tile) {
-          __builtin_amdgcn_wave_barrier();
-          flush_tile<kComp, kPot>(list, cnt, K, lane, stream, S, pi, a.eps2, R, nblk);
-          __builtin_amdgcn_wave_barrier();
-          cnt = 0;
-        }
-      }
-      __builtin_amdgcn_wave_barrier();  // owner table is rewritten next chunk
-      entries += etot;
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-    // overflow and corrupt are wave-uniform: these branches are not
-    // lane-predicated; every lane joins the atomics and stores. Every part
-    // of a split group meets the same overflow (same traversal); part 0
-    // alone hands the group to the retry pass.
-    const bool handoff = overflow && !corrupt && a.retry != nullptr;
-    if (handoff) {
-      if (part == 0u) {
-        const uint32_t slot = __builtin_amdgcn_readfirstlane(
-            atomicAdd(a.nretry, lane == 0 ? 1u : 0u));
-        a.retry[slot] = g;
-      }
-    } else if (overflow || corrupt) {
-      atomicOr(&a.sc->status, overflow ? kStOverflow : kStCorrupt);
-    }
-    if (overflow || corrupt) cnt = 0;
-    __builtin_amdgcn_wave_barrier();
-    flush_tile<kComp, kPot>(list, cnt, K, lane, stream, S, pi, a.eps2, R, nblk);
-    __builtin_amdgcn_wave_barrier();
-    // complete the rotation period (4 / K blocks): then u_k is sum part + K k
-    if constexpr (!kComp)
-      for (; nblk & (RunSums<kComp, kPot>::kNum / K - 1u); ++nblk) R.advance(K);
-    if (K == 1u) {
+    uint32_t entries = 0;
+    const uint32_t end = walk_list<kComp, kHash, kPot, K>(
+        a, l, w, stk, a.fmask + 1u, 1u, part, limit, ncell, lane, R, entries, hsum);
+    // `end` is wave-uniform: these branches are not lane-predicated; every
+    // lane joins the atomics and stores. Every part of a split group ends the
+    // same way (same traversal); a group without results is handed on to the
+    // later passes by its entry count.
+    if (end == kEndCorrupt || (end == kEndOverflow && !a.may_retry))
+      atomicOr(&a.sc->status, end == kEndOverflow ? kStOverflow : kStCorrupt);
+    if constexpr (K == 1u) {
+      // (of no consequence for a group handed on: a later pass writes again)
       float sx, sy, sz, sw;
       R.total(sx, sy, sz, sw);
-      stream_reduce(Wd, sx, sy, sz);
-      store_group_result(a, gb, gc, lane, sx, sy, sz);
-      if constexpr (kPot) {
-        // the member's own entry (r = eps exactly) is in its list: add its
-        // term back, phi_i = G (sum_j -m_j / r_j + m_i / eps)
-        stream_reduce1(Wd, sw);
-        if (lane < gc) {
-          const float self = pi.w * __builtin_amdgcn_rsqf(a.eps2);
-          a.phi[a.perm ? a.perm[gb + lane] : gb + lane] = a.G * (sw + self);
-        }
-      }
-    } else if constexpr (!kComp && !kPot) {
+      finish_group<kPot>(a, w, lane, sx, sy, sz, sw);
+    } else {
       // this part's running sums into the queue slot: [sum][component][lane]
       float *slot = a.split + (size_t)qi * (kSplitSlotBytes / 4);
       slot[((part + 0u) * 3 + 0) * 64 + lane] = R.u0.x;
       slot[((part + 0u) * 3 + 1) * 64 + lane] = R.u0.y;
       slot[((part + 0u) * 3 + 2) * 64 + lane] = R.u0.z;
-      if (K == 2u) {
+      if constexpr (K == 2u) {
         slot[((part + 2u) * 3 + 0) * 64 + lane] = R.u1.x;
         slot[((part + 2u) * 3 + 1) * 64 + lane] = R.u1.y;
         slot[((part + 2u) * 3 + 2) * 64 + lane] = R.u1.z;
       }
     }
     if (part == 0u) {
-      if (kHash) {
-        uint32_t lo = (uint32_t)hsum, hi = (uint32_t)(hsum >> 32);
-        // 64-bit wave sum by 32-bit halves with carries
-        for (int d = 32; d >= 1; d >>= 1) {
-          const uint32_t olo = __shfl_xor(lo, d, 64), ohi = __shfl_xor(hi, d, 64);
-          const uint32_t nlo = lo + olo;
-          hi = hi + ohi + (nlo < lo ? 1u : 0u);
-          lo = nlo;
-        }
-        a.ghash[g] = ((uint64_t)hi << 32) | lo;  // butterfly: every lane holds the sum
-      }
-      a.gent[g] = (overflow || corrupt) ? 0xffffffffu : entries;
+      if (kHash) a.ghash[g] = wave_sum64(hsum);
+      a.gent[g] = end == 0u             ? entries
+                  : end == kEndHeavy    ? kEntHeavy
+                  : end == kEndOverflow ? kEntRetry
+                                        : kEntNone;
     }
   }
 }
 
-// Second kernel of a split walk: per queue position, the four running sums
-// of each lane added in order, then the stream butterfly and the results, as
-// an unsplit walk ends. Groups the walk handed to its retry pass (entry
-// count 0xffffffff) are left to it.
-__global__ __launch_bounds__(256) void k_walk_join(WalkArgs a, uint32_t walk_waves) {
-  const uint32_t ng = *a.qcount;
-  if (split_factor(ng, walk_waves, a.split_slots, a.split_mode, false) == 1u) return;
+template <bool kComp, bool kHash, bool kPot>
+__device__ __forceinline__ void walk_body(const WalkArgs &a, float4 *lds_list) {
+  const uint32_t wv = threadIdx.x >> 6;
   const uint32_t lane = lane_id();
-  const uint32_t nw = gridDim.x * (blockDim.x >> 6);
-  for (uint32_t qi = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x >> 6) +
-                                                    (threadIdx.x >> 6));
+  const WaveLds l = wave_lds(lds_list, wv, a.tile);
+  const uint32_t ng = *a.qcount;
+  // the compensated sum and the potential variant are never split
+  if constexpr (kComp || kPot) {
+    walk_loop<kComp, kHash, kPot, 1>(a, l, ng, wv, lane);
+  } else {
+    const uint32_t K =
+        split_factor(ng, gridDim.x * kWalkWavesPerWG, a.split_slots, a.split_mode, false);
+    if (K == 1u)
+      walk_loop<kComp, kHash, kPot, 1>(a, l, ng, wv, lane);
+    else if (K == 2u)
+      walk_loop<kComp, kHash, kPot, 2>(a, l, ng, wv, lane);
+    else
+      walk_loop<kComp, kHash, kPot, 4>(a, l, ng, wv, lane);
+  }
+}
+
+// ---------------------------------------------------------------- heavy groups
+// Front of a heavy group: starting from its walk root, cells that fail the MAC
+// and hold more than `big` particles are replaced by their children, in order,
+// round by round, until none is left or the front would not fit in kFrontCap
+// cells. NT threads of one workgroup; cur and nxt hold kFrontCap cells each.
+// Returns the front's length, with cur pointing at it (uniform).
+template <int NT>
+__device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t *wsum, uint32_t *total) {
+  const uint32_t inc = wave_incl_scan_dpp(v);
+  if constexpr (NT == 64) {
+    *total = wave_last(inc);
+    return inc - v;
+  } else {
+    const uint32_t w = threadIdx.x >> 6;
+    __syncthreads();  // wsum's last use
+    if (lane_id() == 63) wsum[w] = inc;
+    __syncthreads();
+    uint32_t off = 0, tot = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < NT / 64; ++q) {
+      off += q < w ? wsum[q] : 0u;
+      tot += wsum[q];
+    }
+    *total = tot;
+    return off + inc - v;
+  }
+}
+
+template <int NT>
+__device__ __forceinline__ uint32_t heavy_front(const WalkArgs &a, uint32_t root, float4 glo,
+                                                float4 ghi, uint32_t ncell, uint32_t big,
+                                                uint32_t *&cur, uint32_t *&nxt,
+                                                uint32_t *wsum) {
+  const uint32_t tid = threadIdx.x;
+  if (tid == 0) cur[0] = root;
+  __syncthreads();
+  uint32_t m = 1;
+  for (int round = 0; round <= kMaxLevel; ++round) {
+    uint32_t out = 0, opened = 0;
+    for (uint32_t k0 = 0; k0 < m; k0 += NT) {
+      const bool has = k0 + tid < m;
+      const uint32_t c = has ? cur[k0 + tid] : 0u;
+      uint32_t nout = has ? 1u : 0u, first = c;
+      if (has && c < ncell) {
+        const float4 A = a.nodeA[c], B = a.nodeB[c];
+        const uint32_t w0 = __float_as_uint(B.z), w1 = __float_as_uint(B.w);
+        const bool inner = !(w1 & kLeafBit) && w1 >= 1u && w1 <= 8u && w0 > c &&
+                           w0 < ncell && w1 <= ncell - w0;
+        if (inner && a.cpcount[c] > big &&
+            !mac_accept(A, B.y, glo, ghi, glo.w, a.bootstrap)) {
+          nout = w1;
+          first = w0;
+        }
+      }
+      const bool open = first != c;  // (a child's index is never its parent's)
+      uint32_t tot;
+      const uint32_t ex = block_scan<NT>(nout | (open ? 1u << 16 : 0u), wsum, &tot) & 0xffffu;
+      if (out + (tot & 0xffffu) <= kFrontCap)
+        for (uint32_t q = 0; q < nout; ++q) nxt[out + ex + q] = first + q;
+      out += tot & 0xffffu;
+      opened += tot >> 16;
+    }
+    __syncthreads();
+    if (opened == 0u || out > kFrontCap) break;  // (uniform)
+    uint32_t *t = cur;
+    cur = nxt;
+    nxt = t;
+    m = out;
+  }
+  return m;
+}
+
+// Cuts a front of m cells into parts of about equal weight (an accepted cell
+// weighs 1, another its particles): part r takes the cells [pb[r], pb[r + 1]).
+// Returns the number of parts (uniform); pb is in LDS.
+template <int NT>
+__device__ __forceinline__ uint32_t heavy_parts(const WalkArgs &a, float4 glo, float4 ghi,
+                                                uint32_t ncell, const uint32_t *cur, uint32_t m,
+                                                uint32_t *pb, uint32_t *wsum) {
+  const uint32_t tid = threadIdx.x;
+  auto weight = [&](uint32_t k) -> uint32_t {
+    if (k >= m) return 0u;
+    const uint32_t c = cur[k];
+    if (c >= ncell) return 1u;
+    return mac_accept(a.nodeA[c], a.nodeB[c].y, glo, ghi, glo.w, a.bootstrap)
+               ? 1u
+               : max(a.cpcount[c], 1u);
+  };
+  uint32_t W = 0, tot;
+  for (uint32_t k0 = 0; k0 < m; k0 += NT) {
+    (void)block_scan<NT>(weight(k0 + tid), wsum, &tot);
+    W += tot;
+  }
+  const uint32_t P = min(min((W + kPartWork - 1u) / kPartWork, kMaxParts), m);
+  uint32_t base = 0;
+  for (uint32_t k0 = 0; k0 < m; k0 += NT) {
+    const uint32_t k = k0 + tid, wt = weight(k);
+    const uint32_t pre = base + block_scan<NT>(wt, wsum, &tot);
+    if (k < m) {
+      const uint32_t p0 = (uint32_t)((uint64_t)pre * P / W);
+      const uint32_t p1 = (uint32_t)((uint64_t)(pre + wt) * P / W);
+      for (uint32_t r = p0 + 1u; r <= p1; ++r) pb[r] = k + 1u;
+      if (k == 0u) pb[0] = 0u;
+    }
+    base += tot;
+  }
+  __syncthreads();
+  return P;
+}
+
+// After the main pass. Blocks [0, front_blocks): fronts and parts of the
+// heavy groups (one workgroup per group; a group that finds no room in the
+// part or front buffers is left to k_heavy_end). The other blocks, when the
+// walk was split: per queue position, the four running sums of each lane
+// added in order, then the stream butterfly and the results, as an unsplit
+// walk ends; groups handed on (by their entry count) are left out. With no
+// front blocks (the launch before the retry pass) they also collect that
+// pass's queue.
+constexpr uint32_t kFrontBlocks = 256, kJoinBlocks = 512;
+__global__ __launch_bounds__(256) void k_walk_mid(WalkArgs a, uint32_t walk_waves, int hash,
+                                                  uint32_t front_blocks, int join) {
+  __shared__ uint32_t s_front[2 * kFrontCap];
+  __shared__ uint32_t s_pb[kMaxParts + 1], s_wsum[4], s_at[3], s_list[256];
+  const uint32_t ng = *a.qcount;
+  if (blockIdx.x < front_blocks) {
+    // the heavy ones among queue positions b, b + front_blocks, ...: consecutive
+    // positions go to different workgroups
+    const uint32_t ncell = a.sc->ncell;
+    for (uint32_t q0 = blockIdx.x; q0 < ng; q0 += 256u * front_blocks) {
+      const uint64_t qi = (uint64_t)q0 + (uint64_t)threadIdx.x * front_blocks;
+      if (threadIdx.x == 0) s_at[2] = 0u;
+      __syncthreads();
+      if (qi < ng) {
+        const uint32_t gq = a.order ? a.order[qi] : (uint32_t)qi;
+        if (a.gent[gq] == kEntHeavy) s_list[atomicAdd(&s_at[2], 1u)] = gq;
+      }
+      __syncthreads();
+      const uint32_t nl = s_at[2];
+      for (uint32_t j = 0; j < nl; ++j) {
+        const uint32_t g = s_list[j];
+        const uint32_t root = a.groot ? a.groot[g] : 0u;
+        const float4 glo = a.gbox[2 * g], ghi = a.gbox[2 * g + 1];
+        uint32_t *cur = s_front, *nxt = s_front + kFrontCap;
+        const uint32_t m =
+            heavy_front<256>(a, root, glo, ghi, ncell,
+                             front_cell_max(a.groot ? a.cpcount[root] : a.n), cur, nxt, s_wsum);
+        const uint32_t P = heavy_parts<256>(a, glo, ghi, ncell, cur, m, s_pb, s_wsum);
+        if (threadIdx.x == 0) {
+          const uint32_t h = atomicAdd(&a.sc->nheavy, 1u);
+          const uint32_t s0 = atomicAdd(&a.sc->nhpart, P), f0 = atomicAdd(&a.sc->nhfront, m);
+          const bool room = h < a.hslots && s0 < a.hslots && P <= a.hslots - s0 &&
+                            f0 < a.hfront_cap && m <= a.hfront_cap - f0;
+          a.heavy[h] = g;
+          if (h < a.hslots) a.hrec[h] = room ? make_uint2(s0, P) : make_uint2(0u, 0u);
+          a.gent[g] = 0u;
+          if (hash) a.ghash[g] = 0ull;
+          s_at[0] = s0;
+          s_at[1] = room ? f0 : kEntNone;
+        }
+        __syncthreads();
+        const uint32_t s0 = s_at[0], f0 = s_at[1];
+        const bool room = f0 != kEntNone;
+        for (uint32_t r = threadIdx.x; r < P; r += 256u)
+          if (s0 + r < a.hslots && s0 + r >= s0)
+            a.hparts[s0 + r] =
+                room ? make_uint4(g, f0 + s_pb[r], s_pb[r + 1] - s_pb[r], 0u)
+                     : make_uint4(g, 0u, 0u, 0u);  // nothing to walk
+        if (room)
+          for (uint32_t k = threadIdx.x; k < m; k += 256u) a.hfront[f0 + k] = cur[k];
+        __syncthreads();  // LDS is reused by the next group
+      }
+    }
+    return;
+  }
+  if (front_blocks == 0u) {
+    // before the retry pass: collect its queue
+    for (uint64_t qi = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; qi < ng;
+         qi += (uint64_t)gridDim.x * blockDim.x) {
+      const uint32_t g = a.order ? a.order[qi] : (uint32_t)qi;
+      if (a.gent[g] == kEntRetry) a.retry[atomicAdd(&a.sc->nretry, 1u)] = g;
+    }
+  }
+  if (!join || split_factor(ng, walk_waves, a.split_slots, a.split_mode, false) == 1u) return;
+  const uint32_t lane = lane_id();
+  const uint32_t nw = (gridDim.x - front_blocks) * (blockDim.x >> 6);
+  for (uint32_t qi = __builtin_amdgcn_readfirstlane(
+           (blockIdx.x - front_blocks) * (blockDim.x >> 6) + (threadIdx.x >> 6));
        qi < ng; qi += nw) {
     const uint32_t g = a.order ? a.order[qi] : qi;
-    if (a.gent[g] == 0xffffffffu) continue;
+    // (the front blocks may already have reset a heavy group's count: its
+    // results are written again by k_heavy_end)
+    if (a.gent[g] >= kEntRetry) continue;
     const uint32_t gb = a.gbegin[g], gc = a.gcount[g];
     const float *slot = a.split + (size_t)qi * (kSplitSlotBytes / 4);
     float v[4][3];
@@ -564,6 +878,177 @@ __global__ __launch_bounds__(256) void k_walk_join(WalkArgs a, uint32_t walk_wav
     float sz = ((v[0][2] + v[1][2]) + v[2][2]) + v[3][2];
     stream_reduce(64u / stream_count(gc), sx, sy, sz);
     store_group_result(a, gb, gc, lane, sx, sy, sz);
+  }
+}
+
+// A lane's sums over the parts of a heavy group, added in part order. The
+// compensated form carries each part's sum and correction.
+template <bool kComp, bool kPot>
+struct PartSums {
+  static constexpr uint32_t kWords = kPot ? 4 : 3;
+  float v[4] = {0.f, 0.f, 0.f, 0.f};
+  __device__ __forceinline__ static void store(float *slot, uint32_t lane,
+                                               const RunSums<kComp, kPot> &R) {
+    float x, y, z, w;
+    R.total(x, y, z, w);
+    slot[0 * 64 + lane] = x;
+    slot[1 * 64 + lane] = y;
+    slot[2 * 64 + lane] = z;
+    if constexpr (kPot) slot[3 * 64 + lane] = w;
+  }
+  __device__ __forceinline__ void add(const float (&p)[8]) {
+#pragma unroll
+    for (uint32_t k = 0; k < kWords; ++k) v[k] += p[k];
+  }
+  __device__ __forceinline__ void add(const RunSums<kComp, kPot> &R) {
+    float x, y, z, w;
+    R.total(x, y, z, w);
+    v[0] += x;
+    v[1] += y;
+    v[2] += z;
+    if constexpr (kPot) v[3] += w;
+  }
+  __device__ __forceinline__ float total(uint32_t k) const { return v[k]; }
+};
+template <bool kPot>
+struct PartSums<true, kPot> {
+  static constexpr uint32_t kWords = 8;
+  float v[4] = {0.f, 0.f, 0.f, 0.f}, c[4] = {0.f, 0.f, 0.f, 0.f};
+  __device__ __forceinline__ static void store(float *slot, uint32_t lane,
+                                               const RunSums<true, kPot> &R) {
+    const Acc3<true, kPot> &u = R.u0;
+    slot[0 * 64 + lane] = u.x;
+    slot[1 * 64 + lane] = u.y;
+    slot[2 * 64 + lane] = u.z;
+    slot[3 * 64 + lane] = u.w;
+    slot[4 * 64 + lane] = u.cx;
+    slot[5 * 64 + lane] = u.cy;
+    slot[6 * 64 + lane] = u.cz;
+    slot[7 * 64 + lane] = u.cw;
+  }
+  __device__ __forceinline__ void add(const float (&p)[8]) {
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) {
+      Acc3<true, kPot>::nadd(v[k], c[k], p[k]);
+      c[k] += p[4 + k];
+    }
+  }
+  __device__ __forceinline__ void add(const RunSums<true, kPot> &R) {
+    const Acc3<true, kPot> &u = R.u0;
+    const float p[8] = {u.x, u.y, u.z, u.w, u.cx, u.cy, u.cz, u.cw};
+    add(p);
+  }
+  __device__ __forceinline__ float total(uint32_t k) const { return v[k] + c[k]; }
+};
+
+// The parts of the heavy groups, taken from a queue as the main pass takes
+// groups: each wavefront walks the subtrees of one part's cells and stores
+// its lanes' sums in the part's slot.
+template <bool kComp, bool kHash, bool kPot>
+__global__ __launch_bounds__(64 * kWalkWavesPerWG) void k_heavy_walk(WalkArgs a) {
+  HIP_DYNAMIC_SHARED(float4, lds_list)
+  const uint32_t wv = threadIdx.x >> 6;
+  const uint32_t lane = lane_id();
+  const WaveLds l = wave_lds(lds_list, wv, a.tile);
+  uint32_t *stk =
+      a.frontier + (size_t)(blockIdx.x * kWalkWavesPerWG + wv) * (size_t)(a.fmask + 1);
+  const uint32_t np = min(a.sc->nhpart, a.hslots);
+  const uint32_t ncell = a.sc->ncell;
+  const uint32_t nw = gridDim.x * kWalkWavesPerWG;
+  uint32_t t = __builtin_amdgcn_readfirstlane(blockIdx.x * kWalkWavesPerWG + wv);
+  for (bool first = true; first || np > nw; first = false) {  // claims as in walk_loop
+    if (!first) t = next_task(a, nw, lane);
+    if (t >= np) break;
+    const uint4 part = a.hparts[t];
+    const uint32_t g = __builtin_amdgcn_readfirstlane(part.x);
+    const uint32_t f0 = __builtin_amdgcn_readfirstlane(part.y);
+    const uint32_t m = __builtin_amdgcn_readfirstlane(part.z);
+    const WalkGroup w = load_group(a, g, lane);
+    // (every lane stores; past the end the last cell again)
+    for (uint32_t k = 0; k < m; k += 64u) {
+      const uint32_t q = min(k + lane, m - 1u);
+      stk[q] = a.hfront[f0 + q];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    RunSums<kComp, kPot> R;
+    uint64_t hsum = 0;
+    uint32_t entries = 0;
+    const uint32_t end =
+        walk_list<kComp, kHash, kPot, 1>(a, l, w, stk, a.fmask + 1u, m, 0u, 0xffffffffu, ncell,
+                                         lane, R, entries, hsum);
+    if (end) atomicOr(&a.sc->status, end == kEndOverflow ? kStOverflow : kStCorrupt);
+    PartSums<kComp, kPot>::store(a.hsum + (size_t)t * a.hwords, lane, R);
+    atomicAdd(&a.gent[g], lane == 0 ? entries : 0u);
+    if (kHash) {
+      const unsigned long long hs = wave_sum64(hsum);
+      atomicAdd(&a.ghash[g], lane == 0 ? hs : 0ull);
+    }
+  }
+}
+
+// Results of the heavy groups: one wavefront (workgroup) per group adds its
+// parts' sums in order. A group that found no room for its parts is walked
+// here, part after part, with the same sums. Each workgroup's region of the
+// stack buffer holds a stack of `cap` cells and two fronts.
+template <bool kComp, bool kHash, bool kPot>
+__global__ __launch_bounds__(64) void k_heavy_end(WalkArgs a) {
+  HIP_DYNAMIC_SHARED(float4, lds_list)
+  __shared__ uint32_t s_pb[kMaxParts + 1];
+  using Sums = PartSums<kComp, kPot>;
+  const uint32_t lane = lane_id();
+  const WaveLds l = wave_lds(lds_list, 0u, a.tile);
+  uint32_t *stk = a.frontier + (size_t)blockIdx.x * (size_t)(a.fmask + 1u + 2u * kFrontCap);
+  const uint32_t nh = a.sc->nheavy, ncell = a.sc->ncell;
+  for (uint32_t h = blockIdx.x; h < nh; h += gridDim.x) {
+    const uint32_t g = __builtin_amdgcn_readfirstlane(a.heavy[h]);
+    const WalkGroup w = load_group(a, g, lane);
+    const uint2 rec = h < a.hslots ? a.hrec[h] : make_uint2(0u, 0u);
+    const uint32_t s0 = __builtin_amdgcn_readfirstlane(rec.x);
+    const uint32_t P = __builtin_amdgcn_readfirstlane(rec.y);
+    Sums T;
+    if (P > 0u) {
+      for (uint32_t r = 0; r < P; ++r) {
+        const float *slot = a.hsum + (size_t)(s0 + r) * a.hwords;
+        float p[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (uint32_t k = 0; k < Sums::kWords; ++k) p[k] = slot[k * 64 + lane];
+        T.add(p);
+      }
+    } else {
+      uint32_t *cur = stk + a.fmask + 1u, *nxt = cur + kFrontCap;
+      const uint32_t root = a.groot ? a.groot[g] : 0u;
+      const uint32_t m =
+          heavy_front<64>(a, root, w.glo, w.ghi, ncell,
+                          front_cell_max(a.groot ? a.cpcount[root] : a.n), cur, nxt, nullptr);
+      const uint32_t Q = heavy_parts<64>(a, w.glo, w.ghi, ncell, cur, m, s_pb, nullptr);
+      uint64_t hsum = 0;
+      uint32_t entries = 0, end = 0;
+      for (uint32_t r = 0; r < Q && end == 0u; ++r) {
+        const uint32_t k0 = __builtin_amdgcn_readfirstlane(s_pb[r]);
+        const uint32_t c = __builtin_amdgcn_readfirstlane(s_pb[r + 1]) - k0;
+        for (uint32_t k = 0; k < c; k += 64u) {
+          const uint32_t q = min(k + lane, c - 1u);
+          stk[q] = cur[k0 + q];
+        }
+        __syncthreads();
+        RunSums<kComp, kPot> R;
+        uint32_t ent = 0;
+        end = walk_list<kComp, kHash, kPot, 1>(a, l, w, stk, a.fmask + 1u, c, 0u, 0xffffffffu,
+                                               ncell, lane, R, ent, hsum);
+        entries += ent;
+        T.add(R);
+      }
+      if (end && lane == 0)
+        atomicOr(&a.sc->status, end == kEndOverflow ? kStOverflow : kStCorrupt);
+      if (lane == 0) a.gent[g] = entries;
+      if (kHash) {
+        const uint64_t hs = wave_sum64(hsum);
+        if (lane == 0) a.ghash[g] = hs;
+      }
+      __syncthreads();
+    }
+    finish_group<kPot>(a, w, lane, T.total(0), T.total(1), T.total(2), T.total(3));
   }
 }
 
@@ -646,15 +1131,6 @@ __global__ __launch_bounds__(kStatBlocks) void k_walk_stat_fold(
   }
 }
 
-// Both work queues' claim counters and the retry count start at zero.
-__global__ void k_walk_prep(DevScalars *sc) {
-  if (threadIdx.x == 0) {
-    sc->queue_head = 0;
-    sc->retry_head = 0;
-    sc->nretry = 0;
-  }
-}
-
 // The walk, and its retry pass as a kernel of its own (so that profiles and
 // the walk timing see the main pass alone).
 template <bool kComp, bool kHash>
@@ -713,8 +1189,19 @@ WalkArgs walk_args(const WalkCfg &c, const uint32_t *perm, int64_t n, float *ax,
   a.qcount = c.use_order ? &P.sc->nqueue : &P.sc->ngroup;
   a.groot = c.batch ? P.groot : nullptr;
   a.asort = c.asort_out ? P.asort : nullptr;
+  a.cpcount = P.cpcount;
+  // a stack that holds every cell of the tree cannot overflow: no retry pass
+  a.may_retry = c.frontier_cap < c.heavy_cap ? 1 : 0;
   a.retry = P.retry;
   a.nretry = &P.sc->nretry;
+  a.heavy = P.heavy;
+  a.hparts = P.hparts;
+  a.hrec = P.hrec;
+  a.hfront = P.hfront;
+  a.hsum = P.hsum;
+  a.hslots = (uint32_t)c.heavy_slots;
+  a.hfront_cap = (uint32_t)c.heavy_slots * kHeavyFrontPerSlot;
+  a.hwords = heavy_part_words(c.compensated);
   a.head = &P.sc->queue_head;
   a.frontier = P.frontier;
   a.gent = P.gent;
@@ -737,8 +1224,8 @@ WalkArgs walk_args(const WalkCfg &c, const uint32_t *perm, int64_t n, float *ax,
 }
 
 // per wave: list tile + padding (16 B/entry) + owner table (64 x (16 + 4 + 4) B)
-size_t walk_lds(const WalkCfg &c) {
-  return (size_t)kWalkWavesPerWG * ((c.list_tile + kListPad) * sizeof(float4) + 64 * 24);
+size_t walk_lds(const WalkCfg &c, int waves) {
+  return (size_t)waves * ((c.list_tile + kListPad) * sizeof(float4) + 64 * 24);
 }
 
 }  // namespace
@@ -759,39 +1246,74 @@ size_t walk_lds(const WalkCfg &c) {
     }                                                                          \
   } while (0)
 
+namespace {
+template <bool kComp, bool kHash, bool kPot>
+void heavy_passes(const WalkCfg &c, WalkArgs a, const Ptrs &P, hipStream_t st) {
+  a.frontier = P.frontier;
+  a.fmask = (uint32_t)c.heavy_cap - 1u;
+  a.head = &P.sc->heavy_head;
+  hipLaunchKernelGGL((k_heavy_walk<kComp, kHash, kPot>), dim3(c.heavy_waves / kWalkWavesPerWG),
+                     dim3(64 * kWalkWavesPerWG), walk_lds(c, kWalkWavesPerWG), st, a);
+  hipLaunchKernelGGL((k_heavy_end<kComp, kHash, kPot>), dim3(c.heavy_end_blocks), dim3(64),
+                     walk_lds(c, 1), st, a);
+}
+template <bool kComp>
+void heavy_passes_of(const WalkCfg &c, const WalkArgs &a, const Ptrs &P, hipStream_t st) {
+  if (c.phi)
+    c.hash ? heavy_passes<kComp, true, true>(c, a, P, st)
+           : heavy_passes<kComp, false, true>(c, a, P, st);
+  else
+    c.hash ? heavy_passes<kComp, true, false>(c, a, P, st)
+           : heavy_passes<kComp, false, false>(c, a, P, st);
+}
+}  // namespace
+
+// The main pass; the retry pass (groups that outgrew a stack smaller than the
+// bound, walked again with the largest stacks, by as many wavefronts as the
+// stack buffer then serves; a second overflow is reported, it cannot happen);
+// the fronts of heavy groups and the sums of a split walk; the heavy groups'
+// parts and their sums. (The queue counters are cleared by k_group_bounds,
+// which runs before every walk.)
 void launch_walk(const WalkCfg &c, const uint32_t *perm, int64_t n, float *ax, float *ay,
                  float *az, const Ptrs &P, hipStream_t st) {
   const WalkArgs a = walk_args(c, perm, n, ax, ay, az, P);
-  const int blocks = c.num_cu * c.waves_per_cu / kWalkWavesPerWG;
-  hipLaunchKernelGGL(k_walk_prep, dim3(1), dim3(64), 0, st, P.sc);
-  if (c.phi) {
-    NB_WALK_LAUNCH(k_walk_pot, c, dim3(blocks), walk_lds(c), st, a);
-    return;  // never split
-  }
-  NB_WALK_LAUNCH(k_walk, c, dim3(blocks), walk_lds(c), st, a);
-  // a split walk's results (the kernel returns at once when the walk was not split)
-  if (!c.compensated)
-    hipLaunchKernelGGL(k_walk_join, dim3(512), dim3(256), 0, st, a,
-                       (uint32_t)(blocks * kWalkWavesPerWG));
-}
-
-// Retry pass: the groups that outgrew a small stack (frontier_cap below the
-// bound), walked by a few wavefronts whose stack holds 512 cells per level of
-// the deepest tree; a second overflow is reported (it cannot happen).
-void launch_walk_retry(const WalkCfg &c, const uint32_t *perm, int64_t n, float *ax,
-                       float *ay, float *az, const Ptrs &P, hipStream_t st) {
-  WalkArgs r = walk_args(c, perm, n, ax, ay, az, P);
-  r.order = P.retry;
-  r.qcount = &P.sc->nretry;
-  r.retry = nullptr;
-  r.frontier = P.frontier2;
-  r.fmask = (uint32_t)c.frontier2_cap - 1u;
-  r.head = &P.sc->retry_head;  // cleared with the walk's counters
-  r.split_mode = -1;           // results written by the pass itself
+  // a wavefront for every four particles is more than a tree has tasks
+  // (groups of 8 and more, at most 4 wavefronts each); fewer only share
+  const int blocks = (int)std::min<int64_t>(
+      c.num_cu * c.waves_per_cu / kWalkWavesPerWG,
+      std::max<int64_t>(cdiv(n, 4 * kWalkWavesPerWG), 64));
+  const uint32_t waves = (uint32_t)(blocks * kWalkWavesPerWG);
+  const size_t lds = walk_lds(c, kWalkWavesPerWG);
+  const int join = c.compensated || c.phi ? 0 : 1;  // these are never split
   if (c.phi)
-    NB_WALK_LAUNCH(k_walk_pot, c, dim3(c.retry_waves / kWalkWavesPerWG), walk_lds(c), st, r);
+    NB_WALK_LAUNCH(k_walk_pot, c, dim3(blocks), lds, st, a);
   else
-    NB_WALK_LAUNCH(k_walk_retry, c, dim3(c.retry_waves / kWalkWavesPerWG), walk_lds(c), st, r);
+    NB_WALK_LAUNCH(k_walk, c, dim3(blocks), lds, st, a);
+  if (a.may_retry) {
+    // the split walk's sums first: they leave out the groups handed on
+    hipLaunchKernelGGL(k_walk_mid, dim3(kJoinBlocks), dim3(256), 0, st, a, waves, 0, 0u, join);
+    WalkArgs r = a;
+    r.order = P.retry;
+    r.qcount = &P.sc->nretry;
+    r.may_retry = 0;
+    r.fmask = (uint32_t)c.heavy_cap - 1u;
+    r.head = &P.sc->retry_head;
+    r.split_mode = -1;  // results written by the pass itself
+    const dim3 rgrid(c.heavy_waves / kWalkWavesPerWG);
+    if (c.phi)
+      NB_WALK_LAUNCH(k_walk_pot, c, rgrid, lds, st, r);
+    else
+      NB_WALK_LAUNCH(k_walk_retry, c, rgrid, lds, st, r);
+    hipLaunchKernelGGL(k_walk_mid, dim3(kFrontBlocks), dim3(256), 0, st, a, waves,
+                       c.hash ? 1 : 0, kFrontBlocks, 0);
+  } else {
+    hipLaunchKernelGGL(k_walk_mid, dim3(kFrontBlocks + (join ? kJoinBlocks : 0u)), dim3(256), 0,
+                       st, a, waves, c.hash ? 1 : 0, kFrontBlocks, join);
+  }
+  if (c.compensated)
+    heavy_passes_of<true>(c, a, P, st);
+  else
+    heavy_passes_of<false>(c, a, P, st);
 }
 
 }  // namespace nb

@@ -62,7 +62,9 @@ struct DevScalars {
   uint32_t nactive;        // particles active at the end of the current step
   uint32_t nretry;         // groups handed from the walk to its retry pass
   uint32_t retry_head;     // the retry pass's work queue
-  uint32_t pad[2];
+  uint32_t nheavy;         // groups walked in parts
+  uint32_t nhpart, nhfront;  // parts and front cells asked for
+  uint32_t heavy_head;     // the parts' work queue
   WalkStat wstat;
   unsigned long long bar_epoch;  // launches of the grid-barrier calcNode so far
   uint32_t istart[kLevels + 1];  // internal cells of level l: ilist[istart[l] .. istart[l + 1])
@@ -88,14 +90,17 @@ struct Layout {
       off_cpbegin, off_cpcount, off_cfchild, off_cnchild, off_cparent,
       off_mom64, off_nodeA, off_nodeB, off_gbegin, off_gcount, off_gbox,
       off_gent, off_ghash, off_order, off_frontier, off_prevcnt, off_atmp, off_retry,
-      off_frontier2, off_feat, off_target, off_pred, off_plast, off_okeys, off_qtmp, off_mlpw,
+      off_feat, off_target, off_pred, off_plast, off_okeys, off_qtmp, off_mlpw,
       off_mlpm, off_mlpv, off_mlpg, off_mlppart, off_gref, off_sysoff, off_sysbox, off_groot,
       off_inv, off_asort, off_split, off_gid, off_gflag, off_ilist, off_leaves, off_scan,
-      off_longcnt, off_longslot, off_wpart;
+      off_longcnt, off_longslot, off_wpart, off_heavy, off_hparts, off_hrec, off_hfront, off_hsum;
   size_t off_kpos[2], off_kvel[2], off_kacc[2], off_kmass[2], off_kpt[2], off_klv[2];
-  int64_t frontier2_cap = 0;  // retry pass stack: more than any tree needs
-  int retry_waves = 0;
   int64_t split_slots = 0;  // queue positions with room for split-walk partial sums
+  // heavy groups: part slots, the stack no tree outgrows, and the wavefronts
+  // (k_heavy_walk, the retry pass) and workgroups (k_heavy_end) with such a
+  // stack in `frontier`
+  int64_t heavy_slots = 0, heavy_cap = 0;
+  int heavy_waves = 0, heavy_end_blocks = 0;
   size_t total = 0;
 };
 
@@ -129,7 +134,6 @@ struct Ptrs {
   uint32_t *prevcnt;    // per group: entries of the previous walk (ordering)
   float *atmp;          // [3][n] walk output of a block step (caller order)
   uint32_t *retry;      // groups whose frontier outgrew the main pass
-  uint32_t *frontier2;  // retry pass frontier rings
   // cost model of the walk queue
   float4 *feat;         // per group: 4 features
   float *target;        // per group: log2 interactions of its last walk
@@ -156,6 +160,11 @@ struct Ptrs {
   uint32_t *longcnt;    // per build block: its cells longer than one block (<= kLevels)
   uint32_t *longslot;   // [blocks][kLevels] those cells
   unsigned long long *wpart;  // [kStatBlocks][4] partials of the walk statistics
+  uint32_t *heavy;      // groups over the list limit of one wavefront
+  uint4 *hparts;        // [heavy_slots] their parts: (group, front begin, cells, -)
+  uint2 *hrec;          // [heavy_slots] per such group: first part, parts
+  uint32_t *hfront;     // [heavy_slots][kHeavyFrontPerSlot] front cells
+  float *hsum;          // [heavy_slots][heavy_part_words()] partial sums per lane
   // block steps inside one nbody_step call: the state in key order, two sets
   // (a rebuild permutes set c into set 1 - c)
   double *kpos[2];      // [3][n] x, y, z (FP64)
@@ -166,8 +175,10 @@ struct Ptrs {
   int8_t *klv[2];       // [n] block-step levels
 };
 
-// stepping = false: no room for the key-ordered step state (tree forces only)
-Layout make_layout(const nbody_params &p, int64_t n_max, int num_cu, bool stepping = true);
+// stepping = false: no room for the key-ordered step state and the cost model
+// (tree forces only). split_slots: at most so many split-walk slots.
+Layout make_layout(const nbody_params &p, int64_t n_max, int num_cu, bool stepping = true,
+                   int64_t split_slots = INT64_MAX);
 Ptrs carve(void *base, const Layout &L);
 
 // FP32 coordinates and masses of particle i at x[i * stride], y[i * stride],
@@ -230,20 +241,26 @@ struct WalkCfg {
   int num_cu;
   int use_order;  // walk the groups order[0 .. nqueue) instead of all groups
   bool hash;      // record the per-group entry hash
-  int64_t frontier2_cap;
-  int retry_waves;
   bool batch;     // per-group roots (several systems in one tree)
   bool asort_out;  // also write the outputs, with |a|, to P.asort in key order
   int split;       // wavefronts per group: 0 by queue length, else 1, 2 or 4
   int64_t split_slots;
+  int64_t heavy_slots, heavy_cap;
+  int heavy_waves, heavy_end_blocks;
   float *phi = nullptr;  // potential output (caller order): the potential variant
 };
-// enqueue the walk kernel (after clearing its queue counters), then its
-// retry pass for groups whose stack overflowed
+constexpr uint32_t kFrontCap = 4096;  // cells of a heavy group's front, at most
+// front cells per part slot of the heavy groups' buffers
+constexpr uint32_t kHeavyFrontPerSlot = 64;
+// FP32 words of one part's sums: 64 lanes x (3 components and the potential,
+// twice for the compensated sum and its correction)
+__host__ __device__ constexpr uint32_t heavy_part_words(int compensated) {
+  return 64u * (compensated ? 8u : 4u);
+}
+// enqueue the walk: main pass, retry pass for groups whose stack overflowed,
+// and the passes of the heavy groups
 void launch_walk(const WalkCfg &c, const uint32_t *perm, int64_t n, float *ax,
                  float *ay, float *az, const Ptrs &P, hipStream_t st);
-void launch_walk_retry(const WalkCfg &c, const uint32_t *perm, int64_t n, float *ax,
-                       float *ay, float *az, const Ptrs &P, hipStream_t st);
 void launch_direct(int64_t n, const float *x, const float *y, const float *z,
                    const float *m, float G, float eps, float *ax, float *ay,
                    float *az, hipStream_t st);
