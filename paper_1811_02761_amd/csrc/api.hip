@@ -1246,8 +1246,12 @@ nbody_status nbody_direct64(nbody_ctx *ctx, int64_t n, const float *x, const flo
   if (n < 1 || n_target < 0 || !x || !y || !z || !m || !targets || !ax || !ay || !az)
     return NBODY_EINVAL;
   if (n_target == 0) return NBODY_OK;
+  // scratch of a bound workspace: the cost model's gradient shares, free
+  // between its calls (none is needed: see k_direct64)
+  double *part = ctx->bound ? reinterpret_cast<double *>(ctx->P.mlppart) : nullptr;
   launch_direct64(n, x, y, z, m, n_target, targets, (double)ctx->p.G, (double)ctx->p.eps, ax,
-                  ay, az, aabs, phi, ctx->st);
+                  ay, az, aabs, phi, part,
+                  (int64_t)kMlpWaves * (kMlpMaxParams + 1) / 2, ctx->st);
   return hip_status();
 }
 

@@ -1,4 +1,6 @@
 // k_misc.hip -- direct summation (Eq. 1) and the leapfrog kick / drift.
+#include <algorithm>
+
 #include "nbody_internal.h"
 
 namespace nb {
@@ -49,73 +51,134 @@ __global__ __launch_bounds__(256) void k_direct(int64_t n, const float *__restri
 // walk): inputs are FP32 positions and masses promoted to FP64; every pair
 // j != i (by index) adds G m_j dx / (r^2 + eps^2)^(3/2) to a_i, G m_j |dx| /
 // (r^2 + eps^2)^(3/2) to the scale A_i and -G m_j / (r^2 + eps^2)^(1/2) to
-// phi_i. A workgroup takes 32 targets; its 8 lane groups ("phases") take
-// every 8th particle of each 256-particle tile staged in LDS, and the 8
-// partial sums of a target are added in phase order at the end.
-constexpr int kD64Targets = 32;
-constexpr int kD64Phases = 8;
-__global__ __launch_bounds__(256) void k_direct64(int64_t n, const float *__restrict__ x,
-                                                  const float *__restrict__ y,
-                                                  const float *__restrict__ z,
-                                                  const float *__restrict__ m, int64_t nt,
-                                                  const int64_t *__restrict__ tgt, double G,
-                                                  double eps2, double *__restrict__ ax,
-                                                  double *__restrict__ ay,
-                                                  double *__restrict__ az,
-                                                  double *__restrict__ aabs,
-                                                  double *__restrict__ phi) {
-  __shared__ float4 tile[256];
-  __shared__ double part[5][kD64Phases][kD64Targets];
-  const int t = threadIdx.x % kD64Targets, ph = threadIdx.x / kD64Targets;
-  const int64_t k = (int64_t)blockIdx.x * kD64Targets + t;
-  const bool ok = k < nt;
-  int64_t i = ok ? tgt[k] : -1;
-  if (i >= n) i = -1;
-  const bool live = i >= 0;  // a target outside [0, n) sums nothing
-  const int64_t ii = live ? i : 0;
-  const double xi = x[ii], yi = y[ii], zi = z[ii];
-  double sx = 0.0, sy = 0.0, sz = 0.0, sa = 0.0, sp = 0.0;
-  for (int64_t j0 = 0; j0 < n; j0 += 256) {
-    const int64_t jl = j0 + threadIdx.x;
-    tile[threadIdx.x] = jl < n ? make_float4(x[jl], y[jl], z[jl], m[jl])
-                               : make_float4(0.f, 0.f, 0.f, 0.f);
-    __syncthreads();
-    const int cnt = (int)min((int64_t)256, n - j0);
-    for (int q = ph; live && q < cnt; q += kD64Phases) {
-      if (j0 + q == i) continue;
-      const float4 e = tile[q];
-      const double dx = (double)e.x - xi, dy = (double)e.y - yi, dz = (double)e.z - zi;
-      const double d2 = dx * dx + dy * dy + dz * dz;
-      const double r2 = d2 + eps2;
-      const double r = sqrt(r2);
-      const double w = G * (double)e.w / (r2 * r);
-      sx += w * dx;
-      sy += w * dy;
-      sz += w * dz;
-      sa += w * sqrt(d2);
-      sp -= G * (double)e.w / r;
-    }
-    __syncthreads();
+// phi_i. Bound by FP64 VALU issue: about 45 FP64 instructions per pair. A
+// workgroup takes kD64Targets targets and a slice of the particles, each
+// thread every 256th particle of the slice for all the targets (a load serves
+// four pairs, no LDS); sums over the workgroup's threads in a fixed order.
+// Slices fill the chip when there are few targets; their sums are added in
+// slice order, by k_direct64_fold or (without scratch) in the workgroup, to
+// the same bits. 2048 targets of 2^20 particles: 64 workgroups of 32 targets
+// took 37.3 ms (a quarter of the CUs, IEEE square roots and divisions), this
+// form 2.9 ms.
+constexpr int kD64Targets = 4;
+constexpr int kD64Out = 5 * kD64Targets;  // sums of a workgroup: [target][5]
+
+// 1 / sqrt(x) for finite x > 0: the hardware's estimate and one third-order
+// step, within about 1 ulp.
+__device__ __forceinline__ double rsqrt_refined(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = __builtin_fma(-x * y, y, 1.0);
+  return __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
+}
+
+// Adds the pair (target, particle j) to the target's five sums.
+__device__ __forceinline__ void pair64(double (&a)[5], double dx, double dy, double dz,
+                                       double mj, double eps2) {
+  const double d2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
+  const double r2 = d2 + eps2;
+  const double rinv = r2 < INFINITY ? rsqrt_refined(r2) : __builtin_amdgcn_rsq(r2);
+  // |dx|: squares of FP32 differences are 0 or over 1e-90
+  const double d = d2 * rsqrt_refined(d2 + 1e-300);
+  const double mr = mj * rinv;
+  const double w = mr * (rinv * rinv);
+  a[0] = __builtin_fma(w, dx, a[0]);
+  a[1] = __builtin_fma(w, dy, a[1]);
+  a[2] = __builtin_fma(w, dz, a[2]);
+  a[3] = __builtin_fma(w, d, a[3]);
+  a[4] -= mr;
+}
+
+__global__ __launch_bounds__(256) void k_direct64(
+    int64_t n, const float *__restrict__ x, const float *__restrict__ y,
+    const float *__restrict__ z, const float *__restrict__ m, int64_t nt,
+    const int64_t *__restrict__ tgt, double G, double eps2, int slices, int64_t slice_len,
+    double *__restrict__ part, double *__restrict__ ax, double *__restrict__ ay,
+    double *__restrict__ az, double *__restrict__ aabs, double *__restrict__ phi) {
+  __shared__ double s_sum[4][kD64Out];
+  const int64_t k0 = (int64_t)blockIdx.x * kD64Targets;
+  double xi[kD64Targets], yi[kD64Targets], zi[kD64Targets];
+  int64_t it[kD64Targets];
+#pragma unroll
+  for (int t = 0; t < kD64Targets; ++t) {
+    int64_t i = k0 + t < nt ? tgt[k0 + t] : -1;
+    if (i >= n || i < 0) i = -1;  // a target outside [0, n) sums nothing
+    it[t] = i;
+    const int64_t ii = i < 0 ? 0 : i;
+    xi[t] = x[ii];
+    yi[t] = y[ii];
+    zi[t] = z[ii];
   }
-  part[0][ph][t] = sx;
-  part[1][ph][t] = sy;
-  part[2][ph][t] = sz;
-  part[3][ph][t] = sa;
-  part[4][ph][t] = sp;
-  __syncthreads();
-  if (ph == 0 && ok) {
-    double o[5];
-    for (int c = 0; c < 5; ++c) {
-      double v = 0.0;
-      for (int q = 0; q < kD64Phases; ++q) v += part[c][q][t];
-      o[c] = v;
+  double total = 0.0;  // thread q < kD64Out: sum q over the slices
+  const int s0 = part ? (int)blockIdx.y : 0, s1 = part ? s0 + 1 : slices;
+  for (int sl = s0; sl < s1; ++sl) {
+    const int64_t j0 = sl * slice_len, j1 = min(n, j0 + slice_len);
+    double a[kD64Targets][5];
+#pragma unroll
+    for (int t = 0; t < kD64Targets; ++t)
+#pragma unroll
+      for (int c = 0; c < 5; ++c) a[t][c] = 0.0;
+    for (int64_t jb = j0; jb < j1; jb += 256) {
+      const int64_t j = jb + threadIdx.x;
+      bool self = false;  // (uniform) some target is among these particles
+#pragma unroll
+      for (int t = 0; t < kD64Targets; ++t) self |= it[t] >= jb && it[t] < jb + 256;
+      if (j >= j1) continue;
+      const double xj = x[j], yj = y[j], zj = z[j], mj = m[j];
+      if (self) {
+#pragma unroll
+        for (int t = 0; t < kD64Targets; ++t)
+          if (j != it[t]) pair64(a[t], xj - xi[t], yj - yi[t], zj - zi[t], mj, eps2);
+      } else {
+#pragma unroll
+        for (int t = 0; t < kD64Targets; ++t)
+          pair64(a[t], xj - xi[t], yj - yi[t], zj - zi[t], mj, eps2);
+      }
     }
-    ax[k] = o[0];
-    ay[k] = o[1];
-    az[k] = o[2];
-    if (aabs) aabs[k] = o[3];
-    if (phi) phi[k] = o[4];
+    __syncthreads();  // s_sum's last use
+#pragma unroll
+    for (int t = 0; t < kD64Targets; ++t)
+#pragma unroll
+      for (int c = 0; c < 5; ++c) {
+        double v = a[t][c];
+        for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
+        if (lane_id() == 0) s_sum[threadIdx.x >> 6][5 * t + c] = v;
+      }
+    __syncthreads();
+    if (threadIdx.x < kD64Out) {
+      const int q = threadIdx.x;
+      const double v = ((s_sum[0][q] + s_sum[1][q]) + s_sum[2][q]) + s_sum[3][q];
+      if (part)
+        part[((int64_t)blockIdx.x * slices + sl) * kD64Out + q] = v;
+      else
+        total += v;
+    }
   }
+  if (part || threadIdx.x >= kD64Out) return;
+  const int64_t k = k0 + threadIdx.x / 5;
+  if (k >= nt) return;
+  int64_t i = tgt[k];
+  if (i >= n || i < 0) total = 0.0;
+  double *const out[5] = {ax, ay, az, aabs, phi};
+  double *o = out[threadIdx.x % 5];
+  if (o) o[k] = G * total;
+}
+
+// The slices' sums of each target, in slice order.
+__global__ __launch_bounds__(256) void k_direct64_fold(
+    int64_t n, int64_t nt, const int64_t *__restrict__ tgt, double G, int slices,
+    const double *__restrict__ part, double *__restrict__ ax, double *__restrict__ ay,
+    double *__restrict__ az, double *__restrict__ aabs, double *__restrict__ phi) {
+  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;  // (target, sum)
+  const int64_t k = e / 5, b = k / kD64Targets;
+  if (k >= nt) return;
+  const int q = (int)(e - b * kD64Out);
+  double total = 0.0;
+  for (int sl = 0; sl < slices; ++sl) total += part[(b * slices + sl) * kD64Out + q];
+  const int64_t i = tgt[k];
+  if (i >= n || i < 0) total = 0.0;
+  double *const out[5] = {ax, ay, az, aabs, phi};
+  double *o = out[e % 5];
+  if (o) o[k] = G * total;
 }
 
 // v += a * (dt/2), FP32, one rounding per operation.
@@ -219,9 +282,19 @@ void launch_direct(int64_t n, const float *x, const float *y, const float *z,
 void launch_direct64(int64_t n, const float *x, const float *y, const float *z,
                      const float *m, int64_t nt, const int64_t *tgt, double G, double eps,
                      double *ax, double *ay, double *az, double *aabs, double *phi,
-                     hipStream_t st) {
-  hipLaunchKernelGGL(k_direct64, dim3((unsigned)cdiv(nt, kD64Targets)), dim3(256), 0, st, n, x,
-                     y, z, m, nt, tgt, G, eps * eps, ax, ay, az, aabs, phi);
+                     double *part, int64_t part_words, hipStream_t st) {
+  // about 2048 workgroups (eight per CU; five are resident), each thread with
+  // two particles at least; the same slices with and without scratch
+  const int64_t groups = cdiv(nt, kD64Targets);
+  const int slices = (int)std::max<int64_t>(1, std::min<int64_t>(2048 / groups, cdiv(n, 512)));
+  const int64_t slice_len = cdiv(n, slices);
+  if (slices == 1 || groups * slices * kD64Out > part_words) part = nullptr;
+  hipLaunchKernelGGL(k_direct64, dim3((unsigned)groups, part ? slices : 1), dim3(256), 0, st, n,
+                     x, y, z, m, nt, tgt, G, eps * eps, slices, slice_len, part, ax, ay, az,
+                     aabs, phi);
+  if (part)
+    hipLaunchKernelGGL(k_direct64_fold, dim3((unsigned)cdiv(5 * nt, 256)), dim3(256), 0, st, n,
+                       nt, tgt, G, slices, part, ax, ay, az, aabs, phi);
 }
 
 void launch_kick(int64_t n, float *vx, float *vy, float *vz, const float *ax,

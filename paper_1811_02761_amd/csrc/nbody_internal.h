@@ -264,10 +264,11 @@ void launch_walk(const WalkCfg &c, const uint32_t *perm, int64_t n, float *ax,
 void launch_direct(int64_t n, const float *x, const float *y, const float *z,
                    const float *m, float G, float eps, float *ax, float *ay,
                    float *az, hipStream_t st);
+// part: part_words words of 64 bits of scratch, or null
 void launch_direct64(int64_t n, const float *x, const float *y, const float *z,
                      const float *m, int64_t nt, const int64_t *tgt, double G, double eps,
                      double *ax, double *ay, double *az, double *aabs, double *phi,
-                     hipStream_t st);
+                     double *part, int64_t part_words, hipStream_t st);
 void launch_kick(int64_t n, float *vx, float *vy, float *vz, const float *ax,
                  const float *ay, const float *az, float hdt, hipStream_t st);
 // Where a drift puts the FP32 image of the new positions: with xyzm set,
