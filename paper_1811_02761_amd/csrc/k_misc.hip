@@ -5,10 +5,14 @@
 
 namespace nb {
 
-// Eq. 1 by direct summation, FP32: each lane owns one i, j-tiles of 256 are
-// staged in LDS and read by broadcast. Same interaction arithmetic as the
-// walk's flush, so it calibrates the walk's arithmetic rate. The j == i term
-// contributes exactly zero because eps > 0.
+// Eq. 1 by direct summation, FP32: the interaction arithmetic of the walk's
+// flush, so it calibrates the walk's arithmetic rate. The j == i term
+// contributes exactly zero because eps > 0. A workgroup takes kTg targets and
+// all particles, staged in LDS; its 256 / kTg streams of kTg lanes take every
+// (256 / kTg)-th particle and their sums are added in a fixed order. With one
+// target per lane (kTg = 256) a few thousand particles filled 16 CUs of 256:
+// 4096 particles 131 us, 10.6 us with 4 targets per workgroup.
+template <int kTg>
 __global__ __launch_bounds__(256) void k_direct(int64_t n, const float *__restrict__ x,
                                                 const float *__restrict__ y,
                                                 const float *__restrict__ z,
@@ -16,29 +20,54 @@ __global__ __launch_bounds__(256) void k_direct(int64_t n, const float *__restri
                                                 float eps2, float *__restrict__ ax,
                                                 float *__restrict__ ay,
                                                 float *__restrict__ az) {
-  __shared__ float4 tile[256];
-  const int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x;
+  constexpr int kStreams = 256 / kTg;
+  constexpr int kTile = kTg == 256 ? 256 : 1024;
+  __shared__ float4 tile[kTile];
+  const int t = threadIdx.x % kTg, stream = threadIdx.x / kTg;
+  const int64_t i = blockIdx.x * (int64_t)kTg + t;
   float4 pi = make_float4(0.f, 0.f, 0.f, 0.f);
   if (i < n) pi = make_float4(x[i], y[i], z[i], m[i]);
   float sx = 0.f, sy = 0.f, sz = 0.f;
-  for (int64_t j0 = 0; j0 < n; j0 += 256) {
-    const int64_t j = j0 + threadIdx.x;
-    tile[threadIdx.x] = j < n ? make_float4(x[j], y[j], z[j], m[j]) : make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int64_t j0 = 0; j0 < n; j0 += kTile) {
+#pragma unroll
+    for (int q = 0; q < kTile; q += 256) {
+      const int64_t j = j0 + q + threadIdx.x;
+      tile[q + threadIdx.x] =
+          j < n ? make_float4(x[j], y[j], z[j], m[j]) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
     __syncthreads();
-    const int cnt = (int)min((int64_t)256, n - j0);
+    const int cnt = (int)min((int64_t)kTile, n - j0);
+    float ux = 0.f, uy = 0.f, uz = 0.f;  // the tile's sum (shorter chains of roundings)
 #pragma unroll 8
-    for (int k = 0; k < cnt; ++k) {
+    for (int k = stream; k < cnt; k += kStreams) {
       const float4 e = tile[k];
       const float dx = e.x - pi.x, dy = e.y - pi.y, dz = e.z - pi.z;
       const float r2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, __builtin_fmaf(dx, dx, eps2)));
       const float rinv = __builtin_amdgcn_rsqf(r2);
       const float mr = e.w * rinv;
       const float f = mr * (rinv * rinv);
-      sx = __builtin_fmaf(f, dx, sx);
-      sy = __builtin_fmaf(f, dy, sy);
-      sz = __builtin_fmaf(f, dz, sz);
+      ux = __builtin_fmaf(f, dx, ux);
+      uy = __builtin_fmaf(f, dy, uy);
+      uz = __builtin_fmaf(f, dz, uz);
     }
+    sx += ux;
+    sy += uy;
+    sz += uz;
     __syncthreads();
+  }
+  if constexpr (kTg < 256) {
+    for (int d = kTg; d < 64; d <<= 1) {
+      sx += __shfl_xor(sx, d, 64);
+      sy += __shfl_xor(sy, d, 64);
+      sz += __shfl_xor(sz, d, 64);
+    }
+    // (the tile is free: one sum per wavefront and target)
+    if (lane_id() < kTg) tile[(threadIdx.x >> 6) * kTg + lane_id()] = make_float4(sx, sy, sz, 0.f);
+    __syncthreads();
+    if (threadIdx.x >= kTg) return;
+    sx = ((tile[t].x + tile[kTg + t].x) + tile[2 * kTg + t].x) + tile[3 * kTg + t].x;
+    sy = ((tile[t].y + tile[kTg + t].y) + tile[2 * kTg + t].y) + tile[3 * kTg + t].y;
+    sz = ((tile[t].z + tile[kTg + t].z) + tile[2 * kTg + t].z) + tile[3 * kTg + t].z;
   }
   if (i < n) {
     ax[i] = G * sx;
@@ -275,8 +304,19 @@ static int grid_1d(int64_t n) {
 void launch_direct(int64_t n, const float *x, const float *y, const float *z,
                    const float *m, float G, float eps, float *ax, float *ay, float *az,
                    hipStream_t st) {
-  hipLaunchKernelGGL(k_direct, dim3(cdiv(n, 256)), dim3(256), 0, st, n, x, y, z, m, G,
-                     eps * eps, ax, ay, az);
+  // the most targets per workgroup that still make four workgroups per CU
+  auto go = [&](auto kernel, int64_t tg) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)cdiv(n, tg)), dim3(256), 0, st, n, x, y, z, m, G,
+                       eps * eps, ax, ay, az);
+  };
+  if (n >= 256 * 1024)
+    go(k_direct<256>, 256);
+  else if (n >= 64 * 1024)
+    go(k_direct<64>, 64);
+  else if (n >= 16 * 1024)
+    go(k_direct<16>, 16);
+  else
+    go(k_direct<4>, 4);
 }
 
 void launch_direct64(int64_t n, const float *x, const float *y, const float *z,

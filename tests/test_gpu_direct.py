@@ -1,5 +1,6 @@
 """Direct summation at the edges of its work splits against the CPU oracle:
-FP64 for target counts that are no
+FP32 (targets per workgroup 4, 16, 64 and 256 by the particle count; ragged
+tiles) under the suite's force rule, FP64 for target counts that are no
 multiple of a workgroup's four, with and without scratch (the same bits)."""
 import ctypes as C
 
@@ -7,9 +8,24 @@ import numpy as np
 import pytest
 
 import nbody_inputs as I
-from test_gpu_parity import _dev, _np, nb, torch  # noqa: F401
+from test_gpu_parity import TOL, _dev, _np, _say, nb, torch  # noqa: F401
 
 pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 257, 1023, 1025, 16383, 16384 + 5, 65536 + 3, 262144 + 9])
+def test_direct_fp32_edges(nb, torch, orc, n):
+    p = I.plummer(n, 5)
+    x, y, z, _, _, _, m = p.f32()
+    ctx = nb.Context(nb.Params(), n_max=16)
+    got = np.stack([_np(t) for t in ctx.direct(*(_dev(torch, a) for a in (x, y, z, m)))], 1)
+    ctx.sync()
+    sub = np.unique(np.concatenate([[0, n - 1], np.linspace(0, n - 1, min(n, 200)).astype(int)]))
+    ref, A = orc.direct(np.stack([x, y, z], 1).astype(np.float64), m,
+                        targets=sub.astype(np.int64), want_aabs=True)
+    d = np.linalg.norm(got[sub] - ref, axis=1)
+    _say("direct", n, "max |da| / A %.2g" % (d / np.maximum(A, 1e-300)).max())
+    assert (d <= TOL * A).all()
 
 
 @pytest.mark.parametrize("n,nt", [(1, 1), (300, 3), (5000, 5), (5000, 64), (70001, 17),
