@@ -278,7 +278,7 @@ Layout make_layout(const nbody_params &p, int64_t n, int num_cu, bool stepping,
   L.off_mlpm = take(4 * W);
   L.off_mlpv = take(4 * W);
   L.off_mlpg = take(4 * (W + 1));
-  L.off_mlppart = take(4 * (stepping ? (size_t)kMlpWaves * (W + 1) : 0));
+  L.off_mlppart = take(4 * (stepping ? (size_t)kMlpShares * (W + 1) : 0));
   L.off_gref = take(4 * N);
   L.off_sysoff = take(4 * (size_t)(kMaxSystems + 1));
   L.off_sysbox = take(32 * (size_t)kMaxSystems);
@@ -1251,7 +1251,7 @@ nbody_status nbody_direct64(nbody_ctx *ctx, int64_t n, const float *x, const flo
   double *part = ctx->bound ? reinterpret_cast<double *>(ctx->P.mlppart) : nullptr;
   launch_direct64(n, x, y, z, m, n_target, targets, (double)ctx->p.G, (double)ctx->p.eps, ax,
                   ay, az, aabs, phi, part,
-                  (int64_t)kMlpWaves * (kMlpMaxParams + 1) / 2, ctx->st);
+                  (int64_t)kMlpShares * (kMlpMaxParams + 1) / 2, ctx->st);
   return hip_status();
 }
 
@@ -1427,18 +1427,19 @@ nbody_status nbody_costmodel_train(nbody_ctx *ctx, int32_t hidden, float *w, int
       !(lr > 0.0f) || ((uintptr_t)feat & 15u) != 0)
     return NBODY_EINVAL;
   const Ptrs &P = ctx->P;
-  const int64_t np = mlp_nparams(hidden);
-  launch_mlp_standardize(reinterpret_cast<const float4 *>(feat), rows, w, ctx->st);
-  launch_fill_u32(reinterpret_cast<uint32_t *>(P.mlpm), 0u, np, ctx->st);  // +0.0f
-  launch_fill_u32(reinterpret_cast<uint32_t *>(P.mlpv), 0u, np, ctx->st);
-  for (int32_t t = 1; t <= steps; ++t) {
-    launch_mlp_grad(hidden, w, rows, reinterpret_cast<const float4 *>(feat), target,
-                    P.mlppart, P.mlpg, ctx->st);
-    if (loss_out &&
-        hipMemcpyAsync(&loss_out[t - 1], &P.mlpg[np], sizeof(float), hipMemcpyDeviceToHost,
-                       ctx->st) != hipSuccess)
+  launch_mlp_standardize(hidden, reinterpret_cast<const float4 *>(feat), rows, w, P.mlpm,
+                         P.mlpv, P.mlppart, ctx->st);
+  // the losses stay on the device (mlpg) and are copied in blocks: a copy per
+  // step to the caller's pageable memory made every step wait for the host
+  for (int32_t t0 = 0; t0 < steps; t0 += kMlpMaxParams) {
+    const int32_t nb_steps = std::min<int32_t>(steps - t0, kMlpMaxParams);
+    for (int32_t k = 0; k < nb_steps; ++k)
+      launch_mlp_train_step(hidden, w, rows, reinterpret_cast<const float4 *>(feat), target,
+                            P.mlppart, P.mlpm, P.mlpv, t0 + k + 1, lr, 0.9f, 0.999f, 1e-8f,
+                            P.mlpg + k, ctx->st);
+    if (loss_out && hipMemcpyAsync(loss_out + t0, P.mlpg, sizeof(float) * (size_t)nb_steps,
+                                   hipMemcpyDeviceToHost, ctx->st) != hipSuccess)
       return NBODY_EHIP;
-    launch_adam(np, w, P.mlpg, P.mlpm, P.mlpv, t, lr, 0.9f, 0.999f, 1e-8f, ctx->st);
   }
   if ((s = hip_status()) != NBODY_OK) return s;
   if (hipStreamSynchronize(ctx->st) != hipSuccess) return NBODY_EHIP;

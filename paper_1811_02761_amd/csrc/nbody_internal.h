@@ -374,7 +374,7 @@ void launch_digit_sort(int64_t n, const uint32_t *n_dev, int shift, const uint64
 // cost model of the walk queue
 constexpr int kMlpMaxHidden = 64;
 constexpr int kMlpMaxParams = 8 + 7 * kMlpMaxHidden + kMlpMaxHidden * kMlpMaxHidden + 1;
-constexpr int kMlpWaves = 256;  // wavefronts of the gradient kernel
+constexpr int kMlpShares = 256;  // workgroups of the gradient kernel
 bool mlp_hidden_ok(int H);
 int64_t mlp_nparams(int H);
 void launch_mlp_forward(int H, const float *w, int64_t rows, const uint32_t *rows_dev,
@@ -384,8 +384,16 @@ void launch_mlp_grad(int H, const float *w, int64_t rows, const float4 *feat,
                      const float *target, float *partial, float *grad_loss, hipStream_t st);
 void launch_adam(int64_t np, float *w, const float *g, float *m, float *v, int step, float lr,
                  float b1, float b2, float eps, hipStream_t st);
-// w[0 .. 8): the model's input standardisation from the training rows
-void launch_mlp_standardize(const float4 *feat, int64_t rows, float *w, hipStream_t st);
+// gradient and Adam step in one: w, m, v updated in place, *loss (device) the
+// mean squared error before the step
+void launch_mlp_train_step(int H, float *w, int64_t rows, const float4 *feat,
+                           const float *target, float *partial, float *m, float *v, int step,
+                           float lr, float b1, float b2, float eps, float *loss,
+                           hipStream_t st);
+// w[0 .. 8): the model's input standardisation from the training rows; m and v
+// (the model's parameters) cleared
+void launch_mlp_standardize(int H, const float4 *feat, int64_t rows, float *w, float *m,
+                            float *v, float *scratch, hipStream_t st);
 // features of the queued groups (queued) or of every group
 void launch_cost_features(int64_t n, bool queued, const uint32_t *perm, const Ptrs &P,
                           hipStream_t st);
