@@ -43,9 +43,15 @@
 
 namespace nb {
 
-constexpr int kChunksPerWave = 16;
-constexpr uint32_t kWaveSpan = 64u * kChunksPerWave;  // sorted particles per wavefront
-static_assert(kWaveSpan % kBuildThreads == 0, "wavefront ranges start at build blocks");
+// Sorted particles per wavefront of the big cells' pass, in chunks of 64. A
+// chunk is a serial chain of its levels (about 3.5 us), so a small set takes
+// short ranges (1000 particles on one wavefront: 40 us); every range ends with
+// a merge per level, and the merges of all ranges meet on the few top cells, so
+// a large set takes long ones (1000, 16411 and 200003 particles: 45, 59 and 67
+// us for both parts with ranges of 16 chunks, 8, 11 and 23 with these).
+constexpr int kChunksLarge = 16, kChunksMid = 4, kChunksSmall = 1;
+constexpr int64_t kMidB2 = 32 * 1024, kLargeB2 = 1024 * 1024;  // first n of mid and large
+static_assert(kChunksMid * 64 % kBuildThreads == 0, "ranges start at build blocks");
 constexpr uint32_t kNoCell = 0xffffffffu;
 constexpr uint32_t kSmallCell = 64;   // bigger cells go to the particle pass (the build's E)
 constexpr uint32_t kLeafStage = 512;  // particles staged per wavefront in the leaf pass
@@ -310,15 +316,16 @@ __global__ __launch_bounds__(256) void k_mom_levels_grid(DevScalars *__restrict_
 // b2 of the internal cells of at most kSmallCell particles: 32 lanes per
 // cell (two particles per lane at most), coalesced loads, then a maximum
 // over the half wavefront.
-__global__ __launch_bounds__(256) void k_mom_b2small(DevScalars *__restrict__ sc, uint32_t n,
-                                                     const uint4 *__restrict__ ilist,
-                                                     const uint32_t *__restrict__ cpbegin,
-                                                     const float4 *__restrict__ xyzm,
-                                                     float4 *__restrict__ nodeA) {
+__device__ __forceinline__ void b2_small(DevScalars *__restrict__ sc, uint32_t n,
+                                         const uint4 *__restrict__ ilist,
+                                         const uint32_t *__restrict__ cpbegin,
+                                         const float4 *__restrict__ xyzm,
+                                         float4 *__restrict__ nodeA, uint32_t block,
+                                         uint32_t blocks) {
   const uint32_t ncell = sc->ncell, total = sc->istart[kLevels];
   const uint32_t lane = lane_id(), h = lane & 31u;
-  const uint32_t nhalf = gridDim.x * (blockDim.x >> 5);
-  for (uint32_t t0 = (blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 2u; t0 < total;
+  const uint32_t nhalf = blocks * (blockDim.x >> 5);
+  for (uint32_t t0 = (block * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 2u; t0 < total;
        t0 += nhalf) {
     const uint32_t t = t0 + (lane >> 5);  // this half's cell
     uint4 e = make_uint4(0u, 0u, 0u, 0u);
@@ -363,22 +370,34 @@ __device__ __forceinline__ void b2_merge(float4 *__restrict__ nodeA, uint32_t c,
 // starting next) and the carried run (cell, maximum). At the start of every
 // 64 particles lane l also fetches the centre of mass of the level-l cell
 // they continue (one load for all levels).
-__global__ __launch_bounds__(256) void k_mom_b2big(DevScalars *__restrict__ sc, uint32_t n,
-                                                   uint32_t nblk,
-                                                   const uint32_t *__restrict__ pinfo,
-                                                   const uint32_t *__restrict__ lvlblk,
-                                                   const float4 *__restrict__ xyzm,
-                                                   float4 *__restrict__ nodeA) {
+template <int kChunks>
+__device__ __forceinline__ void b2_big(DevScalars *__restrict__ sc, uint32_t n, uint32_t nblk,
+                                       const uint32_t *__restrict__ pinfo,
+                                       const uint32_t *__restrict__ lvlblk,
+                                       const float4 *__restrict__ xyzm,
+                                       float4 *__restrict__ nodeA, uint32_t block) {
   const uint32_t lane = lane_id();
-  const uint32_t wave = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  const uint64_t r0 = (uint64_t)wave * kWaveSpan;
+  const uint32_t wave = block * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  const uint64_t r0 = (uint64_t)wave * (64u * kChunks);
   if (r0 >= n) return;  // wave-uniform
-  const uint32_t r1 = (uint32_t)std::min<uint64_t>(n, r0 + kWaveSpan);
+  const uint32_t r1 = (uint32_t)std::min<uint64_t>(n, r0 + 64u * kChunks);
   const uint32_t ncell = sc->ncell;
-  const uint64_t le = lanes_le(lane);
   uint32_t base = 0;
   if (lane < (uint32_t)kLevels)
     base = sc->lvl_off[lane] + lvlblk[(size_t)lane * nblk + r0 / kBuildThreads];
+  // a range inside a build block: the starts of the block's particles before it
+  if constexpr (kChunks * 64 < kBuildThreads) {
+    for (uint32_t c0 = (uint32_t)(r0 / kBuildThreads * kBuildThreads); c0 < (uint32_t)r0;
+         c0 += 64u) {
+      const uint32_t q = pinfo[c0 + lane];
+      const int qs = q & 31, qD = (q >> 5) & 31;
+      const uint32_t st = qs <= qD ? ((2u << qD) - (1u << qs)) : 0u;
+      for (int l = 0; l < kLevels; ++l) {
+        const uint32_t c = (uint32_t)__popcll(__ballot((st >> l) & 1u));
+        if (lane == (uint32_t)l) base += c;
+      }
+    }
+  }
   uint32_t ccell = kNoCell, cmax = 0u;
   uint32_t npi = 0u;
   float4 np = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -494,6 +513,24 @@ __global__ __launch_bounds__(256) void k_mom_b2big(DevScalars *__restrict__ sc, 
   if (lane < (uint32_t)kLevels && ccell != kNoCell) b2_merge(nodeA, ccell, cmax);
 }
 
+// Both parts in one launch (they write different cells): the big cells' blocks
+// first, as the longer ones.
+template <int kChunks>
+__global__ __launch_bounds__(256) void k_mom_b2(DevScalars *__restrict__ sc, uint32_t n,
+                                                uint32_t nblk, uint32_t big_blocks,
+                                                const uint32_t *__restrict__ pinfo,
+                                                const uint32_t *__restrict__ lvlblk,
+                                                const uint4 *__restrict__ ilist,
+                                                const uint32_t *__restrict__ cpbegin,
+                                                const float4 *__restrict__ xyzm,
+                                                float4 *__restrict__ nodeA) {
+  if (blockIdx.x < big_blocks)
+    b2_big<kChunks>(sc, n, nblk, pinfo, lvlblk, xyzm, nodeA, blockIdx.x);
+  else
+    b2_small(sc, n, ilist, cpbegin, xyzm, nodeA, blockIdx.x - big_blocks,
+             gridDim.x - big_blocks);
+}
+
 // ---------------------------------------------------------------- phase 4
 __global__ __launch_bounds__(256) void k_mom_q(const DevScalars *__restrict__ sc, float G,
                                                const uint4 *__restrict__ ilist,
@@ -532,10 +569,12 @@ void launch_moments(int64_t n, float G, const Ptrs &P, const Layout &L, int mode
     gl = std::min<int64_t>(std::max<int64_t>(gl, 1), 2048);
     // with level_cells (internal cells per level of a recent tree) runs of
     // levels with at most kNarrowCells cells go to one single-workgroup
-    // launch each (correct for any counts; only the speed depends on them)
+    // launch each (correct for any counts; only the speed depends on them);
+    // without (the first tree, the allocation-free call) every level of a
+    // small tree does: 21 launches of 3 us against about 30 us for 2^16 particles
     int hi = -1;  // top of the open run of narrow levels
     for (int l = kMaxLevel - 1; l >= 0; --l) {
-      const bool narrow = level_cells && level_cells[l] <= kNarrowCells;
+      const bool narrow = level_cells ? level_cells[l] <= kNarrowCells : n <= kNarrowTree;
       if (narrow) {
         if (hi < 0) hi = l;
         if (l > 0) continue;
@@ -554,11 +593,17 @@ void launch_moments(int64_t n, float G, const Ptrs &P, const Layout &L, int mode
   }
   int64_t gi = cdiv(n, 256 * 4);
   gi = std::min<int64_t>(std::max<int64_t>(gi, 1), 4096);
-  hipLaunchKernelGGL(k_mom_b2small, dim3(gi), dim3(256), 0, st, P.sc, (uint32_t)n, P.ilist,
-                     P.cpbegin, P.xyzm, P.nodeA);
-  const uint32_t waves = (uint32_t)cdiv(n, kWaveSpan);
-  hipLaunchKernelGGL(k_mom_b2big, dim3((uint32_t)cdiv(waves, 4)), dim3(256), 0, st, P.sc,
-                     (uint32_t)n, nblk, P.pinfo, P.lvlblk, P.xyzm, P.nodeA);
+  auto b2 = [&](auto kernel, int chunks) {
+    const uint32_t big = (uint32_t)cdiv(n, 4 * 64 * chunks);
+    hipLaunchKernelGGL(kernel, dim3(big + (uint32_t)gi), dim3(256), 0, st, P.sc, (uint32_t)n,
+                       nblk, big, P.pinfo, P.lvlblk, P.ilist, P.cpbegin, P.xyzm, P.nodeA);
+  };
+  if (n >= kLargeB2)
+    b2(k_mom_b2<kChunksLarge>, kChunksLarge);
+  else if (n >= kMidB2)
+    b2(k_mom_b2<kChunksMid>, kChunksMid);
+  else
+    b2(k_mom_b2<kChunksSmall>, kChunksSmall);
   hipLaunchKernelGGL(k_mom_q, dim3(gi), dim3(256), 0, st, P.sc, G, P.ilist, P.nodeA, P.nodeB);
 }
 

@@ -217,6 +217,7 @@ constexpr int kBarSlots = 1024;     // workgroups of the persistent launch, at m
 // kMaxLevel), or null; it only shapes the launches (levels with at most
 // kNarrowCells cells are run by one workgroup), never the result
 constexpr uint32_t kNarrowCells = 1024;
+constexpr int64_t kNarrowTree = 64 * 1024;  // (particles) all levels, without counts
 void launch_moments(int64_t n, float G, const Ptrs &P, const Layout &L, int mode,
                     const uint32_t *level_cells, hipStream_t st);
 // asort (may be null): key-ordered a_old with |a|, read instead of a gather
