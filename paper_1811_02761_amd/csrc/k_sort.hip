@@ -8,6 +8,8 @@
 // lanes sharing a digit; their popcount below the lane is the rank). Ranks
 // follow input position, so each pass is stable and equal keys keep their
 // input order.
+#include <utility>
+
 #include "nbody_internal.h"
 
 namespace nb {
@@ -199,17 +201,163 @@ void launch_digit_sort(int64_t n, const uint32_t *n_dev, int shift, const uint64
                      kin, vin, n, shift, hist, nblk, totals, kout, vout, n_dev);
 }
 
+// One tile of kSortTile pairs sorted in LDS by all eight digits; 1024 threads,
+// item `it` of thread t at position (t / 64) 256 + 64 it + t mod 64, so ranks in
+// (wave, item, lane) order are stable. Values move as 16-bit tile positions.
+constexpr int kTileThreads = 1024;
+constexpr int kTileWaves = kTileThreads / 64;
+constexpr int kTileItems = kSortTile / kTileThreads;
+__global__ __launch_bounds__(kTileThreads) void k_sort_tile(
+    const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vin, int64_t n,
+    uint64_t *__restrict__ kout, uint32_t *__restrict__ vout) {
+  __shared__ uint64_t sk[kSortTile];
+  __shared__ uint16_t si[kSortTile];
+  __shared__ uint32_t cnt[kTileWaves][kSortRadix];
+  __shared__ uint32_t wsum[kSortRadix / 64];
+  const int64_t tile0 = blockIdx.x * (int64_t)kSortTile;
+  const int m = (int)min((int64_t)kSortTile, n - tile0);
+  const int w = threadIdx.x >> 6;
+  const int p0 = w * (64 * kTileItems) + (int)lane_id();
+  uint64_t k[kTileItems];
+  uint32_t v[kTileItems], r[kTileItems];
+#pragma unroll
+  for (int it = 0; it < kTileItems; ++it) {
+    const int p = p0 + 64 * it;
+    k[it] = p < m ? kin[tile0 + p] : 0ull;
+    v[it] = (uint32_t)p;
+  }
+  for (int shift = 0; shift < 64; shift += kSortBits) {
+    for (int t = threadIdx.x; t < kTileWaves * kSortRadix; t += kTileThreads)
+      (&cnt[0][0])[t] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < kTileItems; ++it) {
+      const bool valid = p0 + 64 * it < m;  // valid pairs stay in [0, m)
+      const uint64_t vmask = __ballot(valid);
+      const uint32_t d = (uint32_t)(k[it] >> shift) & (kSortRadix - 1);
+      const uint64_t peers = match_digit(d, vmask);
+      const uint32_t below = (uint32_t)__popcll(peers & lanemask_lt());
+      uint32_t c0 = 0;
+      if (valid) c0 = cnt[w][d];
+      r[it] = c0 + below;
+      __builtin_amdgcn_wave_barrier();
+      if (valid && below == 0) cnt[w][d] = c0 + (uint32_t)__popcll(peers);
+    }
+    __syncthreads();
+    // per digit: the waves' offsets, then the digit's start in the tile
+    uint32_t o = 0, inc = 0;
+    if (threadIdx.x < (unsigned)kSortRadix) {
+      const int d = threadIdx.x;
+      uint32_t c[kTileWaves];
+#pragma unroll
+      for (int q = 0; q < kTileWaves; ++q) c[q] = cnt[q][d];
+#pragma unroll
+      for (int q = 0; q < kTileWaves; ++q) o += c[q];
+      inc = wave_incl_scan_dpp(o);
+      if (lane_id() == 63) wsum[w] = inc;
+    }
+    __syncthreads();
+    if (threadIdx.x < (unsigned)kSortRadix) {
+      const int d = threadIdx.x;
+      uint32_t at = inc - o;
+      for (int q = 0; q < w; ++q) at += wsum[q];
+#pragma unroll
+      for (int q = 0; q < kTileWaves; ++q) {
+        const uint32_t t = cnt[q][d];
+        cnt[q][d] = at;
+        at += t;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < kTileItems; ++it)
+      if (p0 + 64 * it < m) {
+        const uint32_t lp = cnt[w][(uint32_t)(k[it] >> shift) & (kSortRadix - 1)] + r[it];
+        sk[lp] = k[it];
+        si[lp] = (uint16_t)v[it];
+      }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < kTileItems; ++it) {
+      const int p = p0 + 64 * it;
+      if (p < m) {
+        k[it] = sk[p];
+        v[it] = si[p];
+      }
+    }
+  }
+#pragma unroll
+  for (int it = 0; it < kTileItems; ++it) {
+    const int p = p0 + 64 * it;
+    if (p < m) {
+      kout[tile0 + p] = k[it];
+      vout[tile0 + p] = vin[tile0 + v[it]];
+    }
+  }
+}
+
+// Merges groups of four sorted runs of `run` pairs (a power of two): a pair's
+// place is its place in its own run plus, for each other run of the group, the
+// pairs there that come before it (equal keys: those of earlier runs, which
+// keeps the sort stable). The three searches of a thread are independent.
+__global__ __launch_bounds__(256) void k_sort_merge(const uint64_t *__restrict__ kin,
+                                                    const uint32_t *__restrict__ vin, int64_t n,
+                                                    int64_t run, uint64_t *__restrict__ kout,
+                                                    uint32_t *__restrict__ vout) {
+  const int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x;
+  if (i >= n) return;
+  const uint64_t key = kin[i];
+  const int64_t g0 = i / (4 * run) * (4 * run);
+  const int mine = (int)((i - g0) / run);
+  int64_t b[3], len[3], lo[3];
+  bool before[3];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const int s = q + (q >= mine ? 1 : 0);
+    b[q] = g0 + s * run;
+    len[q] = min(max(n - b[q], (int64_t)0), run);
+    before[q] = s < mine;
+    lo[q] = 0;
+  }
+  for (int64_t step = run; step >= 1; step >>= 1) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const int64_t c = lo[q] + step;  // are the run's first c pairs before mine?
+      if (c <= len[q]) {
+        const uint64_t o = kin[b[q] + c - 1];
+        if (before[q] ? o <= key : o < key) lo[q] = c;
+      }
+    }
+  }
+  const int64_t at = g0 + (i - g0 - mine * run) + lo[0] + lo[1] + lo[2];
+  kout[at] = key;
+  vout[at] = vin[i];
+}
+
+constexpr int64_t kMergeSort = 1 << 20;
+
 void launch_sort(int64_t n, uint64_t *keysA, uint32_t *valsA, uint64_t *keysB,
                  uint32_t *valsB, uint32_t *hist, hipStream_t st, uint64_t **keys_out,
                  uint32_t **vals_out) {
-  const int64_t nblk = cdiv(n, kSortTile);
-  uint32_t *totals = hist + (int64_t)kSortRadix * nblk;
   uint64_t *ki = keysA, *ko = keysB;
   uint32_t *vi = valsA, *vo = valsB;
+  if (n <= kMergeSort) {
+    hipLaunchKernelGGL(k_sort_tile, dim3((unsigned)cdiv(n, kSortTile)), dim3(kTileThreads), 0, st,
+                       ki, vi, n, ko, vo);
+    for (int64_t run = kSortTile; run < n; run *= 4) {
+      std::swap(ki, ko);
+      std::swap(vi, vo);
+      hipLaunchKernelGGL(k_sort_merge, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, ki, vi, n,
+                         run, ko, vo);
+    }
+    *keys_out = ko;
+    *vals_out = vo;
+    return;
+  }
   for (int pass = 0; pass < 8; ++pass) {
     launch_digit_sort(n, nullptr, pass * kSortBits, ki, vi, ko, vo, hist, st);
-    uint64_t *tk = ki; ki = ko; ko = tk;
-    uint32_t *tv = vi; vi = vo; vo = tv;
+    std::swap(ki, ko);
+    std::swap(vi, vo);
   }
   *keys_out = ki;
   *vals_out = vi;
