@@ -558,9 +558,7 @@ void span_end(nbody_ctx *ctx, int i) {
 // the span's done event.
 void span_stats(nbody_ctx *ctx, int i, bool queued, bool record) {
   if (i < 0) return;
-  launch_walk_stat(queued, record, ctx->P, ctx->st);
-  (void)hipMemcpyAsync(&ctx->aux[i], &ctx->P.sc->wstat, sizeof(WalkStat),
-                       hipMemcpyDeviceToHost, ctx->st);
+  launch_walk_stat(ctx->n, queued, record, ctx->P, &ctx->aux[i], ctx->st);
 }
 
 void span_done(nbody_ctx *ctx, int i) {
@@ -657,42 +655,37 @@ nbody_status do_build(nbody_ctx *ctx, int64_t n, const Coords &c) {
     launch_sys_keys(c, n, ctx->nsys, ctx->sys_r, P, P.blkcnt,
                     (int64_t)(kLevels + 1) * ctx->L.build_blocks + kLevels + 1, ctx->st);
   } else {
-    launch_bbox(c, n, P.sc, P.blkcnt, ctx->st);  // (block counts are free before the build)
-    launch_keys(c, n, P.sc, P.keysA, P.valsA, ctx->st);
+    // (block counts are free before the build)
+    launch_bbox_keys(c, n, P.sc, P.blkcnt, P.keysA, P.valsA, ctx->st);
   }
   uint64_t *ks;
   uint32_t *pm;
   launch_sort(n, P.keysA, P.valsA, P.keysB, P.valsB, P.hist, ctx->st, &ks, &pm);
   if (ko) launch_ko_ties(n, ks, pm, P.kpt[ctx->ko], ctx->st);  // equal keys: caller order
-  // (key order: the state permute below writes the sorted records)
-  if (!ko) launch_gather(c, pm, n, P.xyzm, ctx->st);
   if (remap) {  // (before inv is rewritten; okeys is free outside a walk)
     launch_asort_remap(pm, P.inv, n, P.asort, reinterpret_cast<float4 *>(P.okeys), ctx->st);
     ctx->asort_epoch = ctx->epoch;
   }
   if (ko) {
     const int c1 = 1 - ctx->ko;
-    launch_ko_permute(n, pm, ko_set(P, ctx->ko, n), ko_set(P, c1, n), P.xyzm, ctx->st);
+    launch_ko_permute(n, pm, ko_set(P, ctx->ko, n), ko_set(P, c1, n), P, ctx->st);
     ctx->ko = c1;
   } else {
-    launch_invert(pm, n, P.inv, ctx->st);
+    launch_gather_new(c, pm, n, P, ctx->st);
   }
-  launch_build(ks, n, ctx->p.leaf_max, ctx->p.group_max, ctx->p.group_merge, ctx->nsys,
-               ctx->sys_r, P, ctx->L, ctx->st);
   const uint32_t *plan = moment_plan(ctx);
-  if (ctx->h_istart && !ctx->capturing && !ctx->istart_pending) {
-    // this tree's counts for the later refits (read once the copy has landed)
-    (void)hipMemcpyAsync(ctx->h_istart, &P.sc->istart, sizeof(uint32_t) * (kLevels + 1),
-                         hipMemcpyDeviceToHost, ctx->st);
+  // this tree's counts for the later refits (written to host memory by the
+  // build, read once its event has passed)
+  const bool counts = ctx->h_istart && !ctx->capturing && !ctx->istart_pending;
+  launch_build(ks, n, ctx->p.leaf_max, ctx->p.group_max, ctx->p.group_merge, ctx->nsys,
+               ctx->sys_r, P, ctx->L, counts ? ctx->h_istart : nullptr, ctx->st);
+  if (counts) {
     (void)hipEventRecord(ctx->ev_istart, ctx->st);
     ctx->istart_pending = true;
   }
   launch_moments(n, ctx->p.G, P, ctx->L, eff_calcnode(ctx->p), plan, ctx->st);
   span_end(ctx, sp);
   span_done(ctx, sp);
-  launch_fill_u32(P.gref, 0u, n, ctx->st);
-  // previous list lengths are those of walks on the current tree (0: none yet)
-  launch_fill_u32(P.plast, 0u, n, ctx->st);
   ctx->keys = ks;
   // the tree's permutation (sorted position -> caller index)
   ctx->perm = ko ? P.kpt[ctx->ko] : pm;
@@ -716,7 +709,8 @@ nbody_status do_refit_sorted(nbody_ctx *ctx) {
 }
 
 // Within a step: mirror the state's accelerations in key order for the
-// current tree (after a rebuild, or at the first step of a call).
+// current tree (after a rebuild, or at the first step of a call; a call's last
+// step makes none: nothing would read it again).
 void ensure_asort(nbody_ctx *ctx, const nbody_state *st) {
   if (ctx->asort_src == st->ax && ctx->asort_epoch == ctx->epoch) return;
   launch_asort_gather(ctx->perm, ctx->n, st->ax, st->ay, st->az, ctx->P.asort, ctx->st);
@@ -1015,9 +1009,10 @@ nbody_status step_block(nbody_ctx *ctx, nbody_state *st, int32_t n_steps) {
   DevScalars *sc = P.sc;
   const bool keyed = ctx->step_layout == 1 || (ctx->step_layout == 0 && n_steps >= kKeyedSteps);
   const unsigned to_f32_grid = (unsigned)std::min<int64_t>(cdiv(n, 1024), 8192);
-  launch_blk_setup((long long)st->tick, sc, ctx->st);
+  const bool steps = n_steps > 0;
   bool force_rebuild = false;
   if (!st->have_acc) {
+    launch_blk_setup((long long)st->tick, sc, ctx->st);
     hipLaunchKernelGGL(k_to_f32, dim3(to_f32_grid), dim3(256), 0, ctx->st, n, st->x, st->y,
                        st->z, st->m, reinterpret_cast<float4 *>(x32));
     if ((s = do_build(ctx, n, records(x32))) != NBODY_OK) return s;
@@ -1025,11 +1020,12 @@ nbody_status step_block(nbody_ctx *ctx, nbody_state *st, int32_t n_steps) {
       return s;
     if ((s = do_calc(ctx, st->ax, st->ay, st->az, st->ax, st->ay, st->az)) != NBODY_OK)
       return s;
-    launch_blk_init(n, st->ax, st->ay, st->az, st->level, bc, sc, P.blkcnt, ctx->st);
+    launch_blk_init(n, st->ax, st->ay, st->az, st->level, bc, (long long)st->tick, steps, sc,
+                    P.blkcnt, ctx->st);
     st->have_acc = 1;
     ctx->since_rebuild = 0;
   } else {
-    launch_blk_scan(n, st->level, bc, sc, P.blkcnt, ctx->st);
+    launch_blk_scan(n, st->level, bc, (long long)st->tick, steps, sc, P.blkcnt, ctx->st);
     if (!ctx->have_tree || ctx->n != n) {
       // no tree of these particles: the first step builds one from the
       // drifted positions (the key-ordered layout needs one for its order
@@ -1074,7 +1070,6 @@ nbody_status step_block(nbody_ctx *ctx, nbody_state *st, int32_t n_steps) {
                                                    : rebuild_due(ctx, 64));
     force_rebuild = false;
     if (keyed) S = ko_set(P, ctx->ko, n);
-    launch_blk_begin(sc, ctx->st);
     // key order: a rebuild reads the drifted positions as (x, y, z, m)
     // records in the old key order, a refit as the tree's sorted positions
     const SortedOut so = !keyed ? drift_out(ctx, st, rebuild)
@@ -1091,10 +1086,11 @@ nbody_status step_block(nbody_ctx *ctx, nbody_state *st, int32_t n_steps) {
       if ((s = do_refit_sorted(ctx)) != NBODY_OK) break;
     }
     launch_blk_queue(n, S.lv, keyed ? nullptr : ctx->perm, P, ctx->st);
-    if (!keyed) ensure_asort(ctx, st);
+    const bool last = k + 1 == n_steps;
+    if (!keyed && !last) ensure_asort(ctx, st);
     if ((s = do_calc(ctx, S.ax, S.ay, S.az, tx, ty, tz, true)) != NBODY_OK) break;
     launch_blk_close(n, S.ax, S.ay, S.az, tx, ty, tz, S.vx, S.vy, S.vz, S.lv, bc,
-                     keyed ? nullptr : P.asort, P.inv, sc, P.blkcnt, ctx->st);
+                     keyed || last ? nullptr : P.asort, P.inv, !last, sc, P.blkcnt, ctx->st);
     ctx->since_rebuild++;
     ctx->steps++;
     s = hip_status();

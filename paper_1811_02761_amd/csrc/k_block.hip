@@ -96,10 +96,24 @@ __device__ void block_fold(int kmax, uint32_t cnt, uint32_t *part) {
   }
 }
 
-// The blocks' maxima and counts: kmax_next = max, and (with_count) nactive
-// += sum.
+// The next block step: it ends at the next boundary of the finest level.
+__device__ __forceinline__ void begin_step(DevScalars *sc) {
+  const long long t0 = sc->tick;
+  const uint32_t k = sc->kmax_next;
+  const long long s = 1ll << (kTickBits - (int)k);
+  sc->tick0 = t0;
+  sc->tick = (t0 / s + 1) * s;
+  sc->kmax = k;
+  sc->kmax_next = 0;
+  sc->nactive = 0;
+}
+
+// The blocks' maxima and counts: kmax_next = max, and (count) nactive += sum;
+// with tick >= 0 the call starts here (the step scalars at that tick); with
+// begin the next step begins here (a launch less per step).
 __global__ __launch_bounds__(256) void k_blk_fold(const uint32_t *__restrict__ part, int nb,
-                                                  DevScalars *sc, int with_count) {
+                                                  DevScalars *sc, int with_count,
+                                                  long long tick, int begin) {
   uint32_t m = 0, c = 0;
   for (int b = threadIdx.x; b < nb; b += blockDim.x) {
     m = max(m, part[2 * b]);
@@ -120,11 +134,22 @@ __global__ __launch_bounds__(256) void k_blk_fold(const uint32_t *__restrict__ p
       m = max(m, s_m[q]);
       c += s_c[q];
     }
+    if (tick >= 0) {
+      sc->tick = tick;
+      sc->tick0 = tick;
+      sc->kmax = 0;
+      sc->kmax_next = 0;
+      sc->nactive = 0;
+      sc->nqueue = 0;
+    }
     sc->kmax_next = max(sc->kmax_next, m);
     if (with_count) sc->nactive += c;
+    if (begin) begin_step(sc);
   }
 }
 
+// The step scalars at `tick`, before the force evaluations of a state without
+// accelerations.
 __global__ void k_blk_setup(long long tick, DevScalars *sc) {
   if (threadIdx.x != 0) return;
   sc->tick = tick;
@@ -139,9 +164,9 @@ __global__ __launch_bounds__(kBlkThreads) void k_blk_init(int64_t n, const float
                                                           const float *__restrict__ ay,
                                                           const float *__restrict__ az,
                                                           int8_t *__restrict__ level,
-                                                          BlkTables t, DevScalars *sc,
+                                                          BlkTables t, long long tick,
                                                           uint32_t *__restrict__ part) {
-  const int lo = max(t.level_min, align_level(sc->tick));
+  const int lo = max(t.level_min, align_level(tick));
   int kmax = 0;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
@@ -166,18 +191,6 @@ __global__ __launch_bounds__(kBlkThreads) void k_blk_scan(int64_t n,
   }
   if (bad) atomicOr(&sc->status, kStCorrupt);
   block_fold(min(kmax, kTickBits), 0u, part);
-}
-
-__global__ void k_blk_begin(DevScalars *sc) {
-  if (threadIdx.x != 0) return;
-  const long long t0 = sc->tick;
-  const uint32_t k = sc->kmax_next;
-  const long long s = 1ll << (kTickBits - (int)k);
-  sc->tick0 = t0;
-  sc->tick = (t0 / s + 1) * s;
-  sc->kmax = k;
-  sc->kmax_next = 0;
-  sc->nactive = 0;
 }
 
 __global__ __launch_bounds__(kBlkThreads) void k_blk_open_drift(
@@ -327,6 +340,38 @@ __global__ __launch_bounds__(kQScanThreads) void k_blk_qscan(uint32_t *__restric
   if (threadIdx.x == 0) sc->nqueue = all;
 }
 
+// The queue of a small set by one workgroup (the groups there are, not the
+// particles, set its length): flags, offsets and groups in one launch.
+__global__ __launch_bounds__(kQScanThreads) void k_blk_queue_one(DevScalars *__restrict__ sc,
+                                                                 uint32_t *__restrict__ gflag,
+                                                                 uint32_t *__restrict__ order) {
+  __shared__ uint32_t wsum[kQScanThreads / 64];
+  const uint32_t ng = sc->ngroup;
+  const int w = threadIdx.x >> 6;
+  uint32_t base = 0;
+  for (uint32_t s0 = 0; s0 < ng; s0 += kQScanThreads * kQPer) {
+    const uint32_t g0 = s0 + threadIdx.x * kQPer;
+    uint32_t bits;
+    const uint32_t c = flagged_run(sc, g0, gflag, &bits);
+    const uint32_t inc = wave_incl_scan(c);
+    __syncthreads();  // wsum's last use
+    if (lane_id() == 63) wsum[w] = inc;
+    __syncthreads();
+    uint32_t off = base + inc - c, all = 0;
+    for (int q = 0; q < kQScanThreads / 64; ++q) {
+      if (q < w) off += wsum[q];
+      all += wsum[q];
+    }
+    for (int k = 0; k < kQPer; ++k)
+      if (bits & (1u << k)) {
+        order[off++] = g0 + (uint32_t)k;
+        gflag[g0 + (uint32_t)k] = 0u;
+      }
+    base += all;
+  }
+  if (threadIdx.x == 0) sc->nqueue = base;
+}
+
 __global__ __launch_bounds__(kBlkThreads) void k_blk_close(
     int64_t n, float *__restrict__ ax, float *__restrict__ ay, float *__restrict__ az,
     const float *__restrict__ nax, const float *__restrict__ nay,
@@ -392,24 +437,22 @@ void launch_blk_setup(long long tick, DevScalars *sc, hipStream_t st) {
 }
 
 void launch_blk_init(int64_t n, const float *ax, const float *ay, const float *az,
-                     int8_t *level, const BlockCfg &c, DevScalars *sc, uint32_t *part,
-                     hipStream_t st) {
+                     int8_t *level, const BlockCfg &c, long long tick, bool begin,
+                     DevScalars *sc, uint32_t *part, hipStream_t st) {
   const unsigned g = blk_grid(n);
   hipLaunchKernelGGL(k_blk_init, dim3(g), dim3(kBlkThreads), 0, st, n, ax, ay, az, level,
-                     make_tables(c), sc, part);
-  hipLaunchKernelGGL(k_blk_fold, dim3(1), dim3(256), 0, st, part, (int)g, sc, 0);
+                     make_tables(c), tick, part);
+  hipLaunchKernelGGL(k_blk_fold, dim3(1), dim3(256), 0, st, part, (int)g, sc, 0, tick,
+                     begin ? 1 : 0);
 }
 
-void launch_blk_scan(int64_t n, const int8_t *level, const BlockCfg &c, DevScalars *sc,
-                     uint32_t *part, hipStream_t st) {
+void launch_blk_scan(int64_t n, const int8_t *level, const BlockCfg &c, long long tick,
+                     bool begin, DevScalars *sc, uint32_t *part, hipStream_t st) {
   const unsigned g = blk_grid(n);
   hipLaunchKernelGGL(k_blk_scan, dim3(g), dim3(kBlkThreads), 0, st, n, level, c.level_min,
                      c.level_max, sc, part);
-  hipLaunchKernelGGL(k_blk_fold, dim3(1), dim3(256), 0, st, part, (int)g, sc, 0);
-}
-
-void launch_blk_begin(DevScalars *sc, hipStream_t st) {
-  hipLaunchKernelGGL(k_blk_begin, dim3(1), dim3(64), 0, st, sc);
+  hipLaunchKernelGGL(k_blk_fold, dim3(1), dim3(256), 0, st, part, (int)g, sc, 0, tick,
+                     begin ? 1 : 0);
 }
 
 void launch_blk_open_drift(int64_t n, double *x, double *y, double *z, float *vx, float *vy,
@@ -426,6 +469,9 @@ void launch_blk_open_drift(int64_t n, double *x, double *y, double *z, float *vx
                      z, vx, vy, vz, ax, ay, az, level, make_tables(c), sc, x32, so);
 }
 
+// (at some ten and more particles per group, two trips of the one workgroup)
+constexpr int64_t kQueueOne = 256 * 1024;
+
 void launch_blk_queue(int64_t n, const int8_t *level, const uint32_t *perm, const Ptrs &P,
                       hipStream_t st) {
   int64_t gm = cdiv(n, 4 * kBlkThreads);
@@ -433,6 +479,11 @@ void launch_blk_queue(int64_t n, const int8_t *level, const uint32_t *perm, cons
   if (gm < 1) gm = 1;
   hipLaunchKernelGGL(k_blk_mark, dim3((unsigned)gm), dim3(kBlkThreads), 0, st, n, P.sc, perm,
                      P.gid, level, P.gflag);
+  if (n <= kQueueOne) {
+    hipLaunchKernelGGL(k_blk_queue_one, dim3(1), dim3(kQScanThreads), 0, st, P.sc, P.gflag,
+                       P.order);
+    return;
+  }
   // ngroup <= n: blocks for n groups; the build's block-count buffer (free
   // outside the build) holds the per-block counts
   const uint32_t nblk = (uint32_t)cdiv(n, kQGroups);
@@ -446,7 +497,7 @@ void launch_blk_queue(int64_t n, const int8_t *level, const uint32_t *perm, cons
 void launch_blk_close(int64_t n, float *ax, float *ay, float *az, const float *nax,
                       const float *nay, const float *naz, float *vx, float *vy, float *vz,
                       int8_t *level, const BlockCfg &c, float4 *asort, const uint32_t *inv,
-                      DevScalars *sc, uint32_t *part, hipStream_t st) {
+                      bool begin, DevScalars *sc, uint32_t *part, hipStream_t st) {
   // one trip of four particles per thread: a thread's loads of the levels
   // and then of the active particles' values are two round trips (a capped
   // grid left each thread eight of them)
@@ -454,7 +505,8 @@ void launch_blk_close(int64_t n, float *ax, float *ay, float *az, const float *n
   g = std::min<int64_t>(std::max<int64_t>(g, 1), 16384);
   hipLaunchKernelGGL(k_blk_close, dim3((unsigned)g), dim3(kBlkThreads), 0, st, n, ax, ay, az,
                      nax, nay, naz, vx, vy, vz, level, make_tables(c), asort, inv, sc, part);
-  hipLaunchKernelGGL(k_blk_fold, dim3(1), dim3(256), 0, st, part, (int)g, sc, 1);
+  hipLaunchKernelGGL(k_blk_fold, dim3(1), dim3(256), 0, st, part, (int)g, sc, 1, -1ll,
+                     begin ? 1 : 0);
 }
 
 }  // namespace nb

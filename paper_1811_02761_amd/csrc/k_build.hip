@@ -203,9 +203,36 @@ __global__ __launch_bounds__(256) void k_scan_apply(uint32_t *__restrict__ rows,
   }
 }
 
+// Rows of a single tile: one launch.
+__global__ __launch_bounds__(256) void k_scan_row(uint32_t *__restrict__ rows, uint32_t len,
+                                                  uint32_t *__restrict__ totals) {
+  __shared__ uint32_t wsum[4];
+  uint32_t *row = rows + (size_t)blockIdx.x * len;
+  const uint32_t b = threadIdx.x * (kScanTile / 256);
+  uint32_t v[kScanTile / 256];
+  uint32_t s = 0;
+#pragma unroll
+  for (uint32_t k = 0; k < kScanTile / 256; ++k) {
+    v[k] = b + k < len ? row[b + k] : 0u;
+    s += v[k];
+  }
+  uint32_t tot;
+  uint32_t run = block_excl_scan256(s, wsum, &tot);
+#pragma unroll
+  for (uint32_t k = 0; k < kScanTile / 256; ++k) {
+    if (b + k < len) row[b + k] = run;
+    run += v[k];
+  }
+  if (threadIdx.x == 0) totals[blockIdx.x] = tot;
+}
+
 void launch_scan_rows(uint32_t *rows, uint32_t len, int nrows, uint32_t *totals,
                       uint32_t *tsum, hipStream_t st) {
   const uint32_t ntile = (uint32_t)std::max<int64_t>(cdiv(len, kScanTile), 1);
+  if (ntile == 1) {
+    hipLaunchKernelGGL(k_scan_row, dim3(nrows), dim3(256), 0, st, rows, len, totals);
+    return;
+  }
   hipLaunchKernelGGL(k_scan_tiles, dim3(ntile, nrows), dim3(256), 0, st, rows, len, ntile, tsum);
   hipLaunchKernelGGL(k_scan_tilesums, dim3(nrows), dim3(256), 0, st, tsum, ntile, totals);
   hipLaunchKernelGGL(k_scan_apply, dim3(ntile, nrows), dim3(256), 0, st, rows, len, ntile, tsum);
@@ -213,24 +240,6 @@ void launch_scan_rows(uint32_t *rows, uint32_t len, int nrows, uint32_t *totals,
 
 int64_t scan_scratch_words(int64_t len, int nrows) {
   return std::max<int64_t>(cdiv(len, kScanTile), 1) * nrows;
-}
-
-// Pass C: level offsets and the cell count.
-__global__ void k_build_c(const uint32_t *__restrict__ totals, DevScalars *sc,
-                          int64_t cell_cap) {
-  if (threadIdx.x != 0) return;
-  sc->nleaf = totals[kLevels];
-  uint32_t o = 0;
-  for (int l = 0; l < kLevels; ++l) {
-    sc->lvl_off[l] = o;
-    o += totals[l];
-  }
-  sc->lvl_off[kLevels] = o;
-  if ((int64_t)o > cell_cap) {
-    atomicOr(&sc->status, kStCapacity);
-    o = 0;
-  }
-  sc->ncell = o;
 }
 
 // Pass D: write every cell (l, i). The level-l run from i (the cell's
@@ -274,9 +283,12 @@ __device__ __forceinline__ uint32_t count_bits(const uint64_t *m, uint32_t r0, u
   return t;
 }
 
+// Every workgroup adds up the level offsets from the rows' totals; the first one
+// stores them with the cell and leaf counts.
 __global__ __launch_bounds__(kB) void k_build_d(
     const uint32_t *__restrict__ pinfo, uint32_t n, const uint32_t *__restrict__ blkcnt,
-    uint32_t nblk, DevScalars *__restrict__ sc, int64_t cell_cap,
+    uint32_t nblk, const uint32_t *__restrict__ totals, DevScalars *__restrict__ sc,
+    int64_t cell_cap,
     int32_t *__restrict__ clevel, uint32_t *__restrict__ cpbegin,
     uint32_t *__restrict__ cpcount, int32_t *__restrict__ cfchild,
     int32_t *__restrict__ cnchild, float4 *__restrict__ nodeB,
@@ -306,7 +318,20 @@ __global__ __launch_bounds__(kB) void k_build_d(
   }
   const uint32_t pi = valid ? pinfo[i] : 0u;
   const int s = pi & 31, D = (pi >> 5) & 31;
-  if (threadIdx.x <= kLevels) lvl_off[threadIdx.x] = sc->lvl_off[threadIdx.x];
+  if (threadIdx.x <= kLevels) {
+    uint32_t o = 0;
+    for (int l = 0; l < kLevels; ++l) o += l < (int)threadIdx.x ? totals[l] : 0u;
+    lvl_off[threadIdx.x] = o;
+    if (blockIdx.x == 0) {
+      sc->lvl_off[threadIdx.x] = o;
+      if (threadIdx.x == kLevels) {
+        const bool over = (int64_t)o > cell_cap;
+        if (over) atomicOr(&sc->status, kStCapacity);
+        sc->ncell = over ? 0u : o;
+        sc->nleaf = totals[kLevels];
+      }
+    }
+  }
   for (int l = 0; l < kLevels; ++l) {
     const uint64_t b = __ballot(valid && s <= l && l <= D);
     if (lane == 0) {
@@ -486,80 +511,6 @@ __global__ __launch_bounds__(256) void k_build_long(
   }
 }
 
-// Pass E: parents and the first-child word of internal walk nodes.
-__global__ __launch_bounds__(256) void k_build_e(DevScalars *__restrict__ sc,
-                                                 const int32_t *__restrict__ clevel,
-                                                 const int32_t *__restrict__ cfchild,
-                                                 const int32_t *__restrict__ cnchild,
-                                                 int32_t *__restrict__ cparent,
-                                                 float4 *__restrict__ nodeB) {
-  const uint32_t nc = sc->ncell;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < nc; c += stride) {
-    if (c == 0) cparent[0] = -1;
-    const int k = cnchild[c];
-    if (k > 0) {
-      const int32_t f = cfchild[c];
-      const int32_t l = clevel[c];
-      if (f <= (int32_t)c || k > 8 || (uint32_t)(f + k) > nc || l < 0 || l >= kMaxLevel) {
-        atomicOr(&sc->status, kStCorrupt);
-        continue;
-      }
-      reinterpret_cast<uint32_t *>(&nodeB[c])[2] = (uint32_t)f;
-      for (int q = 0; q < k; ++q) cparent[f + q] = (int32_t)c;
-    }
-  }
-}
-
-// The list of internal cells in cell order (so level by level), entries
-// (cell, first child, children, particles): internal cells per block of 256
-// cells, a scan of the block counts, then each cell's rank. istart[l] is the
-// rank of cell lvl_off[l] (the internal cells before level l).
-__global__ __launch_bounds__(256) void k_ilist_count(const DevScalars *__restrict__ sc,
-                                                     const int32_t *__restrict__ cnchild,
-                                                     uint32_t *__restrict__ cblk) {
-  __shared__ uint32_t wc[4];
-  const uint32_t c = blockIdx.x * 256u + threadIdx.x;
-  const bool in = c < sc->ncell && cnchild[c] > 0;
-  const uint64_t b = __ballot(in);
-  if (lane_id() == 0) wc[threadIdx.x >> 6] = (uint32_t)__popcll(b);
-  __syncthreads();
-  if (threadIdx.x == 0) cblk[blockIdx.x] = wc[0] + wc[1] + wc[2] + wc[3];
-}
-
-__global__ __launch_bounds__(256) void k_ilist_emit(DevScalars *__restrict__ sc,
-                                                    const uint32_t *__restrict__ cpcount,
-                                                    const int32_t *__restrict__ cfchild,
-                                                    const int32_t *__restrict__ cnchild,
-                                                    const uint32_t *__restrict__ cblk,
-                                                    uint4 *__restrict__ ilist) {
-  __shared__ uint32_t wc[4];
-  const uint32_t nc = sc->ncell;
-  const uint32_t c = blockIdx.x * 256u + threadIdx.x;
-  const int k = c < nc ? cnchild[c] : 0;
-  const bool in = k > 0;
-  const uint64_t b = __ballot(in);
-  const int w = threadIdx.x >> 6;
-  if (lane_id() == 0) wc[w] = (uint32_t)__popcll(b);
-  __syncthreads();
-  uint32_t rank = cblk[blockIdx.x];
-  for (int q = 0; q < w; ++q) rank += wc[q];
-  rank += (uint32_t)__popcll(b & lanemask_lt());  // internal cells before c
-  if (in) ilist[rank] = make_uint4(c, (uint32_t)cfchild[c], (uint32_t)k, cpcount[c]);
-  if (c < nc)
-    for (int l = 0; l < kLevels; ++l)
-      if (sc->lvl_off[l] == c) sc->istart[l] = rank;
-}
-
-// Levels starting at or past the last cell (empty) and the total.
-__global__ void k_ilist_total(const uint32_t *__restrict__ total, DevScalars *sc) {
-  if (threadIdx.x != 0) return;
-  const uint32_t t = total[0], nc = sc->ncell;
-  for (int l = 0; l < kLevels; ++l)
-    if (sc->lvl_off[l] >= nc) sc->istart[l] = t;
-  sc->istart[kLevels] = t;
-}
-
 __device__ __forceinline__ void mark_chunks(uint32_t *__restrict__ pinfo, uint32_t b,
                                             uint32_t cnt, uint32_t gmax) {
   for (uint32_t s = 0; s < cnt; s += gmax) pinfo[b + s] |= kGroupMark;
@@ -572,34 +523,56 @@ __device__ __forceinline__ bool group_ok(int32_t level, uint32_t cnt, int nchild
   return level >= min_level && (cnt <= gmax || nchild == 0);
 }
 
-// Group starts: the root if it may hold a group; otherwise every cell that
-// may not marks the group starts among its children (joining consecutive
-// small siblings when `merge` and the cell lies within one system: above
-// min_level its children are the roots of distinct systems; an over-full
-// leaf is cut into pieces of group_max). Every particle is marked at most
-// once.
-__global__ __launch_bounds__(256) void k_group_mark(DevScalars *__restrict__ sc,
-                                                    const int32_t *__restrict__ clevel,
-                                                    const uint32_t *__restrict__ cpbegin,
-                                                    const uint32_t *__restrict__ cpcount,
-                                                    const int32_t *__restrict__ cfchild,
-                                                    const int32_t *__restrict__ cnchild,
-                                                    uint32_t gmax, int merge, int min_level,
-                                                    uint32_t *__restrict__ pinfo) {
+// Pass E, per cell: parents and the first-child word of internal walk nodes;
+// the internal cells per block of 256 cells (for the list below); group starts.
+// These are the root if it may hold a group; otherwise every cell that may not
+// marks the group starts among its children (joining consecutive small siblings
+// when `merge` and the cell lies within one system: above min_level its children
+// are the roots of distinct systems; an over-full leaf is cut into pieces of
+// group_max). Every particle is marked at most once.
+__global__ __launch_bounds__(256) void k_build_e(DevScalars *__restrict__ sc, uint32_t cblocks,
+                                                 const int32_t *__restrict__ clevel,
+                                                 const uint32_t *__restrict__ cpbegin,
+                                                 const uint32_t *__restrict__ cpcount,
+                                                 const int32_t *__restrict__ cfchild,
+                                                 const int32_t *__restrict__ cnchild,
+                                                 uint32_t gmax, int merge, int min_level,
+                                                 int32_t *__restrict__ cparent,
+                                                 float4 *__restrict__ nodeB,
+                                                 uint32_t *__restrict__ cblk,
+                                                 uint32_t *__restrict__ pinfo) {
+  __shared__ uint32_t wc[4];
   const uint32_t nc = sc->ncell;
-  for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < nc;
-       c += (int64_t)gridDim.x * blockDim.x) {
+  for (uint32_t blk = blockIdx.x; blk < cblocks; blk += gridDim.x) {
+    const uint32_t c = blk * 256u + threadIdx.x;
+    const bool have = c < nc;
+    const int k = have ? cnchild[c] : 0;
+    const uint64_t b = __ballot(k > 0);
+    if (lane_id() == 0) wc[threadIdx.x >> 6] = (uint32_t)__popcll(b);
+    __syncthreads();
+    if (threadIdx.x == 0) cblk[blk] = wc[0] + wc[1] + wc[2] + wc[3];
+    __syncthreads();
+    if (!have) continue;
+    const int32_t f = cfchild[c];
+    const int32_t l = clevel[c];
+    if (c == 0) cparent[0] = -1;
+    if (k > 0) {
+      if (f <= (int32_t)c || k > 8 || (uint32_t)(f + k) > nc || l < 0 || l >= kMaxLevel) {
+        atomicOr(&sc->status, kStCorrupt);
+        continue;
+      }
+      reinterpret_cast<uint32_t *>(&nodeB[c])[2] = (uint32_t)f;
+      for (int q = 0; q < k; ++q) cparent[f + q] = (int32_t)c;
+    }
     const uint32_t cnt = cpcount[c];
-    const int k = cnchild[c];
-    const bool ok = group_ok(clevel[c], cnt, k, gmax, min_level);
+    const bool ok = group_ok(l, cnt, k, gmax, min_level);
     if (c == 0 && ok) {
       mark_chunks(pinfo, cpbegin[0], cnt, gmax);
       continue;
     }
     if (ok || k == 0) continue;
-    const int32_t f = cfchild[c];
     uint32_t run = 0;  // particles in the open joined group (0: none open)
-    const bool join = merge && clevel[c] >= min_level;
+    const bool join = merge && l >= min_level;
     for (int q = 0; q < k; ++q) {
       const uint32_t cb = cpbegin[f + q], cc = cpcount[f + q];
       const bool cok = group_ok(clevel[f + q], cc, cnchild[f + q], gmax, min_level);
@@ -615,6 +588,54 @@ __global__ __launch_bounds__(256) void k_group_mark(DevScalars *__restrict__ sc,
         if (cok) mark_chunks(pinfo, cb, cc, gmax);  // an over-full (level-21) leaf
       }
     }
+  }
+}
+
+// The list of internal cells in cell order (so level by level), entries
+// (cell, first child, children, particles): each cell's rank from the scanned
+// block counts (cblk; the sum in total). istart[l] is the rank of cell
+// lvl_off[l] (the internal cells before level l), also to host_istart
+// (page-locked host memory) when given.
+__global__ __launch_bounds__(256) void k_ilist_emit(DevScalars *__restrict__ sc, uint32_t cblocks,
+                                                    const uint32_t *__restrict__ cpcount,
+                                                    const int32_t *__restrict__ cfchild,
+                                                    const int32_t *__restrict__ cnchild,
+                                                    const uint32_t *__restrict__ cblk,
+                                                    const uint32_t *__restrict__ total,
+                                                    uint4 *__restrict__ ilist,
+                                                    uint32_t *__restrict__ host_istart) {
+  __shared__ uint32_t wc[4];
+  __shared__ uint32_t s_off[kLevels];
+  const uint32_t nc = sc->ncell;
+  if (threadIdx.x < kLevels) s_off[threadIdx.x] = sc->lvl_off[threadIdx.x];
+  __syncthreads();
+  // levels starting at or past the last cell (empty), and the total
+  if (blockIdx.x == 0 && threadIdx.x <= kLevels) {
+    const uint32_t t = total[0];
+    if (threadIdx.x == kLevels || s_off[threadIdx.x] >= nc) {
+      sc->istart[threadIdx.x] = t;
+      if (host_istart) host_istart[threadIdx.x] = t;
+    }
+  }
+  const int w = threadIdx.x >> 6;
+  for (uint32_t blk = blockIdx.x; blk < cblocks && blk * 256u < nc; blk += gridDim.x) {
+    const uint32_t c = blk * 256u + threadIdx.x;
+    const int k = c < nc ? cnchild[c] : 0;
+    const bool in = k > 0;
+    const uint64_t b = __ballot(in);
+    __syncthreads();  // wc's last use
+    if (lane_id() == 0) wc[w] = (uint32_t)__popcll(b);
+    __syncthreads();
+    uint32_t rank = cblk[blk];
+    for (int q = 0; q < w; ++q) rank += wc[q];
+    rank += (uint32_t)__popcll(b & lanemask_lt());  // internal cells before c
+    if (in) ilist[rank] = make_uint4(c, (uint32_t)cfchild[c], (uint32_t)k, cpcount[c]);
+    if (c < nc)
+      for (int l = 0; l < kLevels; ++l)
+        if (s_off[l] == c) {
+          sc->istart[l] = rank;
+          if (host_istart) host_istart[l] = rank;
+        }
   }
 }
 
@@ -635,41 +656,50 @@ __global__ __launch_bounds__(kB) void k_group_count(uint32_t n,
   }
 }
 
-// Group begins in particle order (gblk holds exclusive block offsets), and
-// each particle's group (the number of group starts up to it, minus one).
+// Group begins in particle order (gblk holds exclusive block offsets) and sizes
+// (a group ends where the next one begins, at most group_max <= 64 particles
+// later, so the start of the one before is in the 64 positions before a mark),
+// each particle's group (the number of group starts up to it, minus one), and
+// the group count.
 __global__ __launch_bounds__(kB) void k_group_emit(uint32_t n,
                                                    const uint32_t *__restrict__ pinfo,
                                                    const uint32_t *__restrict__ gblk,
+                                                   const uint32_t *__restrict__ total,
+                                                   DevScalars *__restrict__ sc,
                                                    uint32_t *__restrict__ gbegin,
+                                                   uint32_t *__restrict__ gcount,
                                                    uint32_t *__restrict__ gid) {
-  __shared__ uint32_t wc[kB / 64];
-  const int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x;
+  __shared__ uint64_t wm[kB / 64 + 1];  // marks of the 64 positions before, then per wave
+  const int64_t b0 = (int64_t)blockIdx.x * kB;
+  const int64_t i = b0 + threadIdx.x;
   const bool mk = i < n && (pinfo[i] & kGroupMark);
   const uint64_t b = __ballot(mk);
   const int w = threadIdx.x >> 6;
-  if (lane_id() == 0) wc[w] = (uint32_t)__popcll(b);
+  const uint32_t lane = lane_id();
+  if (lane == 0) wm[w + 1] = b;
+  if (w == 0) {
+    const uint64_t h = __ballot(b0 > 0 && (pinfo[b0 > 0 ? b0 - 64 + lane : 0] & kGroupMark));
+    if (lane == 0) wm[0] = h;
+  }
   __syncthreads();
   uint32_t off = gblk[blockIdx.x];
-  for (int q = 0; q < w; ++q) off += wc[q];
-  const uint32_t before = (uint32_t)__popcll(b & lanemask_lt());
-  if (mk) gbegin[off + before] = (uint32_t)i;
+  for (int q = 0; q < w; ++q) off += (uint32_t)__popcll(wm[q + 1]);
+  const uint64_t below = b & lanemask_lt();
+  const uint32_t before = (uint32_t)__popcll(below);
+  const uint32_t wave0 = (uint32_t)(b0 + 64 * w);
+  // the last group start before this position
+  const uint64_t pm = below ? below : wm[w];
+  const uint32_t prev = (below ? wave0 : wave0 - 64u) + (pm ? 63u - (uint32_t)__builtin_clzll(pm) : 0u);
+  if (mk) {
+    gbegin[off + before] = (uint32_t)i;
+    if (pm) gcount[off + before - 1u] = (uint32_t)i - prev;
+  }
   if (i < n) gid[i] = off + before + (mk ? 1u : 0u) - 1u;  // particle 0 starts group 0
-}
-
-__global__ void k_group_total(const uint32_t *__restrict__ total, uint32_t n,
-                              DevScalars *sc, uint32_t *__restrict__ gbegin) {
-  if (threadIdx.x != 0) return;
-  sc->ngroup = total[0];
-  gbegin[total[0]] = n;
-}
-
-__global__ __launch_bounds__(256) void k_group_size(const DevScalars *__restrict__ sc,
-                                                    const uint32_t *__restrict__ gbegin,
-                                                    uint32_t *__restrict__ gcount) {
-  const uint32_t ng = sc->ngroup;
-  for (int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; g < ng;
-       g += (int64_t)gridDim.x * blockDim.x)
-    gcount[g] = gbegin[g + 1] - gbegin[g];
+  if (i == (int64_t)n - 1) {
+    if (mk || pm) gcount[off + before + (mk ? 1u : 0u) - 1u] = n - (mk ? (uint32_t)i : prev);
+    sc->ngroup = total[0];
+    gbegin[total[0]] = n;
+  }
 }
 
 // Batch: each group's walk starts at its system's root, the level-r cell of
@@ -698,7 +728,7 @@ __global__ __launch_bounds__(256) void k_group_root(const DevScalars *__restrict
 
 void launch_build(const uint64_t *keys, int64_t n, int leaf_max, int group_max,
                   int group_merge, int nsys, int r, const Ptrs &P, const Layout &L,
-                  hipStream_t st) {
+                  uint32_t *host_istart, hipStream_t st) {
   const uint32_t nblk = (uint32_t)cdiv(n, kB);
   // block rows [kLevels][nblk], then kLevels totals; the scanned rows stay
   // for the tree's life (calcNode derives ancestor indices from them)
@@ -707,40 +737,34 @@ void launch_build(const uint64_t *keys, int64_t n, int leaf_max, int group_max,
   hipLaunchKernelGGL(k_build_a, dim3(nblk), dim3(kB), 0, st, keys, (uint32_t)n, leaf_max, r,
                      P.pinfo, P.lvlblk, nblk);
   launch_scan_rows(P.lvlblk, nblk, kLevels + 1, totals, P.scan, st);
-  hipLaunchKernelGGL(k_build_c, dim3(1), dim3(64), 0, st, totals, P.sc, L.cell_cap);
   hipLaunchKernelGGL(k_build_d, dim3(nblk), dim3(kB), 0, st, P.pinfo, (uint32_t)n, P.lvlblk,
-                     nblk, P.sc, L.cell_cap, P.clevel, P.cpbegin, P.cpcount, P.cfchild,
+                     nblk, totals, P.sc, L.cell_cap, P.clevel, P.cpbegin, P.cpcount, P.cfchild,
                      P.cnchild, P.nodeB, P.leafof, P.leaves, P.longcnt, P.longslot);
-  hipLaunchKernelGGL(k_build_long, dim3(1024), dim3(256), 0, st, keys, (uint32_t)n, P.pinfo,
-                     P.sc, P.clevel, P.cpbegin, P.cpcount, P.cfchild, P.cnchild, P.nodeB,
-                     P.leafof, P.longcnt, P.longslot, nblk);
-  int64_t ge = cdiv(n, 256);
-  if (ge > 4096) ge = 4096;
-  hipLaunchKernelGGL(k_build_e, dim3(ge), dim3(256), 0, st, P.sc, P.clevel, P.cfchild,
-                     P.cnchild, P.cparent, P.nodeB);
-  // internal-cell list (block counts in the group scratch, before the groups use it)
-  const uint32_t cblk = (uint32_t)cdiv(L.cell_cap, 256);
+  // (cells longer than a build block)
+  hipLaunchKernelGGL(k_build_long, dim3((uint32_t)std::min<int64_t>(cdiv(nblk, 4), 1024)),
+                     dim3(256), 0, st, keys, (uint32_t)n, P.pinfo, P.sc, P.clevel, P.cpbegin,
+                     P.cpcount, P.cfchild, P.cnchild, P.nodeB, P.leafof, P.longcnt, P.longslot,
+                     nblk);
+  // cells of n particles (the capacity of the bound workspace may be larger)
+  const int64_t cells = std::min<int64_t>(L.cell_cap, n + cdiv(21 * n, leaf_max + 1) + 2);
+  const uint32_t cblk = (uint32_t)cdiv(cells, 256);
+  const uint32_t ge = (uint32_t)std::min<int64_t>(cblk, 8192);
   uint32_t *ib = P.blkcnt, *itot = P.blkcnt + cblk;
-  hipLaunchKernelGGL(k_ilist_count, dim3(cblk), dim3(256), 0, st, P.sc, P.cnchild, ib);
+  hipLaunchKernelGGL(k_build_e, dim3(ge), dim3(256), 0, st, P.sc, cblk, P.clevel, P.cpbegin,
+                     P.cpcount, P.cfchild, P.cnchild, (uint32_t)group_max, group_merge, r,
+                     P.cparent, P.nodeB, ib, P.pinfo);
   launch_scan_rows(ib, cblk, 1, itot, P.scan, st);
-  hipLaunchKernelGGL(k_ilist_emit, dim3(cblk), dim3(256), 0, st, P.sc, P.cpcount, P.cfchild,
-                     P.cnchild, ib, P.ilist);
-  hipLaunchKernelGGL(k_ilist_total, dim3(1), dim3(64), 0, st, itot, P.sc);
+  hipLaunchKernelGGL(k_ilist_emit, dim3(ge), dim3(256), 0, st, P.sc, cblk, P.cpcount, P.cfchild,
+                     P.cnchild, ib, itot, P.ilist, host_istart);
   // groups (scanned in the block-count scratch)
   uint32_t *gblk = P.blkcnt, *gtot = P.blkcnt + nblk;
-  hipLaunchKernelGGL(k_group_mark, dim3(ge), dim3(256), 0, st, P.sc, P.clevel, P.cpbegin,
-                     P.cpcount, P.cfchild, P.cnchild, (uint32_t)group_max, group_merge, r,
-                     P.pinfo);
   hipLaunchKernelGGL(k_group_count, dim3(nblk), dim3(kB), 0, st, (uint32_t)n, P.pinfo, gblk);
   launch_scan_rows(gblk, nblk, 1, gtot, P.scan, st);
-  hipLaunchKernelGGL(k_group_emit, dim3(nblk), dim3(kB), 0, st, (uint32_t)n, P.pinfo, gblk,
-                     P.gbegin, P.gid);
-  hipLaunchKernelGGL(k_group_total, dim3(1), dim3(64), 0, st, gtot, (uint32_t)n, P.sc,
-                     P.gbegin);
-  hipLaunchKernelGGL(k_group_size, dim3(ge), dim3(256), 0, st, P.sc, P.gbegin, P.gcount);
+  hipLaunchKernelGGL(k_group_emit, dim3(nblk), dim3(kB), 0, st, (uint32_t)n, P.pinfo, gblk, gtot,
+                     P.sc, P.gbegin, P.gcount, P.gid);
   if (r > 0)
-    hipLaunchKernelGGL(k_group_root, dim3(ge), dim3(256), 0, st, P.sc, P.gbegin, P.sysoff, nsys,
-                       r, P.groot);
+    hipLaunchKernelGGL(k_group_root, dim3((uint32_t)std::min<int64_t>(cdiv(n, 256), 4096)),
+                       dim3(256), 0, st, P.sc, P.gbegin, P.sysoff, nsys, r, P.groot);
 }
 
 

@@ -13,8 +13,8 @@ namespace nb {
 
 // Bounds of the particles: each workgroup reduces its share to six ordered
 // integers in part[6 * block] (min x, y, z, max x, y, z); k_bbox_fold
-// reduces the blocks (no atomics on the six words: thousands of workgroups
-// contending for them were most of the pass).
+// (or k_keys) reduces the blocks (no atomics on the six words: thousands of
+// workgroups contending for them were most of the pass).
 __global__ __launch_bounds__(256) void k_bbox(Coords c, int64_t n, DevScalars *sc,
                                               uint32_t *__restrict__ part) {
   float lo[3] = {INFINITY, INFINITY, INFINITY};
@@ -72,8 +72,9 @@ __global__ __launch_bounds__(256) void k_bbox(Coords c, int64_t n, DevScalars *s
   }
 }
 
-__global__ __launch_bounds__(256) void k_bbox_fold(const uint32_t *__restrict__ part, int nb,
-                                                   DevScalars *sc) {
+// The partials' bounds (one workgroup of 256; the result in every thread).
+__device__ __forceinline__ void fold_bounds(const uint32_t *__restrict__ part, int nb,
+                                            uint32_t (&out)[6]) {
   uint32_t lo[3] = {0xffffffffu, 0xffffffffu, 0xffffffffu}, hi[3] = {0u, 0u, 0u};
   for (int b = threadIdx.x; b < nb; b += blockDim.x)
 #pragma unroll
@@ -96,16 +97,24 @@ __global__ __launch_bounds__(256) void k_bbox_fold(const uint32_t *__restrict__ 
     }
   }
   __syncthreads();
-  if (threadIdx.x < 3) {
-    const int k = threadIdx.x;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
     uint32_t a = red[k][0], c = red[3 + k][0];
     for (int q = 1; q < (int)(blockDim.x >> 6); ++q) {
       a = min(a, red[k][q]);
       c = max(c, red[3 + k][q]);
     }
-    sc->bbox[k] = a;
-    sc->bbox[3 + k] = c;
+    out[k] = a;
+    out[3 + k] = c;
   }
+}
+
+__global__ __launch_bounds__(256) void k_bbox_fold(const uint32_t *__restrict__ part, int nb,
+                                                   DevScalars *sc) {
+  uint32_t b[6];
+  fold_bounds(part, nb, b);
+  if (threadIdx.x == 0)
+    for (int k = 0; k < 6; ++k) sc->bbox[k] = b[k];
 }
 
 // Spread the low 21 bits of v so that bit b lands on bit 3b.
@@ -128,14 +137,23 @@ __device__ __forceinline__ uint32_t quantise21(float v, double lo, double scale)
 
 __global__ __launch_bounds__(256) void k_keys(Coords c,
                                               int64_t n, DevScalars *sc,
+                                              const uint32_t *__restrict__ part, int nb,
                                               uint64_t *__restrict__ keys,
                                               uint32_t *__restrict__ vals) {
-  // root cube from the reduced bounds (every thread recomputes it)
+  // root cube from the reduced bounds (every thread recomputes it); a few
+  // partials (part) are reduced by every workgroup itself
+  uint32_t bb[6];
+  if (part) {
+    fold_bounds(part, nb, bb);
+  } else {
+#pragma unroll
+    for (int k = 0; k < 6; ++k) bb[k] = sc->bbox[k];
+  }
   double lo[3], ext = 0.0;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    const float a = ord2f(sc->bbox[k]);
-    const float b = ord2f(sc->bbox[3 + k]);
+    const float a = ord2f(bb[k]);
+    const float b = ord2f(bb[3 + k]);
     lo[k] = (double)a;
     const double e = (double)b - (double)a;
     ext = e > ext ? e : ext;
@@ -302,13 +320,7 @@ __global__ __launch_bounds__(256) void k_sys_keys(Coords c, int64_t n,
   }
 }
 
-__global__ __launch_bounds__(256) void k_invert(const uint32_t *__restrict__ perm, int64_t n,
-                                                uint32_t *__restrict__ inv) {
-  for (int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; s < n;
-       s += (int64_t)gridDim.x * blockDim.x)
-    inv[perm[s]] = (uint32_t)s;
-}
-
+// The tree's sorted (x, y, z, m) records.
 __global__ __launch_bounds__(256) void k_gather(Coords c,
                                                 const uint32_t *__restrict__ perm,
                                                 int64_t n, float4 *__restrict__ out) {
@@ -320,6 +332,26 @@ __global__ __launch_bounds__(256) void k_gather(Coords c,
   }
 }
 
+// The same for a new tree, with the inverse permutation and the words that
+// start at zero with it (reference and previous list lengths): one launch
+// instead of four.
+__global__ __launch_bounds__(256) void k_gather_new(Coords c,
+                                                    const uint32_t *__restrict__ perm,
+                                                    int64_t n, float4 *__restrict__ out,
+                                                    uint32_t *__restrict__ inv,
+                                                    uint32_t *__restrict__ gref,
+                                                    uint32_t *__restrict__ plast) {
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    const uint32_t p = perm[i];
+    out[i] = c.stride == 4 ? reinterpret_cast<const float4 *>(c.x)[p]
+                           : make_float4(c.x[p], c.y[p], c.z[p], c.m[p]);
+    inv[p] = (uint32_t)i;
+    gref[i] = 0u;
+    plast[i] = 0u;
+  }
+}
+
 static int grid_for(int64_t n, int per_thread, int cap) {
   int64_t g = cdiv(n, 256LL * per_thread);
   if (g < 1) g = 1;
@@ -327,10 +359,20 @@ static int grid_for(int64_t n, int per_thread, int cap) {
   return (int)g;
 }
 
-void launch_bbox(const Coords &c, int64_t n, DevScalars *sc, uint32_t *part, hipStream_t st) {
+// up to this many partials are folded by every workgroup of k_keys (about 1 us
+// each) instead of by a launch of their own (4 us)
+constexpr int kFoldInKeys = 64;
+
+void launch_bbox_keys(const Coords &c, int64_t n, DevScalars *sc, uint32_t *part,
+                      uint64_t *keys, uint32_t *vals, hipStream_t st) {
   const int nb = grid_for(n, 16, 1024);  // 6 words of part per block
   hipLaunchKernelGGL(k_bbox, dim3(nb), dim3(256), 0, st, c, n, sc, part);
-  hipLaunchKernelGGL(k_bbox_fold, dim3(1), dim3(256), 0, st, part, nb, sc);
+  if (nb > kFoldInKeys) {
+    hipLaunchKernelGGL(k_bbox_fold, dim3(1), dim3(256), 0, st, part, nb, sc);
+    part = nullptr;
+  }
+  hipLaunchKernelGGL(k_keys, dim3(grid_for(n, 4, 8192)), dim3(256), 0, st, c, n, sc, part, nb,
+                     keys, vals);
 }
 
 void launch_sys_keys(const Coords &c, int64_t n, int nsys, int r, const Ptrs &P,
@@ -349,20 +391,16 @@ void launch_sys_keys(const Coords &c, int64_t n, int nsys, int r, const Ptrs &P,
                      P.sysoff, nsys, r, P.sysbox, P.keysA, P.valsA);
 }
 
-void launch_invert(const uint32_t *perm, int64_t n, uint32_t *inv, hipStream_t st) {
-  hipLaunchKernelGGL(k_invert, dim3(grid_for(n, 4, 8192)), dim3(256), 0, st, perm, n, inv);
-}
-
-void launch_keys(const Coords &c, int64_t n, DevScalars *sc, uint64_t *keys, uint32_t *vals,
-                 hipStream_t st) {
-  hipLaunchKernelGGL(k_keys, dim3(grid_for(n, 4, 8192)), dim3(256), 0, st, c, n, sc, keys,
-                     vals);
-}
-
 void launch_gather(const Coords &c, const uint32_t *perm, int64_t n, float4 *xyzm,
                    hipStream_t st) {
   hipLaunchKernelGGL(k_gather, dim3(grid_for(n, 4, 8192)), dim3(256), 0, st, c, perm, n,
                      xyzm);
+}
+
+void launch_gather_new(const Coords &c, const uint32_t *perm, int64_t n, const Ptrs &P,
+                       hipStream_t st) {
+  hipLaunchKernelGGL(k_gather_new, dim3(grid_for(n, 4, 8192)), dim3(256), 0, st, c, perm, n,
+                     P.xyzm, P.inv, P.gref, P.plast);
 }
 
 }  // namespace nb

@@ -1055,57 +1055,77 @@ __global__ __launch_bounds__(64) void k_heavy_end(WalkArgs a) {
 // Interactions of the walked groups, and of those the tree's reference walk
 // also took, now and then (the reference walk records them here): integer
 // sums per workgroup into part[4 * blockIdx.x ..] (same-address atomics from
-// every workgroup would serialise), added up by k_walk_stat_fold.
-__global__ __launch_bounds__(256) void k_walk_stat(DevScalars *__restrict__ sc,
-                                                   const uint32_t *__restrict__ order,
-                                                   const uint32_t *__restrict__ gcount,
-                                                   const uint32_t *__restrict__ gent,
-                                                   uint32_t *__restrict__ gref, int record,
-                                                   unsigned long long *__restrict__ part) {
-  __shared__ unsigned long long s_sum[4][4];
+// every workgroup would serialise), added up by k_walk_stat_fold. A small
+// set's walk (kOne) takes one workgroup, which finishes the statistics itself.
+__device__ __forceinline__ void store_walk_stat(DevScalars *__restrict__ sc, bool queued,
+                                                const unsigned long long (&t)[4],
+                                                WalkStat *__restrict__ host) {
+  WalkStat w;
+  w.ngroup = sc->ngroup;
+  w.queued = queued ? sc->nqueue : sc->ngroup;
+  w.inter = t[0];
+  w.inter_a = t[1];
+  w.inter_ref = t[2];
+  w.entries = t[3];
+  w.tick = sc->tick;
+  w.kmax = sc->kmax;
+  w.pad = 0u;
+  *host = w;  // page-locked host memory: no copy after the kernel
+}
+
+constexpr int kStatThreads = 1024;  // of the single workgroup
+template <bool kOne>
+__global__ __launch_bounds__(kOne ? kStatThreads : 256) void k_walk_stat(
+    DevScalars *__restrict__ sc, const uint32_t *__restrict__ order,
+    const uint32_t *__restrict__ gcount, const uint32_t *__restrict__ gent,
+    uint32_t *__restrict__ gref, int record, unsigned long long *__restrict__ part,
+    WalkStat *__restrict__ host) {
+  constexpr int kWaves = (kOne ? kStatThreads : 256) / 64;
+  __shared__ unsigned long long s_sum[kWaves][4];
   const uint32_t nq = order ? sc->nqueue : sc->ngroup;
-  unsigned long long cur = 0, cur_a = 0, ref = 0, ent = 0;
+  unsigned long long v[4] = {0, 0, 0, 0};  // interactions: all, of reference groups now, then
   for (uint32_t q = blockIdx.x * blockDim.x + threadIdx.x; q < nq;
        q += gridDim.x * blockDim.x) {
     const uint32_t g = order ? order[q] : q;
     const uint32_t e = gent[g], c = gcount[g];
     if (e == 0xffffffffu) continue;
     const unsigned long long ec = (unsigned long long)e * c;
-    cur += ec;
-    ent += e;
+    v[0] += ec;
+    v[3] += e;
     uint32_t r = gref[g];
     if (record && r == 0) {
       r = e;
       gref[g] = e;
     }
     if (r != 0) {
-      cur_a += ec;
-      ref += (unsigned long long)r * c;
+      v[1] += ec;
+      v[2] += (unsigned long long)r * c;
     }
   }
-  for (int d = 32; d >= 1; d >>= 1) {
-    cur += __shfl_xor(cur, d, 64);
-    cur_a += __shfl_xor(cur_a, d, 64);
-    ref += __shfl_xor(ref, d, 64);
-    ent += __shfl_xor(ent, d, 64);
-  }
-  const int w = threadIdx.x >> 6;
-  if (lane_id() == 0) {
-    s_sum[w][0] = cur;
-    s_sum[w][1] = cur_a;
-    s_sum[w][2] = ref;
-    s_sum[w][3] = ent;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    for (int d = 32; d >= 1; d >>= 1) v[k] += __shfl_xor(v[k], d, 64);
+    if (lane_id() == 0) s_sum[threadIdx.x >> 6][k] = v[k];
   }
   __syncthreads();
-  if (threadIdx.x < 4)
+  if constexpr (kOne) {
+    if (threadIdx.x == 0) {
+      unsigned long long t[4] = {0, 0, 0, 0};
+      for (int w = 0; w < kWaves; ++w)
+        for (int k = 0; k < 4; ++k) t[k] += s_sum[w][k];
+      store_walk_stat(sc, order != nullptr, t, host);
+    }
+  } else if (threadIdx.x < 4) {
     part[4 * blockIdx.x + threadIdx.x] = s_sum[0][threadIdx.x] + s_sum[1][threadIdx.x] +
                                          s_sum[2][threadIdx.x] + s_sum[3][threadIdx.x];
+  }
 }
 
 // The walk statistics: the partials' sums and the step's scalars (one
 // workgroup of kStatBlocks threads).
 __global__ __launch_bounds__(kStatBlocks) void k_walk_stat_fold(
-    DevScalars *__restrict__ sc, const unsigned long long *__restrict__ part, int queued) {
+    DevScalars *__restrict__ sc, const unsigned long long *__restrict__ part, int queued,
+    WalkStat *__restrict__ host) {
   __shared__ unsigned long long s_sum[kStatBlocks / 64][4];
   unsigned long long v[4];
 #pragma unroll
@@ -1120,14 +1140,7 @@ __global__ __launch_bounds__(kStatBlocks) void k_walk_stat_fold(
     unsigned long long t[4] = {0, 0, 0, 0};
     for (int w = 0; w < kStatBlocks / 64; ++w)
       for (int k = 0; k < 4; ++k) t[k] += s_sum[w][k];
-    sc->wstat.ngroup = sc->ngroup;
-    sc->wstat.queued = queued ? sc->nqueue : sc->ngroup;
-    sc->wstat.inter = t[0];
-    sc->wstat.inter_a = t[1];
-    sc->wstat.inter_ref = t[2];
-    sc->wstat.entries = t[3];
-    sc->wstat.tick = sc->tick;
-    sc->wstat.kmax = sc->kmax;
+    store_walk_stat(sc, queued != 0, t, host);
   }
 }
 
@@ -1165,12 +1178,22 @@ void launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t st) {
   hipLaunchKernelGGL(k_fill_u32, dim3(g), dim3(256), 0, st, p, v, n);
 }
 
-void launch_walk_stat(bool queued, bool record, const Ptrs &P, hipStream_t st) {
-  hipLaunchKernelGGL(k_walk_stat, dim3(kStatBlocks), dim3(256), 0, st, P.sc,
-                     queued ? P.order : nullptr, P.gcount, P.gent, P.gref, record ? 1 : 0,
-                     P.wpart);
+// Up to this many particles (so, at some ten and more per group, a few
+// thousand groups) the statistics take one workgroup.
+constexpr int64_t kStatOne = 128 * 1024;
+
+void launch_walk_stat(int64_t n, bool queued, bool record, const Ptrs &P, WalkStat *host,
+                      hipStream_t st) {
+  const uint32_t *order = queued ? P.order : nullptr;
+  if (n <= kStatOne) {
+    hipLaunchKernelGGL(k_walk_stat<true>, dim3(1), dim3(kStatThreads), 0, st, P.sc, order,
+                       P.gcount, P.gent, P.gref, record ? 1 : 0, P.wpart, host);
+    return;
+  }
+  hipLaunchKernelGGL(k_walk_stat<false>, dim3(kStatBlocks), dim3(256), 0, st, P.sc, order,
+                     P.gcount, P.gent, P.gref, record ? 1 : 0, P.wpart, host);
   hipLaunchKernelGGL(k_walk_stat_fold, dim3(1), dim3(kStatBlocks), 0, st, P.sc, P.wpart,
-                     queued ? 1 : 0);
+                     queued ? 1 : 0, host);
 }
 
 
@@ -1310,6 +1333,8 @@ void launch_walk(const WalkCfg &c, const uint32_t *perm, int64_t n, float *ax, f
     hipLaunchKernelGGL(k_walk_mid, dim3(kFrontBlocks + (join ? kJoinBlocks : 0u)), dim3(256), 0,
                        st, a, waves, c.hash ? 1 : 0, kFrontBlocks, join);
   }
+  // (a list holds no more entries than there are particles)
+  if (n <= (int64_t)heavy_limit((uint32_t)n)) return;
   if (c.compensated)
     heavy_passes_of<true>(c, a, P, st);
   else

@@ -28,7 +28,7 @@ constexpr int32_t kStOverflow = 2;
 constexpr int32_t kStCapacity = 4;
 constexpr int32_t kStCorrupt = 8;  // internal consistency check failed
 
-// Statistics of the last walk for the rebuild controller (copied to the host).
+// Statistics of a walk for the rebuild controller (written to host memory).
 struct WalkStat {
   uint32_t ngroup, queued;
   unsigned long long inter;      // interactions of the walked groups
@@ -65,7 +65,6 @@ struct DevScalars {
   uint32_t nheavy;         // groups walked in parts
   uint32_t nhpart, nhfront;  // parts and front cells asked for
   uint32_t heavy_head;     // the parts' work queue
-  WalkStat wstat;
   unsigned long long bar_epoch;  // launches of the grid-barrier calcNode so far
   uint32_t istart[kLevels + 1];  // internal cells of level l: ilist[istart[l] .. istart[l + 1])
   uint32_t nleaf;          // leaves of the current tree
@@ -189,21 +188,24 @@ struct Coords {
 };
 
 // ---- launchers (each enqueues on `st`; grid sizes depend only on n) ----
-// part: 6 x ceil(n / 4096) words of scratch
-void launch_bbox(const Coords &c, int64_t n, DevScalars *sc, uint32_t *part, hipStream_t st);
-void launch_keys(const Coords &c, int64_t n, DevScalars *sc, uint64_t *keys, uint32_t *vals,
-                 hipStream_t st);
+// root cube, keys and values 0 .. n - 1; part: 6 x ceil(n / 4096) words of scratch
+void launch_bbox_keys(const Coords &c, int64_t n, DevScalars *sc, uint32_t *part,
+                      uint64_t *keys, uint32_t *vals, hipStream_t st);
 // returns pointer (A or B) holding the sorted result
 void launch_sort(int64_t n, uint64_t *keysA, uint32_t *valsA, uint64_t *keysB,
                  uint32_t *valsB, uint32_t *hist, hipStream_t st, uint64_t **keys_out,
                  uint32_t **vals_out);
 void launch_gather(const Coords &c, const uint32_t *perm, int64_t n, float4 *xyzm,
                    hipStream_t st);
+// of a new tree: also P.inv, and P.gref and P.plast zero
+void launch_gather_new(const Coords &c, const uint32_t *perm, int64_t n, const Ptrs &P,
+                       hipStream_t st);
+// host_istart (may be null): page-locked, kLevels + 1 words, receives sc->istart
 // r > 0: a batch of nsys systems (cells above level r always split, groups
 // at level r or deeper, per-group walk roots in P.groot)
 void launch_build(const uint64_t *keys, int64_t n, int leaf_max, int group_max,
                   int group_merge, int nsys, int r, const Ptrs &P, const Layout &L,
-                  hipStream_t st);
+                  uint32_t *host_istart, hipStream_t st);
 // batch keys into P.keysA / P.valsA from P.sysoff; per-system cubes to P.sysbox
 // (part: part_words words of scratch for partial bounds)
 void launch_sys_keys(const Coords &c, int64_t n, int nsys, int r, const Ptrs &P,
@@ -302,8 +304,6 @@ void launch_rk2_correct(int64_t n, double *x, double *y, double *z, float *vx, f
                         float *vz, const float *ax, const float *ay, const float *az,
                         const float *apx, const float *apy, const float *apz, double dt,
                         float *x32, SortedOut so, hipStream_t st);
-// inv[perm[s]] = s
-void launch_invert(const uint32_t *perm, int64_t n, uint32_t *inv, hipStream_t st);
 
 // Block-step calls of at least this many steps keep the state in key order
 // (the gather on entry and the scatter on exit cost about what eight steps
@@ -345,10 +345,11 @@ void launch_ko_scatter(int64_t n, const KoSet &k, const KoSet &caller, uint4 *re
                        uint32_t *inv, unsigned long long *hash, unsigned long long *part,
                        hipStream_t st);
 // After a rebuild: slot s of the new order is slot perm[s] of the old one;
-// with xyzm, also the tree's sorted (x, y, z, m) records, (float) of the FP64
-// positions (what the drift stored as the records the keys came from).
+// also the tree's sorted (x, y, z, m) records P.xyzm, (float) of the FP64
+// positions (what the drift stored as the records the keys came from), and
+// P.gref and P.plast zero.
 void launch_ko_permute(int64_t n, const uint32_t *perm, const KoSet &from, const KoSet &to,
-                       float4 *xyzm, hipStream_t st);
+                       const Ptrs &P, hipStream_t st);
 // Equal keys in caller order: the sort of a key-ordered state keeps equal
 // keys in their old slot order; each run of equal keys is reordered by the
 // caller index pt_old[vals[j]].
@@ -361,10 +362,12 @@ void launch_scan_rows(uint32_t *rows, uint32_t len, int nrows, uint32_t *totals,
                       uint32_t *tsum, hipStream_t st);
 int64_t scan_scratch_words(int64_t len, int nrows);
 
-// sc->wstat of the walk just finished (queued: order[0 .. nqueue), else all)
+// *host (page-locked) = the statistics of the walk just finished (queued:
+// order[0 .. nqueue), else all)
 // record: this walk is the tree's reference walk (its first with the
 // acceleration criterion); it stores each walked group's list length in gref
-void launch_walk_stat(bool queued, bool record, const Ptrs &P, hipStream_t st);
+void launch_walk_stat(int64_t n, bool queued, bool record, const Ptrs &P, WalkStat *host,
+                      hipStream_t st);
 
 // single 8-bit digit pass of the stable radix sort (digit = key >> shift) of
 // the first min(n, *n_dev) entries (n_dev may be null); n bounds the grid
@@ -418,17 +421,17 @@ struct BlockCfg {
   int level_min, level_max;
 };
 void launch_blk_setup(long long tick, DevScalars *sc, hipStream_t st);
-// level of every particle from a (at the current tick); kmax_next = max level
+// Each of these starts a call's step scalars at `tick`; with begin, the next
+// step (its tick; opening kicks at tick0, drift of every particle to tick).
+// level of every particle from a (at that tick); kmax_next = max level
 // part: scratch of 2 x (workgroups) words for the per-workgroup maxima and
 // counts (the build's block counts, free outside a build)
 void launch_blk_init(int64_t n, const float *ax, const float *ay, const float *az,
-                     int8_t *level, const BlockCfg &c, DevScalars *sc, uint32_t *part,
-                     hipStream_t st);
+                     int8_t *level, const BlockCfg &c, long long tick, bool begin,
+                     DevScalars *sc, uint32_t *part, hipStream_t st);
 // kmax_next = max level; levels outside [level_min, level_max] set kStCorrupt
-void launch_blk_scan(int64_t n, const int8_t *level, const BlockCfg &c, DevScalars *sc,
-                     uint32_t *part, hipStream_t st);
-// next tick; opening kicks at tick0; drift of every particle to tick
-void launch_blk_begin(DevScalars *sc, hipStream_t st);
+void launch_blk_scan(int64_t n, const int8_t *level, const BlockCfg &c, long long tick,
+                     bool begin, DevScalars *sc, uint32_t *part, hipStream_t st);
 void launch_blk_open_drift(int64_t n, double *x, double *y, double *z, float *vx, float *vy,
                            float *vz, const float *ax, const float *ay, const float *az,
                            const int8_t *level, double dt_max, const DevScalars *sc,
@@ -437,11 +440,11 @@ void launch_blk_open_drift(int64_t n, double *x, double *y, double *z, float *vx
 void launch_blk_queue(int64_t n, const int8_t *level, const uint32_t *perm, const Ptrs &P,
                       hipStream_t st);
 // active particles: a = anew (also into the key-ordered mirror asort through
-// inv), closing kick, new level; kmax_next, nactive
+// inv), closing kick, new level; kmax_next, nactive; with begin, the next step
 void launch_blk_close(int64_t n, float *ax, float *ay, float *az, const float *nax,
                       const float *nay, const float *naz, float *vx, float *vy, float *vz,
                       int8_t *level, const BlockCfg &c, float4 *asort, const uint32_t *inv,
-                      DevScalars *sc, uint32_t *part, hipStream_t st);
+                      bool begin, DevScalars *sc, uint32_t *part, hipStream_t st);
 void launch_order_by_count(int64_t n, const Ptrs &P, hipStream_t st);
 
 // ---- device helpers ----
