@@ -505,14 +505,16 @@ __global__ __launch_bounds__(256) void k_adam(int64_t np, const float *__restric
     adam_update(ad, i, g[i]);
 }
 
-// Queue sort keys: one 8-bit digit, larger predicted cost first (quarter-octave
-// buckets); equal digits keep group order in the stable digit sort, which
-// covers the queue's entries only (the count is read on the device). Predicted
-// costs below 2^kBulkLog2 interactions (modes 1 and 2) share one bucket: no
-// such group decides when the walk ends, and in group order neighbours share
-// cells in the caches (2^23 galaxy, block steps, rebuild every 2nd step: 2.44
-// ms per walk with the bulk ordered, 2.36 with it in group order, plain 2.51).
-constexpr float kBulkLog2 = 18.0f;
+// Queue sort keys: one 8-bit digit, larger predicted cost first; equal digits
+// keep group order in the stable digit sort, which covers the queue's entries
+// only (the count is read on the device). Modes 1 and 2 take whole octaves of
+// the predicted interactions: the tail only needs the costs in rough order, and
+// in group order neighbours share cells in the caches. Below 2^14.5 no group
+// decides when the walk ends: one bucket. (2^23 galaxy, block steps, rebuild
+// every 2nd step, per walk: quarter octaves 2.44 ms, quarter octaves with one
+// bucket below 2^18 2.31, octaves 2.21, plain 2.60.) Mode 3 keeps
+// quarter octaves.
+constexpr float kBulkLog2 = 14.0f;
 __global__ __launch_bounds__(256) void k_cost_keys(
     const DevScalars *__restrict__ sc, const uint32_t *__restrict__ queue, int mode,
     const float4 *__restrict__ feat, const float *__restrict__ pred,
@@ -527,8 +529,8 @@ __global__ __launch_bounds__(256) void k_cost_keys(
     // mode 1: log2(count) + log2(1 + previous list length); mode 2: the
     // model; mode 3: the log2 interactions the last ordered walk recorded
     const float c = mode == 2 ? pred[g] : mode == 3 ? target[g] : f.x + f.w;
-    const float lo = mode == 3 ? 0.0f : 4.0f * kBulkLog2;
-    const float q = fminf(fmaxf(c * 4.0f, lo), 254.0f);  // NaN -> lo
+    const float q = mode == 3 ? fminf(fmaxf(c * 4.0f, 0.0f), 254.0f)  // NaN -> 0
+                              : fminf(fmaxf(c + 0.5f, kBulkLog2), 254.0f);
     keys[i] = 254u - (uint32_t)q;
     vals[i] = g;
   }
