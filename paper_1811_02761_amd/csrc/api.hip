@@ -261,8 +261,15 @@ Layout make_layout(const nbody_params &p, int64_t n, int num_cu, bool stepping,
   while (L.heavy_cap < L.cell_cap && L.heavy_cap < 16384) L.heavy_cap <<= 1;
   const int64_t end_words = L.heavy_cap + 2 * (int64_t)kFrontCap;
   const int64_t fwords = std::max<int64_t>(L.walk_waves * L.frontier_cap, 64 * end_words);
-  L.heavy_waves = (int)std::min<int64_t>(L.walk_waves, fwords / L.heavy_cap) / kWalkWavesPerWG *
-                  kWalkWavesPerWG;
+  auto waves_of = [&](int64_t stack) {
+    return (int)std::min<int64_t>(L.walk_waves, fwords / stack) / kWalkWavesPerWG *
+           kWalkWavesPerWG;
+  };
+  L.retry_waves = waves_of(L.heavy_cap);
+  // parts rarely hold more than kFrontCap particles: smaller stacks, more
+  // wavefronts (k_heavy_walk)
+  L.heavy_stack = std::min<int64_t>(L.heavy_cap, std::max<int64_t>(p.frontier_cap, kFrontCap));
+  L.heavy_waves = waves_of(L.heavy_stack);
   L.heavy_end_blocks = (int)std::min<int64_t>(512, fwords / end_words);
   L.off_frontier = take(4 * (size_t)fwords);
   L.off_atmp = take(12 * N);
@@ -529,7 +536,9 @@ WalkCfg walk_cfg(const nbody_ctx *ctx, bool bootstrap, bool queued) {
   c.split_slots = ctx->L.split_slots;
   c.heavy_slots = ctx->L.heavy_slots;
   c.heavy_cap = ctx->L.heavy_cap;
+  c.heavy_stack = ctx->L.heavy_stack;
   c.heavy_waves = ctx->L.heavy_waves;
+  c.retry_waves = ctx->L.retry_waves;
   c.heavy_end_blocks = ctx->L.heavy_end_blocks;
   return c;
 }

@@ -792,7 +792,9 @@ __device__ __forceinline__ uint32_t heavy_parts(const WalkArgs &a, float4 glo, f
 // walk ends; groups handed on (by their entry count) are left out. With no
 // front blocks (the launch before the retry pass) they also collect that
 // pass's queue.
-constexpr uint32_t kFrontBlocks = 256, kJoinBlocks = 512;
+// (1024 front workgroups, four per CU, instead of 256: 214 -> 130 us for the
+// heavy groups of a batch of 64 systems, 3.1 million particles.)
+constexpr uint32_t kFrontBlocks = 1024, kJoinBlocks = 512;
 __global__ __launch_bounds__(256) void k_walk_mid(WalkArgs a, uint32_t walk_waves, int hash,
                                                   uint32_t front_blocks, int join) {
   __shared__ uint32_t s_front[2 * kFrontCap];
@@ -832,15 +834,16 @@ __global__ __launch_bounds__(256) void k_walk_mid(WalkArgs a, uint32_t walk_wave
           if (hash) a.ghash[g] = 0ull;
           s_at[0] = s0;
           s_at[1] = room ? f0 : kEntNone;
+          s_at[2] = h;
         }
         __syncthreads();
-        const uint32_t s0 = s_at[0], f0 = s_at[1];
+        const uint32_t s0 = s_at[0], f0 = s_at[1], h = s_at[2];
         const bool room = f0 != kEntNone;
         for (uint32_t r = threadIdx.x; r < P; r += 256u)
           if (s0 + r < a.hslots && s0 + r >= s0)
             a.hparts[s0 + r] =
-                room ? make_uint4(g, f0 + s_pb[r], s_pb[r + 1] - s_pb[r], 0u)
-                     : make_uint4(g, 0u, 0u, 0u);  // nothing to walk
+                room ? make_uint4(g, f0 + s_pb[r], s_pb[r + 1] - s_pb[r], h)
+                     : make_uint4(g, 0u, 0u, h);  // nothing to walk
         if (room)
           for (uint32_t k = threadIdx.x; k < m; k += 256u) a.hfront[f0 + k] = cur[k];
         __syncthreads();  // LDS is reused by the next group
@@ -941,9 +944,13 @@ struct PartSums<true, kPot> {
   __device__ __forceinline__ float total(uint32_t k) const { return v[k] + c[k]; }
 };
 
-// The parts of the heavy groups, taken from a queue as the main pass takes
-// groups: each wavefront walks the subtrees of one part's cells and stores
-// its lanes' sums in the part's slot.
+// The parts of the heavy groups: each wavefront walks the subtrees of one
+// part's cells and stores its lanes' sums in the part's slot. The parts are
+// about equal, so wavefront w takes parts w, w + nw, ...; taken from a queue,
+// 44000 parts of a batch of 64 systems were 44000 atomics on one word: 572 us,
+// 241 without, and no wavefronts more helped before. A part's stack stays under
+// kFrontCap cells but for trees far from any in use; a part that outgrows it
+// leaves its group to k_heavy_end, whose stacks hold every cell.
 template <bool kComp, bool kHash, bool kPot>
 __global__ __launch_bounds__(64 * kWalkWavesPerWG) void k_heavy_walk(WalkArgs a) {
   HIP_DYNAMIC_SHARED(float4, lds_list)
@@ -955,10 +962,8 @@ __global__ __launch_bounds__(64 * kWalkWavesPerWG) void k_heavy_walk(WalkArgs a)
   const uint32_t np = min(a.sc->nhpart, a.hslots);
   const uint32_t ncell = a.sc->ncell;
   const uint32_t nw = gridDim.x * kWalkWavesPerWG;
-  uint32_t t = __builtin_amdgcn_readfirstlane(blockIdx.x * kWalkWavesPerWG + wv);
-  for (bool first = true; first || np > nw; first = false) {  // claims as in walk_loop
-    if (!first) t = next_task(a, nw, lane);
-    if (t >= np) break;
+  for (uint32_t t = __builtin_amdgcn_readfirstlane(blockIdx.x * kWalkWavesPerWG + wv); t < np;
+       t += nw) {
     const uint4 part = a.hparts[t];
     const uint32_t g = __builtin_amdgcn_readfirstlane(part.x);
     const uint32_t f0 = __builtin_amdgcn_readfirstlane(part.y);
@@ -977,7 +982,8 @@ __global__ __launch_bounds__(64 * kWalkWavesPerWG) void k_heavy_walk(WalkArgs a)
     const uint32_t end =
         walk_list<kComp, kHash, kPot, 1>(a, l, w, stk, a.fmask + 1u, m, 0u, 0xffffffffu, ncell,
                                          lane, R, entries, hsum);
-    if (end) atomicOr(&a.sc->status, end == kEndOverflow ? kStOverflow : kStCorrupt);
+    if (end == kEndOverflow) a.hrec[part.w] = make_uint2(0u, 0u);  // left to k_heavy_end
+    if (end == kEndCorrupt) atomicOr(&a.sc->status, kStCorrupt);
     PartSums<kComp, kPot>::store(a.hsum + (size_t)t * a.hwords, lane, R);
     atomicAdd(&a.gent[g], lane == 0 ? entries : 0u);
     if (kHash) {
@@ -1008,12 +1014,18 @@ __global__ __launch_bounds__(64) void k_heavy_end(WalkArgs a) {
     const uint32_t P = __builtin_amdgcn_readfirstlane(rec.y);
     Sums T;
     if (P > 0u) {
-      for (uint32_t r = 0; r < P; ++r) {
-        const float *slot = a.hsum + (size_t)(s0 + r) * a.hwords;
-        float p[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      // four parts' loads in flight (P is at most kMaxParts)
+      for (uint32_t r = 0; r < P; r += 4u) {
+        float p[4][8];
 #pragma unroll
-        for (uint32_t k = 0; k < Sums::kWords; ++k) p[k] = slot[k * 64 + lane];
-        T.add(p);
+        for (uint32_t j = 0; j < 4; ++j) {
+          const float *slot = a.hsum + (size_t)(s0 + min(r + j, P - 1u)) * a.hwords;
+#pragma unroll
+          for (uint32_t k = 0; k < 8; ++k) p[j][k] = k < Sums::kWords ? slot[k * 64 + lane] : 0.f;
+        }
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j)
+          if (r + j < P) T.add(p[j]);
       }
     } else {
       uint32_t *cur = stk + a.fmask + 1u, *nxt = cur + kFrontCap;
@@ -1273,10 +1285,10 @@ namespace {
 template <bool kComp, bool kHash, bool kPot>
 void heavy_passes(const WalkCfg &c, WalkArgs a, const Ptrs &P, hipStream_t st) {
   a.frontier = P.frontier;
-  a.fmask = (uint32_t)c.heavy_cap - 1u;
-  a.head = &P.sc->heavy_head;
+  a.fmask = (uint32_t)c.heavy_stack - 1u;
   hipLaunchKernelGGL((k_heavy_walk<kComp, kHash, kPot>), dim3(c.heavy_waves / kWalkWavesPerWG),
                      dim3(64 * kWalkWavesPerWG), walk_lds(c, kWalkWavesPerWG), st, a);
+  a.fmask = (uint32_t)c.heavy_cap - 1u;
   hipLaunchKernelGGL((k_heavy_end<kComp, kHash, kPot>), dim3(c.heavy_end_blocks), dim3(64),
                      walk_lds(c, 1), st, a);
 }
@@ -1322,7 +1334,7 @@ void launch_walk(const WalkCfg &c, const uint32_t *perm, int64_t n, float *ax, f
     r.fmask = (uint32_t)c.heavy_cap - 1u;
     r.head = &P.sc->retry_head;
     r.split_mode = -1;  // results written by the pass itself
-    const dim3 rgrid(c.heavy_waves / kWalkWavesPerWG);
+    const dim3 rgrid(c.retry_waves / kWalkWavesPerWG);
     if (c.phi)
       NB_WALK_LAUNCH(k_walk_pot, c, rgrid, lds, st, r);
     else

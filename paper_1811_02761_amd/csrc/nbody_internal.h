@@ -64,7 +64,6 @@ struct DevScalars {
   uint32_t retry_head;     // the retry pass's work queue
   uint32_t nheavy;         // groups walked in parts
   uint32_t nhpart, nhfront;  // parts and front cells asked for
-  uint32_t heavy_head;     // the parts' work queue
   unsigned long long bar_epoch;  // launches of the grid-barrier calcNode so far
   uint32_t istart[kLevels + 1];  // internal cells of level l: ilist[istart[l] .. istart[l + 1])
   uint32_t nleaf;          // leaves of the current tree
@@ -98,8 +97,8 @@ struct Layout {
   // heavy groups: part slots, the stack no tree outgrows, and the wavefronts
   // (k_heavy_walk, the retry pass) and workgroups (k_heavy_end) with such a
   // stack in `frontier`
-  int64_t heavy_slots = 0, heavy_cap = 0;
-  int heavy_waves = 0, heavy_end_blocks = 0;
+  int64_t heavy_slots = 0, heavy_cap = 0, heavy_stack = 0;
+  int heavy_waves = 0, retry_waves = 0, heavy_end_blocks = 0;
   size_t total = 0;
 };
 
@@ -248,8 +247,8 @@ struct WalkCfg {
   bool asort_out;  // also write the outputs, with |a|, to P.asort in key order
   int split;       // wavefronts per group: 0 by queue length, else 1, 2 or 4
   int64_t split_slots;
-  int64_t heavy_slots, heavy_cap;
-  int heavy_waves, heavy_end_blocks;
+  int64_t heavy_slots, heavy_cap, heavy_stack;
+  int heavy_waves, retry_waves, heavy_end_blocks;
   float *phi = nullptr;  // potential output (caller order): the potential variant
 };
 constexpr uint32_t kFrontCap = 4096;  // cells of a heavy group's front, at most
