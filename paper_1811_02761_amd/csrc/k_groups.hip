@@ -24,7 +24,6 @@ __global__ __launch_bounds__(256) void k_group_bounds(
     sc->nretry = 0;
     sc->nheavy = 0;
     sc->nhpart = 0;
-    sc->nhfront = 0;
   }
   // the queued groups (block steps) or every group
   const uint32_t nq = queue ? sc->nqueue : sc->ngroup;

@@ -679,7 +679,8 @@ __device__ __forceinline__ void walk_body(const WalkArgs &a, float4 *lds_list) {
 // and hold more than `big` particles are replaced by their children, in order,
 // round by round, until none is left or the front would not fit in kFrontCap
 // cells. NT threads of one workgroup; cur and nxt hold kFrontCap cells each.
-// Returns the front's length, with cur pointing at it (uniform).
+// Returns the front's length, with cur pointing at it (uniform) and nxt at the
+// cells' weights: 1 for an accepted cell, another's particles.
 template <int NT>
 __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t *wsum, uint32_t *total) {
   const uint32_t inc = wave_incl_scan_dpp(v);
@@ -708,25 +709,37 @@ __device__ __forceinline__ uint32_t heavy_front(const WalkArgs &a, uint32_t root
                                                 uint32_t *&cur, uint32_t *&nxt,
                                                 uint32_t *wsum) {
   const uint32_t tid = threadIdx.x;
+  // w: the cell's weight, nout, first: what it is replaced by (itself, or its
+  // children)
+  auto look = [&](uint32_t c, uint32_t &nout, uint32_t &first) -> uint32_t {
+    nout = 1u;
+    first = c;
+    if (c >= ncell) return 1u;
+    const float4 A = a.nodeA[c], B = a.nodeB[c];
+    const uint32_t w0 = __float_as_uint(B.z), w1 = __float_as_uint(B.w), np = a.cpcount[c];
+    if (mac_accept(A, B.y, glo, ghi, glo.w, a.bootstrap)) return 1u;
+    if (!(w1 & kLeafBit) && w1 >= 1u && w1 <= 8u && w0 > c && w0 < ncell && w1 <= ncell - w0 &&
+        np > big) {
+      nout = w1;
+      first = w0;
+    }
+    return max(np, 1u);
+  };
   if (tid == 0) cur[0] = root;
   __syncthreads();
   uint32_t m = 1;
   for (int round = 0; round <= kMaxLevel; ++round) {
+    // a round that cannot outgrow nxt leaves the weights in cur, in place of the
+    // cells: if it opens none, it was the last, and nxt holds the same cells
+    const bool fits = m <= kFrontCap / 8u;
     uint32_t out = 0, opened = 0;
     for (uint32_t k0 = 0; k0 < m; k0 += NT) {
       const bool has = k0 + tid < m;
       const uint32_t c = has ? cur[k0 + tid] : 0u;
-      uint32_t nout = has ? 1u : 0u, first = c;
-      if (has && c < ncell) {
-        const float4 A = a.nodeA[c], B = a.nodeB[c];
-        const uint32_t w0 = __float_as_uint(B.z), w1 = __float_as_uint(B.w);
-        const bool inner = !(w1 & kLeafBit) && w1 >= 1u && w1 <= 8u && w0 > c &&
-                           w0 < ncell && w1 <= ncell - w0;
-        if (inner && a.cpcount[c] > big &&
-            !mac_accept(A, B.y, glo, ghi, glo.w, a.bootstrap)) {
-          nout = w1;
-          first = w0;
-        }
+      uint32_t nout = 0, first = c;
+      if (has) {
+        const uint32_t wt = look(c, nout, first);
+        if (fits) cur[k0 + tid] = wt;
       }
       const bool open = first != c;  // (a child's index is never its parent's)
       uint32_t tot;
@@ -737,31 +750,35 @@ __device__ __forceinline__ uint32_t heavy_front(const WalkArgs &a, uint32_t root
       opened += tot >> 16;
     }
     __syncthreads();
-    if (opened == 0u || out > kFrontCap) break;  // (uniform)
+    if (opened == 0u || out > kFrontCap) {  // (uniform)
+      if (!fits) {
+        for (uint32_t k = tid; k < m; k += NT) {
+          uint32_t nout, first;
+          nxt[k] = look(cur[k], nout, first);
+        }
+        __syncthreads();
+        return m;
+      }
+      break;
+    }
     uint32_t *t = cur;
     cur = nxt;
     nxt = t;
     m = out;
   }
+  uint32_t *t = cur;
+  cur = nxt;
+  nxt = t;
   return m;
 }
 
-// Cuts a front of m cells into parts of about equal weight (an accepted cell
-// weighs 1, another its particles): part r takes the cells [pb[r], pb[r + 1]).
-// Returns the number of parts (uniform); pb is in LDS.
+// Cuts a front of m cells into parts of about equal weight: part r takes the
+// cells [pb[r], pb[r + 1]). Returns the number of parts (uniform); pb is in LDS.
 template <int NT>
-__device__ __forceinline__ uint32_t heavy_parts(const WalkArgs &a, float4 glo, float4 ghi,
-                                                uint32_t ncell, const uint32_t *cur, uint32_t m,
-                                                uint32_t *pb, uint32_t *wsum) {
+__device__ __forceinline__ uint32_t heavy_parts(const uint32_t *weights, uint32_t m, uint32_t *pb,
+                                                uint32_t *wsum) {
   const uint32_t tid = threadIdx.x;
-  auto weight = [&](uint32_t k) -> uint32_t {
-    if (k >= m) return 0u;
-    const uint32_t c = cur[k];
-    if (c >= ncell) return 1u;
-    return mac_accept(a.nodeA[c], a.nodeB[c].y, glo, ghi, glo.w, a.bootstrap)
-               ? 1u
-               : max(a.cpcount[c], 1u);
-  };
+  auto weight = [&](uint32_t k) -> uint32_t { return k < m ? weights[k] : 0u; };
   uint32_t W = 0, tot;
   for (uint32_t k0 = 0; k0 < m; k0 += NT) {
     (void)block_scan<NT>(weight(k0 + tid), wsum, &tot);
@@ -792,18 +809,21 @@ __device__ __forceinline__ uint32_t heavy_parts(const WalkArgs &a, float4 glo, f
 // walk ends; groups handed on (by their entry count) are left out. With no
 // front blocks (the launch before the retry pass) they also collect that
 // pass's queue.
-// (1024 front workgroups, four per CU, instead of 256: 214 -> 130 us for the
-// heavy groups of a batch of 64 systems, 3.1 million particles.)
+// (Bound by a group's chain of rounds and by the requests on the counters. Heavy
+// groups of a batch of 64 systems, 3.1 million particles: 214 us with 256
+// workgroups, 130 with 1024, four per CU, and 104 with the weights taken in the
+// front's last round and one atomic per group instead of three.)
 constexpr uint32_t kFrontBlocks = 1024, kJoinBlocks = 512;
 __global__ __launch_bounds__(256) void k_walk_mid(WalkArgs a, uint32_t walk_waves, int hash,
                                                   uint32_t front_blocks, int join) {
   __shared__ uint32_t s_front[2 * kFrontCap];
-  __shared__ uint32_t s_pb[kMaxParts + 1], s_wsum[4], s_at[3], s_list[256];
+  __shared__ uint32_t s_pb[kMaxParts + 1], s_wsum[4], s_at[4], s_list[256];
   const uint32_t ng = *a.qcount;
   if (blockIdx.x < front_blocks) {
     // the heavy ones among queue positions b, b + front_blocks, ...: consecutive
     // positions go to different workgroups
     const uint32_t ncell = a.sc->ncell;
+    bool full = false;  // (thread 0) no part slots are left
     for (uint32_t q0 = blockIdx.x; q0 < ng; q0 += 256u * front_blocks) {
       const uint64_t qi = (uint64_t)q0 + (uint64_t)threadIdx.x * front_blocks;
       if (threadIdx.x == 0) s_at[2] = 0u;
@@ -814,25 +834,30 @@ __global__ __launch_bounds__(256) void k_walk_mid(WalkArgs a, uint32_t walk_wave
       }
       __syncthreads();
       const uint32_t nl = s_at[2];
+      if (threadIdx.x == 0 && nl > 0u) s_at[3] = atomicAdd(&a.sc->nheavy, nl);
       for (uint32_t j = 0; j < nl; ++j) {
         const uint32_t g = s_list[j];
         const uint32_t root = a.groot ? a.groot[g] : 0u;
         const float4 glo = a.gbox[2 * g], ghi = a.gbox[2 * g + 1];
+        const uint32_t nr = a.groot ? a.cpcount[root] : a.n;
         uint32_t *cur = s_front, *nxt = s_front + kFrontCap;
         const uint32_t m =
-            heavy_front<256>(a, root, glo, ghi, ncell,
-                             front_cell_max(a.groot ? a.cpcount[root] : a.n), cur, nxt, s_wsum);
-        const uint32_t P = heavy_parts<256>(a, glo, ghi, ncell, cur, m, s_pb, s_wsum);
+            heavy_front<256>(a, root, glo, ghi, ncell, front_cell_max(nr), cur, nxt, s_wsum);
+        const uint32_t P = heavy_parts<256>(nxt, m, s_pb, s_wsum);
         if (threadIdx.x == 0) {
-          const uint32_t h = atomicAdd(&a.sc->nheavy, 1u);
-          const uint32_t s0 = atomicAdd(&a.sc->nhpart, P), f0 = atomicAdd(&a.sc->nhfront, m);
-          const bool room = h < a.hslots && s0 < a.hslots && P <= a.hslots - s0 &&
+          const uint32_t h = s_at[3] + j;
+          // one request for parts (low word) and front cells
+          const unsigned long long at =
+              full ? 0ull : atomicAdd(&a.sc->nhpart, ((unsigned long long)m << 32) | P);
+          const uint32_t s0 = (uint32_t)at, f0 = (uint32_t)(at >> 32);
+          full = full || s0 >= a.hslots;
+          const bool room = !full && h < a.hslots && P <= a.hslots - s0 &&
                             f0 < a.hfront_cap && m <= a.hfront_cap - f0;
           a.heavy[h] = g;
           if (h < a.hslots) a.hrec[h] = room ? make_uint2(s0, P) : make_uint2(0u, 0u);
           a.gent[g] = 0u;
           if (hash) a.ghash[g] = 0ull;
-          s_at[0] = s0;
+          s_at[0] = full ? a.hslots : s0;
           s_at[1] = room ? f0 : kEntNone;
           s_at[2] = h;
         }
@@ -959,7 +984,7 @@ __global__ __launch_bounds__(64 * kWalkWavesPerWG) void k_heavy_walk(WalkArgs a)
   const WaveLds l = wave_lds(lds_list, wv, a.tile);
   uint32_t *stk =
       a.frontier + (size_t)(blockIdx.x * kWalkWavesPerWG + wv) * (size_t)(a.fmask + 1);
-  const uint32_t np = min(a.sc->nhpart, a.hslots);
+  const uint32_t np = min((uint32_t)a.sc->nhpart, a.hslots);
   const uint32_t ncell = a.sc->ncell;
   const uint32_t nw = gridDim.x * kWalkWavesPerWG;
   for (uint32_t t = __builtin_amdgcn_readfirstlane(blockIdx.x * kWalkWavesPerWG + wv); t < np;
@@ -1030,10 +1055,10 @@ __global__ __launch_bounds__(64) void k_heavy_end(WalkArgs a) {
     } else {
       uint32_t *cur = stk + a.fmask + 1u, *nxt = cur + kFrontCap;
       const uint32_t root = a.groot ? a.groot[g] : 0u;
+      const uint32_t nr = a.groot ? a.cpcount[root] : a.n;
       const uint32_t m =
-          heavy_front<64>(a, root, w.glo, w.ghi, ncell,
-                          front_cell_max(a.groot ? a.cpcount[root] : a.n), cur, nxt, nullptr);
-      const uint32_t Q = heavy_parts<64>(a, w.glo, w.ghi, ncell, cur, m, s_pb, nullptr);
+          heavy_front<64>(a, root, w.glo, w.ghi, ncell, front_cell_max(nr), cur, nxt, nullptr);
+      const uint32_t Q = heavy_parts<64>(nxt, m, s_pb, nullptr);
       uint64_t hsum = 0;
       uint32_t entries = 0, end = 0;
       for (uint32_t r = 0; r < Q && end == 0u; ++r) {

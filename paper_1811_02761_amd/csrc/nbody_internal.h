@@ -63,7 +63,7 @@ struct DevScalars {
   uint32_t nretry;         // groups handed from the walk to its retry pass
   uint32_t retry_head;     // the retry pass's work queue
   uint32_t nheavy;         // groups walked in parts
-  uint32_t nhpart, nhfront;  // parts and front cells asked for
+  unsigned long long nhpart;  // parts (low word) and front cells asked for
   unsigned long long bar_epoch;  // launches of the grid-barrier calcNode so far
   uint32_t istart[kLevels + 1];  // internal cells of level l: ilist[istart[l] .. istart[l + 1])
   uint32_t nleaf;          // leaves of the current tree
