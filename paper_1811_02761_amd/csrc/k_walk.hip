@@ -102,14 +102,6 @@ struct WalkArgs {
   uint32_t split_slots;
 };
 
-// Wavefronts per group for a queue of ng groups walked by `waves` wavefronts.
-__device__ __forceinline__ uint32_t split_factor(uint32_t ng, uint32_t waves, uint32_t slots,
-                                                 int mode, bool comp) {
-  if (comp || mode < 0 || ng > slots || ng > 4u * waves) return 1u;
-  if (mode > 0) return (uint32_t)mode;
-  return ng < 2u * waves ? 4u : ng < 4u * waves ? 2u : 1u;
-}
-
 // Longest list that one wavefront walks, for a walk root holding n particles.
 // At 2*10^5 particles a limit of 4096 leaves 1.3 % of the particles over it
 // and bounds the main pass's longest chain. In larger trees lists grow and
@@ -119,6 +111,21 @@ __device__ __forceinline__ uint32_t split_factor(uint32_t ng, uint32_t waves, ui
 __host__ __device__ __forceinline__ uint32_t heavy_limit(uint32_t n) {
   const uint32_t q = n / 64u;
   return q < 4096u ? 4096u : q;
+}
+// Wavefronts per group for a queue of ng groups walked by `waves` wavefronts.
+// Each of them repeats the group's traversal: four pay while they still find a
+// chip with room (galaxies, us per walk of 65536, 90000, 200003 and 400000
+// particles, ng = 1490, 2050, 4500 and 9000: K = 4 135, 176, 331, 649; K = 2
+// 163, 155, 250, 523), two until the queue is several times the chip (10^6
+// particles, ng = 22154: 851 against 1026 with K = 1; 1.5 million: the same).
+// Where longer lists stay in the main pass, four pay for as much longer queues
+// (block steps of the 2^23 galaxy, 16 steps: 50.3 ms, 52.9 with K = 2 from
+// ng = waves / 4 on); `limit` is heavy_limit() of the tree.
+__device__ __forceinline__ uint32_t split_factor(uint32_t ng, uint32_t waves, uint32_t slots,
+                                                 int mode, uint32_t limit) {
+  if (mode < 0 || ng > slots || ng > 4u * waves) return 1u;
+  if (mode > 0) return (uint32_t)mode;
+  return ng < min(waves / 4u * (limit / 4096u), 2u * waves) ? 4u : 2u;
 }
 constexpr uint32_t kPartWork = 1024;   // particles under a part's cells, about
 constexpr uint32_t kMaxParts = 128;
@@ -664,7 +671,8 @@ __device__ __forceinline__ void walk_body(const WalkArgs &a, float4 *lds_list) {
     walk_loop<kComp, kHash, kPot, 1>(a, l, ng, wv, lane);
   } else {
     const uint32_t K =
-        split_factor(ng, gridDim.x * kWalkWavesPerWG, a.split_slots, a.split_mode, false);
+        split_factor(ng, gridDim.x * kWalkWavesPerWG, a.split_slots, a.split_mode,
+                     heavy_limit(a.groot ? 0u : a.n));
     if (K == 1u)
       walk_loop<kComp, kHash, kPot, 1>(a, l, ng, wv, lane);
     else if (K == 2u)
@@ -884,7 +892,7 @@ __global__ __launch_bounds__(256) void k_walk_mid(WalkArgs a, uint32_t walk_wave
       if (a.gent[g] == kEntRetry) a.retry[atomicAdd(&a.sc->nretry, 1u)] = g;
     }
   }
-  if (!join || split_factor(ng, walk_waves, a.split_slots, a.split_mode, false) == 1u) return;
+  if (!join || split_factor(ng, walk_waves, a.split_slots, a.split_mode, 4096u) == 1u) return;
   const uint32_t lane = lane_id();
   const uint32_t nw = (gridDim.x - front_blocks) * (blockDim.x >> 6);
   for (uint32_t qi = __builtin_amdgcn_readfirstlane(
