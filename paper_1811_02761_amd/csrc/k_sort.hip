@@ -1,13 +1,14 @@
-// k_sort.hip -- stable LSD radix sort of (63-bit key, 32-bit index) pairs.
+// k_sort.hip -- stable sort of (63-bit key, 32-bit index) pairs.
 //
 // The paper's tree build spends most of its time in a key/value radix sort
-// (Sec. 4.1). This is a reduce-then-scan LSD sort with 8-bit digits and 8
-// passes, written for wave64: every pass is a per-tile digit histogram (LDS
-// atomics), a per-digit exclusive scan over tiles, and a scatter whose
-// in-tile rank comes from a wave-level multisplit (eight ballots give the
+// (Sec. 4.1). Large sets take a reduce-then-scan LSD radix sort with 8-bit
+// digits and 8 passes, written for wave64: every pass is a per-tile digit
+// histogram (LDS atomics), a per-digit exclusive scan over tiles, and a scatter
+// whose in-tile rank comes from a wave-level multisplit (eight ballots give the
 // lanes sharing a digit; their popcount below the lane is the rank). Ranks
 // follow input position, so each pass is stable and equal keys keep their
-// input order.
+// input order. Smaller sets are sorted in tiles (by counting, or by all digits
+// in LDS) and the tiles merged four at a time.
 #include <utility>
 
 #include "nbody_internal.h"
@@ -296,45 +297,110 @@ __global__ __launch_bounds__(kTileThreads) void k_sort_tile(
   }
 }
 
+// Tiles of kTile pairs sorted by counting: a pair's place in its tile is the
+// number of pairs there that come before it. A workgroup places 64 pairs (one per
+// lane, the same ones in each wavefront), each wavefront counting over 256 pairs
+// of the tile, staged in LDS (as scalar loads the keys came one latency after the
+// other: 15 us instead of 8).
+constexpr uint32_t kRankSlice = 256;
+template <uint32_t kTile>
+__global__ __launch_bounds__(kTile / kRankSlice * 64) void k_sort_rank(
+    const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vin, uint32_t n,
+    uint64_t *__restrict__ kout, uint32_t *__restrict__ vout) {
+  constexpr uint32_t kW = kTile / kRankSlice;
+  __shared__ uint64_t slice[kW][kRankSlice];
+  __shared__ uint32_t part[kW][64];
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = lane_id();
+  const uint32_t i0 = blockIdx.x * 64u, tile0 = i0 / kTile * kTile;
+  const uint32_t i = i0 + lane;
+  const uint64_t key = i < n ? kin[i] : 0ull;
+  const uint32_t b = tile0 + w * kRankSlice, e = min(max(n, b), b + kRankSlice);
+  uint64_t *o = slice[w];
+#pragma unroll
+  for (uint32_t u = 0; u < kRankSlice / 64u; ++u) {
+    const uint32_t j = b + 64u * u + lane;
+    o[64u * u + lane] = j < e ? kin[j] : ~0ull;  // (before no key)
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  uint32_t c = 0;
+  // 64 at a time: those of an earlier 64 come before equal keys, those of a later
+  // one do not
+  for (uint32_t q = 0; q < kRankSlice; q += 64u) {
+    const uint32_t at = b + q;
+    if (at >= e) break;
+    if (at < i0) {
+#pragma unroll 16
+      for (uint32_t j = 0; j < 64u; ++j) c += o[q + j] <= key ? 1u : 0u;
+    } else if (at > i0) {
+#pragma unroll 16
+      for (uint32_t j = 0; j < 64u; ++j) c += o[q + j] < key ? 1u : 0u;
+    } else {
+#pragma unroll 16
+      for (uint32_t j = 0; j < 64u; ++j)
+        c += (j < lane ? o[q + j] <= key : o[q + j] < key) ? 1u : 0u;
+    }
+  }
+  if constexpr (kW > 1) {
+    part[w][lane] = c;
+    __syncthreads();
+    if (w != 0u) return;
+#pragma unroll
+    for (uint32_t q = 1; q < kW; ++q) c += part[q][lane];
+  }
+  if (i < n) {
+    kout[tile0 + c] = key;
+    vout[tile0 + c] = vin[i];
+  }
+}
+
 // Merges groups of four sorted runs of `run` pairs (a power of two): a pair's
 // place is its place in its own run plus, for each other run of the group, the
 // pairs there that come before it (equal keys: those of earlier runs, which
 // keeps the sort stable). The three searches of a thread are independent.
 __global__ __launch_bounds__(256) void k_sort_merge(const uint64_t *__restrict__ kin,
-                                                    const uint32_t *__restrict__ vin, int64_t n,
-                                                    int64_t run, uint64_t *__restrict__ kout,
+                                                    const uint32_t *__restrict__ vin, uint32_t n,
+                                                    uint32_t run, uint64_t *__restrict__ kout,
                                                     uint32_t *__restrict__ vout) {
-  const int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x;
+  const uint32_t i = blockIdx.x * 256u + threadIdx.x;
   if (i >= n) return;
   const uint64_t key = kin[i];
-  const int64_t g0 = i / (4 * run) * (4 * run);
-  const int mine = (int)((i - g0) / run);
-  int64_t b[3], len[3], lo[3];
+  const uint32_t g0 = i / (4u * run) * (4u * run);
+  const uint32_t mine = (i - g0) / run;
+  uint32_t b[3], len[3], lo[3];
   bool before[3];
 #pragma unroll
-  for (int q = 0; q < 3; ++q) {
-    const int s = q + (q >= mine ? 1 : 0);
+  for (uint32_t q = 0; q < 3; ++q) {
+    const uint32_t s = q + (q >= mine ? 1u : 0u);
     b[q] = g0 + s * run;
-    len[q] = min(max(n - b[q], (int64_t)0), run);
+    len[q] = b[q] < n ? min(n - b[q], run) : 0u;
     before[q] = s < mine;
     lo[q] = 0;
   }
-  for (int64_t step = run; step >= 1; step >>= 1) {
+  for (uint32_t step = run; step >= 1u; step >>= 1) {
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const int64_t c = lo[q] + step;  // are the run's first c pairs before mine?
+    for (uint32_t q = 0; q < 3; ++q) {
+      const uint32_t c = lo[q] + step;  // are the run's first c pairs before mine?
       if (c <= len[q]) {
-        const uint64_t o = kin[b[q] + c - 1];
+        const uint64_t o = kin[b[q] + c - 1u];
         if (before[q] ? o <= key : o < key) lo[q] = c;
       }
     }
   }
-  const int64_t at = g0 + (i - g0 - mine * run) + lo[0] + lo[1] + lo[2];
+  const uint32_t at = i - mine * run + lo[0] + lo[1] + lo[2];
   kout[at] = key;
   vout[at] = vin[i];
 }
 
-constexpr int64_t kMergeSort = 1 << 20;
+// Sorts by tiles and merges up to kMergeSort pairs. Tiles sorted by digits (a
+// serial chain of eight passes, 30 to 35 us for any n) leave most of the chip
+// idle below about 2*10^5 pairs; counting grows with n times the tile: 8 us for
+// 1000 pairs, 11 for 16411 in tiles of 4096; at 2*10^5, 24 in tiles of 1024 and
+// a merge of 10. All of a call's forces, us, digits / 4096 / 1024 wide tiles:
+// 1000 particles 168 / 151 / 147, 16411 272 / 248 / 253, 32000 282 / 261 / 264,
+// 65000 317 / 306 / 303, 130000 418 / 425 / 411, 200000 587 / 617 / 588.
+constexpr int64_t kMergeSort = 1 << 20, kRankWide = 32768, kRankNarrow = 131072;
 
 void launch_sort(int64_t n, uint64_t *keysA, uint32_t *valsA, uint64_t *keysB,
                  uint32_t *valsB, uint32_t *hist, hipStream_t st, uint64_t **keys_out,
@@ -342,13 +408,22 @@ void launch_sort(int64_t n, uint64_t *keysA, uint32_t *valsA, uint64_t *keysB,
   uint64_t *ki = keysA, *ko = keysB;
   uint32_t *vi = valsA, *vo = valsB;
   if (n <= kMergeSort) {
-    hipLaunchKernelGGL(k_sort_tile, dim3((unsigned)cdiv(n, kSortTile)), dim3(kTileThreads), 0, st,
-                       ki, vi, n, ko, vo);
-    for (int64_t run = kSortTile; run < n; run *= 4) {
+    uint32_t run = kSortTile;
+    const dim3 g64((unsigned)cdiv(n, 64));
+    if (n <= 1024 || (n > kRankWide && n <= kRankNarrow)) {
+      run = 1024;
+      hipLaunchKernelGGL(k_sort_rank<1024>, g64, dim3(256), 0, st, ki, vi, (uint32_t)n, ko, vo);
+    } else if (n <= kRankWide) {
+      hipLaunchKernelGGL(k_sort_rank<4096>, g64, dim3(1024), 0, st, ki, vi, (uint32_t)n, ko, vo);
+    } else {
+      hipLaunchKernelGGL(k_sort_tile, dim3((unsigned)cdiv(n, kSortTile)), dim3(kTileThreads), 0,
+                         st, ki, vi, n, ko, vo);
+    }
+    for (; run < n; run *= 4) {
       std::swap(ki, ko);
       std::swap(vi, vo);
-      hipLaunchKernelGGL(k_sort_merge, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, ki, vi, n,
-                         run, ko, vo);
+      hipLaunchKernelGGL(k_sort_merge, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, ki, vi,
+                         (uint32_t)n, run, ko, vo);
     }
     *keys_out = ko;
     *vals_out = vo;
