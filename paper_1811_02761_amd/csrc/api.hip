@@ -207,7 +207,7 @@ nbody_status status_from_bits(int32_t b) {
 namespace nb {
 
 Layout make_layout(const nbody_params &p, int64_t n, int num_cu, bool stepping,
-                   int64_t split_slots) {
+                   int64_t split_slots, int64_t heavy_slots) {
   Layout L{};  // offsets not taken below stay 0 (caught by carve_complete)
   L.n_max = n;
   L.cell_cap = n + cdiv(21 * n, p.leaf_max + 1) + 2;
@@ -252,11 +252,14 @@ Layout make_layout(const nbody_params &p, int64_t n, int num_cu, bool stepping,
   L.off_ghash = take(8 * N);
   L.off_order = take(4 * N);
   L.off_prevcnt = take(4 * N);
-  // heavy groups (walked in parts): slots for about one part per 16 particles;
-  // stacks in the main pass's buffer, with room for at least 64 workgroups of
-  // the last pass (a stack and two fronts each). A stack holds at most 512
-  // cells per tree level (22 levels), and no more than the tree has.
-  L.heavy_slots = std::min<int64_t>(std::max<int64_t>(n / (stepping ? 16 : 64), 64), 65536);
+  // heavy groups (walked in parts): slots for about one part per 6 particles,
+  // more for few; stacks in the main pass's buffer, with room for at least 64
+  // workgroups of the last pass (a stack and two fronts each). A stack holds at
+  // most 512 cells per tree level (22 levels), and no more than the tree has.
+  L.heavy_slots = std::max<int64_t>(
+      std::min({std::max<int64_t>(n / 6, std::min<int64_t>(n / 2, 16384)), (int64_t)196608,
+                heavy_slots}),
+      64);
   L.heavy_cap = 64;
   while (L.heavy_cap < L.cell_cap && L.heavy_cap < 16384) L.heavy_cap <<= 1;
   const int64_t end_words = L.heavy_cap + 2 * (int64_t)kFrontCap;
@@ -1678,12 +1681,22 @@ nbody_status nbody_tree_forces_noalloc(const nbody_params *p, void *hip_stream, 
   q.order = 0;
   q.calcnode_sync = kCalcNodeLevels;
   q.frontier_cap = (int32_t)std::min<int64_t>(cap, 256);
-  if (make_layout(q, n, cu, false).total > kStaticScratchBytes) return NBODY_ENOMEM;
+  // whether n fits at all is decided with few part slots; what is left over
+  // goes to parts first, then to the stacks
+  int64_t parts = std::max<int64_t>(n / 64, 1);
+  if (make_layout(q, n, cu, false, INT64_MAX, parts).total > kStaticScratchBytes)
+    return NBODY_ENOMEM;
   const int64_t slots = std::max<int64_t>(n / 8, 64);
-  Layout L = make_layout(q, n, cu, false, slots);
+  Layout L = make_layout(q, n, cu, false, slots, parts);
+  while (parts < n / 4) {
+    const Layout M = make_layout(q, n, cu, false, slots, 2 * parts);
+    if (M.total > kStaticScratchBytes) break;
+    parts *= 2;
+    L = M;
+  }
   while (q.frontier_cap < cap && q.frontier_cap < L.heavy_cap) {
     q.frontier_cap *= 2;
-    const Layout M = make_layout(q, n, cu, false, slots);
+    const Layout M = make_layout(q, n, cu, false, slots, parts);
     if (M.total > kStaticScratchBytes) {
       q.frontier_cap /= 2;
       break;

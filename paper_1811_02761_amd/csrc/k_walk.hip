@@ -127,7 +127,14 @@ __device__ __forceinline__ uint32_t split_factor(uint32_t ng, uint32_t waves, ui
   if (mode > 0) return (uint32_t)mode;
   return ng < min(waves / 4u * (limit / 4096u), 2u * waves) ? 4u : 2u;
 }
-constexpr uint32_t kPartWork = 1024;   // particles under a part's cells, about
+// Particles under a part's cells, about. A part is a chain of its own and ends the
+// walk of a small tree; many parts cost room and repeat the descent from the
+// group's front (10007 particles, two walks a step, 4 steps: 1850 us with 1024,
+// 1665 with 512, 1579 with 256; 65536, 8 steps: 2729, 2599, 2590 with 384; a batch
+// of 64 systems: 15.8 ms, 15.8, 16.0 with 384 for all).
+__host__ __device__ __forceinline__ uint32_t part_work(uint32_t n) {
+  return n <= 32768u ? 256u : 512u;
+}
 constexpr uint32_t kMaxParts = 128;
 // a front cell holding more particles is opened further
 __device__ __forceinline__ uint32_t front_cell_max(uint32_t n) {
@@ -783,8 +790,8 @@ __device__ __forceinline__ uint32_t heavy_front(const WalkArgs &a, uint32_t root
 // Cuts a front of m cells into parts of about equal weight: part r takes the
 // cells [pb[r], pb[r + 1]). Returns the number of parts (uniform); pb is in LDS.
 template <int NT>
-__device__ __forceinline__ uint32_t heavy_parts(const uint32_t *weights, uint32_t m, uint32_t *pb,
-                                                uint32_t *wsum) {
+__device__ __forceinline__ uint32_t heavy_parts(const uint32_t *weights, uint32_t work,
+                                                uint32_t m, uint32_t *pb, uint32_t *wsum) {
   const uint32_t tid = threadIdx.x;
   auto weight = [&](uint32_t k) -> uint32_t { return k < m ? weights[k] : 0u; };
   uint32_t W = 0, tot;
@@ -792,7 +799,7 @@ __device__ __forceinline__ uint32_t heavy_parts(const uint32_t *weights, uint32_
     (void)block_scan<NT>(weight(k0 + tid), wsum, &tot);
     W += tot;
   }
-  const uint32_t P = min(min((W + kPartWork - 1u) / kPartWork, kMaxParts), m);
+  const uint32_t P = min(min((W + work - 1u) / work, kMaxParts), m);
   uint32_t base = 0;
   for (uint32_t k0 = 0; k0 < m; k0 += NT) {
     const uint32_t k = k0 + tid, wt = weight(k);
@@ -851,7 +858,7 @@ __global__ __launch_bounds__(256) void k_walk_mid(WalkArgs a, uint32_t walk_wave
         uint32_t *cur = s_front, *nxt = s_front + kFrontCap;
         const uint32_t m =
             heavy_front<256>(a, root, glo, ghi, ncell, front_cell_max(nr), cur, nxt, s_wsum);
-        const uint32_t P = heavy_parts<256>(nxt, m, s_pb, s_wsum);
+        const uint32_t P = heavy_parts<256>(nxt, part_work(nr), m, s_pb, s_wsum);
         if (threadIdx.x == 0) {
           const uint32_t h = s_at[3] + j;
           // one request for parts (low word) and front cells
@@ -1066,7 +1073,7 @@ __global__ __launch_bounds__(64) void k_heavy_end(WalkArgs a) {
       const uint32_t nr = a.groot ? a.cpcount[root] : a.n;
       const uint32_t m =
           heavy_front<64>(a, root, w.glo, w.ghi, ncell, front_cell_max(nr), cur, nxt, nullptr);
-      const uint32_t Q = heavy_parts<64>(nxt, m, s_pb, nullptr);
+      const uint32_t Q = heavy_parts<64>(nxt, part_work(nr), m, s_pb, nullptr);
       uint64_t hsum = 0;
       uint32_t entries = 0, end = 0;
       for (uint32_t r = 0; r < Q && end == 0u; ++r) {
