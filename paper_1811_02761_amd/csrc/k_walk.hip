@@ -379,14 +379,23 @@ __device__ __forceinline__ void store_group_result(const WalkArgs &a, uint32_t g
 struct WaveLds {
   float4 *base;
   __device__ __forceinline__ float4 *ent() const { return base; }
-  __device__ __forceinline__ uint32_t *incl() const {
+  __device__ __forceinline__ uint32_t *mark() const {
     return reinterpret_cast<uint32_t *>(base + 64);
   }
-  __device__ __forceinline__ uint32_t *src() const { return incl() + 64; }
+  __device__ __forceinline__ uint32_t *src() const { return mark() + 64; }
   __device__ __forceinline__ float4 *list() const { return base + 96; }
 };
 __device__ __forceinline__ WaveLds wave_lds(float4 *lds, uint32_t wv, uint32_t tile) {
   return WaveLds{lds + wv * (tile + kListPad + 96u)};
+}
+
+// Wavefronts per SIMD asked of the compiler: the plain walk keeps the next
+// chunk's nodes in registers while it adds, and left alone takes 84 of them
+// (5 wavefronts; 557, 49.1 ms and 15.4 ms where 6 took 550 us, 48.0 and 14.9 for
+// 200003 particles, the 2^23 block steps and a batch of 64 systems). The other
+// forms would spill.
+constexpr int walk_occupancy(bool comp, bool hash, bool pot) {
+  return comp || hash || pot ? 1 : 6;
 }
 
 // The group a wavefront walks for, per lane.
@@ -408,6 +417,25 @@ __device__ __forceinline__ WalkGroup load_group(const WalkArgs &a, uint32_t g, u
   return w;
 }
 
+// v, v + 1, ... to p[0], p[1], ... (p need not be aligned to the vector).
+__device__ __forceinline__ void store_run2(uint32_t *p, uint32_t v) {
+  typedef uint32_t u2 __attribute__((ext_vector_type(2), aligned(4)));
+  *reinterpret_cast<u2 *>(p) = u2{v, v + 1u};
+}
+__device__ __forceinline__ void store_run4(uint32_t *p, uint32_t v) {
+  typedef uint32_t u4 __attribute__((ext_vector_type(4), aligned(4)));
+  *reinterpret_cast<u4 *>(p) = u4{v, v + 1u, v + 2u, v + 3u};
+}
+
+// p[i] by a global load: next to an LDS load of the same value, a plain one is
+// merged with it into a flat load, which waits for both memories.
+__device__ __forceinline__ float4 load_global(const float4 *p, uint32_t i) {
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  typedef const __attribute__((address_space(1))) f4 *gp;
+  const f4 v = reinterpret_cast<gp>(reinterpret_cast<uintptr_t>(p))[i];
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+
 // Entry counts of groups without results yet.
 constexpr uint32_t kEntNone = 0xffffffffu;   // failed
 constexpr uint32_t kEntHeavy = 0xfffffffeu;  // left to the parts' walk
@@ -418,6 +446,13 @@ constexpr uint32_t kEndOverflow = 1, kEndCorrupt = 2, kEndHeavy = 4;
 // Traverse the subtrees of the `top` cells on the stack and add their list
 // (with K > 1 the blocks of this part) into R; entries counts the list.
 // Stops when the list exceeds `limit` entries.
+// A few wavefronts per SIMD are bound by this loop's chain (stack, nodes, scan,
+// push, copy, sums), a full chip by the vector instructions of the sums and of
+// the rest. So the next chunk's loads go out before this one's entries are
+// copied, children are pushed by at most four stores, and entries find their
+// owners by marks and a scan (a binary search was six dependent LDS reads):
+// 10007 particles, two walks a step, 4 steps 1586 -> 1509 us; 65536, 8 steps
+// 2593 -> 2491; 200003, a call 567 -> 550; the 2^23 block steps 50.1 -> 48.0 ms.
 template <bool kComp, bool kHash, bool kPot, uint32_t K>
 __device__ __forceinline__ uint32_t walk_list(const WalkArgs &a, const WaveLds &l,
                                               const WalkGroup &w, uint32_t *stk, uint32_t F,
@@ -427,29 +462,34 @@ __device__ __forceinline__ uint32_t walk_list(const WalkArgs &a, const WaveLds &
                                               uint64_t &hsum) {
   float4 *list = l.list();
   float4 *s_ent = l.ent();
-  uint32_t *s_incl = l.incl(), *s_src = l.src();
+  uint32_t *s_mark = l.mark(), *s_src = l.src();
   const float dA = w.glo.w;
   const uint32_t npart = a.n;
   uint32_t visited = 0, cnt = 0;
   uint32_t nblk = 0;  // list blocks this wavefront has added
   uint32_t end = 0;
-  while (top > 0) {
-    const uint32_t nc = min(64u, top);
+  // the chunk of up to 64 cells from the stack's top, and their nodes
+  uint32_t nc, c;
+  bool bad_c;
+  float4 A, B;
+  auto pop = [&]() {
+    nc = min(64u, top);
+    top -= nc;
+    const uint32_t cc = lane < nc ? stk[top + lane] : 0u;
+    bad_c = cc >= ncell;
+    c = bad_c ? 0u : cc;
+    A = a.nodeA[c];
+    B = a.nodeB[c];
+  };
+  if (top > 0) pop();
+  else nc = 0u;
+  while (nc > 0) {
     visited += nc;
     if (visited > ncell) {  // a tree visits each cell at most once
       end = kEndCorrupt;
       break;
     }
-    top -= nc;
-    const uint32_t cc = lane < nc ? stk[top + lane] : 0u;
-    const bool bad_c = lane < nc && cc >= ncell;
     const bool has = lane < nc && !bad_c;
-    const uint32_t c = has ? cc : 0u;
-    float4 A = make_float4(0.f, 0.f, 0.f, 0.f), B = A;
-    if (has) {
-      A = a.nodeA[c];
-      B = a.nodeB[c];
-    }
     const uint32_t w0 = __float_as_uint(B.z), w1 = __float_as_uint(B.w);
     {
       const bool lf = (w1 & kLeafBit) != 0u;
@@ -489,21 +529,44 @@ __device__ __forceinline__ uint32_t walk_list(const WalkArgs &a, const WaveLds &
     }
     // every lane has read its candidate before any lane overwrites it
     __builtin_amdgcn_wave_barrier();
-    for (uint32_t k = 0; k < nch; ++k) stk[top + chi - nch + k] = w0 + k;
+    {  // at most four stores (a loop over the children took 8 rounds)
+      uint32_t *d = stk + (top + chi - nch);
+      uint32_t v = w0;
+      if (nch & 8u) {
+        store_run4(d, v);
+        store_run4(d + 4, v + 4u);
+      }
+      if (nch & 4u) {
+        store_run4(d, v);
+        d += 4;
+        v += 4u;
+      }
+      if (nch & 2u) {
+        store_run2(d, v);
+        d += 2;
+        v += 2u;
+      }
+      if (nch & 1u) *d = v;
+    }
     top += chtot;
     // entries -> LDS list (flushing full tiles). Lane k owns entries
-    // [incl_k - ne_k, incl_k); the copy is cooperative: lane r of the wave
-    // fetches entry done + r, finding its owner by binary search. With
-    // K > 1 only this part's blocks are copied.
+    // [ef_k, ei_k); the copy is cooperative: lane r of the wave fetches entry
+    // done + r of the chunk. With K > 1 only this part's blocks are copied.
     if (kHash) {
       if (accept) hsum += mix64((uint64_t)c);
       else if (ne)
         for (uint32_t k = 0; k < ne; ++k) hsum += mix64((1ull << 40) + w0 + k);
     }
-    s_incl[lane] = ei;
-    s_src[lane] = accept ? 0xffffffffu : w0;
+    const uint32_t ef = ei - ne;  // this lane's first entry
+    const uint64_t cells = __ballot(accept);
+    s_src[lane] = w0 - ef;
     if (accept) s_ent[lane] = make_float4(A.x, A.y, A.z, B.x);
     __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    // the next chunk's loads are on their way while this one's entries are added
+    if (top > 0) pop();
+    else nc = 0u;
     uint32_t done = 0;
     while (done < etot) {
       const uint32_t J = entries + done;  // list index of the next entry
@@ -519,15 +582,22 @@ __device__ __forceinline__ uint32_t walk_list(const WalkArgs &a, const WaveLds &
           continue;
         }
       }
-      for (uint32_t r = lane; r < seg; r += 64u) {
-        const uint32_t j = done + r;
-        uint32_t k = 0;
-#pragma unroll
-        for (uint32_t s = 32; s >= 1; s >>= 1)
-          if (s_incl[k + s - 1] <= j) k += s;
-        const uint32_t src = s_src[k];
-        const uint32_t first = k ? s_incl[k - 1] : 0u;
-        list[cnt + r] = (src == 0xffffffffu) ? s_ent[k] : a.xyzm[src + (j - first)];
+      for (uint32_t r0 = 0; r0 < seg; r0 += 64u) {
+        // owners of entries j0 .. j0 + 63: each marks its first one there, and a
+        // maximum over the lanes before gives every entry its owner
+        const uint32_t j0 = done + r0;
+        s_mark[lane] = 0u;
+        __builtin_amdgcn_wave_barrier();
+        if (ei > max(j0, ef) && ef < j0 + 64u) s_mark[ef > j0 ? ef - j0 : 0u] = lane;
+        __builtin_amdgcn_wave_barrier();
+        const uint32_t k = wave_incl_max_dpp(s_mark[lane]);
+        if (r0 + lane < seg) {
+          float4 e = s_ent[k];
+          const uint32_t src = s_src[k];
+          if (!((cells >> k) & 1ull)) e = load_global(a.xyzm, src + j0 + lane);
+          list[cnt + r0 + lane] = e;
+        }
+        __builtin_amdgcn_wave_barrier();
       }
       cnt += seg;
       done += seg;
@@ -544,8 +614,6 @@ __device__ __forceinline__ uint32_t walk_list(const WalkArgs &a, const WaveLds &
       end = kEndHeavy;
       break;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
   if (end) cnt = 0;
   __builtin_amdgcn_wave_barrier();
@@ -992,7 +1060,8 @@ struct PartSums<true, kPot> {
 // kFrontCap cells but for trees far from any in use; a part that outgrows it
 // leaves its group to k_heavy_end, whose stacks hold every cell.
 template <bool kComp, bool kHash, bool kPot>
-__global__ __launch_bounds__(64 * kWalkWavesPerWG) void k_heavy_walk(WalkArgs a) {
+__global__ __launch_bounds__(64 * kWalkWavesPerWG,
+                             walk_occupancy(kComp, kHash, kPot)) void k_heavy_walk(WalkArgs a) {
   HIP_DYNAMIC_SHARED(float4, lds_list)
   const uint32_t wv = threadIdx.x >> 6;
   const uint32_t lane = lane_id();
@@ -1199,13 +1268,15 @@ __global__ __launch_bounds__(kStatBlocks) void k_walk_stat_fold(
 // The walk, and its retry pass as a kernel of its own (so that profiles and
 // the walk timing see the main pass alone).
 template <bool kComp, bool kHash>
-__global__ __launch_bounds__(64 * kWalkWavesPerWG) void k_walk(WalkArgs a) {
+__global__ __launch_bounds__(64 * kWalkWavesPerWG,
+                             walk_occupancy(kComp, kHash, false)) void k_walk(WalkArgs a) {
   HIP_DYNAMIC_SHARED(float4, lds_list)
   walk_body<kComp, kHash, false>(a, lds_list);
 }
 
 template <bool kComp, bool kHash>
-__global__ __launch_bounds__(64 * kWalkWavesPerWG) void k_walk_retry(WalkArgs a) {
+__global__ __launch_bounds__(64 * kWalkWavesPerWG,
+                             walk_occupancy(kComp, kHash, false)) void k_walk_retry(WalkArgs a) {
   HIP_DYNAMIC_SHARED(float4, lds_list)
   walk_body<kComp, kHash, false>(a, lds_list);
 }

@@ -485,6 +485,18 @@ __device__ __forceinline__ uint32_t wave_incl_scan_dpp(uint32_t v) {
   return (uint32_t)x;
 }
 
+// Wave64 inclusive prefix maximum of unsigned values, the same way.
+__device__ __forceinline__ uint32_t wave_incl_max_dpp(uint32_t v) {
+  uint32_t x = v;
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, true));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, true));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, true));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, true));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false));
+  return x;
+}
+
 // value of lane 63, as a wave-uniform scalar
 __device__ __forceinline__ uint32_t wave_last(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
