@@ -695,7 +695,7 @@ nbody_status do_build(nbody_ctx *ctx, int64_t n, const Coords &c) {
     (void)hipEventRecord(ctx->ev_istart, ctx->st);
     ctx->istart_pending = true;
   }
-  launch_moments(n, ctx->p.G, P, ctx->L, eff_calcnode(ctx->p), plan, ctx->st);
+  launch_moments(n, P, ctx->L, eff_calcnode(ctx->p), plan, ctx->st);
   span_end(ctx, sp);
   span_done(ctx, sp);
   ctx->keys = ks;
@@ -708,14 +708,14 @@ nbody_status do_build(nbody_ctx *ctx, int64_t n, const Coords &c) {
 
 nbody_status do_refit(nbody_ctx *ctx, const Coords &c) {
   launch_gather(c, ctx->perm, ctx->n, ctx->P.xyzm, ctx->st);
-  launch_moments(ctx->n, ctx->p.G, ctx->P, ctx->L, eff_calcnode(ctx->p), moment_plan(ctx),
+  launch_moments(ctx->n, ctx->P, ctx->L, eff_calcnode(ctx->p), moment_plan(ctx),
                  ctx->st);
   return hip_status();
 }
 
 // Refit after a drift that wrote the key-ordered positions itself.
 nbody_status do_refit_sorted(nbody_ctx *ctx) {
-  launch_moments(ctx->n, ctx->p.G, ctx->P, ctx->L, eff_calcnode(ctx->p), moment_plan(ctx),
+  launch_moments(ctx->n, ctx->P, ctx->L, eff_calcnode(ctx->p), moment_plan(ctx),
                  ctx->st);
   return hip_status();
 }
@@ -1373,6 +1373,7 @@ nbody_status nbody_export(nbody_ctx *ctx, int32_t what, void *dst, int64_t capac
   if (capacity < count) return NBODY_ENOMEM;
   if (what == NBODY_X_MQ) {
     // nodeB holds m32, q, w0, w1: copy the first two floats of each cell
+    launch_node_q(nc, ctx->p.G, P, ctx->st);
     if (hipMemcpy2DAsync(dst, 8, P.nodeB, 16, 8, (size_t)nc, hipMemcpyDeviceToDevice,
                          ctx->st) != hipSuccess)
       return NBODY_EHIP;

@@ -11,7 +11,7 @@
 // Phases, each over data the previous ones finished:
 //  1. leaves: one lane per leaf (the build lists the leaves in particle
 //     order; a wavefront's 64 leaves are contiguous, so their particles are
-//     staged in LDS with coalesced loads): sums, com, b2, q.
+//     staged in LDS with coalesced loads): sums, com, b2.
 //  2. internal sums, deepest level first, over the build's per-level lists of
 //     internal cells (the children's sums must be final). Planned from the
 //     per-level counts of the latest tree the host has seen: a level with
@@ -36,7 +36,6 @@
 //     particles, and each finished run is merged by an atomic max on the
 //     cell's b2 bit pattern (b2 >= 0: float order = unsigned order; max is
 //     order-free, so the result is exact).
-//  4. q of internal cells.
 #include <algorithm>
 
 #include "nbody_internal.h"
@@ -90,7 +89,7 @@ __device__ __forceinline__ float3 com_of(double M, double Sx, double Sy, double 
 
 // ---------------------------------------------------------------- phase 1
 __global__ __launch_bounds__(256) void k_mom_leaf(DevScalars *__restrict__ sc, uint32_t n,
-                                                  float G, const uint2 *__restrict__ leaves,
+                                                  const uint2 *__restrict__ leaves,
                                                   const float4 *__restrict__ xyzm,
                                                   double4 *__restrict__ mom64,
                                                   float4 *__restrict__ nodeA,
@@ -149,10 +148,9 @@ __global__ __launch_bounds__(256) void k_mom_leaf(DevScalars *__restrict__ sc, u
     bb = d2 > bb ? d2 : bb;
   }
   const float m32 = (float)mm;
-  const float gm = G * m32;
   mom64[e.x] = make_double4(mm, xx, yy, zz);
   nodeA[e.x] = make_float4(c.x, c.y, c.z, bb);
-  *reinterpret_cast<float2 *>(&nodeB[e.x]) = make_float2(m32, gm * bb);
+  nodeB[e.x].x = m32;
 }
 
 // ---------------------------------------------------------------- phase 2
@@ -531,19 +529,22 @@ __global__ __launch_bounds__(256) void k_mom_b2(DevScalars *__restrict__ sc, uin
              gridDim.x - big_blocks);
 }
 
-// ---------------------------------------------------------------- phase 4
+// ---------------------------------------------------------------- q, on demand
+// q = (G m32) b2 of every cell into nodeB.y, as the walk makes it for itself.
 __global__ __launch_bounds__(256) void k_mom_q(const DevScalars *__restrict__ sc, float G,
-                                               const uint4 *__restrict__ ilist,
                                                const float4 *__restrict__ nodeA,
                                                float4 *__restrict__ nodeB) {
-  const uint32_t ncell = sc->ncell, total = sc->istart[kLevels];
-  for (uint32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < total;
-       t += gridDim.x * blockDim.x) {
-    const uint32_t c = ilist[t].x;
-    if (c >= ncell) continue;
+  const uint32_t ncell = sc->ncell;
+  for (uint32_t c = blockIdx.x * blockDim.x + threadIdx.x; c < ncell;
+       c += gridDim.x * blockDim.x) {
     const float gm = G * nodeB[c].x;
     nodeB[c].y = gm * nodeA[c].w;
   }
+}
+
+void launch_node_q(int64_t ncell, float G, const Ptrs &P, hipStream_t st) {
+  const int64_t g = std::min<int64_t>(std::max<int64_t>(cdiv(ncell, 256), 1), 4096);
+  hipLaunchKernelGGL(k_mom_q, dim3((unsigned)g), dim3(256), 0, st, P.sc, G, P.nodeA, P.nodeB);
 }
 
 namespace {
@@ -553,12 +554,12 @@ namespace {
 int grid_blocks(int num_cu) { return std::min(std::max(num_cu, 1), kBarSlots); }
 }  // namespace
 
-void launch_moments(int64_t n, float G, const Ptrs &P, const Layout &L, int mode,
+void launch_moments(int64_t n, const Ptrs &P, const Layout &L, int mode,
                     const uint32_t *level_cells, hipStream_t st) {
   const uint32_t nblk = (uint32_t)cdiv(n, kBuildThreads);
   // leaves <= n: one wavefront per 64 leaves, four per workgroup
   hipLaunchKernelGGL(k_mom_leaf, dim3((uint32_t)cdiv(n, 256)), dim3(256), 0, st, P.sc,
-                     (uint32_t)n, G, P.leaves, P.xyzm, P.mom64, P.nodeA, P.nodeB);
+                     (uint32_t)n, P.leaves, P.xyzm, P.mom64, P.nodeA, P.nodeB);
   if (mode == kCalcNodeGrid) {
     hipLaunchKernelGGL(k_bar_epoch, dim3(1), dim3(1), 0, st, P.sc);
     hipLaunchKernelGGL(k_mom_levels_grid, dim3(grid_blocks(L.num_cu)), dim3(256), 0, st, P.sc,
@@ -604,7 +605,6 @@ void launch_moments(int64_t n, float G, const Ptrs &P, const Layout &L, int mode
     b2(k_mom_b2<kChunksMid>, kChunksMid);
   else
     b2(k_mom_b2<kChunksSmall>, kChunksSmall);
-  hipLaunchKernelGGL(k_mom_q, dim3(gi), dim3(256), 0, st, P.sc, G, P.ilist, P.nodeA, P.nodeB);
 }
 
 }  // namespace nb

@@ -122,7 +122,7 @@ struct Ptrs {
   int32_t *cfchild, *cnchild, *cparent;
   double4 *mom64;       // M, Sx, Sy, Sz
   float4 *nodeA;        // com x, y, z, b2
-  float4 *nodeB;        // m32, q, w0, w1 (bit patterns for w0/w1)
+  float4 *nodeB;        // m32, q (launch_node_q only), w0, w1 (w0, w1: bit patterns)
   uint32_t *gbegin, *gcount;
   float4 *gbox;         // [2g] = lo xyz, dA; [2g+1] = hi xyz, amin
   uint32_t *gent;       // per group: list entries of the last walk
@@ -220,8 +220,10 @@ constexpr int kBarSlots = 1024;     // workgroups of the persistent launch, at m
 // kNarrowCells cells are run by one workgroup), never the result
 constexpr uint32_t kNarrowCells = 1024;
 constexpr int64_t kNarrowTree = 64 * 1024;  // (particles) all levels, without counts
-void launch_moments(int64_t n, float G, const Ptrs &P, const Layout &L, int mode,
+void launch_moments(int64_t n, const Ptrs &P, const Layout &L, int mode,
                     const uint32_t *level_cells, hipStream_t st);
+// q of every cell, for the export of the nodes
+void launch_node_q(int64_t ncell, float G, const Ptrs &P, hipStream_t st);
 // asort (may be null): key-ordered a_old with |a|, read instead of a gather
 // asort in a new key order from itself in the old one (inv_old: the old tree's
 // caller index -> position; tmp: n float4 of scratch)
