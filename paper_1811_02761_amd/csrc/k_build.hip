@@ -591,12 +591,55 @@ __global__ __launch_bounds__(256) void k_build_e(DevScalars *__restrict__ sc, ui
   }
 }
 
+// The sum of the counts before block blk, and of all `len` of them: by every
+// workgroup for itself where a row is a single tile (a scan of its own costs
+// a launch, 4 us, for 1 us of work).
+__device__ __forceinline__ uint32_t counts_before(const uint32_t *__restrict__ cnt, uint32_t len,
+                                                  uint32_t blk, uint32_t (*ws)[4],
+                                                  uint32_t *total) {
+  uint32_t before = 0, all = 0;
+  for (uint32_t k = threadIdx.x; k < len; k += 256u) {
+    const uint32_t v = cnt[k];
+    all += v;
+    before += k < blk ? v : 0u;
+  }
+  before = wave_last(wave_incl_scan_dpp(before));
+  all = wave_last(wave_incl_scan_dpp(all));
+  if (lane_id() == 0) {
+    ws[0][threadIdx.x >> 6] = before;
+    ws[1][threadIdx.x >> 6] = all;
+  }
+  __syncthreads();
+  *total = ws[1][0] + ws[1][1] + ws[1][2] + ws[1][3];
+  return ws[0][0] + ws[0][1] + ws[0][2] + ws[0][3];
+}
+
+// Group marks per block of kB particles.
+__device__ __forceinline__ void group_count(uint32_t n, const uint32_t *__restrict__ pinfo,
+                                            uint32_t blk, uint32_t *__restrict__ gblk,
+                                            uint32_t *wc) {
+  const int64_t i = (int64_t)blk * kB + threadIdx.x;
+  const bool mk = i < n && (pinfo[i] & kGroupMark);
+  const uint64_t b = __ballot(mk);
+  if (lane_id() == 0) wc[threadIdx.x >> 6] = (uint32_t)__popcll(b);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t t = 0;
+    for (int q = 0; q < kB / 64; ++q) t += wc[q];
+    gblk[blk] = t;
+  }
+}
+
 // The list of internal cells in cell order (so level by level), entries
-// (cell, first child, children, particles): each cell's rank from the scanned
-// block counts (cblk; the sum in total). istart[l] is the rank of cell
-// lvl_off[l] (the internal cells before level l), also to host_istart
-// (page-locked host memory) when given.
-__global__ __launch_bounds__(256) void k_ilist_emit(DevScalars *__restrict__ sc, uint32_t cblocks,
+// (cell, first child, children, particles): each cell's rank from the block
+// counts (scanned, with the sum in total; without total as they were counted,
+// at most one tile of them). istart[l] is the rank of cell lvl_off[l] (the
+// internal cells before level l), also to host_istart (page-locked host memory)
+// when given. The workgroups from `emit_blocks` on count group marks.
+static_assert(kB == 256, "both parts use workgroups of one size");
+__global__ __launch_bounds__(256) void k_ilist_emit(uint32_t emit_blocks, uint32_t n,
+                                                    const uint32_t *__restrict__ pinfo,
+                                                    uint32_t *__restrict__ gblk, DevScalars *__restrict__ sc, uint32_t cblocks,
                                                     const uint32_t *__restrict__ cpcount,
                                                     const int32_t *__restrict__ cfchild,
                                                     const int32_t *__restrict__ cnchild,
@@ -604,21 +647,30 @@ __global__ __launch_bounds__(256) void k_ilist_emit(DevScalars *__restrict__ sc,
                                                     const uint32_t *__restrict__ total,
                                                     uint4 *__restrict__ ilist,
                                                     uint32_t *__restrict__ host_istart) {
-  __shared__ uint32_t wc[4];
+  __shared__ uint32_t wc[4], ws[2][4];
   __shared__ uint32_t s_off[kLevels];
+  if (blockIdx.x >= emit_blocks) {
+    group_count(n, pinfo, blockIdx.x - emit_blocks, gblk, wc);
+    return;
+  }
   const uint32_t nc = sc->ncell;
   if (threadIdx.x < kLevels) s_off[threadIdx.x] = sc->lvl_off[threadIdx.x];
+  uint32_t sum, base = 0;
+  if (total)
+    sum = total[0];
+  else  // (one block of cells per workgroup)
+    base = counts_before(cblk, cblocks, blockIdx.x, ws, &sum);
   __syncthreads();
   // levels starting at or past the last cell (empty), and the total
   if (blockIdx.x == 0 && threadIdx.x <= kLevels) {
-    const uint32_t t = total[0];
+    const uint32_t t = sum;
     if (threadIdx.x == kLevels || s_off[threadIdx.x] >= nc) {
       sc->istart[threadIdx.x] = t;
       if (host_istart) host_istart[threadIdx.x] = t;
     }
   }
   const int w = threadIdx.x >> 6;
-  for (uint32_t blk = blockIdx.x; blk < cblocks && blk * 256u < nc; blk += gridDim.x) {
+  for (uint32_t blk = blockIdx.x; blk < cblocks && blk * 256u < nc; blk += emit_blocks) {
     const uint32_t c = blk * 256u + threadIdx.x;
     const int k = c < nc ? cnchild[c] : 0;
     const bool in = k > 0;
@@ -626,7 +678,7 @@ __global__ __launch_bounds__(256) void k_ilist_emit(DevScalars *__restrict__ sc,
     __syncthreads();  // wc's last use
     if (lane_id() == 0) wc[w] = (uint32_t)__popcll(b);
     __syncthreads();
-    uint32_t rank = cblk[blk];
+    uint32_t rank = total ? cblk[blk] : base;
     for (int q = 0; q < w; ++q) rank += wc[q];
     rank += (uint32_t)__popcll(b & lanemask_lt());  // internal cells before c
     if (in) ilist[rank] = make_uint4(c, (uint32_t)cfchild[c], (uint32_t)k, cpcount[c]);
@@ -639,24 +691,8 @@ __global__ __launch_bounds__(256) void k_ilist_emit(DevScalars *__restrict__ sc,
   }
 }
 
-// Group marks per block of kB particles.
-__global__ __launch_bounds__(kB) void k_group_count(uint32_t n,
-                                                    const uint32_t *__restrict__ pinfo,
-                                                    uint32_t *__restrict__ gblk) {
-  __shared__ uint32_t wc[kB / 64];
-  const int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x;
-  const bool mk = i < n && (pinfo[i] & kGroupMark);
-  const uint64_t b = __ballot(mk);
-  if (lane_id() == 0) wc[threadIdx.x >> 6] = (uint32_t)__popcll(b);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t t = 0;
-    for (int q = 0; q < kB / 64; ++q) t += wc[q];
-    gblk[blockIdx.x] = t;
-  }
-}
-
-// Group begins in particle order (gblk holds exclusive block offsets) and sizes
+// Group begins in particle order (gblk holds exclusive block offsets with the sum
+// in total, or the blocks' counts without it) and sizes
 // (a group ends where the next one begins, at most group_max <= 64 particles
 // later, so the start of the one before is in the 64 positions before a mark),
 // each particle's group (the number of group starts up to it, minus one), and
@@ -670,6 +706,7 @@ __global__ __launch_bounds__(kB) void k_group_emit(uint32_t n,
                                                    uint32_t *__restrict__ gcount,
                                                    uint32_t *__restrict__ gid) {
   __shared__ uint64_t wm[kB / 64 + 1];  // marks of the 64 positions before, then per wave
+  __shared__ uint32_t ws[2][4];
   const int64_t b0 = (int64_t)blockIdx.x * kB;
   const int64_t i = b0 + threadIdx.x;
   const bool mk = i < n && (pinfo[i] & kGroupMark);
@@ -682,7 +719,13 @@ __global__ __launch_bounds__(kB) void k_group_emit(uint32_t n,
     if (lane == 0) wm[0] = h;
   }
   __syncthreads();
-  uint32_t off = gblk[blockIdx.x];
+  uint32_t off, sum;
+  if (total) {
+    off = gblk[blockIdx.x];
+    sum = total[0];
+  } else {
+    off = counts_before(gblk, gridDim.x, blockIdx.x, ws, &sum);
+  }
   for (int q = 0; q < w; ++q) off += (uint32_t)__popcll(wm[q + 1]);
   const uint64_t below = b & lanemask_lt();
   const uint32_t before = (uint32_t)__popcll(below);
@@ -697,8 +740,8 @@ __global__ __launch_bounds__(kB) void k_group_emit(uint32_t n,
   if (i < n) gid[i] = off + before + (mk ? 1u : 0u) - 1u;  // particle 0 starts group 0
   if (i == (int64_t)n - 1) {
     if (mk || pm) gcount[off + before + (mk ? 1u : 0u) - 1u] = n - (mk ? (uint32_t)i : prev);
-    sc->ngroup = total[0];
-    gbegin[total[0]] = n;
+    sc->ngroup = sum;
+    gbegin[sum] = n;
   }
 }
 
@@ -753,15 +796,17 @@ void launch_build(const uint64_t *keys, int64_t n, int leaf_max, int group_max,
   hipLaunchKernelGGL(k_build_e, dim3(ge), dim3(256), 0, st, P.sc, cblk, P.clevel, P.cpbegin,
                      P.cpcount, P.cfchild, P.cnchild, (uint32_t)group_max, group_merge, r,
                      P.cparent, P.nodeB, ib, P.pinfo);
-  launch_scan_rows(ib, cblk, 1, itot, P.scan, st);
-  hipLaunchKernelGGL(k_ilist_emit, dim3(ge), dim3(256), 0, st, P.sc, cblk, P.cpcount, P.cfchild,
-                     P.cnchild, ib, itot, P.ilist, host_istart);
-  // groups (scanned in the block-count scratch)
-  uint32_t *gblk = P.blkcnt, *gtot = P.blkcnt + nblk;
-  hipLaunchKernelGGL(k_group_count, dim3(nblk), dim3(kB), 0, st, (uint32_t)n, P.pinfo, gblk);
-  launch_scan_rows(gblk, nblk, 1, gtot, P.scan, st);
-  hipLaunchKernelGGL(k_group_emit, dim3(nblk), dim3(kB), 0, st, (uint32_t)n, P.pinfo, gblk, gtot,
-                     P.sc, P.gbegin, P.gcount, P.gid);
+  // (rows of one tile are scanned by the kernels that use them; the walk's retry
+  // list is free here)
+  if (cblk > kScanTile) launch_scan_rows(ib, cblk, 1, itot, P.scan, st);
+  uint32_t *gblk = P.retry, *gtot = P.retry + nblk;
+  hipLaunchKernelGGL(k_ilist_emit, dim3(ge + nblk), dim3(256), 0, st, ge, (uint32_t)n, P.pinfo,
+                     gblk, P.sc, cblk, P.cpcount, P.cfchild, P.cnchild, ib,
+                     cblk > kScanTile ? itot : (uint32_t *)nullptr, P.ilist, host_istart);
+  if (nblk > kScanTile) launch_scan_rows(gblk, nblk, 1, gtot, P.scan, st);
+  hipLaunchKernelGGL(k_group_emit, dim3(nblk), dim3(kB), 0, st, (uint32_t)n, P.pinfo, gblk,
+                     nblk > kScanTile ? gtot : (uint32_t *)nullptr, P.sc, P.gbegin, P.gcount,
+                     P.gid);
   if (r > 0)
     hipLaunchKernelGGL(k_group_root, dim3((uint32_t)std::min<int64_t>(cdiv(n, 256), 4096)),
                        dim3(256), 0, st, P.sc, P.gbegin, P.sysoff, nsys, r, P.groot);
