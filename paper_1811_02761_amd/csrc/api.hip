@@ -299,7 +299,8 @@ Layout make_layout(const nbody_params &p, int64_t n, int num_cu, bool stepping,
   // 4 x the walk's wavefronts (no walk splits a longer queue)
   L.split_slots = std::max<int64_t>(
       1, std::min<int64_t>(std::min<int64_t>(4 * L.walk_waves, n), split_slots));
-  L.off_split = take((size_t)kSplitSlotBytes * (size_t)L.split_slots);
+  L.slot_bytes = stepping ? kSplitSlotWide : kSplitSlotBytes;
+  L.off_split = take((size_t)L.slot_bytes * (size_t)L.split_slots);
   L.off_gid = take(4 * N);
   L.off_gflag = take(4 * N);
   L.off_ilist = take(16 * C);
@@ -537,6 +538,7 @@ WalkCfg walk_cfg(const nbody_ctx *ctx, bool bootstrap, bool queued) {
   c.asort_out = false;
   c.split = ctx->p.walk_split;
   c.split_slots = ctx->L.split_slots;
+  c.slot_bytes = ctx->L.slot_bytes;
   c.heavy_slots = ctx->L.heavy_slots;
   c.heavy_cap = ctx->L.heavy_cap;
   c.heavy_stack = ctx->L.heavy_stack;

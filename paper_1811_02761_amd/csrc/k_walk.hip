@@ -22,16 +22,18 @@
 // multiples of 64 entries), so each lane's summation order is fixed by the
 // group alone: it does not depend on the tile size, the stack capacity, the
 // queue order, which wave runs the group, or the split below. Results are
-// bit-identical across all of them. (The compensated sum keeps one running
-// sum over the whole list and is never split.)
+// bit-identical across all of them. (The compensated sum keeps two running
+// sums, b mod 2, each with its correction, and is split in two at most. With one
+// it was a single wavefront's chain of up to 4096 entries: potential of 130003
+// particles 1050 us, 874 in two; of 10007 609 and 437.)
 //
 // Split walk: when few groups are queued (block steps often walk a few
 // thousand heavy groups, fewer than the resident wavefronts), K = 2 or 4
 // wavefronts take the same group: each traverses the whole tree (the MAC
 // decisions are the same in each) but adds only the blocks b with
 // b mod K == its part, i.e. the running sums r with r mod K == its part, and
-// stores them; a second kernel (k_walk_join) adds the four sums per lane in
-// order and writes the results. This turns a queue of q heavy groups into
+// stores them; k_walk_mid adds the four sums per lane in order and writes the
+// results. This turns a queue of q heavy groups into
 // K q tasks of a quarter or half the arithmetic each.
 //
 // Heavy groups: a few groups meet far longer lists than the rest (members
@@ -99,7 +101,7 @@ struct WalkArgs {
   int bootstrap;
   int may_retry;           // overflowing groups are walked again (else reported)
   int split_mode;          // -1 never (retry pass), 0 by queue length, else 1, 2, 4
-  uint32_t split_slots;
+  uint32_t split_slots, slot_words;
 };
 
 // Longest list that one wavefront walks, for a walk root holding n particles.
@@ -208,6 +210,18 @@ struct Acc3<true, kPot> {
     nadd(z, cz, f * dz);
     if constexpr (kPot) nadd(w, cw, -mr);
   }
+  __device__ __forceinline__ void merge(const Acc3 &o) {
+    nadd(x, cx, o.x);
+    nadd(y, cy, o.y);
+    nadd(z, cz, o.z);
+    cx += o.cx;
+    cy += o.cy;
+    cz += o.cz;
+    if constexpr (kPot) {
+      nadd(w, cw, o.w);
+      cw += o.cw;
+    }
+  }
   __device__ __forceinline__ void total(float &ox, float &oy, float &oz, float &ow) const {
     ox = x + cx;
     oy = y + cy;
@@ -217,7 +231,7 @@ struct Acc3<true, kPot> {
 };
 
 // The running sums of a lane: four for the plain FP32 sum (block b of the
-// list adds into sum b mod 4), one for the compensated sum. The sum of the
+// list adds into sum b mod 4), two compensated ones (b mod 2). The sum of the
 // block being added is always u0: after each block the sums rotate, so that
 // no register is ever selected by a run-time index. A wavefront taking every
 // K-th block (part p of K) holds the 4 / K sums p, p + K, ... in u0, u1, ...
@@ -252,11 +266,23 @@ struct RunSums<false, kPot> {
 };
 template <bool kPot>
 struct RunSums<true, kPot> {
-  static constexpr uint32_t kNum = 1;
-  Acc3<true, kPot> u0;
-  __device__ __forceinline__ void advance(uint32_t) {}
+  static constexpr uint32_t kNum = 2;
+  Acc3<true, kPot> u0, u1;
+  __device__ __forceinline__ void advance(uint32_t K) {
+    if (K == 1u) {
+      const Acc3<true, kPot> t = u0;
+      u0 = u1;
+      u1 = t;
+    }
+  }
+  // both as one compensated sum
+  __device__ __forceinline__ Acc3<true, kPot> merged() const {
+    Acc3<true, kPot> m = u0;
+    m.merge(u1);
+    return m;
+  }
   __device__ __forceinline__ void total(float &ox, float &oy, float &oz, float &ow) const {
-    u0.total(ox, oy, oz, ow);
+    merged().total(ox, oy, oz, ow);
   }
 };
 
@@ -319,8 +345,8 @@ __device__ __forceinline__ void flush_run(const float4 *__restrict__ list, uint3
 }
 
 // Flush the tile's cnt entries: whole blocks of 64 entries (the last one
-// possibly short), each into u0 followed by a rotation of the sums (the
-// compensated sum: all into its one sum). nblk counts the blocks added.
+// possibly short), each into u0 followed by a rotation of the sums. nblk counts
+// the blocks added.
 template <bool kComp, bool kPot, uint32_t K>
 __device__ __forceinline__ void flush_tile(float4 *__restrict__ list, uint32_t cnt,
                                            uint32_t lane, uint32_t stream, uint32_t S,
@@ -330,10 +356,6 @@ __device__ __forceinline__ void flush_tile(float4 *__restrict__ list, uint32_t c
   // region; slots [cnt, cnt + kListPad) are free
   list[cnt + (lane & (kListPad - 1))] = make_float4(0.f, 0.f, 0.f, 0.f);
   __builtin_amdgcn_wave_barrier();
-  if constexpr (kComp) {
-    flush_run<kComp, kPot>(list, cnt, stream, S, pi, eps2, R.u0);
-    return;
-  }
   for (uint32_t off = 0; off < cnt; off += kBlk) {
     flush_run<kComp, kPot>(list + off, min(kBlk, cnt - off), stream, S, pi, eps2, R.u0);
     R.advance(K);
@@ -622,9 +644,8 @@ __device__ __forceinline__ uint32_t walk_list(const WalkArgs &a, const WaveLds &
   __builtin_amdgcn_wave_barrier();
   flush_tile<kComp, kPot, K>(list, cnt, lane, w.stream, w.S, w.pi, a.eps2, R, nblk);
   __builtin_amdgcn_wave_barrier();
-  // complete the rotation period (4 / K blocks): then u_k is sum part + K k
-  if constexpr (!kComp)
-    for (; nblk & (RunSums<kComp, kPot>::kNum / K - 1u); ++nblk) R.advance(K);
+  // complete the rotation period (kNum / K blocks): then u_k is sum part + K k
+  for (; nblk & (RunSums<kComp, kPot>::kNum / K - 1u); ++nblk) R.advance(K);
   return end;
 }
 
@@ -665,6 +686,24 @@ __device__ __forceinline__ uint32_t next_task(const WalkArgs &a, uint32_t nw, ui
   uint32_t t = __builtin_amdgcn_readfirstlane(claim);
   asm volatile("" : "+s"(t));
   return nw + t;
+}
+
+// Running sum r of a split group: its components, per lane, in the queue slot.
+template <bool kPot>
+__device__ __forceinline__ void store_sums(float *slot, uint32_t r, uint32_t lane,
+                                           const Acc3<false, kPot> &u) {
+  constexpr uint32_t kW = kPot ? 4 : 3;
+  slot[(r * kW + 0) * 64 + lane] = u.x;
+  slot[(r * kW + 1) * 64 + lane] = u.y;
+  slot[(r * kW + 2) * 64 + lane] = u.z;
+  if constexpr (kPot) slot[(r * kW + 3) * 64 + lane] = u.w;
+}
+template <bool kPot>
+__device__ __forceinline__ void store_sums(float *slot, uint32_t r, uint32_t lane,
+                                           const Acc3<true, kPot> &u) {
+  const float v[8] = {u.x, u.y, u.z, u.w, u.cx, u.cy, u.cz, u.cw};
+#pragma unroll
+  for (uint32_t k = 0; k < 8; ++k) slot[(r * 8 + k) * 64 + lane] = v[k];
 }
 
 // The persistent loop with K wavefronts per group (a power of two): task t is
@@ -718,15 +757,9 @@ __device__ __forceinline__ void walk_loop(const WalkArgs &a, const WaveLds &l, u
       finish_group<kPot>(a, w, lane, sx, sy, sz, sw);
     } else {
       // this part's running sums into the queue slot: [sum][component][lane]
-      float *slot = a.split + (size_t)qi * (kSplitSlotBytes / 4);
-      slot[((part + 0u) * 3 + 0) * 64 + lane] = R.u0.x;
-      slot[((part + 0u) * 3 + 1) * 64 + lane] = R.u0.y;
-      slot[((part + 0u) * 3 + 2) * 64 + lane] = R.u0.z;
-      if constexpr (K == 2u) {
-        slot[((part + 2u) * 3 + 0) * 64 + lane] = R.u1.x;
-        slot[((part + 2u) * 3 + 1) * 64 + lane] = R.u1.y;
-        slot[((part + 2u) * 3 + 2) * 64 + lane] = R.u1.z;
-      }
+      float *slot = a.split + (size_t)qi * a.slot_words;
+      store_sums(slot, part, lane, R.u0);
+      if constexpr (!kComp && K == 2u) store_sums(slot, part + 2u, lane, R.u1);
     }
     if (part == 0u) {
       if (kHash) a.ghash[g] = wave_sum64(hsum);
@@ -744,20 +777,15 @@ __device__ __forceinline__ void walk_body(const WalkArgs &a, float4 *lds_list) {
   const uint32_t lane = lane_id();
   const WaveLds l = wave_lds(lds_list, wv, a.tile);
   const uint32_t ng = *a.qcount;
-  // the compensated sum and the potential variant are never split
-  if constexpr (kComp || kPot) {
+  const uint32_t K =
+      split_factor(ng, gridDim.x * kWalkWavesPerWG, a.split_slots, a.split_mode,
+                   heavy_limit(a.groot ? 0u : a.n));
+  if (K == 1u)
     walk_loop<kComp, kHash, kPot, 1>(a, l, ng, wv, lane);
-  } else {
-    const uint32_t K =
-        split_factor(ng, gridDim.x * kWalkWavesPerWG, a.split_slots, a.split_mode,
-                     heavy_limit(a.groot ? 0u : a.n));
-    if (K == 1u)
-      walk_loop<kComp, kHash, kPot, 1>(a, l, ng, wv, lane);
-    else if (K == 2u)
-      walk_loop<kComp, kHash, kPot, 2>(a, l, ng, wv, lane);
-    else
-      walk_loop<kComp, kHash, kPot, 4>(a, l, ng, wv, lane);
-  }
+  else if (kComp || K == 2u)  // (two compensated sums)
+    walk_loop<kComp, kHash, kPot, 2>(a, l, ng, wv, lane);
+  else if constexpr (!kComp)
+    walk_loop<kComp, kHash, kPot, 4>(a, l, ng, wv, lane);
 }
 
 // ---------------------------------------------------------------- heavy groups
@@ -887,6 +915,42 @@ __device__ __forceinline__ uint32_t heavy_parts(const uint32_t *weights, uint32_
   return P;
 }
 
+// Results of a split group from its running sums.
+template <bool kComp>
+__device__ __forceinline__ void join_group(const WalkArgs &a, const WalkGroup &w,
+                                           const float *slot, uint32_t lane) {
+  float sx, sy, sz, sw = 0.f;
+  if constexpr (kComp) {
+    Acc3<true, true> u[2];
+#pragma unroll
+    for (uint32_t r = 0; r < 2; ++r) {
+      float v[8];
+#pragma unroll
+      for (uint32_t k = 0; k < 8; ++k) v[k] = slot[(r * 8 + k) * 64 + lane];
+      u[r].x = v[0], u[r].y = v[1], u[r].z = v[2], u[r].w = v[3];
+      u[r].cx = v[4], u[r].cy = v[5], u[r].cz = v[6], u[r].cw = v[7];
+    }
+    u[0].merge(u[1]);  // (without the potential its sums are zero)
+    u[0].total(sx, sy, sz, sw);
+  } else {
+    const uint32_t W = a.phi ? 4u : 3u;
+    float v[4][4];
+#pragma unroll
+    for (uint32_t r = 0; r < 4; ++r)
+#pragma unroll
+      for (uint32_t k = 0; k < 4; ++k)
+        v[r][k] = k < W ? slot[(r * W + k) * 64 + lane] : 0.f;
+    sx = ((v[0][0] + v[1][0]) + v[2][0]) + v[3][0];
+    sy = ((v[0][1] + v[1][1]) + v[2][1]) + v[3][1];
+    sz = ((v[0][2] + v[1][2]) + v[2][2]) + v[3][2];
+    sw = ((v[0][3] + v[1][3]) + v[2][3]) + v[3][3];
+  }
+  if (a.phi)
+    finish_group<true>(a, w, lane, sx, sy, sz, sw);
+  else
+    finish_group<false>(a, w, lane, sx, sy, sz, sw);
+}
+
 // After the main pass. Blocks [0, front_blocks): fronts and parts of the
 // heavy groups (one workgroup per group; a group that finds no room in the
 // part or front buffers is left to k_heavy_end). The other blocks, when the
@@ -980,18 +1044,12 @@ __global__ __launch_bounds__(256) void k_walk_mid(WalkArgs a, uint32_t walk_wave
     // (the front blocks may already have reset a heavy group's count: its
     // results are written again by k_heavy_end)
     if (a.gent[g] >= kEntRetry) continue;
-    const uint32_t gb = a.gbegin[g], gc = a.gcount[g];
-    const float *slot = a.split + (size_t)qi * (kSplitSlotBytes / 4);
-    float v[4][3];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int k = 0; k < 3; ++k) v[r][k] = slot[(r * 3 + k) * 64 + lane];
-    float sx = ((v[0][0] + v[1][0]) + v[2][0]) + v[3][0];
-    float sy = ((v[0][1] + v[1][1]) + v[2][1]) + v[3][1];
-    float sz = ((v[0][2] + v[1][2]) + v[2][2]) + v[3][2];
-    stream_reduce(64u / stream_count(gc), sx, sy, sz);
-    store_group_result(a, gb, gc, lane, sx, sy, sz);
+    const float *slot = a.split + (size_t)qi * a.slot_words;
+    const WalkGroup w = load_group(a, g, lane);
+    if (a.hwords == heavy_part_words(1))
+      join_group<true>(a, w, slot, lane);
+    else
+      join_group<false>(a, w, slot, lane);
   }
 }
 
@@ -1030,15 +1088,7 @@ struct PartSums<true, kPot> {
   float v[4] = {0.f, 0.f, 0.f, 0.f}, c[4] = {0.f, 0.f, 0.f, 0.f};
   __device__ __forceinline__ static void store(float *slot, uint32_t lane,
                                                const RunSums<true, kPot> &R) {
-    const Acc3<true, kPot> &u = R.u0;
-    slot[0 * 64 + lane] = u.x;
-    slot[1 * 64 + lane] = u.y;
-    slot[2 * 64 + lane] = u.z;
-    slot[3 * 64 + lane] = u.w;
-    slot[4 * 64 + lane] = u.cx;
-    slot[5 * 64 + lane] = u.cy;
-    slot[6 * 64 + lane] = u.cz;
-    slot[7 * 64 + lane] = u.cw;
+    store_sums(slot, 0u, lane, R.merged());
   }
   __device__ __forceinline__ void add(const float (&p)[8]) {
 #pragma unroll
@@ -1048,7 +1098,7 @@ struct PartSums<true, kPot> {
     }
   }
   __device__ __forceinline__ void add(const RunSums<true, kPot> &R) {
-    const Acc3<true, kPot> &u = R.u0;
+    const Acc3<true, kPot> u = R.merged();
     const float p[8] = {u.x, u.y, u.z, u.w, u.cx, u.cy, u.cz, u.cw};
     add(p);
   }
@@ -1368,7 +1418,10 @@ WalkArgs walk_args(const WalkCfg &c, const uint32_t *perm, int64_t n, float *ax,
   a.bootstrap = c.bootstrap;
   a.split = P.split;
   a.split_mode = c.split;
-  a.split_slots = (uint32_t)c.split_slots;
+  // room for the plain sums only: the other forms are not split
+  const bool fits = c.slot_bytes >= (c.compensated || c.phi ? kSplitSlotWide : kSplitSlotBytes);
+  a.split_slots = fits ? (uint32_t)c.split_slots : 0u;
+  a.slot_words = (uint32_t)c.slot_bytes / 4u;
   return a;
 }
 
@@ -1433,14 +1486,13 @@ void launch_walk(const WalkCfg &c, const uint32_t *perm, int64_t n, float *ax, f
       std::max<int64_t>(cdiv(n, 4 * kWalkWavesPerWG), 64));
   const uint32_t waves = (uint32_t)(blocks * kWalkWavesPerWG);
   const size_t lds = walk_lds(c, kWalkWavesPerWG);
-  const int join = c.compensated || c.phi ? 0 : 1;  // these are never split
   if (c.phi)
     NB_WALK_LAUNCH(k_walk_pot, c, dim3(blocks), lds, st, a);
   else
     NB_WALK_LAUNCH(k_walk, c, dim3(blocks), lds, st, a);
   if (a.may_retry) {
     // the split walk's sums first: they leave out the groups handed on
-    hipLaunchKernelGGL(k_walk_mid, dim3(kJoinBlocks), dim3(256), 0, st, a, waves, 0, 0u, join);
+    hipLaunchKernelGGL(k_walk_mid, dim3(kJoinBlocks), dim3(256), 0, st, a, waves, 0, 0u, 1);
     WalkArgs r = a;
     r.order = P.retry;
     r.qcount = &P.sc->nretry;
@@ -1456,8 +1508,8 @@ void launch_walk(const WalkCfg &c, const uint32_t *perm, int64_t n, float *ax, f
     hipLaunchKernelGGL(k_walk_mid, dim3(kFrontBlocks), dim3(256), 0, st, a, waves,
                        c.hash ? 1 : 0, kFrontBlocks, 0);
   } else {
-    hipLaunchKernelGGL(k_walk_mid, dim3(kFrontBlocks + (join ? kJoinBlocks : 0u)), dim3(256), 0,
-                       st, a, waves, c.hash ? 1 : 0, kFrontBlocks, join);
+    hipLaunchKernelGGL(k_walk_mid, dim3(kFrontBlocks + kJoinBlocks), dim3(256), 0, st, a,
+                       waves, c.hash ? 1 : 0, kFrontBlocks, 1);
   }
   // (a list holds no more entries than there are particles)
   if (n <= (int64_t)heavy_limit((uint32_t)n)) return;

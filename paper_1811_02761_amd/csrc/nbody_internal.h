@@ -21,6 +21,8 @@ constexpr int kWalkWavesPerWG = 4;
 constexpr int kStatBlocks = 256;  // workgroups of the walk statistics pass
 // split walk: 4 partial sums x 3 components x 64 lanes (FP32) per queue position
 constexpr int kSplitSlotBytes = 4 * 3 * 64 * 4;
+// the same with the potential's, and for the two compensated sums of 8 words
+constexpr int kSplitSlotWide = 4 * 4 * 64 * 4;
 
 // device status bits (sticky)
 constexpr int32_t kStNonFinite = 1;
@@ -94,6 +96,7 @@ struct Layout {
       off_longcnt, off_longslot, off_wpart, off_heavy, off_hparts, off_hrec, off_hfront, off_hsum;
   size_t off_kpos[2], off_kvel[2], off_kacc[2], off_kmass[2], off_kpt[2], off_klv[2];
   int64_t split_slots = 0;  // queue positions with room for split-walk partial sums
+  int slot_bytes = 0;       // and the room of one
   // heavy groups: part slots, the stack no tree outgrows, and the wavefronts
   // (k_heavy_walk, the retry pass) and workgroups (k_heavy_end) with such a
   // stack in `frontier`
@@ -250,6 +253,7 @@ struct WalkCfg {
   bool asort_out;  // also write the outputs, with |a|, to P.asort in key order
   int split;       // wavefronts per group: 0 by queue length, else 1, 2 or 4
   int64_t split_slots;
+  int slot_bytes;
   int64_t heavy_slots, heavy_cap, heavy_stack;
   int heavy_waves, retry_waves, heavy_end_blocks;
   float *phi = nullptr;  // potential output (caller order): the potential variant
