@@ -1176,17 +1176,17 @@ __global__ __launch_bounds__(64) void k_heavy_end(WalkArgs a) {
     const uint32_t P = __builtin_amdgcn_readfirstlane(rec.y);
     Sums T;
     if (P > 0u) {
-      // four parts' loads in flight (P is at most kMaxParts)
-      for (uint32_t r = 0; r < P; r += 4u) {
-        float p[4][8];
+      // eight parts' loads in flight (P is at most kMaxParts)
+      for (uint32_t r = 0; r < P; r += 8u) {
+        float p[8][8];
 #pragma unroll
-        for (uint32_t j = 0; j < 4; ++j) {
+        for (uint32_t j = 0; j < 8; ++j) {
           const float *slot = a.hsum + (size_t)(s0 + min(r + j, P - 1u)) * a.hwords;
 #pragma unroll
           for (uint32_t k = 0; k < 8; ++k) p[j][k] = k < Sums::kWords ? slot[k * 64 + lane] : 0.f;
         }
 #pragma unroll
-        for (uint32_t j = 0; j < 4; ++j)
+        for (uint32_t j = 0; j < 8; ++j)
           if (r + j < P) T.add(p[j]);
       }
     } else {
