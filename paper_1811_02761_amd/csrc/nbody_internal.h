@@ -220,8 +220,11 @@ constexpr int kCalcNodeGrid = 2;    // one persistent launch with a grid barrier
 constexpr int kBarSlots = 1024;     // workgroups of the persistent launch, at most
 // level_cells: internal cells per level of a recent tree (host array of
 // kMaxLevel), or null; it only shapes the launches (levels with at most
-// kNarrowCells cells are run by one workgroup), never the result
-constexpr uint32_t kNarrowCells = 1024;
+// kNarrowCells cells are run by one workgroup), never the result. A level of its
+// own launch costs about 4.7 us, in one workgroup 1.2 us and more with the cells
+// (limits of 1024 and 512: 200003 particles 543 and 531 us a call, 65536 307 and
+// 305 us a step)
+constexpr uint32_t kNarrowCells = 512;
 constexpr int64_t kNarrowTree = 64 * 1024;  // (particles) all levels, without counts
 void launch_moments(int64_t n, const Ptrs &P, const Layout &L, int mode,
                     const uint32_t *level_cells, hipStream_t st);
