@@ -218,12 +218,35 @@ __global__ __launch_bounds__(1024) void k_mom_levels_narrow(DevScalars *__restri
                                                             double4 *__restrict__ mom64,
                                                             float4 *__restrict__ nodeA,
                                                             float4 *__restrict__ nodeB) {
-  const uint32_t ncell = sc->ncell;
-  for (int l = hi; l >= lo; --l) {
-    const uint32_t t0 = sc->istart[l], t1 = sc->istart[l + 1];
-    for (uint32_t t = t0 + threadIdx.x; t < t1; t += blockDim.x)
+  const uint32_t ncell = sc->ncell, tid = threadIdx.x, lane = lane_id();
+  // every level's bounds in one load (lane l: level l's), and the levels with
+  // cells; an entry is loaded while the level below it is summed. (Read level by
+  // level, bounds and entries were two more latencies each of up to 21 levels.)
+  const uint32_t first = lane < (uint32_t)kLevels ? sc->istart[lane] : 0u;
+  const uint32_t end = lane < (uint32_t)kLevels ? sc->istart[lane + 1] : 0u;
+  uint32_t todo =
+      (uint32_t)__ballot((int)lane >= lo && (int)lane <= hi && lane < 32u && end > first);
+  if (todo == 0u) return;  // (uniform)
+  auto bound = [](uint32_t v, int l) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, l);
+  };
+  int l = 31 - __builtin_clz(todo);
+  uint32_t t0 = bound(first, l), t1 = bound(end, l);
+  uint4 e = ilist[min(t0 + tid, t1 - 1u)];
+  for (;;) {
+    todo &= ~(1u << l);
+    const int up = todo ? 31 - __builtin_clz(todo) : l;
+    const uint32_t u0 = bound(first, up), u1 = bound(end, up);
+    const uint4 eu = ilist[min(u0 + tid, u1 - 1u)];
+    if (t0 + tid < t1) internal_cell(e, ncell, n, sc, cpbegin, xyzm, mom64, nodeA, nodeB);
+    for (uint32_t t = t0 + tid + blockDim.x; t < t1; t += blockDim.x)
       internal_cell(ilist[t], ncell, n, sc, cpbegin, xyzm, mom64, nodeA, nodeB);
+    if (todo == 0u) break;
     __syncthreads();  // (makes the level's global writes visible to the workgroup)
+    l = up;
+    t0 = u0;
+    t1 = u1;
+    e = eu;
   }
 }
 
