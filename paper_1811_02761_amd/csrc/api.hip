@@ -33,12 +33,14 @@ struct nbody_ctx {
   int64_t epoch = 0;      // tree builds so far (tags the spans of each tree)
   double excess_ms = 0.0;  // measured extra walk time of the current tree
   int64_t mac_walks = 0;   // walks of the current tree with the acceleration criterion
-  double t_build_ms = 0.0, t_walk_ms = 0.0;  // latest measured (events)
-  // timed spans: a ring of (start, end, done) events around each tree build
-  // and each walk launch; a walk span's done event follows the copy of its
-  // statistics to pinned host memory
+  double t_build_ms = 0.0, t_walk_ms = 0.0;  // latest measured
+  // timed spans, a ring: start and end events around each tree build; a walk's
+  // times (device clock) and statistics come in pinned host memory, its number
+  // last (three events per walk cost 8 to 15 us)
   static constexpr int kSpans = 64;
-  hipEvent_t ev_a[kSpans] = {}, ev_b[kSpans] = {}, ev_c[kSpans] = {};
+  hipEvent_t ev_a[kSpans] = {}, ev_b[kSpans] = {};  // build spans
+  uint32_t span_seq[kSpans] = {}, walk_seq = 0;     // walk spans: numbers
+  double clock_khz = 1e5;                            // of the device clock
   int span_kind[kSpans] = {};
   int64_t span_epoch[kSpans] = {};
   int sp_head = 0, sp_count = 0;
@@ -558,25 +560,46 @@ int span_begin(nbody_ctx *ctx, int kind) {
   const int i = (ctx->sp_head + ctx->sp_count) % nbody_ctx::kSpans;
   ctx->span_kind[i] = kind;
   ctx->span_epoch[i] = ctx->epoch;
-  (void)hipEventRecord(ctx->ev_a[i], ctx->st);
+  if (kind == 0)
+    (void)hipEventRecord(ctx->ev_a[i], ctx->st);
+  else
+    ctx->span_seq[i] = ++ctx->walk_seq ? ctx->walk_seq : ++ctx->walk_seq;  // (never 0)
   return i;
 }
 
 void span_end(nbody_ctx *ctx, int i) {
   if (i < 0) return;
-  (void)hipEventRecord(ctx->ev_b[i], ctx->st);
+  if (ctx->span_kind[i] == 0) (void)hipEventRecord(ctx->ev_b[i], ctx->st);
   ctx->sp_count++;
 }
 
-// After the end event of walk span i: its statistics to pinned memory, then
-// the span's done event.
+// After walk span i: its times and statistics to pinned memory, then its number.
 void span_stats(nbody_ctx *ctx, int i, bool queued, bool record) {
   if (i < 0) return;
-  launch_walk_stat(ctx->n, queued, record, ctx->P, &ctx->aux[i], ctx->st);
+  __atomic_store_n(&ctx->aux[i].seq, 0u, __ATOMIC_RELAXED);
+  launch_walk_stat(ctx->n, queued, record, ctx->P, &ctx->aux[i], ctx->st, ctx->span_seq[i]);
 }
 
-void span_done(nbody_ctx *ctx, int i) {
-  if (i >= 0) (void)hipEventRecord(ctx->ev_c[i], ctx->st);
+// Whether span i is complete; with block, waits for it. gone: it never will be
+// (its kernels failed to run).
+bool span_ready(nbody_ctx *ctx, int i, bool block, bool *gone) {
+  *gone = false;
+  if (ctx->span_kind[i] == 0)
+    return (block ? hipEventSynchronize(ctx->ev_b[i]) : hipEventQuery(ctx->ev_b[i])) ==
+           hipSuccess;
+  const auto done = [&] {
+    return __atomic_load_n(&ctx->aux[i].seq, __ATOMIC_ACQUIRE) == ctx->span_seq[i];
+  };
+  while (!done()) {
+    if (!block) return false;
+    for (int k = 0; k < 1000 && !done(); ++k) {
+    }
+    if (!done() && hipStreamQuery(ctx->st) != hipErrorNotReady && !done()) {
+      *gone = true;
+      return false;
+    }
+  }
+  return true;
 }
 
 int pending_walks(const nbody_ctx *ctx) {
@@ -592,14 +615,16 @@ void harvest(nbody_ctx *ctx, bool block) {
   bool first = true;
   while (ctx->sp_count > 0) {
     const int i = ctx->sp_head;
-    if (block && first) {
-      if (hipEventSynchronize(ctx->ev_c[i]) != hipSuccess) return;
-    } else if (hipEventQuery(ctx->ev_c[i]) != hipSuccess) {
-      return;
-    }
+    bool gone;
+    if (!span_ready(ctx, i, block && first, &gone) && !gone) return;
     first = false;
     float ms = 0.f;
-    if (hipEventElapsedTime(&ms, ctx->ev_a[i], ctx->ev_b[i]) == hipSuccess) {
+    bool ok = !gone;
+    if (ok && ctx->span_kind[i] == 0)
+      ok = hipEventElapsedTime(&ms, ctx->ev_a[i], ctx->ev_b[i]) == hipSuccess;
+    else if (ok)
+      ms = (float)((double)(ctx->aux[i].t1 - ctx->aux[i].t0) / ctx->clock_khz);
+    if (ok) {
       if (ctx->span_kind[i] == 0) {
         ctx->t_build_ms = ms;
         ctx->build_ms_sum += ms;
@@ -699,7 +724,6 @@ nbody_status do_build(nbody_ctx *ctx, int64_t n, const Coords &c) {
   }
   launch_moments(n, P, ctx->L, eff_calcnode(ctx->p), plan, ctx->st);
   span_end(ctx, sp);
-  span_done(ctx, sp);
   ctx->keys = ks;
   // the tree's permutation (sorted position -> caller index)
   ctx->perm = ko ? P.kpt[ctx->ko] : pm;
@@ -774,7 +798,6 @@ nbody_status do_calc(nbody_ctx *ctx, const float *axo, const float *ayo, const f
   const bool record = !boot && ctx->mac_walks == 0;
   if (!boot) ctx->mac_walks++;
   span_stats(ctx, sp, use_queue, record);
-  span_done(ctx, sp);
   ctx->last_queued = use_queue;
   if (mode != 0) launch_cost_after(ctx->n, true, ctx->perm, P, ctx->st);
   // counted from the walk statistics on the host; a captured step has none
@@ -884,10 +907,13 @@ nbody_status nbody_create(const nbody_params *p, void *hip_stream, nbody_ctx **o
     delete c;
     return NBODY_EHIP;
   }
+  int khz = 0;
+  if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, c->device) == hipSuccess &&
+      khz > 0)
+    c->clock_khz = khz;
   for (int i = 0; i < nbody_ctx::kSpans; ++i)
     if (hipEventCreate(&c->ev_a[i]) != hipSuccess ||
-        hipEventCreate(&c->ev_b[i]) != hipSuccess ||
-        hipEventCreate(&c->ev_c[i]) != hipSuccess) {
+        hipEventCreate(&c->ev_b[i]) != hipSuccess) {
       nbody_destroy(c);
       return NBODY_EHIP;
     }
@@ -914,7 +940,6 @@ void nbody_destroy(nbody_ctx *ctx) {
   for (int i = 0; i < nbody_ctx::kSpans; ++i) {
     if (ctx->ev_a[i]) (void)hipEventDestroy(ctx->ev_a[i]);
     if (ctx->ev_b[i]) (void)hipEventDestroy(ctx->ev_b[i]);
-    if (ctx->ev_c[i]) (void)hipEventDestroy(ctx->ev_c[i]);
   }
   if (ctx->aux || ctx->h_istart) (void)hipStreamSynchronize(ctx->st);
   if (ctx->aux) (void)hipHostFree(ctx->aux);

@@ -1233,6 +1233,7 @@ __global__ __launch_bounds__(64) void k_heavy_end(WalkArgs a) {
 // set's walk (kOne) takes one workgroup, which finishes the statistics itself.
 __device__ __forceinline__ void store_walk_stat(DevScalars *__restrict__ sc, bool queued,
                                                 const unsigned long long (&t)[4],
+                                                unsigned long long t1, uint32_t seq,
                                                 WalkStat *__restrict__ host) {
   WalkStat w;
   w.ngroup = sc->ngroup;
@@ -1243,8 +1244,12 @@ __device__ __forceinline__ void store_walk_stat(DevScalars *__restrict__ sc, boo
   w.entries = t[3];
   w.tick = sc->tick;
   w.kmax = sc->kmax;
-  w.pad = 0u;
+  w.t0 = sc->walk_t0;
+  w.t1 = t1;
+  w.seq = 0u;
   *host = w;  // page-locked host memory: no copy after the kernel
+  // (the host reads the rest once it sees the number)
+  __hip_atomic_store(&host->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 constexpr int kStatThreads = 1024;  // of the single workgroup
@@ -1253,7 +1258,8 @@ __global__ __launch_bounds__(kOne ? kStatThreads : 256) void k_walk_stat(
     DevScalars *__restrict__ sc, const uint32_t *__restrict__ order,
     const uint32_t *__restrict__ gcount, const uint32_t *__restrict__ gent,
     uint32_t *__restrict__ gref, int record, unsigned long long *__restrict__ part,
-    WalkStat *__restrict__ host) {
+    uint32_t seq, WalkStat *__restrict__ host) {
+  const unsigned long long t1 = wall_clock64();  // the walk has ended
   constexpr int kWaves = (kOne ? kStatThreads : 256) / 64;
   __shared__ unsigned long long s_sum[kWaves][4];
   const uint32_t nq = order ? sc->nqueue : sc->ngroup;
@@ -1287,11 +1293,12 @@ __global__ __launch_bounds__(kOne ? kStatThreads : 256) void k_walk_stat(
       unsigned long long t[4] = {0, 0, 0, 0};
       for (int w = 0; w < kWaves; ++w)
         for (int k = 0; k < 4; ++k) t[k] += s_sum[w][k];
-      store_walk_stat(sc, order != nullptr, t, host);
+      store_walk_stat(sc, order != nullptr, t, t1, seq, host);
     }
   } else if (threadIdx.x < 4) {
     part[4 * blockIdx.x + threadIdx.x] = s_sum[0][threadIdx.x] + s_sum[1][threadIdx.x] +
                                          s_sum[2][threadIdx.x] + s_sum[3][threadIdx.x];
+    if (blockIdx.x == 0 && threadIdx.x == 0) sc->walk_t1 = t1;
   }
 }
 
@@ -1299,7 +1306,7 @@ __global__ __launch_bounds__(kOne ? kStatThreads : 256) void k_walk_stat(
 // workgroup of kStatBlocks threads).
 __global__ __launch_bounds__(kStatBlocks) void k_walk_stat_fold(
     DevScalars *__restrict__ sc, const unsigned long long *__restrict__ part, int queued,
-    WalkStat *__restrict__ host) {
+    uint32_t seq, WalkStat *__restrict__ host) {
   __shared__ unsigned long long s_sum[kStatBlocks / 64][4];
   unsigned long long v[4];
 #pragma unroll
@@ -1314,7 +1321,7 @@ __global__ __launch_bounds__(kStatBlocks) void k_walk_stat_fold(
     unsigned long long t[4] = {0, 0, 0, 0};
     for (int w = 0; w < kStatBlocks / 64; ++w)
       for (int k = 0; k < 4; ++k) t[k] += s_sum[w][k];
-    store_walk_stat(sc, queued != 0, t, host);
+    store_walk_stat(sc, queued != 0, t, sc->walk_t1, seq, host);
   }
 }
 
@@ -1359,17 +1366,17 @@ void launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t st) {
 constexpr int64_t kStatOne = 128 * 1024;
 
 void launch_walk_stat(int64_t n, bool queued, bool record, const Ptrs &P, WalkStat *host,
-                      hipStream_t st) {
+                      hipStream_t st, uint32_t seq) {
   const uint32_t *order = queued ? P.order : nullptr;
   if (n <= kStatOne) {
     hipLaunchKernelGGL(k_walk_stat<true>, dim3(1), dim3(kStatThreads), 0, st, P.sc, order,
-                       P.gcount, P.gent, P.gref, record ? 1 : 0, P.wpart, host);
+                       P.gcount, P.gent, P.gref, record ? 1 : 0, P.wpart, seq, host);
     return;
   }
   hipLaunchKernelGGL(k_walk_stat<false>, dim3(kStatBlocks), dim3(256), 0, st, P.sc, order,
-                     P.gcount, P.gent, P.gref, record ? 1 : 0, P.wpart, host);
+                     P.gcount, P.gent, P.gref, record ? 1 : 0, P.wpart, seq, host);
   hipLaunchKernelGGL(k_walk_stat_fold, dim3(1), dim3(kStatBlocks), 0, st, P.sc, P.wpart,
-                     queued ? 1 : 0, host);
+                     queued ? 1 : 0, seq, host);
 }
 
 

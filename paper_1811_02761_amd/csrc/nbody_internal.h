@@ -39,7 +39,9 @@ struct WalkStat {
   unsigned long long inter_ref;  // the same groups' interactions in that walk
   unsigned long long entries;    // list entries of the walked groups
   long long tick;                // block steps: the walk's step ends at this tick
-  uint32_t kmax, pad;            // block steps: finest occupied level of that step
+  uint32_t kmax;                 // block steps: finest occupied level of that step
+  uint32_t seq;                  // the walk's number, written last
+  unsigned long long t0, t1;     // device clock at the walk's start and end
 };
 
 // Device scalars kept in the workspace.
@@ -73,6 +75,7 @@ struct DevScalars {
   // hashes of the caller's block-step state: [0] when a key-ordered call
   // scattered it back, [1] on entry to the next such call
   unsigned long long ko_hash[2];
+  unsigned long long walk_t0, walk_t1;  // device clock around the latest walk
 };
 
 // Offsets of the workspace, all 256-byte aligned.
@@ -376,7 +379,8 @@ int64_t scan_scratch_words(int64_t len, int nrows);
 // record: this walk is the tree's reference walk (its first with the
 // acceleration criterion); it stores each walked group's list length in gref
 void launch_walk_stat(int64_t n, bool queued, bool record, const Ptrs &P, WalkStat *host,
-                      hipStream_t st);
+                      hipStream_t st,
+                      uint32_t seq);
 
 // single 8-bit digit pass of the stable radix sort (digit = key >> shift) of
 // the first min(n, *n_dev) entries (n_dev may be null); n bounds the grid
