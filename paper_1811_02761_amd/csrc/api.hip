@@ -792,6 +792,7 @@ nbody_status do_calc(nbody_ctx *ctx, const float *axo, const float *ayo, const f
   wc.asort_out = keep_mirror;
   wc.phi = phi;
   const int sp = span_begin(ctx, 1);
+  if (mode != 0 && sp >= 0) launch_walk_begin(P, ctx->st);
   launch_walk(wc, out_perm, ctx->n, ax, ay, az, P, ctx->st);
   span_end(ctx, sp);
   // the tree's first walk with the acceleration criterion is its reference

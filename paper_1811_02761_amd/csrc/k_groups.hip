@@ -63,6 +63,12 @@ __global__ __launch_bounds__(256) void k_group_bounds(
   if (blockIdx.x + 64u >= gridDim.x && threadIdx.x == 0) sc->walk_t0 = wall_clock64();
 }
 
+// The same note where other passes (the queue's ordering) come between.
+__global__ void k_walk_begin(DevScalars *sc) { sc->walk_t0 = wall_clock64(); }
+void launch_walk_begin(const Ptrs &P, hipStream_t st) {
+  hipLaunchKernelGGL(k_walk_begin, dim3(1), dim3(1), 0, st, P.sc);
+}
+
 void launch_group_bounds(const float *axo, const float *ayo, const float *azo,
                          const float4 *asort, const uint32_t *perm, int64_t n,
                          float delta_acc, bool queued, const Ptrs &P, hipStream_t st) {
