@@ -174,8 +174,8 @@ typedef struct {
  *  group member and a list entry);
  *  t_build_ms, t_walk_ms: latest measured tree build / walk kernel time;
  *  walk_ms_sum/walk_calls, build_ms_sum/build_calls, entries_sum and
- *  interactions_sum: totals since the last nbody_timing call (HIP events on
- *  the context's stream around each walk launch and each build);
+ *  interactions_sum: totals since the last nbody_timing call (walks: the device
+ *  clock before and after; builds: HIP events on the context's stream);
  *  queued: groups walked by the last walk; active: particles whose step
  *  ended in the last block step; queued_sum, ngroup_sum: groups walked and
  *  groups present, summed over the walks counted in walk_calls; retried:

@@ -1,7 +1,7 @@
 """Autotuner of the walk: list tile, wavefronts per compute unit and group size.
 
 Each candidate is measured on the caller's particles (device time of the walk
-kernel, HIP events) after one warm-up walk; all candidates use the same
+kernel, the library's own timing) after one warm-up walk; all candidates use the same
 previous accelerations, so the work differs only through the group size. The
 list tile and the wavefront count never change the results; the group size
 changes them within the tree method's accuracy (different groups share
