@@ -355,42 +355,106 @@ __global__ __launch_bounds__(kTile / kRankSlice * 64) void k_sort_rank(
   }
 }
 
-// Merges groups of four sorted runs of `run` pairs (a power of two): a pair's
-// place is its place in its own run plus, for each other run of the group, the
-// pairs there that come before it (equal keys: those of earlier runs, which
-// keeps the sort stable). The three searches of a thread are independent.
+// Pairs of a run of len keys at r that come before `key` (equal keys too, if le),
+// for two keys at once, found by a whole wavefront: 64 probes a round, three
+// rounds for 2^18 keys.
+__device__ __forceinline__ void wave_count_before(const uint64_t *__restrict__ r, uint32_t len,
+                                                  const uint64_t (&key)[2], bool le,
+                                                  uint32_t (&lo)[2]) {
+  uint32_t m[2] = {len, len};
+  lo[0] = lo[1] = 0u;
+  while ((m[0] | m[1]) != 0u) {
+    uint32_t step[2], c[2];
+    uint64_t o[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      step[k] = (m[k] + 63u) / 64u;
+      c[k] = (lane_id() + 1u) * step[k];
+      o[k] = r[max(lo[k] + min(c[k], m[k]), 1u) - 1u];  // (in the run, which is not empty)
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const bool yes = c[k] <= m[k] && (le ? o[k] <= key[k] : o[k] < key[k]);
+      const uint32_t t = m[k] ? (uint32_t)__popcll(__ballot(yes)) : 0u;
+      lo[k] += t * step[k];
+      m[k] = m[k] ? min(step[k] - 1u, m[k] - t * step[k]) : 0u;
+    }
+  }
+}
+
+// Merges groups of four sorted runs of `run` pairs (a power of two, 1024 or more):
+// a pair's place is its place in its own run plus, for each other run of the
+// group, the pairs there that come before it (equal keys: those of earlier runs,
+// which keeps the sort stable). A workgroup's 256 pairs are neighbours in one run,
+// so their answers lie between those of its first and its last pair: three
+// wavefronts find these, the keys between go to LDS (or, if they are too many, are
+// searched in memory), and every pair searches there. (A search of a whole run
+// by every pair was a chain of up to 17 loads: 8.8, 11.2 and 15.0 us per merge at
+// 16411, 50000 and 200003 pairs, 7.1, 10.1 and 12.0 this way.)
+constexpr uint32_t kMergeStage = 2048;
 __global__ __launch_bounds__(256) void k_sort_merge(const uint64_t *__restrict__ kin,
                                                     const uint32_t *__restrict__ vin, uint32_t n,
                                                     uint32_t run, uint64_t *__restrict__ kout,
                                                     uint32_t *__restrict__ vout) {
-  const uint32_t i = blockIdx.x * 256u + threadIdx.x;
-  if (i >= n) return;
-  const uint64_t key = kin[i];
-  const uint32_t g0 = i / (4u * run) * (4u * run);
-  const uint32_t mine = (i - g0) / run;
-  uint32_t b[3], len[3], lo[3];
-  bool before[3];
+  __shared__ uint64_t stage[kMergeStage];
+  __shared__ uint32_t s_lo[3], s_hi[3];
+  const uint32_t i0 = blockIdx.x * 256u, i = i0 + threadIdx.x;  // (i0 < n)
+  const uint32_t g0 = i0 / (4u * run) * (4u * run);
+  const uint32_t mine = (i0 - g0) / run;
+  const uint64_t key = kin[min(i, n - 1u)];
+  const uint32_t vi = vin[min(i, n - 1u)];
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t b[3], len[3];
+  bool le[3];
 #pragma unroll
   for (uint32_t q = 0; q < 3; ++q) {
     const uint32_t s = q + (q >= mine ? 1u : 0u);
     b[q] = g0 + s * run;
     len[q] = b[q] < n ? min(n - b[q], run) : 0u;
-    before[q] = s < mine;
-    lo[q] = 0;
+    le[q] = s < mine;
   }
-  for (uint32_t step = run; step >= 1u; step >>= 1) {
+  const uint64_t ends[2] = {kin[i0], kin[min(i0 + 255u, n - 1u)]};
+#pragma unroll
+  for (uint32_t q = 0; q < 3; ++q)
+    if (w == q) {
+      uint32_t at[2];
+      wave_count_before(kin + b[q], len[q], ends, le[q], at);
+      s_lo[q] = at[0];
+      s_hi[q] = at[1];
+    }
+  __syncthreads();
+  uint32_t off[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+  for (uint32_t q = 0; q < 3; ++q) {
+    b[q] += s_lo[q];
+    len[q] = s_hi[q] - s_lo[q];
+    off[q + 1] = off[q] + len[q];
+  }
+  const bool staged = off[3] <= kMergeStage;
+  if (staged) {
+#pragma unroll
+    for (uint32_t q = 0; q < 3; ++q)
+      for (uint32_t k = threadIdx.x; k < len[q]; k += 256u) stage[off[q] + k] = kin[b[q] + k];
+    __syncthreads();
+  }
+  if (i >= n) return;
+  const uint32_t most = max(max(len[0], len[1]), len[2]);
+  uint32_t lo[3] = {0u, 0u, 0u};
+  for (uint32_t step = most ? 1u << (31 - __builtin_clz(most)) : 0u; step >= 1u; step >>= 1) {
 #pragma unroll
     for (uint32_t q = 0; q < 3; ++q) {
-      const uint32_t c = lo[q] + step;  // are the run's first c pairs before mine?
+      const uint32_t c = lo[q] + step;  // are the first c pairs before mine?
       if (c <= len[q]) {
-        const uint64_t o = kin[b[q] + c - 1u];
-        if (before[q] ? o <= key : o < key) lo[q] = c;
+        const uint64_t o = staged ? stage[off[q] + c - 1u] : kin[b[q] + c - 1u];
+        if (le[q] ? o <= key : o < key) lo[q] = c;
       }
     }
   }
-  const uint32_t at = i - mine * run + lo[0] + lo[1] + lo[2];
+  uint32_t at = i - mine * run;
+#pragma unroll
+  for (uint32_t q = 0; q < 3; ++q) at += s_lo[q] + lo[q];
   kout[at] = key;
-  vout[at] = vin[i];
+  vout[at] = vi;
 }
 
 // Sorts by tiles and merges up to kMergeSort pairs. Tiles sorted by digits (a
