@@ -204,7 +204,9 @@ __device__ __forceinline__ void mlp_tile_forward(const float *__restrict__ w, co
       s = __builtin_fmaf(L.w1[ub].y, z.y, s);
       s = __builtin_fmaf(L.w1[ub].z, z.z, s);
       s = __builtin_fmaf(L.w1[ub].w, z.w, s);
-      const float h = tanhf(s);
+      // (a padded unit is 0 whatever the inputs: with zero weights alone an
+      // infinite feature, a group without mass, would make it NaN)
+      const float h = 32 * ub + col < H ? tanhf(s) : 0.f;
       h1[ub][r] = h;
       t.x[mlp_row(r, lane) * LD + 32 * ub + col] = h;
     }
