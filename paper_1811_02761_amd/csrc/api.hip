@@ -1171,7 +1171,7 @@ nbody_status step_rk2(nbody_ctx *ctx, nbody_state *st, int32_t n_steps) {
   for (int32_t k = 0; k < n_steps; ++k) {
     bool rebuild = st->rebuild_interval > 0 ? ctx->since_rebuild >= st->rebuild_interval
                                             : rebuild_due(ctx, 64);
-    if (ctx->n != n) rebuild = true;
+    if (!ctx->have_tree || ctx->n != n) rebuild = true;
     launch_rk2_predict(n, st->x, st->y, st->z, st->vx, st->vy, st->vz, st->dt, x32,
                        drift_out(ctx, st, rebuild), ctx->st);
     if (rebuild) {
@@ -1218,7 +1218,7 @@ nbody_status step_global(nbody_ctx *ctx, nbody_state *st, int32_t n_steps) {
   for (int32_t k = 0; k < n_steps; ++k) {
     bool rebuild = st->rebuild_interval > 0 ? ctx->since_rebuild >= st->rebuild_interval
                                             : rebuild_due(ctx, 64);
-    if (ctx->n != n) rebuild = true;
+    if (!ctx->have_tree || ctx->n != n) rebuild = true;
     launch_kick(n, st->vx, st->vy, st->vz, st->ax, st->ay, st->az, hdt, ctx->st);
     launch_drift(n, st->x, st->y, st->z, st->vx, st->vy, st->vz, st->dt, x32,
                  drift_out(ctx, st, rebuild), ctx->st);
