@@ -63,13 +63,20 @@ struct nbody_ctx {
   hipStream_t cap_st = nullptr;  // capture and replay stream (default priority)
   hipEvent_t cap_ev[2] = {};
   hipGraphExec_t gexec[2] = {};  // [0] refit step, [1] rebuild step
+  // what a captured step depends on: the state's arrays and numbers, the queue
+  // order with its model, whether walks are counted, the workspace and systems
+  // (by their number), and for a refit the tree's permutation
   struct GraphKey {
     const void *p[10];
     int64_t n;
     double dt;
-    int order, nsys;
+    int order, nsys, hidden, counting;
     int64_t epoch_sys;
+    const void *perm;
   } gkey[2] = {};
+  int64_t epoch_sys = 0;  // workspaces bound and systems set so far
+  uint64_t *gkeys = nullptr;  // the captured rebuild step's sorted keys and
+  uint32_t *gperm = nullptr;  // permutation
   int64_t sys_n = 0;            // particles of the batch
   int mlp_hidden = 0;  // hidden width of the installed cost model (0: none)
   // rebuild rule: per step kind the last walk time scaled to a fresh tree,
@@ -980,6 +987,7 @@ nbody_status nbody_bind_workspace(nbody_ctx *ctx, void *dev_ptr, size_t bytes,
   ctx->P = carve(dev_ptr, L);
   ctx->bound = true;
   ctx->have_tree = false;
+  ctx->epoch_sys++;
   ctx->sticky = NBODY_OK;
   hipLaunchKernelGGL(k_scalars_init, dim3(1), dim3(1), 0, ctx->st, ctx->P.sc);
   launch_fill_u32(ctx->P.plast, 0u, n_max, ctx->st);
@@ -1532,6 +1540,7 @@ nbody_status nbody_set_systems(nbody_ctx *ctx, int32_t n_sys, const int64_t *off
   ctx->sys_r = r;
   ctx->sys_n = offsets[n_sys];
   ctx->have_tree = false;
+  ctx->epoch_sys++;
   return NBODY_OK;
 }
 
@@ -1562,7 +1571,7 @@ nbody_status step_body(nbody_ctx *ctx, nbody_state *st, bool rebuild) {
   return hip_status();
 }
 
-nbody_ctx::GraphKey graph_key(const nbody_ctx *ctx, const nbody_state *st) {
+nbody_ctx::GraphKey graph_key(const nbody_ctx *ctx, const nbody_state *st, int kind) {
   nbody_ctx::GraphKey k{};
   const void *p[10] = {st->x, st->y, st->z, st->vx, st->vy, st->vz, st->m, st->ax, st->ay, st->az};
   memcpy(k.p, p, sizeof(p));
@@ -1570,6 +1579,10 @@ nbody_ctx::GraphKey graph_key(const nbody_ctx *ctx, const nbody_state *st) {
   k.dt = st->dt;
   k.order = (ctx->order == 2 && ctx->mlp_hidden == 0) ? 0 : ctx->order;
   k.nsys = ctx->nsys;
+  k.hidden = k.order == 2 ? ctx->mlp_hidden : 0;
+  k.counting = ctx->counting ? 1 : 0;
+  k.epoch_sys = ctx->epoch_sys;
+  k.perm = kind == 0 ? ctx->perm : nullptr;
   return k;
 }
 
@@ -1583,6 +1596,7 @@ nbody_status capture_step(nbody_ctx *ctx, nbody_state *st, int kind) {
   // a replay may follow changes to the state made between calls: every
   // captured step mirrors the accelerations afresh
   ctx->asort_src = nullptr;
+  const nbody_ctx::GraphKey key = graph_key(ctx, st, kind);
   if (hipStreamBeginCapture(ctx->cap_st, hipStreamCaptureModeThreadLocal) != hipSuccess) {
     s = NBODY_EHIP;
   } else {
@@ -1591,11 +1605,16 @@ nbody_status capture_step(nbody_ctx *ctx, nbody_state *st, int kind) {
   }
   ctx->capturing = false;
   ctx->st = orig;
+  // a captured build has not run yet: the tree is there once it is replayed
+  if (kind == 1) ctx->have_tree = false;
   if (s != NBODY_OK) {
     if (g) (void)hipGraphDestroy(g);
     return s;
   }
-  if (ctx->gexec[kind]) (void)hipGraphExecDestroy(ctx->gexec[kind]);
+  if (ctx->gexec[kind]) {  // (an earlier replay may still be running)
+    (void)hipStreamSynchronize(ctx->cap_st);
+    (void)hipGraphExecDestroy(ctx->gexec[kind]);
+  }
   ctx->gexec[kind] = nullptr;
   const hipError_t e = hipGraphInstantiate(&ctx->gexec[kind], g, nullptr, nullptr, 0);
   (void)hipGraphDestroy(g);
@@ -1603,7 +1622,11 @@ nbody_status capture_step(nbody_ctx *ctx, nbody_state *st, int kind) {
     ctx->gexec[kind] = nullptr;
     return NBODY_EHIP;
   }
-  ctx->gkey[kind] = graph_key(ctx, st);
+  ctx->gkey[kind] = key;
+  if (kind == 1) {
+    ctx->gkeys = ctx->keys;
+    ctx->gperm = ctx->perm;
+  }
   return NBODY_OK;
 }
 
@@ -1625,20 +1648,31 @@ nbody_status nbody_step_graph(nbody_ctx *ctx, nbody_state *st, int32_t n_steps) 
   // argument checks and the first force evaluation, eagerly
   if ((s = nbody_step(ctx, st, 0)) != NBODY_OK) return s;
   if (n_steps == 0) return NBODY_OK;
-  const nbody_ctx::GraphKey key = graph_key(ctx, st);
   if (hipEventRecord(ctx->cap_ev[0], ctx->st) != hipSuccess ||
       hipStreamWaitEvent(ctx->cap_st, ctx->cap_ev[0], 0) != hipSuccess)
     return NBODY_EHIP;
   for (int32_t k = 0; k < n_steps; ++k) {
-    const int kind = (ctx->n != st->n || ctx->since_rebuild >= st->rebuild_interval) ? 1 : 0;
+    const int kind = (!ctx->have_tree || ctx->n != st->n ||
+                      ctx->since_rebuild >= st->rebuild_interval)
+                         ? 1
+                         : 0;
+    const nbody_ctx::GraphKey key = graph_key(ctx, st, kind);
     if (!ctx->gexec[kind] || memcmp(&ctx->gkey[kind], &key, sizeof(key)) != 0)
       if ((s = capture_step(ctx, st, kind)) != NBODY_OK) return s;
     if (hipGraphLaunch(ctx->gexec[kind], ctx->cap_st) != hipSuccess) return NBODY_EHIP;
-    if (kind == 1) {
+    if (kind == 1) {  // the tree is the replay's, whatever was built in between
       ctx->rebuilds++;
       ctx->since_rebuild = 0;
       ctx->n = st->n;
+      ctx->keys = ctx->gkeys;
+      ctx->perm = ctx->gperm;
+      ctx->have_tree = true;
+      ctx->epoch++;
+      ctx->excess_ms = 0.0;
+      ctx->growth = 1.0;
+      ctx->mac_walks = 1;  // (a captured walk is in no statistics)
     }
+    ctx->last_queued = key.order != 0;
     ctx->since_rebuild++;
     ctx->steps++;
     st->t += st->dt;
