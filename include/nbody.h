@@ -249,7 +249,8 @@ nbody_status nbody_workspace_query(const nbody_params *p, int64_t n_max,
 
 /* Bind caller-owned device memory (>= nbody_workspace_query bytes, 256-byte
  * aligned) for up to n_max particles. The library keeps no other device
- * state; rebinding drops the tree. */
+ * state; rebinding drops the tree and an installed cost model, and keeps the
+ * systems of a batch. */
 nbody_status nbody_bind_workspace(nbody_ctx *ctx, void *dev_ptr, size_t bytes,
                                   int64_t n_max);
 

@@ -20,7 +20,7 @@ struct nbody_ctx {
   void *ws = nullptr;
   size_t ws_bytes = 0;
   Layout L;
-  Ptrs P;
+  Ptrs P{};
   bool bound = false;
   int64_t n = 0;
   bool have_tree = false;
@@ -78,6 +78,7 @@ struct nbody_ctx {
   uint64_t *gkeys = nullptr;  // the captured rebuild step's sorted keys and
   uint32_t *gperm = nullptr;  // permutation
   int64_t sys_n = 0;            // particles of the batch
+  std::vector<uint32_t> sys_off;  // its offsets, for the next workspace
   int mlp_hidden = 0;  // hidden width of the installed cost model (0: none)
   // rebuild rule: per step kind the last walk time scaled to a fresh tree,
   // the growth I / I_ref of the last walk on the current tree, and the tick
@@ -984,7 +985,9 @@ nbody_status nbody_bind_workspace(nbody_ctx *ctx, void *dev_ptr, size_t bytes,
   ctx->ws = dev_ptr;
   ctx->ws_bytes = bytes;
   ctx->L = L;
+  const float *old_mlpw = ctx->P.mlpw;
   ctx->P = carve(dev_ptr, L);
+  if (ctx->P.mlpw != old_mlpw) ctx->mlp_hidden = 0;  // its weights lay in the old workspace
   ctx->bound = true;
   ctx->have_tree = false;
   ctx->epoch_sys++;
@@ -994,6 +997,11 @@ nbody_status nbody_bind_workspace(nbody_ctx *ctx, void *dev_ptr, size_t bytes,
   launch_fill_u32(ctx->P.gflag, 0u, n_max, ctx->st);  // cleared again by each queue build
   // grid barrier flags start below every goal
   launch_fill_u32(reinterpret_cast<uint32_t *>(ctx->P.bar), 0u, 4 * (int64_t)kBarSlots, ctx->st);
+  // a batch stays configured: its offsets into the new workspace
+  if (ctx->sys_r > 0 &&
+      hipMemcpyAsync(ctx->P.sysoff, ctx->sys_off.data(), sizeof(uint32_t) * ctx->sys_off.size(),
+                     hipMemcpyHostToDevice, ctx->st) != hipSuccess)
+    return NBODY_EHIP;
   return hip_status();
 }
 
@@ -1528,7 +1536,8 @@ nbody_status nbody_set_systems(nbody_ctx *ctx, int32_t n_sys, const int64_t *off
   for (int32_t i = 0; i < n_sys; ++i)
     if (offsets[i + 1] <= offsets[i]) return NBODY_EINVAL;  // every system non-empty
   if (offsets[n_sys] > ctx->L.n_max) return NBODY_ENOMEM;
-  std::vector<uint32_t> off((size_t)n_sys + 1);
+  std::vector<uint32_t> &off = ctx->sys_off;
+  off.resize((size_t)n_sys + 1);
   for (int32_t i = 0; i <= n_sys; ++i) off[i] = (uint32_t)offsets[i];
   if (hipMemcpyAsync(ctx->P.sysoff, off.data(), sizeof(uint32_t) * off.size(),
                      hipMemcpyHostToDevice, ctx->st) != hipSuccess ||

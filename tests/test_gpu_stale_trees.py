@@ -88,3 +88,22 @@ def test_graph_steps_after_other_calls(nb, torch, change, interval):
     np.testing.assert_array_equal(ends[0][1], ends[1][1])
     for k in ("steps", "rebuilds", "ncell", "list_entries", "queued"):
         assert ends[0][2][k] == ends[1][2][k], k
+
+
+def test_systems_stay_with_another_workspace(nb, torch):
+    off = [0, 700, 1900, N]
+    ctx, want = nb.Context(nb.Params(order=2), n_max=N), nb.Context(nb.Params(), n_max=N)
+    ctx.set_cost_model(8, torch.ones(nb.mlp_nparams(8), device="cuda"))
+    ctx.set_systems(off)
+    want.set_systems(off)
+    a, b = _state(nb, 2), _state(nb, 2)
+    ctx.step(a, 2)
+    old = ctx.ws
+    _rebind(nb, torch, ctx, N + 5000)
+    old.fill_(255)  # (nothing of the old memory is used again)
+    ctx.step(a, 2)
+    want.step(b, 4)
+    ctx.sync()
+    assert ctx.stats()["queued"] == ctx.stats()["ngroup"]
+    # (the tree was dropped after the second step, so both rebuild before the third)
+    _same(a, b)
