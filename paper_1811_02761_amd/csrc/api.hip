@@ -261,30 +261,47 @@ Layout make_layout(const nbody_params &p, int64_t n, int num_cu, bool stepping,
   L.off_gent = take(4 * N);
   L.off_ghash = take(8 * N);
   L.off_order = take(4 * N);
-  L.off_prevcnt = take(4 * N);
-  // heavy groups (walked in parts): slots for about one part per 6 particles,
-  // more for few; stacks in the main pass's buffer, with room for at least 64
-  // workgroups of the last pass (a stack and two fronts each). A stack holds at
-  // most 512 cells per tree level (22 levels), and no more than the tree has.
-  L.heavy_slots = std::max<int64_t>(
-      std::min({std::max<int64_t>(n / 6, std::min<int64_t>(n / 2, 16384)), (int64_t)196608,
-                heavy_slots}),
-      64);
+  L.off_greach = take(4 * N);
+  // Heavy groups (walked in parts) share the main pass's stack buffer, which is
+  // free by then: stacks first, with room for at least 64 workgroups of the last
+  // pass (a stack and two fronts each), then the parts: slots for about one per 6
+  // particles, more for few, and what the stacks leave. A stack holds at most 512
+  // cells per tree level (22 levels), and no more than the tree has.
   L.heavy_cap = 64;
   while (L.heavy_cap < L.cell_cap && L.heavy_cap < 16384) L.heavy_cap <<= 1;
-  const int64_t end_words = L.heavy_cap + 2 * (int64_t)kFrontCap;
-  const int64_t fwords = std::max<int64_t>(L.walk_waves * L.frontier_cap, 64 * end_words);
-  auto waves_of = [&](int64_t stack) {
-    return (int)std::min<int64_t>(L.walk_waves, fwords / stack) / kWalkWavesPerWG *
-           kWalkWavesPerWG;
-  };
-  L.retry_waves = waves_of(L.heavy_cap);
   // parts rarely hold more than kFrontCap particles: smaller stacks, more
   // wavefronts (k_heavy_walk)
   L.heavy_stack = std::min<int64_t>(L.heavy_cap, std::max<int64_t>(p.frontier_cap, kFrontCap));
-  L.heavy_waves = waves_of(L.heavy_stack);
-  L.heavy_end_blocks = (int)std::min<int64_t>(512, fwords / end_words);
+  const int64_t end_words = L.heavy_cap + 2 * (int64_t)kFrontCap;
+  const int64_t hwords = heavy_part_words(p.compensated);
+  const int64_t slot_words = 4 + 2 + kHeavyFrontPerSlot + hwords, pad_words = 4 * 64;
+  const int64_t min_slots = std::max<int64_t>(
+      std::min({std::max<int64_t>(n / 6, std::min<int64_t>(n / 2, 16384)), (int64_t)196608,
+                heavy_slots}),
+      64);
+  const int64_t part_words = min_slots * slot_words + pad_words;
+  const int64_t fwords = (std::max<int64_t>(L.walk_waves * L.frontier_cap,
+                                            64 * end_words + part_words) + 63) / 64 * 64;
+  const int64_t stack_words =
+      std::min(fwords - part_words, std::max(L.walk_waves * L.heavy_stack, 512 * end_words)) /
+      64 * 64;
+  L.heavy_slots = std::min({(fwords - stack_words - pad_words) / slot_words,
+                            std::max(min_slots, n), std::max<int64_t>(heavy_slots, 64)});
+  auto waves_of = [&](int64_t words, int64_t stack) {
+    return (int)std::min<int64_t>(L.walk_waves, words / stack) / kWalkWavesPerWG *
+           kWalkWavesPerWG;
+  };
+  L.retry_waves = waves_of(fwords, L.heavy_cap);
+  L.heavy_waves = waves_of(stack_words, L.heavy_stack);
+  L.heavy_end_blocks = (int)std::min<int64_t>(512, stack_words / end_words);
   L.off_frontier = take(4 * (size_t)fwords);
+  const size_t after = o;
+  o = L.off_frontier + 4 * (size_t)stack_words;
+  L.off_hparts = take(16 * (size_t)L.heavy_slots);
+  L.off_hrec = take(8 * (size_t)L.heavy_slots);
+  L.off_hfront = take(4 * (size_t)kHeavyFrontPerSlot * (size_t)L.heavy_slots);
+  L.off_hsum = take(4 * (size_t)hwords * (size_t)L.heavy_slots);
+  o = std::max(o, after);
   L.off_atmp = take(12 * N);
   L.off_retry = take(4 * N);
   L.off_plast = take(4 * N);
@@ -322,10 +339,6 @@ Layout make_layout(const nbody_params &p, int64_t n, int num_cu, bool stepping,
   L.off_longslot = take(4 * (size_t)L.build_blocks * kLevels);
   L.off_wpart = take(8 * 4 * (size_t)kStatBlocks);
   L.off_heavy = take(4 * N);
-  L.off_hparts = take(16 * (size_t)L.heavy_slots);
-  L.off_hrec = take(8 * (size_t)L.heavy_slots);
-  L.off_hfront = take(4 * (size_t)kHeavyFrontPerSlot * (size_t)L.heavy_slots);
-  L.off_hsum = take(4 * (size_t)heavy_part_words(p.compensated) * (size_t)L.heavy_slots);
   // key-ordered block-step state, two sets (none without stepping: the
   // pointers then share one empty offset and are never used); each set's
   // region, from its positions on, spans at least 64 bytes per particle: it
@@ -388,7 +401,7 @@ Ptrs carve(void *base, const Layout &L) {
   P.gent = reinterpret_cast<uint32_t *>(b + L.off_gent);
   P.ghash = reinterpret_cast<unsigned long long *>(b + L.off_ghash);
   P.order = reinterpret_cast<uint32_t *>(b + L.off_order);
-  P.prevcnt = reinterpret_cast<uint32_t *>(b + L.off_prevcnt);
+  P.greach = reinterpret_cast<float *>(b + L.off_greach);
   P.frontier = reinterpret_cast<uint32_t *>(b + L.off_frontier);
   P.atmp = reinterpret_cast<float *>(b + L.off_atmp);
   P.retry = reinterpret_cast<uint32_t *>(b + L.off_retry);

@@ -41,13 +41,21 @@
 // nearly every particle is an entry). One group's walk is a serial chain, so
 // such a group decided the walk's time (sphere of 2*10^5 particles: mean list
 // 1840, longest 199938; 3.2 ms, of which all other groups needed 0.4). A group
-// whose list exceeds heavy_limit() of its walk root's particles is therefore
-// left by the main pass and walked in parts: k_walk_mid cuts the part of the
-// tree that the group meets into an ordered front of cells (breadth first,
-// the group's own MAC) and the front into parts of about equal particle
-// counts; k_heavy_walk walks each part like a group of its own (its stack
-// starts with the part's cells), and k_heavy_end adds the parts' sums in
-// order. Front, parts and sums depend on the tree and the group alone.
+// with more entries in its reach (k_group_bounds) than heavy_limit() of its walk
+// root's particles is therefore left by the main pass and walked in parts:
+// k_walk_mid cuts the part of the tree that the group meets into an ordered front
+// of cells (breadth first, the group's own MAC) and the front into parts of about
+// equal particle counts; k_heavy_walk walks each part like a group of its own (its
+// stack starts with the part's cells), and k_heavy_end adds the parts' sums in
+// order. Reach, front, parts and sums depend on the tree, the group and its a_old
+// alone.
+// Where all lists are long (a small delta_acc, large leaves, a_old far too small)
+// nothing is gained by parts: the groups keep the chip busy, and every one is
+// walked up to the limit first. With a limit on the whole list a sphere of 300007
+// particles at 2^-12 took 17.3 ms instead of 5.7 without parts, a galaxy of 200000
+// with 64-particle leaves at 2^-11 2.4 instead of 0.63; by the entries in reach 3.6
+// and 0.5. Over-full leaves (particles that the keys do not tell apart) do not
+// count: no cut into cells divides them.
 //
 // Lane layout: groups of at most 8, 16 or 32 members use S = 8, 4 or 2
 // "streams": lane = stream * (64 / S) + member, stream s adds the entries
@@ -72,6 +80,7 @@ struct WalkArgs {
   const uint32_t *gbegin;
   const uint32_t *gcount;
   const float4 *gbox;
+  const float *greach;
   const uint32_t *perm;
   const uint32_t *order;   // queue -> group (nullptr: identity)
   const uint32_t *qcount;  // queue length (device)
@@ -147,12 +156,13 @@ __device__ __forceinline__ uint32_t front_cell_max(uint32_t n) {
 // Group-wise MAC (see above): the cell with node words A = (com, b^2) and mass m
 // against the group's box, dA = delta_acc |a_old|. G m b^2 is made here: as a word
 // of the node it cost every tree a launch of its own, 4 to 5 us.
+// The squared distance comes back in d2.
 __device__ __forceinline__ bool mac_accept(float4 A, float m, float G, float4 glo, float4 ghi,
-                                           float dA, int bootstrap) {
+                                           float dA, int bootstrap, float &d2) {
   const float tx = fmaxf(fmaxf(glo.x - A.x, A.x - ghi.x), 0.0f);
   const float ty = fmaxf(fmaxf(glo.y - A.y, A.y - ghi.y), 0.0f);
   const float tz = fmaxf(fmaxf(glo.z - A.z, A.z - ghi.z), 0.0f);
-  const float d2 = __builtin_fmaf(tz, tz, __builtin_fmaf(ty, ty, tx * tx));
+  d2 = __builtin_fmaf(tz, tz, __builtin_fmaf(ty, ty, tx * tx));
   bool accept = false;
   if (d2 > A.w) {
     if (bootstrap) {
@@ -238,6 +248,7 @@ struct Acc3<true, kPot> {
 // (rotating among those); after a whole number of rotation periods u_k holds
 // sum p + K k.
 constexpr uint32_t kBlk = 64;  // list entries per block
+constexpr uint32_t kFullLeaf = 64;  // the largest leaf_max: bigger leaves are over-full
 template <bool kComp, bool kPot>
 struct RunSums;
 template <bool kPot>
@@ -482,7 +493,7 @@ template <bool kComp, bool kHash, bool kPot, uint32_t K>
 __device__ __forceinline__ uint32_t walk_list(const WalkArgs &a, const WaveLds &l,
                                               const WalkGroup &w, uint32_t *stk, uint32_t F,
                                               uint32_t top, uint32_t part, uint32_t limit,
-                                              uint32_t ncell, uint32_t lane,
+                                              float reach, uint32_t ncell, uint32_t lane,
                                               RunSums<kComp, kPot> &R, uint32_t &entries,
                                               uint64_t &hsum) {
   float4 *list = l.list();
@@ -493,6 +504,8 @@ __device__ __forceinline__ uint32_t walk_list(const WalkArgs &a, const WaveLds &
   uint32_t visited = 0, cnt = 0;
   uint32_t nblk = 0;  // list blocks this wavefront has added
   uint32_t end = 0;
+  uint32_t nnear = 0;  // per lane: entries in reach, over-full leaves aside
+  uint32_t check = limit;
   // the chunk of up to 64 cells from the stack's top, and their nodes
   uint32_t nc, c;
   bool bad_c;
@@ -526,7 +539,9 @@ __device__ __forceinline__ uint32_t walk_list(const WalkArgs &a, const WaveLds &
         break;
       }
     }
-    const bool accept = has && mac_accept(A, B.x, a.G, w.glo, w.ghi, dA, a.bootstrap);
+    float d2;
+    const bool accept = mac_accept(A, B.x, a.G, w.glo, w.ghi, dA, a.bootstrap, d2) && has;
+    const bool near = !(d2 > A.w && d2 > reach);
     const bool leaf = (w1 & kLeafBit) != 0u;
     const uint32_t ne = !has ? 0u : accept ? 1u : leaf ? (w1 & ~kLeafBit) : 0u;
     const uint32_t nch = (has && !accept && !leaf) ? w1 : 0u;
@@ -535,6 +550,7 @@ __device__ __forceinline__ uint32_t walk_list(const WalkArgs &a, const WaveLds &
     // 512 per chunk: 10 bits; entries in the 22 bits above), or two scans
     // when a leaf is so large (coincident particles) that they might not fit
     uint32_t chi, chtot, ei, etot;
+    nnear += near && ne <= kFullLeaf ? ne : 0u;
     if (__ballot(ne >= 65536u) == 0ull) {  // (wave-uniform)
       const uint32_t both = wave_incl_scan_dpp((ne << 10) | nch);
       const uint32_t btot = wave_last(both);
@@ -635,9 +651,13 @@ __device__ __forceinline__ uint32_t walk_list(const WalkArgs &a, const WaveLds &
     }
     __builtin_amdgcn_wave_barrier();  // owner table is rewritten next chunk
     entries += etot;
-    if (entries > limit) {
-      end = kEndHeavy;
-      break;
+    if (entries > check) {  // (wave-uniform)
+      const uint32_t m = wave_last(wave_incl_scan_dpp(nnear));
+      if (m > limit) {
+        end = kEndHeavy;
+        break;
+      }
+      check = entries + (limit - m);  // (not passed before)
     }
   }
   if (end) cnt = 0;
@@ -682,7 +702,12 @@ __device__ __forceinline__ void finish_group(const WalkArgs &a, const WalkGroup 
 // Claims the next task beyond the nw first ones. The empty asm pins the
 // wave-uniform result here, before the loop's back edge.
 __device__ __forceinline__ uint32_t next_task(const WalkArgs &a, uint32_t nw, uint32_t lane) {
-  const uint32_t claim = atomicAdd(a.head, lane == 0 ? 1u : 0u);
+  // (the first empty asm keeps a spilled pointer's reload out of the claim)
+  typedef __attribute__((address_space(1))) uint32_t *gp;
+  gp head = reinterpret_cast<gp>(reinterpret_cast<uintptr_t>(a.head));
+  asm volatile("" : "+s"(head));
+  const uint32_t claim = __hip_atomic_fetch_add(head, lane == 0 ? 1u : 0u, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT);
   uint32_t t = __builtin_amdgcn_readfirstlane(claim);
   asm volatile("" : "+s"(t));
   return nw + t;
@@ -738,12 +763,13 @@ __device__ __forceinline__ void walk_loop(const WalkArgs &a, const WaveLds &l, u
     const WalkGroup w = load_group(a, g, lane);
     const uint32_t root = a.groot ? a.groot[g] : 0u;
     const uint32_t limit = heavy_limit(a.groot ? a.cpcount[root] : a.n);
+    const float reach = a.greach[g];
     stk[0] = root;  // (same value in every lane)
     RunSums<kComp, kPot> R;
     uint64_t hsum = 0;
     uint32_t entries = 0;
     const uint32_t end = walk_list<kComp, kHash, kPot, K>(
-        a, l, w, stk, a.fmask + 1u, 1u, part, limit, ncell, lane, R, entries, hsum);
+        a, l, w, stk, a.fmask + 1u, 1u, part, limit, reach, ncell, lane, R, entries, hsum);
     // `end` is wave-uniform: these branches are not lane-predicated; every
     // lane joins the atomics and stores. Every part of a split group ends the
     // same way (same traversal); a group without results is handed on to the
@@ -831,7 +857,8 @@ __device__ __forceinline__ uint32_t heavy_front(const WalkArgs &a, uint32_t root
     if (c >= ncell) return 1u;
     const float4 A = a.nodeA[c], B = a.nodeB[c];
     const uint32_t w0 = __float_as_uint(B.z), w1 = __float_as_uint(B.w), np = a.cpcount[c];
-    if (mac_accept(A, B.x, a.G, glo, ghi, glo.w, a.bootstrap)) return 1u;
+    float d2;
+    if (mac_accept(A, B.x, a.G, glo, ghi, glo.w, a.bootstrap, d2)) return 1u;
     if (!(w1 & kLeafBit) && w1 >= 1u && w1 <= 8u && w0 > c && w0 < ncell && w1 <= ncell - w0 &&
         np > big) {
       nout = w1;
@@ -973,7 +1000,7 @@ __global__ __launch_bounds__(256) void k_walk_mid(WalkArgs a, uint32_t walk_wave
     // the heavy ones among queue positions b, b + front_blocks, ...: consecutive
     // positions go to different workgroups
     const uint32_t ncell = a.sc->ncell;
-    bool full = false;  // (thread 0) no part slots are left
+    bool full = false;  // (uniform) no part slots are left
     for (uint32_t q0 = blockIdx.x; q0 < ng; q0 += 256u * front_blocks) {
       const uint64_t qi = (uint64_t)q0 + (uint64_t)threadIdx.x * front_blocks;
       if (threadIdx.x == 0) s_at[2] = 0u;
@@ -984,9 +1011,20 @@ __global__ __launch_bounds__(256) void k_walk_mid(WalkArgs a, uint32_t walk_wave
       }
       __syncthreads();
       const uint32_t nl = s_at[2];
+      __syncthreads();  // (s_at[2] is used again)
       if (threadIdx.x == 0 && nl > 0u) s_at[3] = atomicAdd(&a.sc->nheavy, nl);
       for (uint32_t j = 0; j < nl; ++j) {
         const uint32_t g = s_list[j];
+        if (full) {  // (uniform) left to k_heavy_end
+          if (threadIdx.x == 0) {
+            const uint32_t h = s_at[3] + j;
+            a.heavy[h] = g;
+            if (h < a.hslots) a.hrec[h] = make_uint2(0u, 0u);
+            a.gent[g] = 0u;
+            if (hash) a.ghash[g] = 0ull;
+          }
+          continue;
+        }
         const uint32_t root = a.groot ? a.groot[g] : 0u;
         const float4 glo = a.gbox[2 * g], ghi = a.gbox[2 * g + 1];
         const uint32_t nr = a.groot ? a.cpcount[root] : a.n;
@@ -998,22 +1036,22 @@ __global__ __launch_bounds__(256) void k_walk_mid(WalkArgs a, uint32_t walk_wave
           const uint32_t h = s_at[3] + j;
           // one request for parts (low word) and front cells
           const unsigned long long at =
-              full ? 0ull : atomicAdd(&a.sc->nhpart, ((unsigned long long)m << 32) | P);
+              atomicAdd(&a.sc->nhpart, ((unsigned long long)m << 32) | P);
           const uint32_t s0 = (uint32_t)at, f0 = (uint32_t)(at >> 32);
-          full = full || s0 >= a.hslots;
-          const bool room = !full && h < a.hslots && P <= a.hslots - s0 &&
+          const bool room = s0 < a.hslots && h < a.hslots && P <= a.hslots - s0 &&
                             f0 < a.hfront_cap && m <= a.hfront_cap - f0;
           a.heavy[h] = g;
           if (h < a.hslots) a.hrec[h] = room ? make_uint2(s0, P) : make_uint2(0u, 0u);
           a.gent[g] = 0u;
           if (hash) a.ghash[g] = 0ull;
-          s_at[0] = full ? a.hslots : s0;
+          s_at[0] = s0;
           s_at[1] = room ? f0 : kEntNone;
           s_at[2] = h;
         }
         __syncthreads();
         const uint32_t s0 = s_at[0], f0 = s_at[1], h = s_at[2];
         const bool room = f0 != kEntNone;
+        full = s0 >= a.hslots;
         for (uint32_t r = threadIdx.x; r < P; r += 256u)
           if (s0 + r < a.hslots && s0 + r >= s0)
             a.hparts[s0 + r] =
@@ -1142,8 +1180,8 @@ __global__ __launch_bounds__(64 * kWalkWavesPerWG,
     uint64_t hsum = 0;
     uint32_t entries = 0;
     const uint32_t end =
-        walk_list<kComp, kHash, kPot, 1>(a, l, w, stk, a.fmask + 1u, m, 0u, 0xffffffffu, ncell,
-                                         lane, R, entries, hsum);
+        walk_list<kComp, kHash, kPot, 1>(a, l, w, stk, a.fmask + 1u, m, 0u, 0xffffffffu, 0.f,
+                                         ncell, lane, R, entries, hsum);
     if (end == kEndOverflow) a.hrec[part.w] = make_uint2(0u, 0u);  // left to k_heavy_end
     if (end == kEndCorrupt) atomicOr(&a.sc->status, kStCorrupt);
     PartSums<kComp, kPot>::store(a.hsum + (size_t)t * a.hwords, lane, R);
@@ -1209,7 +1247,7 @@ __global__ __launch_bounds__(64) void k_heavy_end(WalkArgs a) {
         RunSums<kComp, kPot> R;
         uint32_t ent = 0;
         end = walk_list<kComp, kHash, kPot, 1>(a, l, w, stk, a.fmask + 1u, c, 0u, 0xffffffffu,
-                                               ncell, lane, R, ent, hsum);
+                                               0.f, ncell, lane, R, ent, hsum);
         entries += ent;
         T.add(R);
       }
@@ -1390,6 +1428,7 @@ WalkArgs walk_args(const WalkCfg &c, const uint32_t *perm, int64_t n, float *ax,
   a.gbegin = P.gbegin;
   a.gcount = P.gcount;
   a.gbox = P.gbox;
+  a.greach = P.greach;
   a.perm = perm;
   a.order = c.use_order ? P.order : nullptr;
   a.qcount = c.use_order ? &P.sc->nqueue : &P.sc->ngroup;

@@ -92,7 +92,7 @@ struct Layout {
       off_xyzm, off_x32, off_pinfo, off_leafof, off_blkcnt, off_clevel,
       off_cpbegin, off_cpcount, off_cfchild, off_cnchild, off_cparent,
       off_mom64, off_nodeA, off_nodeB, off_gbegin, off_gcount, off_gbox,
-      off_gent, off_ghash, off_order, off_frontier, off_prevcnt, off_atmp, off_retry,
+      off_gent, off_ghash, off_order, off_frontier, off_greach, off_atmp, off_retry,
       off_feat, off_target, off_pred, off_plast, off_okeys, off_qtmp, off_mlpw,
       off_mlpm, off_mlpv, off_mlpg, off_mlppart, off_gref, off_sysoff, off_sysbox, off_groot,
       off_inv, off_asort, off_split, off_gid, off_gflag, off_ilist, off_leaves, off_scan,
@@ -100,9 +100,9 @@ struct Layout {
   size_t off_kpos[2], off_kvel[2], off_kacc[2], off_kmass[2], off_kpt[2], off_klv[2];
   int64_t split_slots = 0;  // queue positions with room for split-walk partial sums
   int slot_bytes = 0;       // and the room of one
-  // heavy groups: part slots, the stack no tree outgrows, and the wavefronts
-  // (k_heavy_walk, the retry pass) and workgroups (k_heavy_end) with such a
-  // stack in `frontier`
+  // heavy groups: part slots (in the memory of `frontier`, behind the stacks of the
+  // passes that use them), the stack no tree outgrows, and the wavefronts
+  // (k_heavy_walk, the retry pass) and workgroups (k_heavy_end) with such a stack
   int64_t heavy_slots = 0, heavy_cap = 0, heavy_stack = 0;
   int heavy_waves = 0, retry_waves = 0, heavy_end_blocks = 0;
   size_t total = 0;
@@ -135,7 +135,7 @@ struct Ptrs {
   unsigned long long *ghash;
   uint32_t *order;      // walk queue order
   uint32_t *frontier;   // per wave ring
-  uint32_t *prevcnt;    // per group: entries of the previous walk (ordering)
+  float *greach;        // per group: squared reach of its near entries (k_group_bounds)
   float *atmp;          // [3][n] walk output of a block step (caller order)
   uint32_t *retry;      // groups whose frontier outgrew the main pass
   // cost model of the walk queue
