@@ -556,6 +556,7 @@ WalkCfg walk_cfg(const nbody_ctx *ctx, bool bootstrap, bool queued) {
   c.hash = ctx->p.checks != 0;
   c.waves_per_cu = eff_waves(ctx->p);
   c.num_cu = ctx->num_cu;
+  c.group_max = ctx->p.group_max;
   c.use_order = queued ? 1 : 0;
   c.batch = ctx->sys_r > 0;
   c.asort_out = false;

@@ -110,7 +110,7 @@ struct WalkArgs {
   int bootstrap;
   int may_retry;           // overflowing groups are walked again (else reported)
   int split_mode;          // -1 never (retry pass), 0 by queue length, else 1, 2, 4
-  uint32_t split_slots, slot_words;
+  uint32_t split_slots, slot_words, split_waves;
 };
 
 // Longest list that one wavefront walks, for a walk root holding n particles.
@@ -428,10 +428,11 @@ __device__ __forceinline__ WaveLds wave_lds(float4 *lds, uint32_t wv, uint32_t t
 // Wavefronts per SIMD asked of the compiler: the plain walk keeps the next
 // chunk's nodes in registers while it adds, and left alone takes 84 of them
 // (5 wavefronts; 557, 49.1 ms and 15.4 ms where 6 took 550 us, 48.0 and 14.9 for
-// 200003 particles, the 2^23 block steps and a batch of 64 systems). The other
-// forms would spill.
+// 200003 particles, the 2^23 block steps and a batch of 64 systems). The plain sums
+// with the potential keep 5 (left alone 4: 1.1 million particles with hashes 1146
+// us, 1073 with 5). The other forms would spill.
 constexpr int walk_occupancy(bool comp, bool hash, bool pot) {
-  return comp || hash || pot ? 1 : 6;
+  return comp ? 1 : pot ? 5 : hash ? 1 : 6;
 }
 
 // The group a wavefront walks for, per lane.
@@ -804,7 +805,7 @@ __device__ __forceinline__ void walk_body(const WalkArgs &a, float4 *lds_list) {
   const WaveLds l = wave_lds(lds_list, wv, a.tile);
   const uint32_t ng = *a.qcount;
   const uint32_t K =
-      split_factor(ng, gridDim.x * kWalkWavesPerWG, a.split_slots, a.split_mode,
+      split_factor(ng, a.split_waves, a.split_slots, a.split_mode,
                    heavy_limit(a.groot ? 0u : a.n));
   if (K == 1u)
     walk_loop<kComp, kHash, kPot, 1>(a, l, ng, wv, lane);
@@ -991,8 +992,8 @@ __device__ __forceinline__ void join_group(const WalkArgs &a, const WalkGroup &w
 // workgroups, 130 with 1024, four per CU, and 104 with the weights taken in the
 // front's last round and one atomic per group instead of three.)
 constexpr uint32_t kFrontBlocks = 1024, kJoinBlocks = 512;
-__global__ __launch_bounds__(256) void k_walk_mid(WalkArgs a, uint32_t walk_waves, int hash,
-                                                  uint32_t front_blocks, int join) {
+__global__ __launch_bounds__(256) void k_walk_mid(WalkArgs a, int hash, uint32_t front_blocks,
+                                                  int join) {
   __shared__ uint32_t s_front[2 * kFrontCap];
   __shared__ uint32_t s_pb[kMaxParts + 1], s_wsum[4], s_at[4], s_list[256];
   const uint32_t ng = *a.qcount;
@@ -1072,7 +1073,7 @@ __global__ __launch_bounds__(256) void k_walk_mid(WalkArgs a, uint32_t walk_wave
       if (a.gent[g] == kEntRetry) a.retry[atomicAdd(&a.sc->nretry, 1u)] = g;
     }
   }
-  if (!join || split_factor(ng, walk_waves, a.split_slots, a.split_mode, 4096u) == 1u) return;
+  if (!join || split_factor(ng, a.split_waves, a.split_slots, a.split_mode, 4096u) == 1u) return;
   const uint32_t lane = lane_id();
   const uint32_t nw = (gridDim.x - front_blocks) * (blockDim.x >> 6);
   for (uint32_t qi = __builtin_amdgcn_readfirstlane(
@@ -1381,7 +1382,8 @@ __global__ __launch_bounds__(64 * kWalkWavesPerWG,
 
 // The potential variant (also writes phi; never split), main and retry pass.
 template <bool kComp, bool kHash>
-__global__ __launch_bounds__(64 * kWalkWavesPerWG) void k_walk_pot(WalkArgs a) {
+__global__ __launch_bounds__(64 * kWalkWavesPerWG,
+                             walk_occupancy(kComp, kHash, true)) void k_walk_pot(WalkArgs a) {
   HIP_DYNAMIC_SHARED(float4, lds_list)
   walk_body<kComp, kHash, true>(a, lds_list);
 }
@@ -1524,13 +1526,18 @@ void heavy_passes_of(const WalkCfg &c, const WalkArgs &a, const Ptrs &P, hipStre
 // which runs before every walk.)
 void launch_walk(const WalkCfg &c, const uint32_t *perm, int64_t n, float *ax, float *ay,
                  float *az, const Ptrs &P, hipStream_t st) {
-  const WalkArgs a = walk_args(c, perm, n, ax, ay, az, P);
-  // a wavefront for every four particles is more than a tree has tasks
-  // (groups of 8 and more, at most 4 wavefronts each); fewer only share
+  WalkArgs a = walk_args(c, perm, n, ax, ay, az, P);
+  // four wavefronts for every group there may be (of 16 particles, or group_max if
+  // that is smaller) are more than a tree has tasks; fewer only share
   const int blocks = (int)std::min<int64_t>(
       c.num_cu * c.waves_per_cu / kWalkWavesPerWG,
-      std::max<int64_t>(cdiv(n, 4 * kWalkWavesPerWG), 64));
-  const uint32_t waves = (uint32_t)(blocks * kWalkWavesPerWG);
+      std::max<int64_t>(cdiv(4 * n, kWalkWavesPerWG * std::min(c.group_max, 16)), 64));
+  a.split_waves = (uint32_t)(blocks * kWalkWavesPerWG);
+  // Small groups add little per entry, so that a second traversal costs more than
+  // it saves once the queue fills the chip (potential of 40000 particles in groups
+  // of up to 4, 13000 of them: 332 us unsplit, 400 with K = 2)
+  if (c.phi && c.split == 0 && c.group_max <= 16)
+    a.split_slots = std::min(a.split_slots, a.split_waves / 4u);
   const size_t lds = walk_lds(c, kWalkWavesPerWG);
   if (c.phi)
     NB_WALK_LAUNCH(k_walk_pot, c, dim3(blocks), lds, st, a);
@@ -1538,7 +1545,7 @@ void launch_walk(const WalkCfg &c, const uint32_t *perm, int64_t n, float *ax, f
     NB_WALK_LAUNCH(k_walk, c, dim3(blocks), lds, st, a);
   if (a.may_retry) {
     // the split walk's sums first: they leave out the groups handed on
-    hipLaunchKernelGGL(k_walk_mid, dim3(kJoinBlocks), dim3(256), 0, st, a, waves, 0, 0u, 1);
+    hipLaunchKernelGGL(k_walk_mid, dim3(kJoinBlocks), dim3(256), 0, st, a, 0, 0u, 1);
     WalkArgs r = a;
     r.order = P.retry;
     r.qcount = &P.sc->nretry;
@@ -1551,11 +1558,11 @@ void launch_walk(const WalkCfg &c, const uint32_t *perm, int64_t n, float *ax, f
       NB_WALK_LAUNCH(k_walk_pot, c, rgrid, lds, st, r);
     else
       NB_WALK_LAUNCH(k_walk_retry, c, rgrid, lds, st, r);
-    hipLaunchKernelGGL(k_walk_mid, dim3(kFrontBlocks), dim3(256), 0, st, a, waves,
+    hipLaunchKernelGGL(k_walk_mid, dim3(kFrontBlocks), dim3(256), 0, st, a,
                        c.hash ? 1 : 0, kFrontBlocks, 0);
   } else {
     hipLaunchKernelGGL(k_walk_mid, dim3(kFrontBlocks + kJoinBlocks), dim3(256), 0, st, a,
-                       waves, c.hash ? 1 : 0, kFrontBlocks, 1);
+                       c.hash ? 1 : 0, kFrontBlocks, 1);
   }
   // (a list holds no more entries than there are particles)
   if (n <= (int64_t)heavy_limit((uint32_t)n)) return;

@@ -256,6 +256,7 @@ struct WalkCfg {
   int frontier_cap;
   int waves_per_cu;
   int num_cu;
+  int group_max;
   int use_order;  // walk the groups order[0 .. nqueue) instead of all groups
   bool hash;      // record the per-group entry hash
   bool batch;     // per-group roots (several systems in one tree)
