@@ -217,7 +217,7 @@ nbody_status status_from_bits(int32_t b) {
 namespace nb {
 
 Layout make_layout(const nbody_params &p, int64_t n, int num_cu, bool stepping,
-                   int64_t split_slots, int64_t heavy_slots) {
+                   int64_t split_slots, int64_t heavy_slots, int end_blocks) {
   Layout L{};  // offsets not taken below stay 0 (caught by carve_complete)
   L.n_max = n;
   L.cell_cap = n + cdiv(21 * n, p.leaf_max + 1) + 2;
@@ -263,8 +263,8 @@ Layout make_layout(const nbody_params &p, int64_t n, int num_cu, bool stepping,
   L.off_order = take(4 * N);
   L.off_greach = take(4 * N);
   // Heavy groups (walked in parts) share the main pass's stack buffer, which is
-  // free by then: stacks first, with room for at least 64 workgroups of the last
-  // pass (a stack and two fronts each), then the parts: slots for about one per 6
+  // free by then: stacks first, with room for at least end_blocks workgroups of the
+  // last pass (a stack and two fronts each), then the parts: slots for about one per 6
   // particles, more for few, and what the stacks leave. A stack holds at most 512
   // cells per tree level (22 levels), and no more than the tree has.
   L.heavy_cap = 64;
@@ -281,7 +281,8 @@ Layout make_layout(const nbody_params &p, int64_t n, int num_cu, bool stepping,
       64);
   const int64_t part_words = min_slots * slot_words + pad_words;
   const int64_t fwords = (std::max<int64_t>(L.walk_waves * L.frontier_cap,
-                                            64 * end_words + part_words) + 63) / 64 * 64;
+                                            end_blocks * end_words + part_words) +
+                          63) / 64 * 64;
   const int64_t stack_words =
       std::min(fwords - part_words, std::max(L.walk_waves * L.heavy_stack, 512 * end_words)) /
       64 * 64;
@@ -1767,27 +1768,31 @@ nbody_status nbody_tree_forces_noalloc(const nbody_params *p, void *hip_stream, 
   q.order = 0;
   q.calcnode_sync = kCalcNodeLevels;
   q.frontier_cap = (int32_t)std::min<int64_t>(cap, 256);
-  // whether n fits at all is decided with few part slots; what is left over
-  // goes to parts first, then to the stacks
-  int64_t parts = std::max<int64_t>(n / 64, 1);
-  if (make_layout(q, n, cu, false, INT64_MAX, parts).total > kStaticScratchBytes)
+  // whether n fits at all is decided with the fewest part slots and workgroups of
+  // the last pass; what is left over goes to these, then to parts, then to the stacks
+  int64_t parts = 64;
+  int ends = 16;
+  if (make_layout(q, n, cu, false, INT64_MAX, parts, ends).total > kStaticScratchBytes)
     return NBODY_ENOMEM;
   const int64_t slots = std::max<int64_t>(n / 8, 64);
-  Layout L = make_layout(q, n, cu, false, slots, parts);
-  while (parts < n / 4) {
-    const Layout M = make_layout(q, n, cu, false, slots, 2 * parts);
-    if (M.total > kStaticScratchBytes) break;
-    parts *= 2;
+  Layout L = make_layout(q, n, cu, false, slots, parts, ends);
+  const auto take = [&](int64_t next_parts, int next_ends) {
+    const Layout M = make_layout(q, n, cu, false, slots, next_parts, next_ends);
+    if (M.total > kStaticScratchBytes) return false;
+    parts = next_parts;
+    ends = next_ends;
     L = M;
-  }
+    return true;
+  };
+  (void)take(parts, 64);
+  for (int64_t next = std::max<int64_t>(n / 64, parts); next < n / 2 && take(next, ends);)
+    next *= 2;
   while (q.frontier_cap < cap && q.frontier_cap < L.heavy_cap) {
     q.frontier_cap *= 2;
-    const Layout M = make_layout(q, n, cu, false, slots, parts);
-    if (M.total > kStaticScratchBytes) {
+    if (!take(parts, ends)) {
       q.frontier_cap /= 2;
       break;
     }
-    L = M;
   }
   nbody_ctx c;  // on the stack: no events, no pinned memory
   c.p = q;

@@ -181,9 +181,11 @@ struct Ptrs {
 
 // stepping = false: no room for the key-ordered step state and the cost model
 // (tree forces only). split_slots, heavy_slots: at most so many slots for the
-// split walk's sums and for heavy groups' parts.
+// split walk's sums and for heavy groups' parts; end_blocks: at least so many
+// workgroups of the heavy groups' last pass.
 Layout make_layout(const nbody_params &p, int64_t n_max, int num_cu, bool stepping = true,
-                   int64_t split_slots = INT64_MAX, int64_t heavy_slots = INT64_MAX);
+                   int64_t split_slots = INT64_MAX, int64_t heavy_slots = INT64_MAX,
+                   int end_blocks = 64);
 Ptrs carve(void *base, const Layout &L);
 
 // FP32 coordinates and masses of particle i at x[i * stride], y[i * stride],
