@@ -82,7 +82,7 @@ __global__ __launch_bounds__(256) void k_direct(int64_t n, const float *__restri
 // (r^2 + eps^2)^(3/2) to the scale A_i and -G m_j / (r^2 + eps^2)^(1/2) to
 // phi_i. Bound by FP64 VALU issue: about 45 FP64 instructions per pair. A
 // workgroup takes kD64Targets targets and a slice of the particles, each
-// thread every 256th particle of the slice for all the targets (a load serves
+// thread every 256th (kThreads-th) particle of the slice for all the targets (a load serves
 // four pairs, no LDS); sums over the workgroup's threads in a fixed order.
 // Slices fill the chip when there are few targets; their sums are added in
 // slice order, by k_direct64_fold or (without scratch) in the workgroup, to
@@ -117,13 +117,14 @@ __device__ __forceinline__ void pair64(double (&a)[5], double dx, double dy, dou
   a[4] -= mr;
 }
 
-__global__ __launch_bounds__(256) void k_direct64(
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void k_direct64(
     int64_t n, const float *__restrict__ x, const float *__restrict__ y,
     const float *__restrict__ z, const float *__restrict__ m, int64_t nt,
     const int64_t *__restrict__ tgt, double G, double eps2, int slices, int64_t slice_len,
     double *__restrict__ part, double *__restrict__ ax, double *__restrict__ ay,
     double *__restrict__ az, double *__restrict__ aabs, double *__restrict__ phi) {
-  __shared__ double s_sum[4][kD64Out];
+  __shared__ double s_sum[kThreads / 64][kD64Out];
   const int64_t k0 = (int64_t)blockIdx.x * kD64Targets;
   double xi[kD64Targets], yi[kD64Targets], zi[kD64Targets];
   int64_t it[kD64Targets];
@@ -146,11 +147,11 @@ __global__ __launch_bounds__(256) void k_direct64(
     for (int t = 0; t < kD64Targets; ++t)
 #pragma unroll
       for (int c = 0; c < 5; ++c) a[t][c] = 0.0;
-    for (int64_t jb = j0; jb < j1; jb += 256) {
+    for (int64_t jb = j0; jb < j1; jb += kThreads) {
       const int64_t j = jb + threadIdx.x;
       bool self = false;  // (uniform) some target is among these particles
 #pragma unroll
-      for (int t = 0; t < kD64Targets; ++t) self |= it[t] >= jb && it[t] < jb + 256;
+      for (int t = 0; t < kD64Targets; ++t) self |= it[t] >= jb && it[t] < jb + kThreads;
       if (j >= j1) continue;
       const double xj = x[j], yj = y[j], zj = z[j], mj = m[j];
       if (self) {
@@ -175,7 +176,9 @@ __global__ __launch_bounds__(256) void k_direct64(
     __syncthreads();
     if (threadIdx.x < kD64Out) {
       const int q = threadIdx.x;
-      const double v = ((s_sum[0][q] + s_sum[1][q]) + s_sum[2][q]) + s_sum[3][q];
+      double v = s_sum[0][q];
+#pragma unroll
+      for (int w = 1; w < kThreads / 64; ++w) v += s_sum[w][q];
       if (part)
         part[((int64_t)blockIdx.x * slices + sl) * kD64Out + q] = v;
       else
@@ -329,9 +332,18 @@ void launch_direct64(int64_t n, const float *x, const float *y, const float *z,
   const int slices = (int)std::max<int64_t>(1, std::min<int64_t>(2048 / groups, cdiv(n, 512)));
   const int64_t slice_len = cdiv(n, slices);
   if (slices == 1 || groups * slices * kD64Out > part_words) part = nullptr;
-  hipLaunchKernelGGL(k_direct64, dim3((unsigned)groups, part ? slices : 1), dim3(256), 0, st, n,
-                     x, y, z, m, nt, tgt, G, eps * eps, slices, slice_len, part, ax, ay, az,
-                     aabs, phi);
+  const auto go = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)groups, part ? slices : 1), dim3(threads), 0, st, n,
+                       x, y, z, m, nt, tgt, G, eps * eps, slices, slice_len, part, ax, ay, az,
+                       aabs, phi);
+  };
+  // targets by the thousand over a few hundred particles: the sums over the
+  // workgroup's threads are the work (a call of 9000 targets, 257 particles: 53 us with 256
+  // threads, 36 with 64; 34 with 32 targets per workgroup)
+  if (n <= 512 && groups >= 1024)
+    go(k_direct64<64>, 64);
+  else
+    go(k_direct64<256>, 256);
   if (part)
     hipLaunchKernelGGL(k_direct64_fold, dim3((unsigned)cdiv(5 * nt, 256)), dim3(256), 0, st, n,
                        nt, tgt, G, slices, part, ax, ay, az, aabs, phi);
