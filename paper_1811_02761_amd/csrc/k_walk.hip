@@ -147,6 +147,7 @@ __host__ __device__ __forceinline__ uint32_t part_work(uint32_t n) {
   return n <= 32768u ? 256u : 512u;
 }
 constexpr uint32_t kMaxParts = 128;
+constexpr uint32_t kPartSlice = 1u << 31;  // a part of particles, not of cells
 // a front cell holding more particles is opened further
 __device__ __forceinline__ uint32_t front_cell_max(uint32_t n) {
   const uint32_t q = n / 256u;
@@ -430,9 +431,10 @@ __device__ __forceinline__ WaveLds wave_lds(float4 *lds, uint32_t wv, uint32_t t
 // (5 wavefronts; 557, 49.1 ms and 15.4 ms where 6 took 550 us, 48.0 and 14.9 for
 // 200003 particles, the 2^23 block steps and a batch of 64 systems). The plain sums
 // with the potential keep 5 (left alone 4: 1.1 million particles with hashes 1146
-// us, 1073 with 5). The other forms would spill.
+// us, 1073 with 5), the compensated ones without hashes 5. The other forms would
+// spill.
 constexpr int walk_occupancy(bool comp, bool hash, bool pot) {
-  return comp ? 1 : pot ? 5 : hash ? 1 : 6;
+  return comp ? (hash || pot ? 1 : 5) : pot ? 5 : hash ? 1 : 6;
 }
 
 // The group a wavefront walks for, per lane.
@@ -670,6 +672,30 @@ __device__ __forceinline__ uint32_t walk_list(const WalkArgs &a, const WaveLds &
   return end;
 }
 
+// Adds the particles [p0, p0 + m) as a list of their own into R.
+template <bool kComp, bool kHash, bool kPot>
+__device__ __forceinline__ void add_range(const WalkArgs &a, const WaveLds &l,
+                                          const WalkGroup &w, uint32_t p0, uint32_t m,
+                                          uint32_t lane, RunSums<kComp, kPot> &R,
+                                          uint64_t &hsum) {
+  float4 *list = l.list();
+  uint32_t nblk = 0;
+  for (uint32_t t = 0; t < m; t += a.tile) {
+    const uint32_t cnt = min(a.tile, m - t);
+    for (uint32_t k = 0; k < cnt; k += 64u) {  // (every lane stores; past the end the last again)
+      const uint32_t q = min(k + lane, cnt - 1u);
+      list[q] = load_global(a.xyzm, p0 + t + q);
+      if (kHash && k + lane < cnt) hsum += mix64((1ull << 40) + p0 + t + q);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    flush_tile<kComp, kPot, 1>(list, cnt, lane, w.stream, w.S, w.pi, a.eps2, R, nblk);
+    __builtin_amdgcn_wave_barrier();
+  }
+  for (; nblk & (RunSums<kComp, kPot>::kNum - 1u); ++nblk) R.advance(1u);
+}
+
 // 64-bit sum over the wavefront, in every lane.
 __device__ __forceinline__ uint64_t wave_sum64(uint64_t v) {
   uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
@@ -821,7 +847,9 @@ __device__ __forceinline__ void walk_body(const WalkArgs &a, float4 *lds_list) {
 // round by round, until none is left or the front would not fit in kFrontCap
 // cells. NT threads of one workgroup; cur and nxt hold kFrontCap cells each.
 // Returns the front's length, with cur pointing at it (uniform) and nxt at the
-// cells' weights: 1 for an accepted cell, another's particles.
+// cells' weights: 1 for an accepted cell, another's particles, with kWeightFull for
+// an over-full leaf.
+constexpr uint32_t kWeightFull = 1u << 31;
 template <int NT>
 __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t *wsum, uint32_t *total) {
   const uint32_t inc = wave_incl_scan_dpp(v);
@@ -848,7 +876,7 @@ template <int NT>
 __device__ __forceinline__ uint32_t heavy_front(const WalkArgs &a, uint32_t root, float4 glo,
                                                 float4 ghi, uint32_t ncell, uint32_t big,
                                                 uint32_t *&cur, uint32_t *&nxt,
-                                                uint32_t *wsum) {
+                                                uint32_t *wsum, bool &any_full) {
   const uint32_t tid = threadIdx.x;
   // w: the cell's weight, nout, first: what it is replaced by (itself, or its
   // children)
@@ -865,7 +893,7 @@ __device__ __forceinline__ uint32_t heavy_front(const WalkArgs &a, uint32_t root
       nout = w1;
       first = w0;
     }
-    return max(np, 1u);
+    return max(np, 1u) | ((w1 & kLeafBit) && np > kFullLeaf ? kWeightFull : 0u);
   };
   if (tid == 0) cur[0] = root;
   __syncthreads();
@@ -875,21 +903,26 @@ __device__ __forceinline__ uint32_t heavy_front(const WalkArgs &a, uint32_t root
     // cells: if it opens none, it was the last, and nxt holds the same cells
     const bool fits = m <= kFrontCap / 8u;
     uint32_t out = 0, opened = 0;
+    any_full = false;
     for (uint32_t k0 = 0; k0 < m; k0 += NT) {
       const bool has = k0 + tid < m;
       const uint32_t c = has ? cur[k0 + tid] : 0u;
-      uint32_t nout = 0, first = c;
+      uint32_t nout = 0, first = c, wt = 0;
       if (has) {
-        const uint32_t wt = look(c, nout, first);
+        wt = look(c, nout, first);
         if (fits) cur[k0 + tid] = wt;
       }
       const bool open = first != c;  // (a child's index is never its parent's)
+      // one scan: cells put out (12 bits: 8 per thread), opened and over-full ones
+      static_assert(8 * NT < 4096 && NT < 512, "fields of the scan");
       uint32_t tot;
-      const uint32_t ex = block_scan<NT>(nout | (open ? 1u << 16 : 0u), wsum, &tot) & 0xffffu;
-      if (out + (tot & 0xffffu) <= kFrontCap)
+      const uint32_t v = nout | (open ? 1u << 12 : 0u) | ((wt & kWeightFull) ? 1u << 21 : 0u);
+      const uint32_t ex = block_scan<NT>(v, wsum, &tot) & 0xfffu;
+      if (out + (tot & 0xfffu) <= kFrontCap)
         for (uint32_t q = 0; q < nout; ++q) nxt[out + ex + q] = first + q;
-      out += tot & 0xffffu;
-      opened += tot >> 16;
+      out += tot & 0xfffu;
+      opened += (tot >> 12) & 0x1ffu;
+      any_full = any_full || (tot >> 21) != 0u;
     }
     __syncthreads();
     if (opened == 0u || out > kFrontCap) {  // (uniform)
@@ -915,18 +948,32 @@ __device__ __forceinline__ uint32_t heavy_front(const WalkArgs &a, uint32_t root
 }
 
 // Cuts a front of m cells into parts of about equal weight: part r takes the
-// cells [pb[r], pb[r + 1]). Returns the number of parts (uniform); pb is in LDS.
+// cells [pb[r], pb[r + 1]), or, where any_full and ps[r] is not 0, slice ps[r] % 256 of
+// ps[r] / 256 % 256 of the over-full leaf at front position ps[r] / 65536 - 1 (half
+// of 40000 particles at one point: as one part a leaf of 20000 was a chain of 511
+// us, 554 us for the whole walk before there were parts).
+// Returns the number of parts (uniform); pb and ps are in LDS.
 template <int NT>
 __device__ __forceinline__ uint32_t heavy_parts(const uint32_t *weights, uint32_t work,
-                                                uint32_t m, uint32_t *pb, uint32_t *wsum) {
+                                                uint32_t m, bool any_full, uint32_t *pb,
+                                                uint32_t *ps, uint32_t *wsum) {
   const uint32_t tid = threadIdx.x;
-  auto weight = [&](uint32_t k) -> uint32_t { return k < m ? weights[k] : 0u; };
-  uint32_t W = 0, tot;
+  auto weight = [&](uint32_t k) -> uint32_t { return k < m ? weights[k] & ~kWeightFull : 0u; };
+  auto full = [&](uint32_t k) -> bool { return k < m && (weights[k] & kWeightFull) != 0u; };
+  uint32_t W = 0, tot, nfull = 0;  // (particles of over-full leaves)
   for (uint32_t k0 = 0; k0 < m; k0 += NT) {
     (void)block_scan<NT>(weight(k0 + tid), wsum, &tot);
     W += tot;
+    if (any_full) {  // (uniform)
+      (void)block_scan<NT>(full(k0 + tid) ? weight(k0 + tid) : 0u, wsum, &tot);
+      nfull += tot;
+    }
   }
-  const uint32_t P = min(min((W + work - 1u) / work, kMaxParts), m);
+  const uint32_t P = min(min((W + work - 1u) / work, kMaxParts), m + nfull / work);
+  if (any_full) {
+    for (uint32_t r = tid; r < P; r += NT) ps[r] = 0u;
+    __syncthreads();
+  }
   uint32_t base = 0;
   for (uint32_t k0 = 0; k0 < m; k0 += NT) {
     const uint32_t k = k0 + tid, wt = weight(k);
@@ -934,13 +981,28 @@ __device__ __forceinline__ uint32_t heavy_parts(const uint32_t *weights, uint32_
     if (k < m) {
       const uint32_t p0 = (uint32_t)((uint64_t)pre * P / W);
       const uint32_t p1 = (uint32_t)((uint64_t)(pre + wt) * P / W);
-      for (uint32_t r = p0 + 1u; r <= p1; ++r) pb[r] = k + 1u;
+      // an over-full leaf fills the parts after the one it starts in, up to the
+      // one it ends in
+      const uint32_t ns = any_full && full(k) && p1 > p0 + 1u ? p1 - p0 - 1u : 0u;
+      for (uint32_t r = p0 + 1u; r <= p1; ++r) {
+        pb[r] = ns != 0u && r == p0 + 1u ? k : k + 1u;
+        if (r <= p0 + ns) ps[r] = ((k + 1u) << 16) | (ns << 8) | (r - p0 - 1u);
+      }
       if (k == 0u) pb[0] = 0u;
     }
     base += tot;
   }
   __syncthreads();
   return P;
+}
+
+// Slice ps (see heavy_parts) of the over-full leaf c: its particles [x, x + y).
+__device__ __forceinline__ uint2 leaf_slice(const WalkArgs &a, uint32_t c, uint32_t ps) {
+  const float4 B = a.nodeB[c];
+  const uint32_t b = __float_as_uint(B.z), i = ps & 255u, of = (ps >> 8) & 255u;
+  const uint32_t n = b < a.n ? min(__float_as_uint(B.w) & ~kLeafBit, a.n - b) : 0u;
+  const uint32_t lo = (uint32_t)((uint64_t)n * i / of);
+  return make_uint2(b + lo, (uint32_t)((uint64_t)n * (i + 1u) / of) - lo);
 }
 
 // Results of a split group from its running sums.
@@ -995,7 +1057,7 @@ constexpr uint32_t kFrontBlocks = 1024, kJoinBlocks = 512;
 __global__ __launch_bounds__(256) void k_walk_mid(WalkArgs a, int hash, uint32_t front_blocks,
                                                   int join) {
   __shared__ uint32_t s_front[2 * kFrontCap];
-  __shared__ uint32_t s_pb[kMaxParts + 1], s_wsum[4], s_at[4], s_list[256];
+  __shared__ uint32_t s_pb[kMaxParts + 1], s_ps[kMaxParts], s_wsum[4], s_at[5], s_list[256];
   const uint32_t ng = *a.qcount;
   if (blockIdx.x < front_blocks) {
     // the heavy ones among queue positions b, b + front_blocks, ...: consecutive
@@ -1012,7 +1074,6 @@ __global__ __launch_bounds__(256) void k_walk_mid(WalkArgs a, int hash, uint32_t
       }
       __syncthreads();
       const uint32_t nl = s_at[2];
-      __syncthreads();  // (s_at[2] is used again)
       if (threadIdx.x == 0 && nl > 0u) s_at[3] = atomicAdd(&a.sc->nheavy, nl);
       for (uint32_t j = 0; j < nl; ++j) {
         const uint32_t g = s_list[j];
@@ -1030,9 +1091,11 @@ __global__ __launch_bounds__(256) void k_walk_mid(WalkArgs a, int hash, uint32_t
         const float4 glo = a.gbox[2 * g], ghi = a.gbox[2 * g + 1];
         const uint32_t nr = a.groot ? a.cpcount[root] : a.n;
         uint32_t *cur = s_front, *nxt = s_front + kFrontCap;
-        const uint32_t m =
-            heavy_front<256>(a, root, glo, ghi, ncell, front_cell_max(nr), cur, nxt, s_wsum);
-        const uint32_t P = heavy_parts<256>(nxt, part_work(nr), m, s_pb, s_wsum);
+        bool any_full;
+        const uint32_t m = heavy_front<256>(a, root, glo, ghi, ncell, front_cell_max(nr), cur, nxt,
+                                            s_wsum, any_full);
+        const uint32_t P = heavy_parts<256>(nxt, part_work(nr), m, any_full, s_pb, s_ps,
+                                              s_wsum);
         if (threadIdx.x == 0) {
           const uint32_t h = s_at[3] + j;
           // one request for parts (low word) and front cells
@@ -1047,17 +1110,23 @@ __global__ __launch_bounds__(256) void k_walk_mid(WalkArgs a, int hash, uint32_t
           if (hash) a.ghash[g] = 0ull;
           s_at[0] = s0;
           s_at[1] = room ? f0 : kEntNone;
-          s_at[2] = h;
+          s_at[4] = h;
         }
         __syncthreads();
-        const uint32_t s0 = s_at[0], f0 = s_at[1], h = s_at[2];
+        const uint32_t s0 = s_at[0], f0 = s_at[1], h = s_at[4];
         const bool room = f0 != kEntNone;
         full = s0 >= a.hslots;
         for (uint32_t r = threadIdx.x; r < P; r += 256u)
-          if (s0 + r < a.hslots && s0 + r >= s0)
-            a.hparts[s0 + r] =
-                room ? make_uint4(g, f0 + s_pb[r], s_pb[r + 1] - s_pb[r], h)
-                     : make_uint4(g, 0u, 0u, h);  // nothing to walk
+          if (s0 + r < a.hslots && s0 + r >= s0) {
+            uint4 part = make_uint4(g, 0u, 0u, h);  // nothing to walk
+            if (room && any_full && s_ps[r] != 0u) {
+              const uint2 sl = leaf_slice(a, cur[(s_ps[r] >> 16) - 1u], s_ps[r]);
+              part = make_uint4(g, sl.x, sl.y | kPartSlice, h);
+            } else if (room) {
+              part = make_uint4(g, f0 + s_pb[r], s_pb[r + 1] - s_pb[r], h);
+            }
+            a.hparts[s0 + r] = part;
+          }
         if (room)
           for (uint32_t k = threadIdx.x; k < m; k += 256u) a.hfront[f0 + k] = cur[k];
         __syncthreads();  // LDS is reused by the next group
@@ -1170,19 +1239,23 @@ __global__ __launch_bounds__(64 * kWalkWavesPerWG,
     const uint32_t f0 = __builtin_amdgcn_readfirstlane(part.y);
     const uint32_t m = __builtin_amdgcn_readfirstlane(part.z);
     const WalkGroup w = load_group(a, g, lane);
-    // (every lane stores; past the end the last cell again)
-    for (uint32_t k = 0; k < m; k += 64u) {
-      const uint32_t q = min(k + lane, m - 1u);
-      stk[q] = a.hfront[f0 + q];
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     RunSums<kComp, kPot> R;
     uint64_t hsum = 0;
-    uint32_t entries = 0;
-    const uint32_t end =
-        walk_list<kComp, kHash, kPot, 1>(a, l, w, stk, a.fmask + 1u, m, 0u, 0xffffffffu, 0.f,
-                                         ncell, lane, R, entries, hsum);
+    uint32_t entries = 0, end = 0;
+    if (m & kPartSlice) {  // (uniform)
+      entries = m & ~kPartSlice;
+      add_range<kComp, kHash, kPot>(a, l, w, f0, entries, lane, R, hsum);
+    } else {
+      // (every lane stores; past the end the last cell again)
+      for (uint32_t k = 0; k < m; k += 64u) {
+        const uint32_t q = min(k + lane, m - 1u);
+        stk[q] = a.hfront[f0 + q];
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      end = walk_list<kComp, kHash, kPot, 1>(a, l, w, stk, a.fmask + 1u, m, 0u, 0xffffffffu,
+                                             0.f, ncell, lane, R, entries, hsum);
+    }
     if (end == kEndOverflow) a.hrec[part.w] = make_uint2(0u, 0u);  // left to k_heavy_end
     if (end == kEndCorrupt) atomicOr(&a.sc->status, kStCorrupt);
     PartSums<kComp, kPot>::store(a.hsum + (size_t)t * a.hwords, lane, R);
@@ -1201,7 +1274,7 @@ __global__ __launch_bounds__(64 * kWalkWavesPerWG,
 template <bool kComp, bool kHash, bool kPot>
 __global__ __launch_bounds__(64) void k_heavy_end(WalkArgs a) {
   HIP_DYNAMIC_SHARED(float4, lds_list)
-  __shared__ uint32_t s_pb[kMaxParts + 1];
+  __shared__ uint32_t s_pb[kMaxParts + 1], s_ps[kMaxParts];
   using Sums = PartSums<kComp, kPot>;
   const uint32_t lane = lane_id();
   const WaveLds l = wave_lds(lds_list, 0u, a.tile);
@@ -1232,12 +1305,24 @@ __global__ __launch_bounds__(64) void k_heavy_end(WalkArgs a) {
       uint32_t *cur = stk + a.fmask + 1u, *nxt = cur + kFrontCap;
       const uint32_t root = a.groot ? a.groot[g] : 0u;
       const uint32_t nr = a.groot ? a.cpcount[root] : a.n;
-      const uint32_t m =
-          heavy_front<64>(a, root, w.glo, w.ghi, ncell, front_cell_max(nr), cur, nxt, nullptr);
-      const uint32_t Q = heavy_parts<64>(nxt, part_work(nr), m, s_pb, nullptr);
+      bool any_full;
+      const uint32_t m = heavy_front<64>(a, root, w.glo, w.ghi, ncell, front_cell_max(nr), cur, nxt,
+                                         nullptr, any_full);
+      const uint32_t Q = heavy_parts<64>(nxt, part_work(nr), m, any_full, s_pb, s_ps, nullptr);
       uint64_t hsum = 0;
       uint32_t entries = 0, end = 0;
       for (uint32_t r = 0; r < Q && end == 0u; ++r) {
+        const uint32_t sl = any_full ? __builtin_amdgcn_readfirstlane(s_ps[r]) : 0u;
+        RunSums<kComp, kPot> R;
+        if (sl != 0u) {
+          const uint2 range = leaf_slice(a, cur[(sl >> 16) - 1u], sl);
+          const uint32_t n = __builtin_amdgcn_readfirstlane(range.y);
+          add_range<kComp, kHash, kPot>(a, l, w, __builtin_amdgcn_readfirstlane(range.x), n, lane,
+                                        R, hsum);
+          entries += n;
+          T.add(R);
+          continue;
+        }
         const uint32_t k0 = __builtin_amdgcn_readfirstlane(s_pb[r]);
         const uint32_t c = __builtin_amdgcn_readfirstlane(s_pb[r + 1]) - k0;
         for (uint32_t k = 0; k < c; k += 64u) {
@@ -1245,7 +1330,6 @@ __global__ __launch_bounds__(64) void k_heavy_end(WalkArgs a) {
           stk[q] = cur[k0 + q];
         }
         __syncthreads();
-        RunSums<kComp, kPot> R;
         uint32_t ent = 0;
         end = walk_list<kComp, kHash, kPot, 1>(a, l, w, stk, a.fmask + 1u, c, 0u, 0xffffffffu,
                                                0.f, ncell, lane, R, ent, hsum);
@@ -1558,11 +1642,11 @@ void launch_walk(const WalkCfg &c, const uint32_t *perm, int64_t n, float *ax, f
       NB_WALK_LAUNCH(k_walk_pot, c, rgrid, lds, st, r);
     else
       NB_WALK_LAUNCH(k_walk_retry, c, rgrid, lds, st, r);
-    hipLaunchKernelGGL(k_walk_mid, dim3(kFrontBlocks), dim3(256), 0, st, a,
-                       c.hash ? 1 : 0, kFrontBlocks, 0);
+    hipLaunchKernelGGL(k_walk_mid, dim3(kFrontBlocks), dim3(256), 0, st, a, c.hash ? 1 : 0,
+                       kFrontBlocks, 0);
   } else {
-    hipLaunchKernelGGL(k_walk_mid, dim3(kFrontBlocks + kJoinBlocks), dim3(256), 0, st, a,
-                       c.hash ? 1 : 0, kFrontBlocks, 1);
+    hipLaunchKernelGGL(k_walk_mid, dim3(kFrontBlocks + kJoinBlocks), dim3(256), 0, st, a, c.hash ? 1 : 0,
+                       kFrontBlocks, 1);
   }
   // (a list holds no more entries than there are particles)
   if (n <= (int64_t)heavy_limit((uint32_t)n)) return;
