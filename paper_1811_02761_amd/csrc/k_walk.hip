@@ -53,9 +53,10 @@
 // nothing is gained by parts: the groups keep the chip busy, and every one is
 // walked up to the limit first. With a limit on the whole list a sphere of 300007
 // particles at 2^-12 took 17.3 ms instead of 5.7 without parts, a galaxy of 200000
-// with 64-particle leaves at 2^-11 2.4 instead of 0.63; by the entries in reach 3.6
-// and 0.5. Over-full leaves (particles that the keys do not tell apart) do not
-// count: no cut into cells divides them.
+// with 64-particle leaves at 2^-11 2.4 instead of 0.62; by the entries in reach 1.1
+// and 0.61. Over-full leaves (particles that the keys do not tell apart) do not
+// count: every group that lies in one meets it (half of 200000 particles at one
+// point: 13.0 ms with them, 4.6 without, 3.8 before there were parts).
 //
 // Lane layout: groups of at most 8, 16 or 32 members use S = 8, 4 or 2
 // "streams": lane = stream * (64 / S) + member, stream s adds the entries
@@ -114,8 +115,8 @@ struct WalkArgs {
 };
 
 // Longest list that one wavefront walks, for a walk root holding n particles.
-// At 2*10^5 particles a limit of 4096 leaves 1.3 % of the particles over it
-// and bounds the main pass's longest chain. In larger trees lists grow and
+// At 2*10^5 particles 1.3 % of the particles have lists of over 4096 entries;
+// the limit bounds the main pass's longest chain. In larger trees lists grow and
 // thousands of groups keep the chip busy while a long one is walked: the limit
 // grows with them (in the 2^23 galaxy, 32768 instead of 2^17 made the block
 // steps' walks 4 % shorter in group order and 1 % longer in the learned order).
@@ -484,7 +485,7 @@ constexpr uint32_t kEndOverflow = 1, kEndCorrupt = 2, kEndHeavy = 4;
 
 // Traverse the subtrees of the `top` cells on the stack and add their list
 // (with K > 1 the blocks of this part) into R; entries counts the list.
-// Stops when the list exceeds `limit` entries.
+// Stops when the list holds more than `limit` entries in `reach`.
 // A few wavefronts per SIMD are bound by this loop's chain (stack, nodes, scan,
 // push, copy, sums), a full chip by the vector instructions of the sums and of
 // the rest. So the next chunk's loads go out before this one's entries are
@@ -544,17 +545,17 @@ __device__ __forceinline__ uint32_t walk_list(const WalkArgs &a, const WaveLds &
     }
     float d2;
     const bool accept = mac_accept(A, B.x, a.G, w.glo, w.ghi, dA, a.bootstrap, d2) && has;
-    const bool near = !(d2 > A.w && d2 > reach);
     const bool leaf = (w1 & kLeafBit) != 0u;
     const uint32_t ne = !has ? 0u : accept ? 1u : leaf ? (w1 & ~kLeafBit) : 0u;
     const uint32_t nch = (has && !accept && !leaf) ? w1 : 0u;
     // children -> stack (over the popped chunk, in lane order) and entries
     // -> list: one scan of both counts (children <= 8 per lane, so at most
     // 512 per chunk: 10 bits; entries in the 22 bits above), or two scans
-    // when a leaf is so large (coincident particles) that they might not fit
+    // with an over-full leaf, whose entries might not fit and are not counted
+    // as near
     uint32_t chi, chtot, ei, etot;
-    nnear += near && ne <= kFullLeaf ? ne : 0u;
-    if (__ballot(ne >= 65536u) == 0ull) {  // (wave-uniform)
+    nnear += !(d2 > A.w && d2 > reach) ? ne : 0u;
+    if (__ballot(ne > kFullLeaf) == 0ull) {  // (wave-uniform)
       const uint32_t both = wave_incl_scan_dpp((ne << 10) | nch);
       const uint32_t btot = wave_last(both);
       chi = both & 1023u;
@@ -566,6 +567,7 @@ __device__ __forceinline__ uint32_t walk_list(const WalkArgs &a, const WaveLds &
       chtot = wave_last(chi);
       ei = wave_incl_scan_dpp(ne);
       etot = wave_last(ei);
+      nnear -= ne > kFullLeaf && !(d2 > A.w && d2 > reach) ? ne : 0u;
     }
     if (top + chtot > F) {
       end = kEndOverflow;
@@ -1464,7 +1466,7 @@ __global__ __launch_bounds__(64 * kWalkWavesPerWG,
   walk_body<kComp, kHash, false>(a, lds_list);
 }
 
-// The potential variant (also writes phi; never split), main and retry pass.
+// The potential variant (also writes phi), main and retry pass.
 template <bool kComp, bool kHash>
 __global__ __launch_bounds__(64 * kWalkWavesPerWG,
                              walk_occupancy(kComp, kHash, true)) void k_walk_pot(WalkArgs a) {
@@ -1550,7 +1552,8 @@ WalkArgs walk_args(const WalkCfg &c, const uint32_t *perm, int64_t n, float *ax,
   a.bootstrap = c.bootstrap;
   a.split = P.split;
   a.split_mode = c.split;
-  // room for the plain sums only: the other forms are not split
+  // (room for the plain sums only, on the allocation-free call's scratch: its
+  // compensated sums are not split)
   const bool fits = c.slot_bytes >= (c.compensated || c.phi ? kSplitSlotWide : kSplitSlotBytes);
   a.split_slots = fits ? (uint32_t)c.split_slots : 0u;
   a.slot_words = (uint32_t)c.slot_bytes / 4u;
