@@ -91,15 +91,20 @@ enum {
  *                within one system are joined: a group never spans systems.
  *  walk_split  : wavefronts sharing one group's interaction list: 0 chosen
  *                per walk from the queued group count q and the walk's
- *                wavefront count w (4 if q < 2w, 2 if q < 4w, else 1), or
- *                1, 2, 4 fixed (1 whenever q > 4w).
+ *                wavefront count w (4 if q < w/4, in trees of more than 2^18
+ *                particles up to 2w, 2 if q <= 4w, else 1; the potential of
+ *                groups of up to 16 is not split from q = w/4 on), or 1, 2, 4
+ *                fixed (1 whenever q > 4w).
  *                A group's list is cut into blocks of 64 entries in
  *                traversal order and each lane keeps 4 FP32 partial sums,
  *                block b adding into sum b mod 4, which are added in that
  *                order at the end; with k wavefronts per group, wavefront j
  *                adds the blocks b with b mod k == j and a second kernel
  *                adds the sums. Results are bit-identical for every value.
- *                The compensated sum (compensated = 1) is never split.
+ *                The compensated sum (compensated = 1) keeps two partial sums,
+ *                each with its correction (block b into sum b mod 2), and is
+ *                split in two at most. nbody_tree_forces_noalloc does not split
+ *                it; groups that are walked in parts are not split.
  *  calcnode_sync: how the moment pass ("calcNode", Sec. 2.2) waits for each
  *                tree level's children before their parents (App. A):
  *                0 = library default (1); 1 = one kernel launch per level;
@@ -281,8 +286,9 @@ nbody_status nbody_calc_acc(nbody_ctx *ctx, const float *ax_old,
  * order, FP32) from the same interaction lists: phi_i = -G sum over the
  * entries j of m_j / (r_ij^2 + eps^2)^(1/2), the particle's own entry left
  * out (the softened potential of Eq. 1's force; W = sum_i m_i phi_i / 2 is
- * the potential energy of long-run energy checks). The walk is never split
- * across wavefronts; accelerations are bit-identical to nbody_calc_acc.
+ * the potential energy of long-run energy checks). The walk is split across
+ * wavefronts as walk_split says; accelerations are bit-identical to
+ * nbody_calc_acc.
  * Needs a tree (ENOTREE); phi must not be NULL. */
 nbody_status nbody_calc_acc_pot(nbody_ctx *ctx, const float *ax_old,
                                 const float *ay_old, const float *az_old,
