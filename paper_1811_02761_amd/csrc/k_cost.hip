@@ -557,9 +557,10 @@ __global__ __launch_bounds__(256) void k_adam(int64_t np, const float *__restric
 // the predicted interactions: the tail only needs the costs in rough order, and
 // in group order neighbours share cells in the caches. Below 2^14.5 no group
 // decides when the walk ends: one bucket. (2^23 galaxy, block steps, rebuild
-// every 2nd step, per walk: quarter octaves 2.44 ms, quarter octaves with one
-// bucket below 2^18 2.31, octaves 2.21, plain 2.60.) Mode 3 keeps
-// quarter octaves.
+// every 2nd step, per walk over 16 steps: quarter octaves 2.44 ms, quarter octaves
+// with one bucket below 2^18 2.31, octaves 2.21, plain 2.60; over 20 steps, where
+// the rebuilds fall on other steps, octaves 2.18, plain 2.20.) Mode 3 keeps quarter
+// octaves.
 constexpr float kBulkLog2 = 14.0f;
 __global__ __launch_bounds__(256) void k_cost_keys(
     const DevScalars *__restrict__ sc, const uint32_t *__restrict__ queue, int mode,
